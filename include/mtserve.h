@@ -181,8 +181,10 @@ int32_t mts_kv_append_layers(const mts_cache_desc* cache, int32_t layer_begin, i
                              const void* k_new, const void* v_new, int64_t rows_layer_stride_bytes,
                              const mts_batch_meta* meta, void* stream);
 
-/* Workspace mts_attn_incremental needs for this cache and batch shape (host-only, >= 0;
- * < 0 on bad arguments).  The workspace is device memory, 256-byte aligned, needs no
+/* Workspace mts_attn_incremental makes use of for this cache and batch shape (host-only, >= 0;
+ * < 0 on bad arguments).  Calls with short new segments are refused with MTS_ERR_WORKSPACE if they get
+ * less; calls with long ones (>= 256 new tokens of one user, >= 128 on average) also run with less or
+ * none, slower where few users or one long history would leave most of the chip idle.  The workspace is device memory, 256-byte aligned, needs no
  * initialisation and may be reused by later calls on the same stream (never by calls that
  * overlap in time). */
 int64_t mts_attn_workspace_bytes(const mts_cache_desc* cache, const mts_batch_meta* meta);
@@ -196,8 +198,10 @@ int64_t mts_attn_workspace_bytes(const mts_cache_desc* cache, const mts_batch_me
  */
 enum { MTS_ATTN_KERNEL_AUTO = 0, MTS_ATTN_KERNEL_STREAMING = 1, MTS_ATTN_KERNEL_PREFILL = 2, MTS_ATTN_KERNEL_PLAIN = 3 };
 typedef struct mts_attn_tuning {
-  int32_t min_tiles; /* least kv tiles (32 tokens) of a wavefront's share in the streaming kernel */
-  int32_t max_waves; /* most wavefronts of a streaming launch (multiple of 4, <= 1024) */
+  int32_t min_tiles; /* least kv tiles (32 tokens) of a wavefront's share in the streaming kernel, of a
+                        workgroup's share in a split dense-prefill launch */
+  int32_t max_waves; /* most wavefronts of a streaming launch (multiple of 4, <= 1024); a dense-prefill
+                        launch is split over max_waves / 4 workgroups (<= 512) */
   int32_t pair_cost; /* schedule allowance per (query tile, head), in tiles */
   int32_t kernel;    /* MTS_ATTN_KERNEL_*: force the split-kv streaming kernel, the dense-prefill kernel
                         (where it applies) or the plain fp32-accumulate kernel */
@@ -228,9 +232,9 @@ int32_t mts_attn_incremental(const mts_cache_desc* cache, int32_t layer, const v
  * Same operation, arguments, preconditions and results as mts_attn_incremental, but the split-kv
  * partials live in a buffer the library owns: a file-scope device array of
  * MTS_NOALLOC_SCRATCH_BYTES, one copy on every GPU the library is loaded on, held until the
- * process ends.  The call allocates and frees nothing.  Shapes whose workspace
- * (mts_attn_workspace_bytes) exceeds that size are refused with MTS_ERR_WORKSPACE before anything
- * is launched.  All calls on one GPU share the one buffer: calls that overlap in time on the same
+ * process ends.  The call allocates and frees nothing.  Shapes that cannot do without a larger
+ * workspace are refused with MTS_ERR_WORKSPACE before anything is launched; shapes that also run
+ * without one (long new segments, fp32) do not touch the buffer.  All calls on one GPU share the one buffer: calls that overlap in time on the same
  * GPU (different streams, different host threads) race and give wrong results; calls ordered on
  * one stream are safe.  The first call on a device looks the buffer's address up in the runtime:
  * make it outside stream capture.

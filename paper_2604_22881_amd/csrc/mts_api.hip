@@ -165,6 +165,42 @@ int32_t set_error(int32_t code, const char* fmt, ...) {
 // mts_attn_set_tuning: 0 = automatic
 std::atomic<int> g_tune_min_tiles{0}, g_tune_max_waves{0}, g_tune_pair_cost{0}, g_tune_kernel{0};
 
+// two partial blocks (leading and trailing piece) of a workgroup of a split prefill launch
+static int64_t prefill_partial_bytes(const PoolGeom& g) {
+  return 2ll * attn_prefill_block(g) * (g.D + 2) * (int64_t)sizeof(float);
+}
+
+// Whether the prefill kernel splits the call's work evenly over a persistent launch, or runs one
+// workgroup per (user, head, query block).
+static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b) {
+  const int64_t max_tiles = ((int64_t)b.max_total_len + 31) / 32 + 1;
+  const int QB = attn_prefill_block(g);
+  const int64_t blocks = (int64_t)g.H * (b.total_new / QB + b.batch);        // at most
+  // allowance of a block and least share, in tile steps: swept 3..16 and 12..24, flat within 5 %
+  p.pair_cost = 10;
+  if (const int v = g_tune_pair_cost.load(std::memory_order_relaxed); v > 0) p.pair_cost = v < 64 ? v : 64;
+  p.min_tiles = 24;
+  if (const int v = g_tune_min_tiles.load(std::memory_order_relaxed); v >= 1) p.min_tiles = v;
+  if (b.batch > kPrefillSplitMaxBatch || blocks * (max_tiles + p.pair_cost) >= (1ll << 31)) return;
+  int wgs = kPrefillMaxWgs;
+  if (const int v = g_tune_max_waves.load(std::memory_order_relaxed); v >= 4) {   // forces the split
+    wgs = v / 4 < wgs ? v / 4 : wgs;
+  } else {
+    // Unsplit, the longest block bounds the launch (0.62 us per 32-token step of a workgroup alone
+    // on its CU); split, the even share does (1.2 us per step with two on a CU), plus about 20 us
+    // for the partial blocks and the merge launch.  Measured at head_dim 128, steps per workgroup s
+    // against steps of the longest block L (us unsplit / split): s 27, L 163: 107 / 58;
+    // s 36, L 375: 215 / 100; s 66, L 129: 122 / 104; s 30, L 60: 57 / 66; s 132, L 129: 165 / 184;
+    // s 4, L 32: 25 / 33.  The two meet near s = L - 32.
+    const double mean_total = (double)b.total_pages * g.S / b.batch, mean_new = (double)b.total_new / b.batch;
+    const double steps = (double)blocks * (mean_total - 0.5 * mean_new) / 32;
+    if (steps / kPrefillMaxWgs >= (double)max_tiles - 32) return;
+  }
+  p.prefill_wgs = wgs;
+  p.ws_desc_bytes = roundup((int64_t)wgs * 32, 256);
+  p.ws_bytes = p.ws_desc_bytes + (int64_t)wgs * prefill_partial_bytes(g);
+}
+
 AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   AttnPlan p{};
   const int force = g_tune_kernel.load(std::memory_order_relaxed);
@@ -178,7 +214,11 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   bool prefill = max_new >= 256 && (int64_t)b.total_new >= 128ll * b.batch;
   if (force == MTS_ATTN_KERNEL_PREFILL) prefill = true;
   if (force == MTS_ATTN_KERNEL_STREAMING) prefill = false;
-  if (prefill && attn_prefill_applicable(g, b)) { p.use_prefill = true; return p; }
+  if (prefill && attn_prefill_applicable(g, b)) {
+    p.use_prefill = true;
+    plan_prefill_split(p, g, b);
+    return p;
+  }
   p.q_tile = roundup(max_new, 16) < 64 ? roundup(max_new, 16) : 64;
   p.q_tiles_max = (max_new + p.q_tile - 1) / p.q_tile;
   const int64_t items = (int64_t)b.batch * p.q_tiles_max;
@@ -204,7 +244,18 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   if (p.max_waves < 4) p.max_waves = 4;
   p.ws_desc_bytes = roundup((int64_t)p.max_waves * 32, 256);
   p.ws_bytes = p.ws_desc_bytes + (int64_t)p.max_waves * 2 * p.q_tile * (g.D + 2) * (int64_t)sizeof(float);
+  p.ws_required = p.ws_bytes;
   return p;
+}
+
+void fit_plan_to_workspace(AttnPlan& p, const PoolGeom& g, const void* workspace, int64_t workspace_bytes) {
+  if (p.prefill_wgs <= 0) return;
+  // a split prefill call takes as many workgroups as it has partial buffers for; with room for
+  // fewer than half of the CUs it runs unsplit, which needs none
+  if (!workspace || !aligned(workspace, 256)) { p.prefill_wgs = 0; return; }
+  const int64_t per_wg = prefill_partial_bytes(g);
+  const int64_t wgs = (workspace_bytes - p.ws_desc_bytes) / per_wg;
+  if (wgs < p.prefill_wgs) p.prefill_wgs = wgs < 128 ? 0 : (int32_t)(wgs / 8 * 8);
 }
 
 }  // namespace mts
@@ -403,21 +454,22 @@ int32_t attention_call(const char* name, const mts_cache_desc* cache, int32_t la
     if (!aligned(k_new, 16) || !aligned(v_new, 16))
       return fail(MTS_ERR_INVALID_ARG, "k_new / v_new is not 16-byte aligned");
   }
-  const mts::AttnPlan plan = mts::plan_attention(g, b);
+  mts::AttnPlan plan = mts::plan_attention(g, b);
   if (plan.too_large)
     return fail(MTS_ERR_UNSUPPORTED, "batch %d exceeds 4096 users, batch x ceil(max_new %d / 64) exceeds 16384 "
                 "query tiles, or the call has 2^31 or more kv tiles", b.batch, b.max_new);
-  if (plan.ws_bytes > 0) {
-    if (!workspace) return fail(MTS_ERR_WORKSPACE, "workspace is NULL but %lld bytes are needed", (long long)plan.ws_bytes);
-    if (workspace_bytes < plan.ws_bytes)
+  if (plan.ws_required > 0) {
+    if (!workspace) return fail(MTS_ERR_WORKSPACE, "workspace is NULL but %lld bytes are needed", (long long)plan.ws_required);
+    if (workspace_bytes < plan.ws_required)
       return fail(MTS_ERR_WORKSPACE, "workspace has %lld bytes, %lld needed", (long long)workspace_bytes,
-                  (long long)plan.ws_bytes);
+                  (long long)plan.ws_required);
     if (!aligned(workspace, 256)) return fail(MTS_ERR_WORKSPACE, "workspace is not 256-byte aligned");
   }
+  mts::fit_plan_to_workspace(plan, g, workspace, workspace_bytes);
   const float scale = sm_scale > 0.f ? sm_scale : 1.0f / sqrtf((float)g.D);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (plan.use_mfma && !plan.use_prefill && !(unappended && !rows_fit_32bit(g, b)))
-    return hip_status(mts::launch_attn_mfma(g, plan, q, out, b, scale, inv_norm, plan.ws_bytes > 0 ? workspace : nullptr, s,
+    return hip_status(mts::launch_attn_mfma(g, plan, q, out, b, scale, inv_norm, workspace, s,
                                             unappended ? k_new : nullptr, unappended ? v_new : nullptr, hist), name);
   if (hist)
     return fail(MTS_ERR_UNSUPPORTED, "histories in the onload buffer are read by the streaming bf16 kernel only "
@@ -430,7 +482,7 @@ int32_t attention_call(const char* name, const mts_cache_desc* cache, int32_t la
     if (e != hipSuccess) return hip_status(e, name);
   }
   if (plan.use_mfma && plan.use_prefill)
-    return hip_status(mts::launch_attn_prefill(g, q, out, b, scale, inv_norm, s), name);
+    return hip_status(mts::launch_attn_prefill(g, plan, q, out, b, scale, inv_norm, workspace, s), name);
   return hip_status(mts::launch_attn_generic(g, q, out, b, scale, inv_norm, s), name);
 }
 
@@ -455,15 +507,20 @@ int32_t mts_attn_incremental_noalloc(const mts_cache_desc* cache, int32_t layer,
   if ((st = check_meta(meta, true, true, &b)) != MTS_OK) return st;
   const mts::AttnPlan plan = mts::plan_attention(g, b);
   if (plan.too_large) return fail(MTS_ERR_UNSUPPORTED, "too many query tiles or kv tiles for one call");
-  if (plan.ws_bytes > kScratchBytes)
+  if (plan.ws_required > kScratchBytes)
     return fail(MTS_ERR_WORKSPACE, "this shape needs %lld bytes of scratch, the library-owned buffer of "
                 "mts_attn_incremental_noalloc holds %lld: use mts_attn_incremental with a workspace",
-                (long long)plan.ws_bytes, (long long)kScratchBytes);
+                (long long)plan.ws_required, (long long)kScratchBytes);
   if (b.batch == 0 || b.total_new == 0) return MTS_OK;
-  void* ws = scratch_on_current_device();
-  if (!ws) return MTS_ERR_HIP;
+  // the scratch only goes to the shapes that cannot do without it: the others stay independent of
+  // one another
+  void* ws = nullptr;
+  if (plan.ws_required > 0) {
+    ws = scratch_on_current_device();
+    if (!ws) return MTS_ERR_HIP;
+  }
   return attention_call("mts_attn_incremental_noalloc launch", cache, layer, q, out, meta, sm_scale, 0.f, ws,
-                        kScratchBytes, stream);
+                        ws ? kScratchBytes : 0, stream);
 }
 
 int32_t mts_attn_pointwise(const mts_cache_desc* cache, int32_t layer, const void* q, void* out,

@@ -56,7 +56,13 @@ struct AttnPlan {
   int32_t max_waves;     // most wavefronts the launch may use (sizes the partial buffers)
   int64_t ws_desc_bytes; // per-wavefront merge descriptors at the start of the workspace
   int64_t ws_bytes;      // whole workspace
+  int64_t ws_required;   // what the call cannot do without (the rest only lets it split further)
+  int32_t prefill_wgs;   // prefill kernel: workgroups of a split launch, 0 = one per query block
 };
+// Fits the plan to the workspace that the caller handed over (any pointer, any size).
+void fit_plan_to_workspace(AttnPlan& p, const PoolGeom& g, const void* workspace, int64_t workspace_bytes);
+constexpr int kPrefillMaxWgs = 512;          // 256 CUs x 2 resident workgroups
+constexpr int kPrefillSplitMaxBatch = 1024;  // users whose schedule a workgroup keeps in LDS
 AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b);
 constexpr int kAttnMaxWaves = 1024;   // 256 CUs x 4 SIMDs: one wavefront per SIMD
 
@@ -66,8 +72,9 @@ constexpr int kAttnMaxWaves = 1024;   // 256 CUs x 4 SIMDs: one wavefront per SI
 hipError_t launch_attn_generic(const PoolGeom& g, const void* q, void* out, const BatchDev& b,
                                float sm_scale, float inv_norm, hipStream_t stream);
 bool attn_prefill_applicable(const PoolGeom& g, const BatchDev& b);
-hipError_t launch_attn_prefill(const PoolGeom& g, const void* q, void* out, const BatchDev& b,
-                               float sm_scale, float inv_norm, hipStream_t stream);
+int attn_prefill_block(const PoolGeom& g);
+hipError_t launch_attn_prefill(const PoolGeom& g, const AttnPlan& plan, const void* q, void* out, const BatchDev& b,
+                               float sm_scale, float inv_norm, void* workspace, hipStream_t stream);
 // Prefixes still in the contiguous onload buffer (device arrays; see mts_attn_incremental_staged).
 struct StagedHistories {
   const void*    rows;        // the layer's runs, [2][n][H][D] each

@@ -1,0 +1,93 @@
+"""The split launch of the dense-prefill kernel (long new segments, work cut evenly over a persistent
+launch): shares that cut blocks once, many times and not at all, shares that walk through several
+blocks, heads and users, users without new tokens, pieces without a visible key, every workspace size."""
+import numpy as np
+import pytest
+
+import mts_workloads as W
+import oracle
+from conftest import KERNEL_PREFILL
+from helpers import as_values, draw_step_data
+from test_gpu_parity import FILL, _harness, _oracle_store, check_attention
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # name: (D, S, prefix, new)
+    "one_user": (128, 16, [0], [389]),                            # 128-query blocks, a ragged last one
+    "one_user_d64": (64, 32, [31], [513]),                        # 256-query blocks
+    "mixed": (128, 32, [1500, 0, 700, 33, 0], [8, 300, 0, 1, 127]),
+    "mixed_d64": (64, 64, [0, 1291, 5, 640], [600, 17, 0, 64]),
+}
+SPLITS = {
+    "one_step_shares": dict(min_tiles=1, max_waves=1024, pair_cost=1),
+    "one_workgroup": dict(max_waves=4),
+    "odd_shares": dict(min_tiles=3, max_waves=28, pair_cost=7),
+    "xcd_shares": dict(min_tiles=2, max_waves=32),
+}
+
+
+def _workload(name):
+    D, S, prefix, new = CASES[name]
+    return W.custom_workload(name, 300 + len(name), "bf16", 1, 2, D, S, prefix, new, chunk_tokens=1024)
+
+
+@pytest.mark.parametrize("split", list(SPLITS))
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_prefill_matches_oracle(name, split, attn_tuning):
+    attn_tuning(kernel=KERNEL_PREFILL, **SPLITS[split])
+    G, w = _harness(), _workload(name)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    assert step.ws_bytes > 0
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    check_attention(w, step.attention(data, 0), ref)
+    inv = 1.0 / float(w.total_lens.max())
+    ref = oracle.attn_pointwise(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr, inv)
+    check_attention(w, step.attention_pointwise(data, 0, inv), ref)
+
+
+def test_split_prefill_with_less_or_no_workspace():
+    """A call that would split runs with any workspace: fewer shares, then none, the same result."""
+    import torch
+    import paper_2604_22881_amd as mts
+    G = _harness()
+    w = W.custom_workload("little_room", 11, "bf16", 1, 2, 64, 16, [0, 2200], [1300, 40], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    store = _oracle_store(w, data)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    assert step.ws_bytes > 0
+    full, q = step.ws_bytes, G.to_dev(data["q"][0])
+    for ws, nbytes in ((step.ws, full), (step.ws, full // 3), (step.ws, 1000), (step.ws[16:], full - 16), (None, 0)):
+        out = torch.full((w.total_new, w.heads, w.head_dim), -1, dtype=q.dtype, device=G.DEV)
+        mts.mts_attn_incremental(step.cache.desc, 0, q, out, step.batch.meta, 0.0, ws, nbytes)
+        torch.cuda.synchronize()
+        check_attention(w, G.to_host(out, w.np_dtype), ref)
+
+
+def test_split_prefill_redoes_a_piece_whose_reference_overflows(attn_tuning):
+    """The reference max of a piece comes from its own first tile; a far larger key later in the
+    piece overflows the weights and the piece is redone with the exact max before the merge."""
+    attn_tuning(kernel=KERNEL_PREFILL, min_tiles=8, max_waves=64)
+    G = _harness()
+    w = W.custom_workload("late_key", 13, "bf16", 1, 2, 128, 16, [900, 0], [40, 260])
+    data = draw_step_data(w)
+    h = np.array(data["hist"][0][0])
+    h[0] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(h[0]) * 0.01)
+    h[0, 411] = W.f32_to_bf16_bits(np.full((w.heads, w.head_dim), 60.0, np.float32))
+    data["hist"][0][0] = h
+    data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    got = step.attention(data, 0)
+    assert np.isfinite(as_values(got)).all()
+    check_attention(w, got, ref)
