@@ -483,7 +483,8 @@ int32_t attention_call(const char* name, const mts_cache_desc* cache, int32_t la
   }
   if (plan.use_mfma && plan.use_prefill)
     return hip_status(mts::launch_attn_prefill(g, plan, q, out, b, scale, inv_norm, workspace, s), name);
-  return hip_status(mts::launch_attn_generic(g, q, out, b, scale, inv_norm, s), name);
+  return hip_status(g.es == 4 ? mts::launch_attn_f32(g, q, out, b, scale, inv_norm, s)
+                              : mts::launch_attn_generic(g, q, out, b, scale, inv_norm, s), name);
 }
 
 }  // namespace

@@ -45,7 +45,7 @@ hipError_t launch_append(const PoolGeom& g, const void* k_new, const void* v_new
 
 // Shape plan of one attention call: computed on the host from the scalar bounds only.
 struct AttnPlan {
-  bool    use_mfma;      // bf16 matrix-core kernel, else the plain fp32-accumulate kernel
+  bool    use_mfma;      // bf16 matrix-core kernel, else the plain kernel (bf16) or the fp32 one
   bool    use_prefill;   // workgroup-per-query-block kernel for long new segments (no workspace)
   bool    too_large;     // more (user, query tile) items than the schedule can hold
   int32_t q_tile;        // queries per query tile (multiple of 16, <= 64)
@@ -71,6 +71,8 @@ constexpr int kAttnMaxWaves = 1024;   // 256 CUs x 4 SIMDs: one wavefront per SI
 // out = inv_norm * sum_j silu(sm_scale * q.k_j) v_j (no softmax statistics).
 hipError_t launch_attn_generic(const PoolGeom& g, const void* q, void* out, const BatchDev& b,
                                float sm_scale, float inv_norm, hipStream_t stream);
+hipError_t launch_attn_f32(const PoolGeom& g, const void* q, void* out, const BatchDev& b, float sm_scale,
+                           float inv_norm, hipStream_t stream);
 bool attn_prefill_applicable(const PoolGeom& g, const BatchDev& b);
 int attn_prefill_block(const PoolGeom& g);
 hipError_t launch_attn_prefill(const PoolGeom& g, const AttnPlan& plan, const void* q, void* out, const BatchDev& b,
