@@ -50,7 +50,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;   // one 16-byte fragment
 
 using merge_detail::MergeDesc;
-using merge_detail::attn_merge_kernel;
 
 constexpr int kTile = 32;        // kv tokens per step
 constexpr int kXcds = 8;
@@ -587,9 +586,8 @@ hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan
                        (int)(id_bytes / 4), plan.pair_cost, plan.min_tiles, ws_desc, ws_o, ws_ml);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_merge_kernel<D, PW>), dim3((unsigned)plan.prefill_wgs, kBlockQ * (D / 4) / 256), dim3(256), 0,
-                       stream, out, c, inv_norm, kBlockQ, g.H, ws_desc, ws_o, ws_ml);
-    return hipGetLastError();
+    return merge_detail::launch_merge<D, PW>(out, c, inv_norm, kBlockQ, g.H, plan.prefill_wgs,
+                                             (int64_t)g.H * (b.total_new / kBlockQ + b.batch), ws_desc, ws_o, ws_ml, stream);
   }
   const hipError_t attr = allow_lds<D, PFD, WPS, NQB, PW, false>();
   if (attr != hipSuccess) return attr;

@@ -1,0 +1,91 @@
+"""Share boundaries that the streaming kernel closes inside a workgroup: pairs that end in the next
+wavefront's share, span several wavefronts, whole workgroups or several of them, pairs cut inside their
+schedule allowance; and the per-wavefront partials that a schedule of very many users falls back to."""
+import numpy as np
+import pytest
+
+import mts_workloads as W
+import oracle
+from conftest import KERNEL_STREAMING
+from helpers import as_values, draw_step_data
+from test_gpu_parity import FILL, _harness, _oracle_store, check_attention
+
+pytestmark = pytest.mark.gpu
+
+# shares of one to a few tiles over 95-tile, 22-tile and single-tile pairs; launches of one workgroup,
+# of few, and of as many as the shares fill; allowances that shares begin and end in
+PLANS = [dict(min_tiles=1, pair_cost=1), dict(min_tiles=2, pair_cost=3), dict(min_tiles=5, pair_cost=9),
+         dict(max_waves=4, pair_cost=1), dict(max_waves=28, pair_cost=4), {}]
+
+
+def _check_all_forms(w, step, data):
+    store = _oracle_store(w, data)
+    args = (store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    ref = oracle.attn_incremental(*args)
+    inv = 1.0 / float(w.total_lens.max())
+    pw = oracle.attn_pointwise(*args, inv)
+    yield lambda: check_attention(w, step.attention_unappended(data, 0), ref)
+    yield lambda: check_attention(w, step.attention(data, 0), ref)
+    yield lambda: check_attention(w, step.attention_pointwise(data, 0, inv), pw)
+    yield lambda: check_attention(w, step.attention_unappended(data, 0, inv_norm=inv), pw)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("top", [16, 40, 64])
+def test_joined_pieces_match_oracle(D, top, attn_tuning):
+    import torch
+    import paper_2604_22881_amd as mts
+    G = _harness()
+    w = W.custom_workload("join", 40 + D + top, "bf16", 1, 3, D, 16, [3030, 5, 0, 700, 31, 64, 1],
+                          [top, 1, min(33, top), 16, 1, 0, top - 7], chunk_tokens=1024)
+    data = draw_step_data(w)
+    attn_tuning(kernel=KERNEL_STREAMING)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    for check in _check_all_forms(w, step, data):
+        for plan in PLANS:
+            attn_tuning(kernel=KERNEL_STREAMING, **plan)
+            need = mts.mts_attn_workspace_bytes(step.cache.desc, step.batch.meta)
+            if need > step.ws_bytes:
+                step.ws, step.ws_bytes = torch.full((need,), 0xA5, dtype=torch.uint8, device=G.DEV), need
+            check()
+
+
+def test_joined_piece_with_a_far_larger_reference(attn_tuning):
+    """One piece of a cut pair holds a key that outweighs everything in the others: the fold scales
+    them down to nothing without overflow."""
+    attn_tuning(kernel=KERNEL_STREAMING, min_tiles=2, pair_cost=1)
+    G = _harness()
+    w = W.custom_workload("late_key", 13, "bf16", 1, 2, 64, 16, [900], [40])
+    data = draw_step_data(w)
+    h = np.array(data["hist"][0][0])
+    h[0] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(h[0]) * 0.01)
+    h[0, 411] = W.f32_to_bf16_bits(np.full((w.heads, w.head_dim), 60.0, np.float32))
+    data["hist"][0][0] = h
+    data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    store = _oracle_store(w, data)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    got = step.attention(data, 0)
+    assert np.isfinite(as_values(got)).all()
+    check_attention(w, got, ref)
+
+
+def test_schedule_of_many_users_leaves_no_room_to_join(attn_tuning):
+    """head_dim 128, 64-query tiles: beyond about 1100 users (unappended; 3300 from the pool) the
+    schedule and the handed-over pieces do not fit the LDS together."""
+    attn_tuning(kernel=KERNEL_STREAMING)
+    G = _harness()
+    rng = np.random.default_rng(3)
+    prefix, new = rng.integers(0, 12, 1300), np.ones(1300, np.int64)
+    prefix[[3, 700]], new[[3, 5, 700]] = (1500, 400), (64, 50, 33)
+    w = W.custom_workload("many", 9, "bf16", 1, 1, 128, 16, list(prefix), list(new), chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    for check in _check_all_forms(w, step, data):
+        check()
