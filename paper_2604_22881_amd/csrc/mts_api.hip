@@ -176,25 +176,30 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
   const int64_t max_tiles = ((int64_t)b.max_total_len + 31) / 32 + 1;
   const int QB = attn_prefill_block(g);
   const int64_t blocks = (int64_t)g.H * (b.total_new / QB + b.batch);        // at most
-  // allowance of a block and least share, in tile steps: swept 3..16 and 12..24, flat within 5 %
+  // allowance of a block and least share, in tile steps: swept 4..10 and 8..24, flat within 5 %
   p.pair_cost = 10;
   if (const int v = g_tune_pair_cost.load(std::memory_order_relaxed); v > 0) p.pair_cost = v < 64 ? v : 64;
-  p.min_tiles = 24;
+  p.min_tiles = 12;
   if (const int v = g_tune_min_tiles.load(std::memory_order_relaxed); v >= 1) p.min_tiles = v;
   if (b.batch > kPrefillSplitMaxBatch || blocks * (max_tiles + p.pair_cost) >= (1ll << 31)) return;
   int wgs = kPrefillMaxWgs;
   if (const int v = g_tune_max_waves.load(std::memory_order_relaxed); v >= 4) {   // forces the split
     wgs = v / 4 < wgs ? v / 4 : wgs;
   } else {
-    // Unsplit, the longest block bounds the launch (0.62 us per 32-token step of a workgroup alone
-    // on its CU); split, the even share does (1.2 us per step with two on a CU), plus about 20 us
-    // for the partial blocks and the merge launch.  Measured at head_dim 128, steps per workgroup s
-    // against steps of the longest block L (us unsplit / split): s 27, L 163: 107 / 58;
-    // s 36, L 375: 215 / 100; s 66, L 129: 122 / 104; s 30, L 60: 57 / 66; s 132, L 129: 165 / 184;
-    // s 4, L 32: 25 / 33.  The two meet near s = L - 32.
+    // Unsplit, a call takes as long as its longest block (0.55 us per 32-token step of a workgroup
+    // alone on its CU, 1.1 where the blocks fill the CUs twice) or as its work takes on all CUs (0.56
+    // us per step and CU); split, only the latter, plus about 20 us for the partial blocks, their
+    // merge and the second launch; neither is shorter than reading K and V once.  Measured, us
+    // unsplit / split (steps of the longest block, steps per CU; blocks): 93 / 51 (163, 54; 164),
+    // 190 / 75 (377, 93; 288), 52 / 41 (79, 27; 160), 49 / 49 (82, 47; 160), 38 / 42 (63, 34; 256),
+    // 29 / 35 (42, 18; 200), 53 / 75 (47, 78; 768), 150 / 151 (188, 225; 576); bound by reading K and V
+    // (160 us): 171-251, with luck in where the dispatcher puts them, / 177 (309, 197; 304).
     const double mean_total = (double)b.total_pages * g.S / b.batch, mean_new = (double)b.total_new / b.batch;
-    const double steps = (double)blocks * (mean_total - 0.5 * mean_new) / 32;
-    if (steps / kPrefillMaxWgs >= (double)max_tiles - 32) return;
+    const double filled = (double)g.H * ((double)b.total_new / QB + 0.5 * b.batch);
+    const double all_cus = 0.56 / 256 * (double)blocks * (mean_total - 0.5 * mean_new) / 32;
+    const double longest = (filled <= 288 ? 0.55 : 1.1) * (double)max_tiles;
+    const double read = (double)b.total_pages * (double)g.page_bytes / 5e6;
+    if (longest <= (all_cus > read ? all_cus : read) + 20) return;
   }
   p.prefill_wgs = wgs;
   p.ws_desc_bytes = roundup((int64_t)wgs * 32, 256);

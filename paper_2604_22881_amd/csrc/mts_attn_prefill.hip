@@ -3,21 +3,35 @@
 // recompute baseline, Sec. 5.1), laid out for the case of MANY new tokens per user, where the
 // work is a dense contraction and K/V reuse across queries decides the speed.
 //
-// A workgroup (4 wavefronts) owns one (user, head, block of 4*16*NQB new tokens): wavefront w
-// takes queries 16*NQB*w .. 16*NQB*(w+1)-1 of the block.  All four walk the same kv tiles, so each
-// 32-token K/V tile is fetched from global memory ONCE per workgroup: every wavefront loads a
-// quarter of the tile's 16-byte MFMA fragments, parks them in LDS in fragment order (lane l of
-// fragment f at f*1 KiB + l*16 B: reads and writes are conflict-free), and after one barrier
-// all four read the whole tile back as ready-made operands.  Two LDS stages, one barrier per
-// tile; global loads run PFD tiles ahead through a register ring, and the block's page ids are
-// copied to LDS once, so that no load in the loop depends on another load.
+// A workgroup (4 wavefronts) owns one (user, head, block of 128*NQ new tokens): wavefront w takes
+// queries 32*NQ*w .. 32*NQ*(w+1)-1 of the block.  All four walk the same kv tiles, so each 32-token
+// K/V tile is fetched from global memory ONCE per workgroup: every wavefront moves a quarter of it
+// straight into LDS (16 bytes per lane, no registers), in fragment order (lane l of fragment f at
+// f*1 KiB + l*16 B), so that all reads back are whole, conflict-free operands.  The block's page ids
+// are copied to LDS once, so that no load in the loop depends on another load.
 //
-// Operand flow, pool layout and the fixed-reference softmax are those of the streaming kernel
-// (S^T = K Q^T, O^T = V^T P^T with v_mfma_f32_16x16x32_bf16; reference max from the first tile,
-// no rescaling; an overflowed denominator makes the whole workgroup redo its block with the
-// exact max, found by a K-only pass).  Workgroups of one (user, head) land on one XCD, longest
-// block first, so that its K/V stays in that XCD's L2 while the blocks re-read it.  Every block
-// writes its output rows itself; nothing is merged.
+// Operand flow: S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16; queries are the columns,
+// so a lane's 16 scores belong to ONE query, and the order in which a tile's tokens are the rows of
+// S^T makes them 8 consecutive tokens of either sub-block: the two operands of P.V without a shuffle.
+//
+// Pipeline: a stage of the three in LDS holds the values of tile t and the keys of tile t+2.  Step t
+// fetches the stage of step t+2, reads its values, multiplies the keys of tile t+1 (in registers since
+// the step before) while the vector units take the weights of tile t, then reads the keys of tile t+2
+// while the matrix cores work on P.V.  One barrier per step, across which the newest fetch stays in
+// flight.
+//
+// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1135 to
+// 1165 us (942-970 TFLOP/s at about 1.93 GHz), 959 us on zeros; a library matrix product of 8192^3
+// reaches 1250 TFLOP/s here.  With v_mfma_f32_16x16x32_bf16, tiles parked from registers and no
+// pipelining across tiles the same call took 1163 to 1200 us (1018 on zeros), 64-dim heads 697 (632
+// now), one user of 5189 tokens x 4 heads 55.5 (51).  Tried and slower: 256-query blocks of eight
+// wavefronts (1192 against 1162), raised wavefront priority around the matrix work (1-3 %).
+//
+// The softmax reference is fixed, as in the streaming kernel (max of the first tile, no rescaling; an
+// overflowed denominator makes the whole workgroup redo its block with the exact max, found by a
+// K-only pass); the denominator sums the rounded weights in fp32 (v_dot2_f32_bf16 against ones).
+// Workgroups of one (user, head) land on one XCD, longest block first, so that its K/V stays in that
+// XCD's L2 while the blocks re-read it.
 //
 // SPLIT is the form for calls that would leave the chip idle that way: a single first-time user
 // (fewer blocks than CUs, the longest of them the whole launch), or a batch in which some users
@@ -26,10 +40,10 @@
 // contiguous share of it, and a block that a share boundary cuts is written as unnormalised fp32
 // pieces that a merge kernel finishes.  Every workgroup derives the schedule by itself from the
 // device-resident lengths (a prefix sum over the users in LDS; positions inside a user are closed
-// forms).  Measured, attention of one layer, head_dim 128: 1 user x 5189 new tokens x 4 heads
-// 107 -> 58 us (kernel 49 + merge 9); 6 users with 4-12 K histories and 8-64 new tokens beside 2
-// first-time ones 215 -> 98 us.  What is left there is a share's two or three block starts (about
-// 4 us each) and the fp32 pieces (64 KB each, about 45 MB written and read back).
+// forms).  Measured, attention of one layer, head_dim 128, unsplit -> split: 1 user x 5189 new tokens
+// x 4 heads 93 -> 51 us; 6 users with 4-12 K histories and 8-64 new tokens beside 2 first-time ones
+// 190 -> 75 us.  What is left there is a share's two or three block starts (about 4 us each) and the
+// fp32 pieces (64 KB each, about 45 MB written and read back).
 //
 // PW selects the pointwise aggregation out = inv_norm * sum_j silu(c * q.k_j) v_j: no reference
 // max, no denominator, no redo; hidden keys carry logit 0 (silu(0) = 0).
@@ -46,7 +60,9 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;   // one 16-byte fragment
 
 using merge_detail::MergeDesc;
@@ -61,43 +77,66 @@ __device__ __forceinline__ float fast_silu(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + fast_exp2(-1.4426950408889634f * x));
 }
 
-__device__ __forceinline__ float quad_row_max(float v) {
-  unsigned u = __float_as_uint(v);
+// over the 2 lanes that hold the same query (lane, lane^32)
+__device__ __forceinline__ float pair_max(float v) {
+  const unsigned u = __float_as_uint(v);
   auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  u = __float_as_uint(v);
-  auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float pair_sum(float v) {
+  const unsigned u = __float_as_uint(v);
+  auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
+// 16 bytes per lane from global memory to LDS byte address `to` (wavefront-uniform) + 16 * lane, without
+// passing through registers.  As an instruction of its own because the compiler, given the builtin,
+// waits for all such loads before any LDS read; here the waits are wait_and_barrier's.
+__device__ __forceinline__ void load_to_lds(const char* from, uint32_t to) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(from), "s"(to) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
+// Workgroup barrier that leaves the newest `kInFlight` loads of the wavefront in flight; its LDS
+// reads are done, and memory operations stay on their side of it.
+template <int kInFlight>
+__device__ __forceinline__ void wait_and_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((kInFlight & 15) | ((kInFlight >> 4) << 14) | (7 << 4));   // vmcnt(kInFlight) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // SPLIT: a persistent launch over one sequence of tile steps (see the head of the file) instead of
 // one workgroup per (user, head, query block).
-template <int D, int PFD, int WPS, int kNQB, bool PW, bool SPLIT>
-__global__ __launch_bounds__(256, WPS) void attn_prefill_kernel(PoolGeom g, BatchDev b,
+template <int D, int NST, int NQ, bool PW, bool SPLIT>
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchDev b,
                                                                 const uint16_t* __restrict__ q,
                                                                 uint16_t* __restrict__ out, float c, float inv_norm,
-                                                                int q_blocks_max, int n_pairs, int id_cap,
+                                                                int q_blocks_max, int n_pairs, int pair_group, int id_cap,
                                                                 int block_cost, int min_steps,
                                                                 MergeDesc* __restrict__ ws_desc,
                                                                 float* __restrict__ ws_o, float* __restrict__ ws_ml) {
-  constexpr int kWaveQ = 16 * kNQB;    // queries per wavefront
+  constexpr int kWaveQ = 32 * NQ;      // queries per wavefront
   constexpr int kBlockQ = 4 * kWaveQ;  // new tokens per workgroup
   constexpr int kBlockTiles = kBlockQ / kTile;
-  constexpr int KS = D / 32;           // k-steps of Q.K
-  constexpr int DB = D / 16;           // 16-dim blocks of the output
-  constexpr int FR = 2 * KS + DB;      // 16-byte fragments per lane and tile: K (half, step), then V (dim block)
+  constexpr int KS = D / 16;           // k-steps of Q.K
+  constexpr int DB = D / 32;           // 32-dim blocks of the output
+  constexpr int FR = KS + 2 * DB;      // 1 KiB fragments of a tile: K (step), then V (dim block, sub-block)
   constexpr int FQ = FR / 4;           // fragments each wavefront fetches: FQ/2 of K, FQ/2 of V
-  static_assert(FQ % 2 == 0 && FQ >= 2, "fragment split");
+  static_assert(FQ % 2 == 0 && FQ >= 2 && NST == 3, "fragment split");
 
   extern __shared__ int s_ids[];       // physical page of every logical page the block reads
-  __shared__ u32x4 stage[2][FR * 64];  // two tiles in fragment order
+  __shared__ u32x4 stage[NST][FR * 64];  // tiles in fragment order: lane l of fragment f at f * 1 KiB + l * 16 B
   __shared__ int redo_flag;
   __shared__ int wave_total[4];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = uniform(tid >> 6);
-  const int r = lane & 15, gq = lane >> 4;
+  const int r = lane & 31, hf = lane >> 5;
   const int H = g.H, S = g.S;
 
   // The block (or, SPLIT, the segment of a block) being worked on.
@@ -157,11 +196,13 @@ __global__ __launch_bounds__(256, WPS) void attn_prefill_kernel(PoolGeom g, Batc
     pos = lo;
     if (tid == 0) ws_desc[wid].valid = 0;
   } else {
-    // blockIdx -> XCD is round-robin: all blocks of one (user, head) share blockIdx % 8
-    const int slot = blockIdx.x / kXcds;
-    const int pair = (slot / q_blocks_max) * kXcds + (blockIdx.x % kXcds);
+    // blockIdx -> XCD is round-robin: all blocks of one (user, head) share blockIdx % 8.  An XCD
+    // takes `pair_group` pairs at a time, the longest causal rows of all of them first.
+    const int slot = blockIdx.x / kXcds, per_group = pair_group * q_blocks_max;
+    const int in_group = slot % per_group;
+    const int pair = (slot / per_group * pair_group + in_group % pair_group) * kXcds + (blockIdx.x % kXcds);
     if (pair >= n_pairs) return;
-    qblk = q_blocks_max - 1 - (slot % q_blocks_max);              // longest causal rows first
+    qblk = q_blocks_max - 1 - in_group / pair_group;
     u = pair / H;
     h = pair % H;
     tok0 = b.new_indptr[u];
@@ -239,167 +280,157 @@ __global__ __launch_bounds__(256, WPS) void attn_prefill_kernel(PoolGeom g, Batc
   const int64_t v_off = (int64_t)S * D * 2;
   const char* head_base = g.layer_base + (int64_t)h * 2 * S * D * 2;
 
-  auto tile_bases = [&](int tile, const char*& kb0, const char*& kb1) __attribute__((always_inline)) {
-    const int sb0 = tile * 2, sb1 = sb0 + 1;
-    const int id0 = s_ids[(sb0 >> g.sub_shift) - lp_beg], id1 = s_ids[(sb1 >> g.sub_shift) - lp_beg];
-    kb0 = head_base + (int64_t)id0 * g.page_bytes + (int64_t)(sb0 & sub_mask) * 16 * D * 2;
-    kb1 = head_base + (int64_t)id1 * g.page_bytes + (int64_t)(sb1 & sub_mask) * 16 * D * 2;
-  };
-  // K fragment (half hf, k-step s): rows 0-7 from sub-block 0, rows 8-15 from sub-block 1
-  auto k_ptr = [&](const char* kb0, const char* kb1, int hf, int s) __attribute__((always_inline)) {
-    return reinterpret_cast<const u32x4*>(((r < 8) ? kb0 : kb1) + (r & 7) * 16 +
-                                          ((hf * (D / 8) + 4 * s + gq) * 8) * 16);
-  };
-  // V^T fragment db: dim 16*db + r, tokens 8*gq .. +7 of the tile
-  auto v_ptr = [&](const char* kb0, const char* kb1, int db) __attribute__((always_inline)) {
-    return reinterpret_cast<const u32x4*>(((gq < 2) ? kb0 : kb1) + v_off + (r * 16 + (gq & 1) * 8) * 2 +
-                                          db * 16 * 16 * 2);
-  };
-
-  // Register ring: slot p holds this wavefront's quarter of tile j, j % PFD == p, on its way to
-  // LDS.  Fragment f = 4*j + wave: the first FQ/2 are K fragments, the rest V fragments.
-  u32x4 ring[PFD][FQ];
   const int last_tile = t_end - 1;
-  auto load = [&](auto slot_c, int tile) __attribute__((always_inline)) {
-    constexpr int p = decltype(slot_c)::value;
-    const char *kb0, *kb1;
-    tile_bases(tile < last_tile ? tile : last_tile, kb0, kb1);   // past the end: repeat (never used)
+  // K fragment s: lane (r, hf) holds dims 16 s + 8 hf .. + 7 of tile row r.  The row order makes the 16
+  // accumulator values of a lane its tokens 8 hf .. + 7 of sub-block 0, then of sub-block 1.
+  const int k_lane = ((((r >> 3) & 1) * (D / 8) + 2 * wave + hf) * 8 + (r & 7)) * 16;
+  // V^T fragment (db, sb): dim 32 db + r, tokens 8 hf .. + 7 of sub-block sb
+  const int64_t v_lane = v_off + (r * 2 + hf) * 16 + (wave >> 1) * 1024;
+  const uint32_t stage_lds = lds_address(&stage[0][0]) + wave * 1024;
+  // page ids of a tile (past the end: of the last one, whose data is then fetched again, never used)
+  auto page_ids = [&](int tile, int& id0, int& id1) __attribute__((always_inline)) {
+    const int sb0 = (tile < last_tile ? tile : last_tile) * 2;
+    id0 = s_ids[(sb0 >> g.sub_shift) - lp_beg];
+    id1 = s_ids[((sb0 + 1) >> g.sub_shift) - lp_beg];
+  };
+  // A stage holds the keys of tile `tile` and the values of the tile two before it.  Fetches this
+  // wavefront's quarter of it (fragments 4 j + wave) straight into LDS; the first two stages of a
+  // segment are keys only.
+  const char *v_1 = nullptr, *v_2 = nullptr;                     // the values of tiles tile - 1 and tile - 2
+  auto load = [&](int st, int tile, int id0, int id1, auto with_v) __attribute__((always_inline)) {
+    const int sb0 = (tile < last_tile ? tile : last_tile) * 2;
+    const uint32_t page = (uint32_t)g.page_bytes;                // at most 2 GiB: 65535 heads of 64 x 128 bf16
+    const char* kb0 = head_base + (uint64_t)(uint32_t)uniform(id0) * page + (uint32_t)((sb0 & sub_mask) * 16 * D * 2);
+    const char* kb1 = head_base + (uint64_t)(uint32_t)uniform(id1) * page + (uint32_t)(((sb0 + 1) & sub_mask) * 16 * D * 2);
+    const char* ka = (r < 16 ? kb0 : kb1) + k_lane;
+    const char* va = v_2 + v_lane;
+    v_2 = v_1;
+    v_1 = (wave & 1) ? kb1 : kb0;
+    const uint32_t to = stage_lds + st * (FR * 1024);
 #pragma unroll
     for (int j = 0; j < FQ / 2; ++j) {
-      const int f = 4 * j + wave;
-      ring[p][j] = *k_ptr(kb0, kb1, f / KS, f % KS);
+      load_to_lds(ka + j * 1024, to + 4 * j * 1024);
+      if constexpr (decltype(with_v)::value) load_to_lds(va + j * 2048, to + (KS + 4 * j) * 1024);
     }
-#pragma unroll
-    for (int j = FQ / 2; j < FQ; ++j) ring[p][j] = *v_ptr(kb0, kb1, 4 * j + wave - 2 * KS);
-  };
-  auto park = [&](auto slot_c, int st) __attribute__((always_inline)) {
-    constexpr int p = decltype(slot_c)::value;
-#pragma unroll
-    for (int j = 0; j < FQ; ++j) stage[st][(4 * j + wave) * 64 + lane] = ring[p][j];
   };
 
-  // Q^T fragments: lane (r, gq) holds query q0+16*qb+r, dims 32*s + 8*gq .. +7.
-  bf16x8 qf[kNQB][KS];
+  // Q^T fragments: lane (r, hf) holds query q0 + 32 qb + r, dims 16 s + 8 hf .. + 7.
+  bf16x8 qf[NQ][KS];
 #pragma unroll
-  for (int qb = 0; qb < kNQB; ++qb) {
-    const int i = q0 + 16 * qb + r;
+  for (int qb = 0; qb < NQ; ++qb) {
+    const int i = q0 + 32 * qb + r;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       if (i < n_u) {
-        qf[qb][s] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)(tok0 + i) * H + h) * D + 32 * s + 8 * gq);
+        qf[qb][s] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)(tok0 + i) * H + h) * D + 16 * s + 8 * hf);
       } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) qf[qb][s][e] = (__bf16)0.0f;
       }
     }
   }
-  bf16x8 ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
 
-  f32x4 o[DB][kNQB];
-  f32x4 lacc[kNQB];                // softmax denominators (all 4 entries of a lane are equal)
-  float m[kNQB], mcq[kNQB];        // reference max: raw logit units / scaled for the base-2 exponent
+  f32x16 o[NQ][DB];
+  float l[NQ];                     // softmax denominators: this lane's tokens only
+  float m[NQ], mcq[NQ];            // reference max: raw logit units / scaled for the base-2 exponent
 #pragma unroll
-  for (int qb = 0; qb < kNQB; ++qb) { m[qb] = -INFINITY; mcq[qb] = 0.f; }
+  for (int qb = 0; qb < NQ; ++qb) { m[qb] = -INFINITY; mcq[qb] = 0.f; }
 
-  bf16x8 kf[2][KS];
-  bf16x8 vf[DB];
-  auto read_k = [&](int st) __attribute__((always_inline)) {
-#pragma unroll
-    for (int f = 0; f < 2 * KS; ++f) {
-      const u32x4 v = stage[st][f * 64 + lane];
-      kf[f / KS][f % KS] = *reinterpret_cast<const bf16x8*>(&v);
-    }
+  auto fragment = [&](int st, int f) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, stage[st][f * 64 + lane]);
   };
-  auto read_v = [&](int st) __attribute__((always_inline)) {
+  // S^T of query block qb; with `masked`, keys the query must not see (causal order among the new
+  // tokens) are set to -inf.
+  auto scores = [&](const bf16x8 (&kf)[KS], int qb, int tb, bool masked) __attribute__((always_inline)) {
+    f32x16 z;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const u32x4 v = stage[st][(2 * KS + db) * 64 + lane];
-      vf[db] = *reinterpret_cast<const bf16x8*>(&v);
-    }
-  };
-
-  // S^T of query block qb against kf.  The lane holds, for query q0+16*qb+r, keys
-  // tb + 8*gq + {0..3} (s0) and {4..7} (s1); with `masked`, keys the query must not see
-  // (causal order among the new tokens) are set to -inf.
-  auto scores = [&](int qb, int tb, bool masked, f32x4& s0, f32x4& s1) __attribute__((always_inline)) {
-    s0 = f32x4{0.f, 0.f, 0.f, 0.f};
-    s1 = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 16; ++e) z[e] = 0.f;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][s], qf[qb][s], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[1][s], qf[qb][s], s1, 0, 0, 0);
-    }
+    for (int s = 0; s < KS; ++s) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[qb][s], z, 0, 0, 0);
     if (masked) {
-      const int qpos = first_query_pos + 16 * qb + r;
-      const int kbase = tb + 8 * gq;
+      const int qpos = first_query_pos + 32 * qb + r;
+      const int kbase = tb + 8 * hf;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (kbase + e > qpos) s0[e] = PW ? 0.f : -INFINITY;
-        if (kbase + 4 + e > qpos) s1[e] = PW ? 0.f : -INFINITY;
+      for (int e = 0; e < 16; ++e)
+        if (kbase + 16 * (e >> 3) + (e & 7) > qpos) z[e] = PW ? 0.f : -INFINITY;
+    }
+    return z;
+  };
+  auto max16 = [](const f32x16& z) __attribute__((always_inline)) {
+    float v = z[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) v = fmaxf(v, z[e]);
+    return v;
+  };
+  // Weights of a tile from its scores, and their sum.
+  auto weights = [&](const f32x16& z, int qb, bf16x8 (&pf)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = z[8 * sb + e];
+        if constexpr (PW) pf[sb][e] = (__bf16)fast_silu(x * c);
+        else pf[sb][e] = (__bf16)fast_exp2(fmaf(x, c, -mcq[qb]));
+      }
+      if constexpr (!PW) {
+        // the rounded weights are summed, as P.V does
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const bf16x2 w = {pf[sb][e], pf[sb][e + 1]}, one = {(__bf16)1.0f, (__bf16)1.0f};
+          l[qb] = __builtin_amdgcn_fdot2_f32_bf16(w, one, l[qb], false);
+        }
       }
     }
   };
-  auto max8 = [](const f32x4& s0, const f32x4& s1) __attribute__((always_inline)) {
-    return fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                 fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
-  };
-  auto accumulate = [&](int qb, int tb, bool masked) __attribute__((always_inline)) {
-    f32x4 s0, s1;
-    scores(qb, tb, masked, s0, s1);
-    bf16x8 pf;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if constexpr (PW) {
-        pf[e] = (__bf16)fast_silu(s0[e] * c);
-        pf[4 + e] = (__bf16)fast_silu(s1[e] * c);
-      } else {
-        pf[e] = (__bf16)fast_exp2(fmaf(s0[e], c, -mcq[qb]));
-        pf[4 + e] = (__bf16)fast_exp2(fmaf(s1[e], c, -mcq[qb]));
-      }
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-      o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pf, o[db][qb], 0, 0, 0);
-    // row sums of the (rounded) weights on the matrix core: every row of ones . P^T
-    if constexpr (!PW) lacc[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf, lacc[qb], 0, 0, 0);
-  };
-  // One tile from LDS stage st for all four query blocks, with no branch between them.  Query
-  // blocks past the segment's end hold zero queries and are never written; a wavefront whose
-  // queries all lie before the tile would compute weights of exactly zero (step() skips those
-  // tiles in the causal tail).  MASKED adds what only
-  // the causal tail needs: the mask, and zeroing of V slots past the user's last token (they
-  // may hold anything).
-  auto compute = [&](auto masked_c, int st, int tile) __attribute__((always_inline)) {
+  // Step `t`: the scores of tile t+1, whose keys are in registers, go into z_next while the weights
+  // of tile t are taken from z; its values come from stage `st`, and so do the keys of tile t+2,
+  // which travel to registers while the matrix cores work on P.V.
+  // The barrier publishes the stage and retires every read of the one before it, which the fetch
+  // for step t+2 overwrites; the fetch for step t+1 stays in flight across it.
+  int next_id0 = 0, next_id1 = 0;      // page ids of the tile that the next step fetches
+  bf16x8 kf[KS];
+  auto step = [&](auto masked_c, int t, int st, f32x16 (&z)[NQ], f32x16 (&z_next)[NQ]) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    read_k(st);
-    read_v(st);
-    const int tb = tile * kTile;
-    if constexpr (MASKED) {
-      if (tb + kTile > T_u) {
+    wait_and_barrier<FQ>();
+    load(st == 0 ? NST - 1 : st - 1, t + 4, next_id0, next_id1, std::true_type{});
+    page_ids(t + 5, next_id0, next_id1);
+    // tiles past the wavefront's own last query hold no key it may see (the later wavefronts of
+    // the block still need them): it only helps to move them
+    const bool here = !MASKED || t < tiles_w, next = !MASKED || t + 1 < tiles_w;
+    bf16x8 vf[2 * DB];
+    if (here) {
+#pragma unroll
+      for (int f = 0; f < 2 * DB; ++f) vf[f] = fragment(st, KS + f);
+    }
+    if (next) {
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) z_next[qb] = scores(kf, qb, (t + 1) * kTile, MASKED);
+    }
+    if (here) {
+      bf16x8 pf[NQ][2];
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) weights(z[qb], qb, pf[qb]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) kf[s] = fragment(st, s);
+      const int tb = t * kTile;
+      if constexpr (MASKED) {                                      // slots past the user's last token may hold anything
+        if (tb + kTile > T_u) {
+#pragma unroll
+          for (int f = 0; f < 2 * DB; ++f)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (tb + 16 * (f & 1) + 8 * hf + e >= T_u) vf[f][e] = (__bf16)0.0f;
+        }
+      }
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (tb + 8 * gq + e >= T_u) vf[db][e] = (__bf16)0.0f;
-      }
+          for (int qb = 0; qb < NQ; ++qb)
+            o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * db + sb], pf[qb][sb], o[qb][db], 0, 0, 0);
     }
-#pragma unroll
-    for (int qb = 0; qb < kNQB; ++qb) accumulate(qb, tb, MASKED);
-  };
-  // Step `tile` (ring slot k = tile % PFD): compute it from its stage, move tile+1 from the ring
-  // to the other stage, refill that ring slot PFD tiles ahead.  The barrier both publishes
-  // tile+1 and retires every read of the stage that tile+2 will overwrite.
-  auto step = [&](auto masked_c, auto slot_c, int tile) __attribute__((always_inline)) {
-    constexpr int pn = (decltype(slot_c)::value + 1) % PFD;
-    const int st = (tile - t_beg) & 1;
-    // tiles past the wavefront's own last query hold no key it may see (the later wavefronts of
-    // the block still need them): it only helps to move them
-    if (!decltype(masked_c)::value || tile < tiles_w) compute(masked_c, st, tile);
-    park(std::integral_constant<int, pn>{}, st ^ 1);
-    load(std::integral_constant<int, pn>{}, tile + 1 + PFD);
-    __syncthreads();
   };
   // tiles below hide no key from any query of the block (its first wavefront sees the least)
   int fast_all = (P + Q0 + 1) / kTile;
@@ -410,75 +441,79 @@ __global__ __launch_bounds__(256, WPS) void attn_prefill_kernel(PoolGeom g, Batc
   __syncthreads();                                               // page table visible
   for (int attempt = 0; attempt < 2; ++attempt) {                // workgroup-uniform
 #pragma unroll
-    for (int qb = 0; qb < kNQB; ++qb) {
-      lacc[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int qb = 0; qb < NQ; ++qb) {
+      l[qb] = 0.f;
 #pragma unroll
-      for (int db = 0; db < DB; ++db) o[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[qb][db][e] = 0.f;
     }
     if (!PW && attempt == 1) {
       // exact max of every query over its whole visible range: K only, straight from global
-      float mx[kNQB];
+      float mx[NQ];
 #pragma unroll
-      for (int qb = 0; qb < kNQB; ++qb) mx[qb] = -INFINITY;
+      for (int qb = 0; qb < NQ; ++qb) mx[qb] = -INFINITY;
       for (int tile = t_beg; tile < tiles_w; ++tile) {         // tiles past tiles_w hold no visible key
-        const char *kb0, *kb1;
-        tile_bases(tile, kb0, kb1);
+        const int sb = tile * 2 + (r >> 4);
+        const char* ka = head_base + (int64_t)s_ids[(sb >> g.sub_shift) - lp_beg] * g.page_bytes +
+                         (int64_t)(sb & sub_mask) * 16 * D * 2 + k_lane - wave * 256;
+        bf16x8 kf[KS];
 #pragma unroll
-        for (int f = 0; f < 2 * KS; ++f) {
-          const u32x4 v = *k_ptr(kb0, kb1, f / KS, f % KS);
-          kf[f / KS][f % KS] = *reinterpret_cast<const bf16x8*>(&v);
-        }
-        const int tb = tile * kTile;
+        for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(ka + s * 256);
 #pragma unroll
-        for (int qb = 0; qb < kNQB; ++qb) {
-          f32x4 s0, s1;
-          scores(qb, tb, true, s0, s1);
-          mx[qb] = fmaxf(mx[qb], max8(s0, s1));
-        }
+        for (int qb = 0; qb < NQ; ++qb) mx[qb] = fmaxf(mx[qb], max16(scores(kf, qb, tile * kTile, true)));
       }
 #pragma unroll
-      for (int qb = 0; qb < kNQB; ++qb) {
-        m[qb] = quad_row_max(mx[qb]);
+      for (int qb = 0; qb < NQ; ++qb) {
+        m[qb] = pair_max(mx[qb]);
         mcq[qb] = (m[qb] == -INFINITY ? 0.f : m[qb]) * c;
       }
     }
 
-    // prologue: the first tile into stage 0, the next PFD into the ring
-    load(std::integral_constant<int, 0>{}, t_beg);
-    park(std::integral_constant<int, 0>{}, 0);
-    if constexpr (PFD > 1) load(std::integral_constant<int, 1 % PFD>{}, t_beg + 1);
-    if constexpr (PFD > 2) load(std::integral_constant<int, 2 % PFD>{}, t_beg + 2);
-    if constexpr (PFD > 3) load(std::integral_constant<int, 3 % PFD>{}, t_beg + 3);
-    load(std::integral_constant<int, 0>{}, t_beg + PFD);
-    __syncthreads();
-
-    if (!PW && attempt == 0) {
-      // reference max = max of the first tile; a query that sees none of its keys (a segment of a
-      // cut block that begins past it) gets -inf and weighs nothing
-      read_k(0);
+    // prologue: the keys of the first two tiles, the stage of the first step, the first tile's scores
+    auto fetch = [&](int st, int tile, auto with_v) __attribute__((always_inline)) {
+      page_ids(tile, next_id0, next_id1);
+      load(st, tile, next_id0, next_id1, with_v);
+    };
+    fetch(0, t_beg, std::false_type{});
+    fetch(1, t_beg + 1, std::false_type{});
+    fetch(2, t_beg + 2, std::true_type{});
+    wait_and_barrier<FQ + FQ / 2>();
+    f32x16 za[NQ], zb[NQ];
 #pragma unroll
-      for (int qb = 0; qb < kNQB; ++qb) {
-        f32x4 s0, s1;
-        scores(qb, t_beg * kTile, true, s0, s1);
-        m[qb] = quad_row_max(max8(s0, s1));
+    for (int s = 0; s < KS; ++s) kf[s] = fragment(0, s);
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+      za[qb] = scores(kf, qb, t_beg * kTile, true);
+      if (!PW && attempt == 0) {
+        // reference max = max of the first tile; a query that sees none of its keys (a segment of a
+        // cut block that begins past it) gets -inf and weighs nothing
+        m[qb] = pair_max(max16(za[qb]));
         mcq[qb] = (m[qb] == -INFINITY ? 0.f : m[qb]) * c;
       }
     }
+    wait_and_barrier<FQ>();
+    fetch(0, t_beg + 3, std::true_type{});
+    page_ids(t_beg + 4, next_id0, next_id1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = fragment(1, s);
 
-    int tile = t_beg;
-    while (tile + PFD <= fast_all) {                               // steady state: fully visible tiles
-      step(body, std::integral_constant<int, 0>{}, tile);
-      if constexpr (PFD > 1) step(body, std::integral_constant<int, 1>{}, tile + 1);
-      if constexpr (PFD > 2) step(body, std::integral_constant<int, 2>{}, tile + 2);
-      if constexpr (PFD > 3) step(body, std::integral_constant<int, 3>{}, tile + 3);
-      tile += PFD;
+    int tile = t_beg, st = 2;
+    auto after = [](int st) __attribute__((always_inline)) { return st == NST - 1 ? 0 : st + 1; };
+    while (tile + 2 < fast_all) {                                  // steady state: fully visible tiles
+      step(body, tile, st, za, zb);
+      st = after(st);
+      step(body, tile + 1, st, zb, za);
+      st = after(st);
+      tile += 2;
     }
-    for (; tile < t_end; tile += PFD) {                         // causal tail, and what is left over
-      step(tail, std::integral_constant<int, 0>{}, tile);
-      if constexpr (PFD > 1) { if (tile + 1 < t_end) step(tail, std::integral_constant<int, 1>{}, tile + 1); }
-      if constexpr (PFD > 2) { if (tile + 2 < t_end) step(tail, std::integral_constant<int, 2>{}, tile + 2); }
-      if constexpr (PFD > 3) { if (tile + 3 < t_end) step(tail, std::integral_constant<int, 3>{}, tile + 3); }
+    for (; tile < t_end; tile += 2) {                              // causal tail, and what is left over
+      step(tail, tile, st, za, zb);
+      st = after(st);
+      if (tile + 1 < t_end) step(tail, tile + 1, st, zb, za);
+      st = after(st);
     }
+    wait_and_barrier<0>();                                         // no load is in flight, no stage is read
 
     if constexpr (PW) break;                                     // no statistics, nothing to redo
     // A reference far below the true max shows up as an overflowed (or NaN) denominator of a
@@ -487,52 +522,62 @@ __global__ __launch_bounds__(256, WPS) void attn_prefill_kernel(PoolGeom g, Batc
     // accumulator values is infinite or NaN as soon as one of them is)
     bool bad = false;
 #pragma unroll
-    for (int qb = 0; qb < kNQB; ++qb) {
+    for (int qb = 0; qb < NQ; ++qb) {
+      l[qb] = pair_sum(l[qb]);
       float mag = 0.f;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) mag += fabsf(o[db][qb][k]);
-      bad |= (16 * qb + r < nq) && (!(lacc[qb][0] < 1e37f) || !(mag < 3.0e38f));
+        for (int e = 0; e < 16; ++e) mag += fabsf(o[qb][db][e]);
+      bad |= (32 * qb + r < nq) && (!(l[qb] < 1e37f) || !(mag < 3.0e38f));
     }
     if (tid == 0) redo_flag = 0;
     __syncthreads();
     if (bad) redo_flag = 1;
     __syncthreads();
     const int redo = redo_flag;
-    __syncthreads();                                             // everyone has read the flag and left the stages
+    __syncthreads();                                             // everyone has read the flag
     if (!redo) break;
   }
 
   if (!SPLIT || (t_beg == 0 && t_end == tiles_blk)) {
 #pragma unroll
-    for (int qb = 0; qb < kNQB; ++qb) {
-      const int qi = 16 * qb + r;
+    for (int qb = 0; qb < NQ; ++qb) {
+      const int qi = 32 * qb + r;
       if (qi < nq) {
-        const float inv = PW ? inv_norm : 1.0f / lacc[qb][0];
-        uint16_t* orow = out + ((int64_t)(tok0 + q0 + qi) * H + h) * D + 4 * gq;
+        const float inv = PW ? inv_norm : 1.0f / l[qb];
+        uint16_t* orow = out + ((int64_t)(tok0 + q0 + qi) * H + h) * D + 4 * hf;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          bf16x4 ob;
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int k = 0; k < 4; ++k) ob[k] = (__bf16)(o[db][qb][k] * inv);
-          *reinterpret_cast<bf16x4*>(orow + 16 * db) = ob;
-        }
+          for (int g8 = 0; g8 < 4; ++g8) {                         // accumulator rows 8 g8 + 4 hf .. + 3
+            bf16x4 ob;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) ob[k] = (__bf16)(o[qb][db][4 * g8 + k] * inv);
+            *reinterpret_cast<bf16x4*>(orow + 32 * db + 8 * g8) = ob;
+          }
       }
     }
   } else {
     const int slot = (pos == lo) ? 0 : 1;              // leading or trailing piece of this share
     const int64_t prow = ((int64_t)wid * 2 + slot) * kBlockQ + kWaveQ * wave;
 #pragma unroll
-    for (int qb = 0; qb < kNQB; ++qb) {
-      const int qi = 16 * qb + r;
+    for (int qb = 0; qb < NQ; ++qb) {
+      const int qi = 32 * qb + r;
       if (qi < nq) {
-        float* po = ws_o + (prow + qi) * D + 4 * gq;
+        float* po = ws_o + (prow + qi) * D + 4 * hf;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(po + 16 * db) = o[db][qb];
-        if (!PW && gq == 0) {
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int g8 = 0; g8 < 4; ++g8) {
+            f32x4 piece;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) piece[k] = o[qb][db][4 * g8 + k];
+            *reinterpret_cast<f32x4*>(po + 32 * db + 8 * g8) = piece;
+          }
+        if (!PW && hf == 0) {
           ws_ml[(prow + qi) * 2] = m[qb];
-          ws_ml[(prow + qi) * 2 + 1] = lacc[qb][0];
+          ws_ml[(prow + qi) * 2 + 1] = l[qb];
         }
       }
     }
@@ -558,46 +603,53 @@ __global__ __launch_bounds__(256, WPS) void attn_prefill_kernel(PoolGeom g, Batc
 // LDS of the schedule of a split launch: users' prefix sums, lengths and page offsets
 int64_t schedule_bytes(int batch) { return ((int64_t)4 * batch + 3) * 4; }
 
-template <int D, int PFD, int WPS, int NQB, bool PW, bool SPLIT>
+template <int D, int NST, int NQ, bool PW, bool SPLIT>
 hipError_t allow_lds() {
   static std::once_flag attr_once;                               // static + dynamic LDS may pass 64 KiB
   static hipError_t attr_status = hipSuccess;
   std::call_once(attr_once, [] {
-    attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_kernel<D, PFD, WPS, NQB, PW, SPLIT>),
+    attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_kernel<D, NST, NQ, PW, SPLIT>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize,
                                       kMaxIdBytes + (SPLIT ? (int)schedule_bytes(kPrefillSplitMaxBatch) : 0));
   });
   return attr_status;
 }
 
-template <int D, int PFD, int WPS, int NQB, bool PW>
+template <int D, int NST, int NQ, bool PW>
 hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan, const uint16_t* q, uint16_t* out,
                       float c, float inv_norm, int64_t id_bytes, void* workspace, hipStream_t stream) {
-  constexpr int kBlockQ = 64 * NQB;
+  constexpr int kBlockQ = 128 * NQ;
   if (plan.prefill_wgs > 0) {
-    const hipError_t attr = allow_lds<D, PFD, WPS, NQB, PW, true>();
+    const hipError_t attr = allow_lds<D, NST, NQ, PW, true>();
     if (attr != hipSuccess) return attr;
     char* ws = static_cast<char*>(workspace);
     MergeDesc* ws_desc = reinterpret_cast<MergeDesc*>(ws);
     float* ws_o = reinterpret_cast<float*>(ws + plan.ws_desc_bytes);
     float* ws_ml = ws_o + (int64_t)plan.prefill_wgs * 2 * kBlockQ * D;
-    hipLaunchKernelGGL((attn_prefill_kernel<D, PFD, WPS, NQB, PW, true>), dim3((unsigned)plan.prefill_wgs), dim3(256),
-                       (size_t)(id_bytes + schedule_bytes(b.batch)), stream, g, b, q, out, c, inv_norm, 1, 0,
+    hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, true>), dim3((unsigned)plan.prefill_wgs), dim3(256),
+                       (size_t)(id_bytes + schedule_bytes(b.batch)), stream, g, b, q, out, c, inv_norm, 1, 0, 1,
                        (int)(id_bytes / 4), plan.pair_cost, plan.min_tiles, ws_desc, ws_o, ws_ml);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return merge_detail::launch_merge<D, PW>(out, c, inv_norm, kBlockQ, g.H, plan.prefill_wgs,
                                              (int64_t)g.H * (b.total_new / kBlockQ + b.batch), ws_desc, ws_o, ws_ml, stream);
   }
-  const hipError_t attr = allow_lds<D, PFD, WPS, NQB, PW, false>();
+  const hipError_t attr = allow_lds<D, NST, NQ, PW, false>();
   if (attr != hipSuccess) return attr;
   int q_blocks_max = (b.max_new + kBlockQ - 1) / kBlockQ;
   if (q_blocks_max < 1) q_blocks_max = 1;
   const int n_pairs = b.batch * g.H;
-  const int64_t grid = (int64_t)((n_pairs + kXcds - 1) / kXcds) * kXcds * q_blocks_max;
+  const int xcd_pairs = (n_pairs + kXcds - 1) / kXcds;
+  // Four to seven pairs at a time, evenly: with one, the last pair's longest block starts last and the
+  // launch waits for it; with many, their K/V no longer share the XCD's 4 MB L2.  us a call at groups
+  // of 1 / 4 / all: 16 users x 4096, 16 heads 1197 / 1155 / 1557; 8 x 1500, 8 heads 66 / 55 / 57;
+  // 7 x 5000, 4 heads 246 / 221 / 221 (head_dim 128).
+  const int groups = xcd_pairs >= 4 ? xcd_pairs / 4 : 1;
+  const int pair_group = (xcd_pairs + groups - 1) / groups;
+  const int64_t grid = (int64_t)((xcd_pairs + pair_group - 1) / pair_group * pair_group) * kXcds * q_blocks_max;
   if (grid <= 0 || grid > 0x7fffffffll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_prefill_kernel<D, PFD, WPS, NQB, PW, false>), dim3((unsigned)grid), dim3(256), (size_t)id_bytes,
-                     stream, g, b, q, out, c, inv_norm, q_blocks_max, n_pairs, (int)(id_bytes / 4), 0, 0, nullptr, nullptr,
+  hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, false>), dim3((unsigned)grid), dim3(256), (size_t)id_bytes,
+                     stream, g, b, q, out, c, inv_norm, q_blocks_max, n_pairs, pair_group, (int)(id_bytes / 4), 0, 0, nullptr, nullptr,
                      nullptr);
   return hipGetLastError();
 }
@@ -610,7 +662,7 @@ bool attn_prefill_applicable(const PoolGeom& g, const BatchDev& b) {
   return ids * 4 <= kMaxIdBytes;
 }
 
-// New tokens per workgroup block (the template's 64 * NQB below).
+// New tokens per workgroup block (the template's 128 * NQ below).
 int attn_prefill_block(const PoolGeom& g) { return g.D == 64 ? 256 : 128; }
 
 hipError_t launch_attn_prefill(const PoolGeom& g, const AttnPlan& plan, const void* q, void* out, const BatchDev& b,
@@ -626,14 +678,15 @@ hipError_t launch_attn_prefill(const PoolGeom& g, const AttnPlan& plan, const vo
   uint16_t* op = reinterpret_cast<uint16_t*>(out);
   // Two wavefronts per SIMD in both shapes (<= 256 registers each): one wavefront alone issues
   // in order and leaves its LDS operand reads and MFMA -> VALU dependencies exposed.  At
-  // D = 128 that means 32 queries per wavefront (64-register accumulator) and 128-query blocks.
+  // D = 128 that means 32 queries per wavefront (64-register accumulator) and 128-query blocks, at
+  // D = 64 twice that.
   switch (g.D) {
     case 64:
-      return pw ? launch_one<64, 3, 2, 4, true>(g, b, plan, qp, op, c, inv_norm, id_bytes, workspace, stream)
-                : launch_one<64, 3, 2, 4, false>(g, b, plan, qp, op, c, 0.f, id_bytes, workspace, stream);
+      return pw ? launch_one<64, 3, 2, true>(g, b, plan, qp, op, c, inv_norm, id_bytes, workspace, stream)
+                : launch_one<64, 3, 2, false>(g, b, plan, qp, op, c, 0.f, id_bytes, workspace, stream);
     case 128:
-      return pw ? launch_one<128, 2, 2, 2, true>(g, b, plan, qp, op, c, inv_norm, id_bytes, workspace, stream)
-                : launch_one<128, 2, 2, 2, false>(g, b, plan, qp, op, c, 0.f, id_bytes, workspace, stream);
+      return pw ? launch_one<128, 3, 1, true>(g, b, plan, qp, op, c, inv_norm, id_bytes, workspace, stream)
+                : launch_one<128, 3, 1, false>(g, b, plan, qp, op, c, 0.f, id_bytes, workspace, stream);
     default: return hipErrorInvalidValue;
   }
 }
