@@ -389,11 +389,14 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // for step t+2 overwrites; the fetch for step t+1 stays in flight across it.
   int next_id0 = 0, next_id1 = 0;      // page ids of the tile that the next step fetches
   bf16x8 kf[KS];
-  auto step = [&](auto masked_c, int t, int st, f32x16 (&z)[NQ], f32x16 (&z_next)[NQ]) __attribute__((always_inline)) {
-    constexpr bool MASKED = decltype(masked_c)::value;
+  auto move = [&](int t, int st) __attribute__((always_inline)) {
     wait_and_barrier<FQ>();
     load(st == 0 ? NST - 1 : st - 1, t + 4, next_id0, next_id1, std::true_type{});
     page_ids(t + 5, next_id0, next_id1);
+  };
+  auto step = [&](auto masked_c, int t, int st, f32x16 (&z)[NQ], f32x16 (&z_next)[NQ]) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    move(t, st);
     // tiles past the wavefront's own last query hold no key it may see (the later wavefronts of
     // the block still need them): it only helps to move them
     const bool here = !MASKED || t < tiles_w, next = !MASKED || t + 1 < tiles_w;
@@ -500,6 +503,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 
     int tile = t_beg, st = 2;
     auto after = [](int st) __attribute__((always_inline)) { return st == NST - 1 ? 0 : st + 1; };
+    if (nq == 0) {                                                 // no query of this wavefront's: it only moves tiles
+      for (; tile < t_end; ++tile) {
+        move(tile, st);
+        st = after(st);
+      }
+    }
     while (tile + 2 < fast_all) {                                  // steady state: fully visible tiles
       step(body, tile, st, za, zb);
       st = after(st);
