@@ -17,6 +17,13 @@ template <typename T> struct ElemVec;                                // one gran
 template <> struct ElemVec<uint16_t> { typedef uint16_t type __attribute__((ext_vector_type(8))); };
 template <> struct ElemVec<uint32_t> { typedef uint32_t type __attribute__((ext_vector_type(4))); };
 
+// Element of a table that no kernel of this file writes: a scalar load whatever surrounds it (the
+// index is wavefront-uniform).
+template <typename I>
+__device__ __forceinline__ I scalar_load(const I* p) {
+  return *(const __attribute__((address_space(4))) I*)(uintptr_t)p;
+}
+
 enum { MODE_UNPACK = 0, MODE_APPEND = 1, MODE_PACK = 2 };
 
 constexpr int kBulkWaves = 4;      // wavefronts (= units) per bulk workgroup
@@ -50,26 +57,37 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
   if (MODE == MODE_APPEND) src_b += (int64_t)blockIdx.z * contig_layer_stride;
   if (MODE == MODE_PACK) dst_contig += (int64_t)blockIdx.z * contig_layer_stride;
 
-  // Resolve the run: user, first pool token, length, and the contiguous K / V planes.  The
-  // loads are ordered so that as few of them as possible wait for one another: nothing below
-  // returns early between two loads that do not depend on each other.
-  int u, pos;
+  // Resolve the run: user, first pool token, length, and the contiguous K / V planes.  A step's append
+  // moves little and costs its chain of memory round trips, so whatever can travel together does: the
+  // tables are read by scalar loads (nothing here writes them), all of a run's bounds at once, then the
+  // page id, then the rows without waiting for it.  Left to itself the compiler made eight or nine
+  // round trips of these four (each masked pair of rows waited for): an append of one user's 32 rows of
+  // 4 heads of 128 5.1 -> 4.2 us, of 64 users' 8-64 rows of 8 heads of 64 7.7 -> 6.5.
+  int u, pos, pbeg, pend;
   int64_t n, t0;
+  bool user_ok = true;                                          // an append's grid has one row per user
   if (MODE == MODE_APPEND) {
     u = s;
-    t0 = b.new_indptr[u];
-    n = (int64_t)b.new_indptr[u + 1] - t0;
-    pos = b.prefix_lens[u];
+    int r0 = scalar_load(b.new_indptr + u), r1 = scalar_load(b.new_indptr + u + 1);
+    pos = scalar_load(b.prefix_lens + u);
+    pbeg = scalar_load(b.page_indptr + u);
+    pend = scalar_load(b.page_indptr + u + 1);
+    asm volatile("" : "+s"(r0), "+s"(r1), "+s"(pos), "+s"(pbeg), "+s"(pend));   // one wait for all of them
+    t0 = r0;
+    n = (int64_t)r1 - t0;
   } else {
-    u = segs.seg_user[s];
-    pos = segs.seg_pos[s];
-    t0 = segs.seg_tok_indptr[s];
-    n = segs.seg_tok_indptr[s + 1] - t0;
+    u = scalar_load(segs.seg_user + s);
+    pos = scalar_load(segs.seg_pos + s);
+    t0 = scalar_load(segs.seg_tok_indptr + s);
+    int64_t t1 = scalar_load(segs.seg_tok_indptr + s + 1);
+    asm volatile("" : "+s"(u), "+s"(pos), "+s"(t0), "+s"(t1));
+    n = t1 - t0;
+    user_ok = u >= 0 && u < b.batch;
+    const int uc = user_ok ? u : 0;
+    pbeg = scalar_load(b.page_indptr + uc);
+    pend = scalar_load(b.page_indptr + uc + 1);
   }
-  const bool user_ok = (u >= 0 && u < b.batch);
-  const int uc = user_ok ? u : 0;
-  const int pbeg = b.page_indptr[uc];
-  const int npg = b.page_indptr[uc + 1] - pbeg;
+  const int npg = pend - pbeg;
 
   const T* k_plane;
   const T* v_plane;
@@ -95,25 +113,24 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
   if (full_hi < full_lo || bulk_blocks == 0) full_hi = full_lo;   // a launch of short runs: every sub-block takes the masked form
 
   // Which sub-block this wavefront moves, and which of its 16 tokens belong to the run.
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int64_t first_sb = ppos >> 4, last_sb = (ppos + npos - 1) >> 4;
+  // unit = 4 * block + wave of a part, as (sub-block, head) = (unit / H, unit % H) in 32 bits
+  const bool in_bulk = (int)blockIdx.x < bulk_blocks;
+  const unsigned blk = in_bulk ? blockIdx.x : blockIdx.x - (unsigned)bulk_blocks;
+  const unsigned blk_q = blk / (unsigned)H, rest = (blk - blk_q * (unsigned)H) * kBulkWaves + (unsigned)wave;
+  const unsigned rest_q = rest / (unsigned)H;
+  const int64_t k = (int64_t)blk_q * kBulkWaves + rest_q;
+  const int h = (int)(rest - rest_q * (unsigned)H);
   int64_t sb;
-  int h;
-  bool masked;
-  if ((int)blockIdx.x < bulk_blocks) {
+  const bool masked = !in_bulk;
+  if (in_bulk) {
     // whole sub-blocks: one wavefront per (sub-block, head)
-    const int64_t unit = (int64_t)blockIdx.x * kBulkWaves + wave;
-    sb = full_lo + unit / H;
-    h = (int)(unit % H);
-    masked = false;
+    sb = full_lo + k;
     if (!run_ok || sb >= full_hi) return;                       // wavefront-uniform; no block barrier below
   } else {
     // the sub-blocks the whole-sub-block part leaves: all of a run's when the launch has no such
-    // part (unit k = k-th sub-block of the run), else the partly covered ones at its two ends
-    const int64_t unit = (int64_t)(blockIdx.x - bulk_blocks) * kBulkWaves + wave;
-    const int64_t k = unit / H;
-    h = (int)(unit % H);
-    masked = true;
+    // part (k-th sub-block of the run), else the partly covered ones at its two ends
     if (bulk_blocks == 0) {
       sb = first_sb + k;
     } else {
@@ -133,14 +150,6 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
   // masked_c: compile-time copy of `masked`, so that the whole-sub-block form carries no checks
   auto move_sub_block = [&](auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    const int64_t lp = sbase / S;
-    if (lp >= npg) return;
-    const int page = b.page_indices[pbeg + lp];
-    if ((unsigned)page >= (unsigned)g.num_pages) return;
-    const int sub = (int)(sb & ((S >> 4) - 1));
-    char* head = g.layer_base + (int64_t)page * g.page_bytes;
-    T* kblk = reinterpret_cast<T*>(head + head_block_offset(0, h, S, D, sizeof(T))) + (int64_t)sub * 16 * D;
-    T* vblk = reinterpret_cast<T*>(head + head_block_offset(1, h, S, D, sizeof(T))) + (int64_t)sub * 16 * D;
     const int64_t row0 = sbase - ppos;                          // contiguous-side row of the sub-block's token 0
     T* lt = tile[wave];                                         // [16 tokens][PITCH]: K first, then V
     // LDS operations of one wavefront execute in order; the fence only pins the compiler's order
@@ -150,17 +159,25 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
     };
     auto in_run = [&](int t) { return !MASKED || (t >= t_lo && t < t_hi); };
     typedef typename ElemVec<T>::type EV;
-    const u32x4 zero = {0u, 0u, 0u, 0u};
     u32x4 kg[NIT], vg[NIT];
+    const int64_t lp = sb >> g.sub_shift;
+    if (lp >= npg) return;
+    const int page = scalar_load(b.page_indices + pbeg + lp);
+    const bool page_ok = (unsigned)page < (unsigned)g.num_pages;
+    const int sub = (int)(sb & ((S >> 4) - 1));
+    char* head = g.layer_base + (int64_t)page * g.page_bytes;
+    T* kblk = reinterpret_cast<T*>(head + head_block_offset(0, h, S, D, sizeof(T))) + (int64_t)sub * 16 * D;
+    T* vblk = reinterpret_cast<T*>(head + head_block_offset(1, h, S, D, sizeof(T))) + (int64_t)sub * 16 * D;
     if (MODE != MODE_PACK) {
-      // rows in (whole D*es-byte runs), granules out in pool order
+      // rows in (whole D*es-byte runs); a row outside the run repeats one inside it and goes nowhere
 #pragma unroll
       for (int j = 0; j < NIT; ++j) {
-        const int gi = j * 64 + lane, t = gi / dch, c = gi % dch;
+        const int gi = j * 64 + lane, c = gi % dch;
+        int t = gi / dch;
+        if (MASKED) t = t < t_lo ? t_lo : (t < t_hi ? t : t_hi - 1);
         const int64_t off = (row0 + t) * H * D + (int64_t)h * D + c * G;
-        const bool ok = in_run(t);
-        kg[j] = ok ? *reinterpret_cast<const u32x4*>(k_plane + (ok ? off : 0)) : zero;
-        vg[j] = ok ? *reinterpret_cast<const u32x4*>(v_plane + (ok ? off : 0)) : zero;
+        kg[j] = *reinterpret_cast<const u32x4*>(k_plane + off);
+        vg[j] = *reinterpret_cast<const u32x4*>(v_plane + off);
       }
 #pragma unroll
       for (int j = 0; j < NIT; ++j) {
@@ -191,6 +208,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
         for (int e = 0; e < G; ++e) o[e] = lt[(part * G + e) * PITCH + d];
         vg[j] = __builtin_bit_cast(u32x4, o);
       }
+      if (!page_ok) return;                                     // here, so that the rows do not wait for the page id
 #pragma unroll
       for (int j = 0; j < NIT; ++j) {
         const int p = j * 64 + lane;
@@ -213,6 +231,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
         }
       }
     } else {
+      if (!page_ok) return;
       // granules in, in pool order; whole rows out
 #pragma unroll
       for (int j = 0; j < NIT; ++j) {

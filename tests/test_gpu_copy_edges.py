@@ -1,0 +1,55 @@
+"""The data-movement kernel where its pieces begin and end: short and long appends (128 new tokens of
+one user switch the launch) that start and end at every kind of place inside a 16-token sub-block,
+head counts that do not divide a workgroup's four units, and pages that the pool does not have."""
+import numpy as np
+import pytest
+
+import mts_workloads as W
+import oracle
+from helpers import draw_step_data
+from test_gpu_parity import FILL, _harness, _oracle_store
+
+pytestmark = pytest.mark.gpu
+
+NEW = {"short": [1, 16, 15, 17, 33, 0, 127, 2], "long": [1, 16, 128, 131, 33, 0, 300, 2]}
+PREFIX = [0, 16, 1, 15, 31, 7, 5, 30]
+
+
+@pytest.mark.parametrize("new", list(NEW))
+@pytest.mark.parametrize("dtype,H,D,S", [("bf16", 1, 128, 16), ("bf16", 5, 64, 32), ("bf16", 7, 32, 64),
+                                         ("f32", 3, 128, 16), ("f32", 6, 32, 32)])
+def test_append_at_sub_block_edges(dtype, H, D, S, new):
+    G = _harness()
+    w = W.custom_workload("edges", 900 + H + D, dtype, 1, H, D, S, PREFIX, NEW[new], chunk_tokens=13)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    store = _oracle_store(w, data)
+    assert np.array_equal(step.pool_image(0), G.expected_pool_image(w, store, 0, FILL))
+    users = [u for u in range(w.batch) if w.total_lens[u]]
+    pos = [u % 3 if w.total_lens[u] > 3 else 0 for u in users]
+    cnt = [int(w.total_lens[u]) - p for u, p in zip(users, pos)]
+    for u, p, n, g in zip(users, pos, cnt, step.pack(0, users, pos, cnt)):
+        assert g.tobytes() == oracle.pack(store, 0, w.user_pages(u), p, n).tobytes(), f"user {u}"
+
+
+@pytest.mark.parametrize("new", [40, 200])
+@pytest.mark.parametrize("page", [-1, 1 << 20])
+def test_rows_of_a_page_outside_the_pool_go_nowhere(page, new):
+    """The kernel checks every page id: rows for one that the pool does not have are dropped, all
+    others are stored."""
+    import torch
+    G = _harness()
+    w = W.custom_workload("bad_page", 31, "bf16", 1, 2, 64, 16, [5, 9], [new, new], chunk_tokens=64)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.append(data, 0)
+    want = step.pool_image(0).reshape(w.num_pages, -1).copy()
+    lost = int(w.page_indices[1])                             # user 0's second page
+    want[lost] = FILL
+    again = G.GpuStep(w, fill_byte=FILL)
+    again.batch.page_indices[1] = page
+    torch.cuda.synchronize()
+    again.append(data, 0)
+    assert np.array_equal(again.pool_image(0).reshape(w.num_pages, -1), want)
