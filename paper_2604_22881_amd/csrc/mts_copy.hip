@@ -157,12 +157,13 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
   // masked_c: compile-time copy of `masked`, so that the whole-sub-block form carries no checks
   auto move_sub_block = [&](auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    // Restored and offloaded rows are read once and written for readers far behind: stored the plain way
-    // they fill an L2 that writes them back at the kernel's end and push out what the next kernel reads.
-    // 12 users' histories scattered and 12 gathered, 4 GB moved: 768 -> 712 us.  An append's rows are
-    // read by the attention that follows (16 x 4096 rows x 16 heads of 128, a step of 8 layers: 10.45 ms
-    // kept, 10.6 not).
-    constexpr bool KEEP = MODE == MODE_APPEND;
+    // Rows are read once and, but for the whole sub-blocks of a long append, written for few or late
+    // readers: stored the plain way they fill an L2 that writes them back at the kernel's end and push
+    // out what the next kernel reads.  12 users' histories scattered and 12 gathered, 4 GB moved:
+    // 768 -> 712 us; a step's short appends too, 64 returning users 247 -> 230, 256 users 1109 -> 1064.
+    // A whole prefill's append keeps its rows, the attention that follows reads them all: 16 x 4096 rows
+    // x 16 heads of 128, a step of 8 layers, 10.45 ms kept, 10.6 not.
+    constexpr bool KEEP = MODE == MODE_APPEND && !MASKED;
     const int64_t row0 = sbase - ppos;                          // contiguous-side row of the sub-block's token 0
     T* lt = tile[wave];                                         // [16 tokens][PITCH]: K first, then V
     // LDS operations of one wavefront execute in order; the fence only pins the compiler's order
