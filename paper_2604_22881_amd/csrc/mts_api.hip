@@ -214,7 +214,7 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   if (!p.use_mfma || b.total_new <= 0 || b.batch <= 0) return p;
   const int max_new = b.max_new > 0 ? b.max_new : 1;
   // Long new segments (a cache miss, Sec. 5.1's full prefill) are a dense contraction: the
-  // workgroup-per-query-block kernel shares K/V tiles through LDS and needs no workspace.
+  // workgroup-per-query-block kernel shares K/V tiles through LDS and can do without a workspace.
   // Short ones with long prefixes need the split-kv schedule of the streaming kernel.
   bool prefill = max_new >= 256 && (int64_t)b.total_new >= 128ll * b.batch;
   if (force == MTS_ATTN_KERNEL_PREFILL) prefill = true;
