@@ -585,7 +585,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
             *reinterpret_cast<f32x4*>(po + 32 * db + 8 * g8) = piece;
           }
         if (!PW && hf == 0) {
-          ws_ml[(prow + qi) * 2] = m[qb];
+          // a first tile of infinite logits names no reference: what was weighed has been weighed against 0
+          ws_ml[(prow + qi) * 2] = m[qb] == -INFINITY && l[qb] != 0.f ? 0.f : m[qb];
           ws_ml[(prow + qi) * 2 + 1] = l[qb];
         }
       }

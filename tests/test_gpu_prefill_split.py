@@ -50,6 +50,26 @@ def test_split_prefill_matches_oracle(name, split, attn_tuning):
     check_attention(w, step.attention_pointwise(data, 0, inv), ref)
 
 
+def test_split_prefill_block_whose_first_keys_weigh_nothing(attn_tuning):
+    """Infinite keys: the first 48 tokens have logit -inf for every query, so the first tile names no
+    reference; the pieces of the later tiles still count."""
+    attn_tuning(kernel=KERNEL_PREFILL, min_tiles=2, max_waves=64, pair_cost=1)
+    G = _harness()
+    w = W.custom_workload("silent_start", 14, "bf16", 1, 2, 64, 16, [300, 0], [40, 270])
+    data = draw_step_data(w)
+    data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
+    h = np.array(data["hist"][0][0])
+    h[0, :48, :, 7] = W.f32_to_bf16_bits(np.full((48, w.heads), -np.inf, np.float32))
+    data["hist"][0][0] = h
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    assert np.isfinite(ref).all()
+    check_attention(w, step.attention(data, 0), ref)
+
+
 def test_split_prefill_with_less_or_no_workspace():
     """A call that would split runs with any workspace: fewer shares, then none, the same result."""
     import torch

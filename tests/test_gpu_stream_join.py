@@ -74,6 +74,28 @@ def test_joined_piece_with_a_far_larger_reference(attn_tuning):
     check_attention(w, got, ref)
 
 
+@pytest.mark.parametrize("min_tiles", [3, 5, 8])
+@pytest.mark.parametrize("D", [64, 128])
+def test_pieces_after_a_first_tile_that_weighs_nothing(D, min_tiles, attn_tuning):
+    """The first 48 tokens have logit -inf for every query (infinite keys): a piece whose first tile names
+    no reference still counts when the pieces are joined or merged."""
+    attn_tuning(kernel=KERNEL_STREAMING, min_tiles=min_tiles, pair_cost=1)
+    G = _harness()
+    w = W.custom_workload("silent_start", 15, "bf16", 1, 2, D, 16, [900], [40])
+    data = draw_step_data(w)
+    data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
+    h = np.array(data["hist"][0][0])
+    h[0, :48, :, 7] = W.f32_to_bf16_bits(np.full((48, w.heads), -np.inf, np.float32))
+    data["hist"][0][0] = h
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    store = _oracle_store(w, data)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    assert np.isfinite(ref).all()
+    check_attention(w, step.attention(data, 0), ref)
+
+
 def test_schedule_of_many_users_leaves_no_room_to_join(attn_tuning):
     """head_dim 128, 64-query tiles: beyond about 1100 users (unappended; 3300 from the pool) the
     schedule and the handed-over pieces do not fit the LDS together."""
