@@ -27,10 +27,10 @@
 // now), one user of 5189 tokens x 4 heads 55.5 (51).  Tried and slower: 256-query blocks of eight
 // wavefronts (1192 against 1162), raised wavefront priority around the matrix work (1-3 %).
 //
-// The softmax reference is fixed, as in the streaming kernel (max of the first tile, no rescaling; an
-// overflowed denominator makes the whole workgroup redo its block with the exact max, found by a
-// K-only pass); the denominator sums the rounded weights in fp32 (v_dot2_f32_bf16 against ones).
-// Workgroups of one (user, head) land on one XCD, longest block first, so that its K/V stays in that
+// The softmax reference is fixed, as in the streaming kernel (max of the block's first tile, no
+// rescaling; an overflowed denominator makes the whole workgroup redo its block, or its piece of a cut
+// one, with the exact max, found by a K-only pass); the denominator sums the rounded weights in fp32
+// (v_dot2_f32_bf16 against ones).  Workgroups of one (user, head) land on one XCD, longest block first, so that its K/V stays in that
 // XCD's L2 while the blocks re-read it.
 //
 // SPLIT is the form for calls that would leave the chip idle that way: a single first-time user
@@ -132,6 +132,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   __shared__ u32x4 stage[NST][FR * 64];  // tiles in fragment order: lane l of fragment f at f * 1 KiB + l * 16 B
   __shared__ int redo_flag;
   __shared__ int wave_total[4];
+  __shared__ int first_ids[2];         // SPLIT: pages of the user's first tile
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -270,6 +271,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     pos = seg_end;
     continue;
   }
+  if (SPLIT && !PW && tid < 2) {
+    int id = (tid >> g.sub_shift) < npg ? b.page_indices[pbeg + (tid >> g.sub_shift)] : 0;
+    if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
+    first_ids[tid] = id;
+  }
   for (int i = tid; i < n_ids; i += 256) {
     int id = lp_beg + i < npg ? b.page_indices[pbeg + lp_beg + i] : 0;
     if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
@@ -361,6 +367,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 #pragma unroll
     for (int e = 1; e < 16; ++e) v = fmaxf(v, z[e]);
     return v;
+  };
+  // reference max from the scores of a tile; with nothing visible or all of them -inf, any will do
+  auto set_reference = [&](const f32x16& z, int qb) __attribute__((always_inline)) {
+    m[qb] = pair_max(max16(z));
+    mcq[qb] = (m[qb] == -INFINITY ? 0.f : m[qb]) * c;
   };
   // Weights of a tile from its scores, and their sum.
   auto weights = [&](const f32x16& z, int qb, bf16x8 (&pf)[2]) __attribute__((always_inline)) {
@@ -478,22 +489,34 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       page_ids(tile, next_id0, next_id1);
       load(st, tile, next_id0, next_id1, with_v);
     };
+    // SPLIT: the reference of a piece is that of its whole block, the max of the user's first tile.  So its
+    // weights are rounded as those of an uncut block, and how a call is cut changes its result by the
+    // order of fp32 sums alone.  The tile's keys travel beside the piece's own, into the room of the
+    // values that stage 0 does not hold yet; 8 layers of one user's 5189 tokens x 4 heads take 478 us with
+    // it and 469 with a reference of each piece's own.
+    constexpr bool kBlockReference = SPLIT && !PW;
+    if (kBlockReference && attempt == 0) {
+      const char* ka = head_base + (int64_t)first_ids[r >> 4] * g.page_bytes + (int64_t)((r >> 4) & sub_mask) * 16 * D * 2 + k_lane;
+#pragma unroll
+      for (int j = 0; j < FQ / 2; ++j) load_to_lds(ka + j * 1024, stage_lds + (KS + 4 * j) * 1024);
+    }
     fetch(0, t_beg, std::false_type{});
     fetch(1, t_beg + 1, std::false_type{});
     fetch(2, t_beg + 2, std::true_type{});
     wait_and_barrier<FQ + FQ / 2>();
     f32x16 za[NQ], zb[NQ];
+    if (kBlockReference && attempt == 0) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) kf[s] = fragment(0, KS + s);
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) set_reference(scores(kf, qb, 0, true), qb);
+    }
 #pragma unroll
     for (int s = 0; s < KS; ++s) kf[s] = fragment(0, s);
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
       za[qb] = scores(kf, qb, t_beg * kTile, true);
-      if (!PW && attempt == 0) {
-        // reference max = max of the first tile; a query that sees none of its keys (a segment of a
-        // cut block that begins past it) gets -inf and weighs nothing
-        m[qb] = pair_max(max16(za[qb]));
-        mcq[qb] = (m[qb] == -INFINITY ? 0.f : m[qb]) * c;
-      }
+      if (!PW && !kBlockReference && attempt == 0) set_reference(za[qb], qb);
     }
     wait_and_barrier<FQ>();
     fetch(0, t_beg + 3, std::true_type{});

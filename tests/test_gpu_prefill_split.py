@@ -50,6 +50,37 @@ def test_split_prefill_matches_oracle(name, split, attn_tuning):
     check_attention(w, step.attention_pointwise(data, 0, inv), ref)
 
 
+# A cut block weighs its keys against the reference of the uncut one, so that split and unsplit results
+# differ by the order of fp32 sums alone: the sum of a row's w * v (a few hundred to a few thousand terms) moves by
+# about 1e-6 of sum |w * v|, which is at most 60 times the row's root mean square here, and a bf16 output is
+# rounded the other way only within that distance of a tie: about 1e-6 * 60 / 2^-8 = 1.5 % of the values
+# if every sum moved that far, by one unit in the last place (2^-7 of the value).  References of the pieces' own
+# round all weights anew: 4 to 45 % of the values differ.
+def _same_but_for_fp32_order(a, b):
+    rms = np.sqrt((b * b).mean())
+    assert (a != b).mean() <= 0.015
+    assert (np.abs(a - b) <= 2.0 ** -7 * np.maximum(np.abs(a), np.abs(b)) + 6e-5 * rms).all()
+
+
+@pytest.mark.parametrize("split", list(SPLITS))
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_prefill_equals_unsplit(name, split, attn_tuning):
+    import torch
+    import paper_2604_22881_amd as mts
+    attn_tuning(kernel=KERNEL_PREFILL, **SPLITS[split])
+    G, w = _harness(), _workload(name)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    got = as_values(step.attention(data, 0))
+    q = G.to_dev(data["q"][0])
+    out = torch.full((w.total_new, w.heads, w.head_dim), -1, dtype=q.dtype, device=G.DEV)
+    mts.mts_attn_incremental(step.cache.desc, 0, q, out, step.batch.meta, 0.0, None, 0)     # no room to split
+    torch.cuda.synchronize()
+    _same_but_for_fp32_order(got, as_values(G.to_host(out, w.np_dtype)))
+
+
 def test_split_prefill_block_whose_first_keys_weigh_nothing(attn_tuning):
     """Infinite keys: the first 48 tokens have logit -inf for every query, so the first tile names no
     reference; the pieces of the later tiles still count."""
@@ -92,7 +123,7 @@ def test_split_prefill_with_less_or_no_workspace():
 
 
 def test_split_prefill_redoes_a_piece_whose_reference_overflows(attn_tuning):
-    """The reference max of a piece comes from its own first tile; a far larger key later in the
+    """The reference max of a block comes from its first tile; a far larger key in a later
     piece overflows the weights and the piece is redone with the exact max before the merge."""
     attn_tuning(kernel=KERNEL_PREFILL, min_tiles=8, max_waves=64)
     G = _harness()
