@@ -236,10 +236,11 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   if (items > 16384 || b.batch > 4096 || tiles_upper >= (1ll << 31)) { p.too_large = true; return p; }
   p.n_items = (int)items;
   // A wavefront's share is never shorter than this: below it, the start of a share costs more than
-  // its tiles.  Swept 2..12 over calls of 1 to 64 users: flat within 5 % from 2 to 6 tiles, with the
-  // longer tiles of head_dim 128 a little lower (one user's 6 K history of 4 heads, 32 queries: 16.5 us
-  // at 3, 17.6 at 4, 19.9 at 8), except for the large pieces of 48 and 64 queries (22.8 / 22.8 / 26.2).
-  p.min_tiles = g.D == 128 && p.q_tile <= 32 ? 3 : 4;
+  // its tiles.  Swept 2..12 over calls of 1 to 64 users: flat within 5 % from 2 to 6 tiles (one user's
+  // 6 K history of 4 heads of 128, 32 queries: 16.5 us at 3, 17.6 at 4, 19.9 at 8).  It decides where a
+  // call is cut, and every piece rounds its bf16 weights against a reference of its own: another
+  // value gives other results, within the precision of the type.
+  p.min_tiles = 4;
   if (const int v = g_tune_min_tiles.load(std::memory_order_relaxed); v >= 1) p.min_tiles = v;
   int64_t waves = (tiles_upper + p.min_tiles - 1) / p.min_tiles;
   waves = (waves + 3) / 4 * 4;

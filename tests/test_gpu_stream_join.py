@@ -111,3 +111,22 @@ def test_schedule_of_many_users_leaves_no_room_to_join(attn_tuning):
     step.append(data, 0)
     for check in _check_all_forms(w, step, data):
         check()
+
+
+@pytest.mark.parametrize("D,new", [(32, 20), (64, 32), (128, 1), (128, 32), (128, 50)])
+def test_automatic_shares_are_cut_at_four_tiles(D, new, attn_tuning):
+    """Where a call is cut decides how its weights round: the automatic cut is the same for every head
+    and query size, so that results do not change from one release to the next."""
+    G = _harness()
+    w = W.custom_workload("cuts", 21 + D + new, "bf16", 1, 2, D, 32, [2000], [new], chunk_tokens=1024)
+    data = draw_step_data(w)
+
+    def attention(**plan):
+        attn_tuning(kernel=KERNEL_STREAMING, **plan)
+        step = G.GpuStep(w, fill_byte=FILL)
+        step.unpack_histories(data, 0)
+        step.append(data, 0)
+        return np.array(step.attention(data, 0))
+
+    assert (attention() == attention(min_tiles=4)).all()
+    assert (attention() != attention(min_tiles=3)).any()
