@@ -210,6 +210,7 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   AttnPlan p{};
   const int force = g_tune_kernel.load(std::memory_order_relaxed);
   p.use_mfma = (g.es == 2) && force != MTS_ATTN_KERNEL_PLAIN;
+  p.use_f32 = (g.es == 4) && force != MTS_ATTN_KERNEL_PLAIN;
   p.q_tile = 16; p.q_tiles_max = 1; p.n_items = 0; p.min_tiles = 4; p.max_waves = 4;
   if (!p.use_mfma || b.total_new <= 0 || b.batch <= 0) return p;
   const int max_new = b.max_new > 0 ? b.max_new : 1;
@@ -492,8 +493,8 @@ int32_t attention_call(const char* name, const mts_cache_desc* cache, int32_t la
   }
   if (plan.use_mfma && plan.use_prefill)
     return hip_status(mts::launch_attn_prefill(g, plan, q, out, b, scale, inv_norm, workspace, s), name);
-  return hip_status(g.es == 4 ? mts::launch_attn_f32(g, q, out, b, scale, inv_norm, s)
-                              : mts::launch_attn_generic(g, q, out, b, scale, inv_norm, s), name);
+  return hip_status(plan.use_f32 ? mts::launch_attn_f32(g, q, out, b, scale, inv_norm, s)
+                                 : mts::launch_attn_generic(g, q, out, b, scale, inv_norm, s), name);
 }
 
 }  // namespace

@@ -1,7 +1,8 @@
 // Plain incremental attention (Sec. 2, Eq. 6-7): one wavefront per (new token, head),
 // fp32 logits, running-max softmax and fp32 accumulation, no matrix cores.  PW selects the
 // pointwise aggregation instead (silu of the scaled logit, times a normaliser; no softmax).  It is
-// the slow, simple path for bf16 calls that the matrix-core kernels do not take.
+// the slow, simple path: for bf16 calls that the matrix-core kernels do not take, and for either
+// type where MTS_ATTN_KERNEL_PLAIN asks for it, as a second implementation to check the others by.
 #include <math.h>
 
 #include "mts_internal.hpp"
@@ -9,8 +10,10 @@
 namespace mts {
 namespace {
 
+__device__ __forceinline__ float to_float(uint32_t bits) { return __uint_as_float(bits); }
 __device__ __forceinline__ float to_float(uint16_t bits) { return __uint_as_float((uint32_t)bits << 16); }
 
+__device__ __forceinline__ void store_elem(uint32_t* p, float v) { *p = __float_as_uint(v); }
 __device__ __forceinline__ void store_elem(uint16_t* p, float v) {   // round to nearest even
   uint32_t u = __float_as_uint(v);
   if ((u & 0x7fffffffu) > 0x7f800000u) { *p = (uint16_t)((u >> 16) | 0x40); return; }  // NaN stays NaN
@@ -29,11 +32,10 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-template <bool PW>
+template <typename T, bool PW>
 __global__ __launch_bounds__(64) void attn_generic_kernel(PoolGeom g, BatchDev b,
-                                                          const uint16_t* __restrict__ q,
-                                                          uint16_t* __restrict__ out, float scale, float inv_norm) {
-  typedef uint16_t T;
+                                                          const T* __restrict__ q,
+                                                          T* __restrict__ out, float scale, float inv_norm) {
   constexpr int G = 16 / sizeof(T);
   const int tok = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
   const int H = g.H, D = g.D, S = g.S;
@@ -114,9 +116,13 @@ hipError_t launch_attn_generic(const PoolGeom& g, const void* q, void* out, cons
   if (b.total_new <= 0) return hipSuccess;
   dim3 grid((unsigned)b.total_new, (unsigned)g.H, 1), block(64, 1, 1);
   const bool pw = inv_norm > 0.f;
-  if (g.es != 2) return hipErrorInvalidValue;
-  auto kern = pw ? attn_generic_kernel<true> : attn_generic_kernel<false>;
-  hipLaunchKernelGGL(kern, grid, block, 0, stream, g, b, (const uint16_t*)q, (uint16_t*)out, sm_scale, inv_norm);
+  if (g.es == 2) {
+    auto kern = pw ? attn_generic_kernel<uint16_t, true> : attn_generic_kernel<uint16_t, false>;
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, g, b, (const uint16_t*)q, (uint16_t*)out, sm_scale, inv_norm);
+  } else {
+    auto kern = pw ? attn_generic_kernel<uint32_t, true> : attn_generic_kernel<uint32_t, false>;
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, g, b, (const uint32_t*)q, (uint32_t*)out, sm_scale, inv_norm);
+  }
   return hipGetLastError();
 }
 

@@ -45,7 +45,8 @@ hipError_t launch_append(const PoolGeom& g, const void* k_new, const void* v_new
 
 // Shape plan of one attention call: computed on the host from the scalar bounds only.
 struct AttnPlan {
-  bool    use_mfma;      // bf16 matrix-core kernel, else the plain kernel (bf16) or the fp32 one
+  bool    use_mfma;      // bf16 matrix-core kernels; with neither this nor use_f32, the plain kernel
+  bool    use_f32;       // fp32 matrix-core kernel
   bool    use_prefill;   // workgroup-per-query-block kernel for long new segments (workspace optional)
   bool    too_large;     // more (user, query tile) items than the schedule can hold
   int32_t q_tile;        // queries per query tile (multiple of 16, <= 64)

@@ -5,6 +5,7 @@ import pytest
 
 import mts_workloads as W
 import oracle
+from conftest import KERNEL_PLAIN
 from helpers import as_values, draw_step_data
 from test_gpu_parity import FILL, _harness, _oracle_store, check_attention
 
@@ -56,3 +57,24 @@ def test_f32_hidden_infinity_stays_hidden(pointwise):
     assert np.isnan(got[30:, :, 9]).all()
     keep = [d for d in range(64) if d not in (5, 9)]
     assert np.abs(got[..., keep] - plain[..., keep]).max() <= 1e-6 * np.abs(plain).max()
+
+
+@pytest.mark.parametrize("D,S", [(32, 16), (64, 32), (128, 64)])
+def test_f32_plain_kernel_can_be_forced(D, S, attn_tuning):
+    """The plain kernel is a second implementation for this type too: it sums in another order, so
+    it matches the oracle with other bits than the matrix-core kernel."""
+    G = _harness()
+    w = W.custom_workload("f32_plain", 80 + D, "f32", 1, 3, D, S, *SHAPES[0], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    args = (store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    inv = 1.0 / float(w.total_lens.max())
+    automatic = np.array(step.attention(data, 0)), np.array(step.attention_pointwise(data, 0, inv))
+    attn_tuning(kernel=KERNEL_PLAIN)
+    plain = np.array(step.attention(data, 0)), np.array(step.attention_pointwise(data, 0, inv))
+    for got, other, ref in zip(plain, automatic, (oracle.attn_incremental(*args), oracle.attn_pointwise(*args, inv))):
+        check_attention(w, got, ref)
+        assert (got != other).any()
