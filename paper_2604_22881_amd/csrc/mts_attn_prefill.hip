@@ -91,10 +91,15 @@ __device__ __forceinline__ float pair_sum(float v) {
 
 // 16 bytes per lane from global memory to LDS byte address `to` (wavefront-uniform) + 16 * lane, without
 // passing through registers.  As an instruction of its own because the compiler, given the builtin,
-// waits for all such loads before any LDS read; here the waits are wait_and_barrier's.
+// waits for all such loads before any LDS read; here the waits are wait_and_barrier's.  m0 is declared
+// as overwritten, so that no value of the compiler's own is taken to outlive the statement in it; the
+// warning says that the statement does not restore it.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const char* from, uint32_t to) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(from), "s"(to) : "memory");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(from), "s"(to) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
