@@ -184,7 +184,10 @@ int32_t mts_kv_append_layers(const mts_cache_desc* cache, int32_t layer_begin, i
 /* Workspace mts_attn_incremental makes use of for this cache and batch shape (host-only, >= 0;
  * < 0 on bad arguments).  Calls with short new segments are refused with MTS_ERR_WORKSPACE if they get
  * less; calls with long ones (>= 256 new tokens of one user, >= 128 on average) also run with less or
- * none, slower where few users or one long history would leave most of the chip idle.  The workspace is device memory, 256-byte aligned, needs no
+ * none: slower where few users or one long history would leave most of the chip idle, and cut into
+ * other shares, which changes the results by the order of fp32 sums alone (a bf16 output may round to
+ * its neighbour; where a softmax reference overflows, the weights of the share concerned round anew).
+ * The workspace is device memory, 256-byte aligned, needs no
  * initialisation and may be reused by later calls on the same stream (never by calls that
  * overlap in time). */
 int64_t mts_attn_workspace_bytes(const mts_cache_desc* cache, const mts_batch_meta* meta);
@@ -229,12 +232,15 @@ int32_t mts_attn_incremental(const mts_cache_desc* cache, int32_t layer, const v
 /*
  * mts_attn_incremental for callers that cannot allocate device memory or hand over a workspace:
  * code running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same operation, arguments, preconditions and results as mts_attn_incremental, but the split-kv
+ * Same operation, arguments and preconditions as mts_attn_incremental, but the split-kv
  * partials live in a buffer the library owns: a file-scope device array of
  * MTS_NOALLOC_SCRATCH_BYTES, one copy on every GPU the library is loaded on, held until the
  * process ends.  The call allocates and frees nothing.  Shapes that cannot do without a larger
  * workspace are refused with MTS_ERR_WORKSPACE before anything is launched; shapes that also run
- * without one (long new segments, fp32) do not touch the buffer.  All calls on one GPU share the one buffer: calls that overlap in time on the same
+ * without one (long new segments, fp32) do not touch the buffer.  The results are those of
+ * mts_attn_incremental, bit for bit, with the workspace it asks for (short new segments, fp32) or
+ * without one (long new segments, where mts_attn_workspace_bytes says what a workspace changes).
+ * All calls on one GPU share the one buffer: calls that overlap in time on the same
  * GPU (different streams, different host threads) race and give wrong results; calls ordered on
  * one stream are safe.  The first call on a device looks the buffer's address up in the runtime:
  * make it outside stream capture.

@@ -96,13 +96,15 @@ def test_pieces_after_a_first_tile_that_weighs_nothing(D, min_tiles, attn_tuning
     check_attention(w, step.attention(data, 0), ref)
 
 
-def test_schedule_of_many_users_leaves_no_room_to_join(attn_tuning):
-    """head_dim 128, 64-query tiles: beyond about 1100 users (unappended; 3300 from the pool) the
-    schedule and the handed-over pieces do not fit the LDS together."""
+@pytest.mark.parametrize("users", [1300, 4090])
+def test_schedule_of_many_users_leaves_no_room_to_join(users, attn_tuning):
+    """head_dim 128, 64-query tiles: the schedule (4 words a user) and the handed-over pieces (108 KB, 96
+    pointwise) do not fit the LDS together beyond about 1100 users unappended, 3320 from the pool and 4087
+    pointwise from the pool."""
     attn_tuning(kernel=KERNEL_STREAMING)
     G = _harness()
     rng = np.random.default_rng(3)
-    prefix, new = rng.integers(0, 12, 1300), np.ones(1300, np.int64)
+    prefix, new = rng.integers(0, 12, users), np.ones(users, np.int64)
     prefix[[3, 700]], new[[3, 5, 700]] = (1500, 400), (64, 50, 33)
     w = W.custom_workload("many", 9, "bf16", 1, 1, 128, 16, list(prefix), list(new), chunk_tokens=1024)
     data = draw_step_data(w)

@@ -58,6 +58,34 @@ def test_two_calls_in_a_row_second_smaller():
     _compare(small, got, ref)
 
 
+def test_long_segments_run_without_the_buffer():
+    """A call that is cut into shares with a workspace runs uncut here: the bits of the call without a
+    workspace, and those of the cut one but for the order of fp32 sums (bound in test_gpu_prefill_split)."""
+    import torch
+    import gpu_harness as G
+    import paper_2604_22881_amd as mts
+    from test_gpu_prefill_split import _same_but_for_fp32_order
+    w = W.custom_workload("noalloc_long", 34, "bf16", 1, 2, 128, 32, [0, 1700], [1500, 40], chunk_tokens=1024)
+    data = draw_step_data(w, layers=[0])
+    step = G.GpuStep(w, fill_byte=0xFF)
+    assert step.ws_bytes > 0                                       # cut where it gets the room
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    q = G.to_dev(data["q"][0])
+
+    def output(call, *workspace):
+        out = torch.full((w.total_new, w.heads, w.head_dim), -1, dtype=q.dtype, device=G.DEV)
+        call(step.cache.desc, 0, q, out, step.batch.meta, 0.0, *workspace)
+        torch.cuda.synchronize()
+        return as_values(G.to_host(out, w.np_dtype))
+
+    got = output(mts.mts_attn_incremental_noalloc)
+    cut = output(mts.mts_attn_incremental, step.ws, step.ws_bytes)
+    assert np.array_equal(got, output(mts.mts_attn_incremental, None, 0))
+    assert (got != cut).any()
+    _same_but_for_fp32_order(got, cut)
+
+
 def test_refuses_shapes_beyond_the_buffer():
     import torch
     import gpu_harness as G
