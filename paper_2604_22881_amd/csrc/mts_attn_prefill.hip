@@ -653,6 +653,26 @@ hipError_t allow_lds() {
   return attr_status;
 }
 
+// Pairs (user, head) that an XCD takes at a time.  One after the other, the last pair's longest block
+// starts last and the launch waits for it; all together, the longest blocks of all start first, but
+// where their K/V are several times the XCD's 4 MB L2 the blocks no longer find in it what the others
+// read.  In between, four to seven, evenly, if the users are about as long as one another; if not, as many
+// as half fill the XCD's 64 workgroup slots: the last group's longest blocks are a tail again.
+// A step's time against one pair at a time (head_dim 128 unless stated; users x tokens x heads, MB of K/V
+// per XCD; 4-7 / all at a time): 8 x 300 x 16 (1) 1.00 / 0.90, 20 x 100-700 x 4 (2) 1.05 / 0.96, 20 x 300 x 8
+// of head_dim 64 (2) 1.00 / 0.92, 32 x 400 x 8 (7) 0.96 / 0.89, 12 x 600-2500 x 8 (10) 1.06 / 0.95,
+// 8 x 1500 x 8 (6) 0.86 / 0.91; 24 x 550 x 16 (14) 0.99 / 1.01, 32 x 1500 x 16 (49) 0.96 / 1.27, 64 x 600 x 16
+// (39) 1.00 / 1.22; unequal and large, 2 / 4-7 / all: 24 x 1000-4000 x 8 (31) 1.05 / 1.17 / 1.12, 32 x 400-1500
+// x 16 (30) 0.96 / 1.01 / 1.00, 64 x 100-400 x 16 (16) 0.88 / 0.83 / 0.82.
+int prefill_pair_group(const PoolGeom& g, const BatchDev& b, int xcd_pairs, int q_blocks_max) {
+  const int64_t mean_len = ((int64_t)b.total_pages * g.S + b.batch - 1) / b.batch;
+  if (xcd_pairs * mean_len * g.D * 4 <= (12ll << 20)) return xcd_pairs;
+  if (4ll * b.max_new * b.batch > 5ll * b.total_new)             // the longest new segment above 1.25 times the mean
+    return q_blocks_max >= 32 ? 1 : (32 / q_blocks_max < xcd_pairs ? 32 / q_blocks_max : xcd_pairs);
+  const int groups = xcd_pairs >= 4 ? xcd_pairs / 4 : 1;
+  return (xcd_pairs + groups - 1) / groups;
+}
+
 template <int D, int NST, int NQ, bool PW>
 hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan, const uint16_t* q, uint16_t* out,
                       float c, float inv_norm, int64_t id_bytes, void* workspace, hipStream_t stream) {
@@ -678,12 +698,7 @@ hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan
   if (q_blocks_max < 1) q_blocks_max = 1;
   const int n_pairs = b.batch * g.H;
   const int xcd_pairs = (n_pairs + kXcds - 1) / kXcds;
-  // Four to seven pairs at a time, evenly: with one, the last pair's longest block starts last and the
-  // launch waits for it; with many, their K/V no longer share the XCD's 4 MB L2.  us a call at groups
-  // of 1 / 4 / all: 16 users x 4096, 16 heads 1197 / 1155 / 1557; 8 x 1500, 8 heads 66 / 55 / 57;
-  // 7 x 5000, 4 heads 246 / 221 / 221 (head_dim 128).
-  const int groups = xcd_pairs >= 4 ? xcd_pairs / 4 : 1;
-  const int pair_group = (xcd_pairs + groups - 1) / groups;
+  const int pair_group = prefill_pair_group(g, b, xcd_pairs, q_blocks_max);
   const int64_t grid = (int64_t)((xcd_pairs + pair_group - 1) / pair_group * pair_group) * kXcds * q_blocks_max;
   if (grid <= 0 || grid > 0x7fffffffll) return hipErrorInvalidValue;
   hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, false>), dim3((unsigned)grid), dim3(256), (size_t)id_bytes,

@@ -40,6 +40,28 @@ def test_prefill_blocks_match_oracle(name, D, S, split, attn_tuning):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("name,heads,new", [("equal", 5, [140] * 13), ("unequal", 5, [300] + [70] * 12), ("one_pair", 1, [150, 20]),
+                                            ("long", 9, [1100, 3, 3])])
+def test_order_of_the_blocks_does_not_matter(name, heads, new, D, attn_tuning):
+    """How many (user, head) pairs an XCD takes at a time depends on how much K/V the call states and on
+    how unequal its segments are: every block is worked on once whatever the order, with the same bits."""
+    attn_tuning(kernel=KERNEL_PREFILL)
+    G = _harness()
+    w = W.custom_workload(name, 600 + D + heads, "bf16", 1, heads, D, 16, [40] * len(new), new, chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.ws_bytes = 0                                              # one workgroup per block
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    few = np.array(step.attention(data, 0))                        # all of an XCD's pairs at a time
+    check_attention(w, few, oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens,
+                                                    w.new_indptr))
+    step.batch.meta.total_pages = 1 << 20                          # groups of pairs
+    assert np.array_equal(few, np.array(step.attention(data, 0)))
+
+
+@pytest.mark.parametrize("D", [64, 128])
 def test_prefill_redoes_a_block_whose_reference_overflows(D, attn_tuning):
     """A far larger key behind the first tile: the block goes round again with the exact max, all its
     stages fetched anew."""
