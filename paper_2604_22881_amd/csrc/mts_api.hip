@@ -186,20 +186,21 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
   if (const int v = g_tune_max_waves.load(std::memory_order_relaxed); v >= 4) {   // forces the split
     wgs = v / 4 < wgs ? v / 4 : wgs;
   } else {
-    // Unsplit, a call takes as long as its longest block (0.55 us per 32-token step of a workgroup
-    // alone on its CU, 1.1 where the blocks fill the CUs twice) or as its work takes on all CUs (0.56
-    // us per step and CU); split, only the latter, plus about 20 us for the partial blocks, their
-    // merge and the second launch; neither is shorter than reading K and V once.  Measured, us
-    // unsplit / split (steps of the longest block, steps per CU; blocks): 93 / 51 (163, 54; 164),
-    // 190 / 75 (377, 93; 288), 52 / 41 (79, 27; 160), 49 / 49 (82, 47; 160), 38 / 42 (63, 34; 256),
-    // 29 / 35 (42, 18; 200), 53 / 75 (47, 78; 768), 150 / 151 (188, 225; 576); bound by reading K and V
-    // (160 us): 171-251, with luck in where the dispatcher puts them, / 177 (309, 197; 304).
+    // Unsplit, a call takes as long as its longest block (0.6 us per 32-token step of a workgroup alone
+    // on its CU, 0.75 where the blocks fill the CUs twice) or as its work takes on all CUs (0.45 us per
+    // step and CU, counted from the mean length, which overstates it); split, only the latter, plus 32 us
+    // for block starts, partial blocks, their merge and the second launch; neither is shorter than
+    // reading K and V once.  Fitted to 437 calls of 1 to 100 users, head_dim 64 and 128: 1.1 % above the
+    // faster form on average (with 20 us, 0.55, 1.1 and 0.56 per step: 2.7 %, up to 58 %).  Measured, us
+    // unsplit / split (steps of the longest block, steps per CU, blocks): 98 / 40 (194, 39, 176),
+    // 102 / 79 (162, 79, 252), 60 / 55 (93, 34, 224), 214 / 103 (382, 336, 408), 157 / 174 (165, 249, 884), 40 / 54
+    // (52, 43, 432), 58 / 74 (80, 59, 612), 29 / 45 (46, 4, 60), 24 / 38 (28, 13, 380).
     const double mean_total = (double)b.total_pages * g.S / b.batch, mean_new = (double)b.total_new / b.batch;
     const double filled = (double)g.H * ((double)b.total_new / QB + 0.5 * b.batch);
-    const double all_cus = 0.56 / 256 * (double)blocks * (mean_total - 0.5 * mean_new) / 32;
-    const double longest = (filled <= 288 ? 0.55 : 1.1) * (double)max_tiles;
+    const double all_cus = 0.45 / 256 * (double)blocks * (mean_total - 0.5 * mean_new) / 32;
+    const double longest = (filled <= 288 ? 0.6 : 0.75) * (double)max_tiles;
     const double read = (double)b.total_pages * (double)g.page_bytes / 5e6;
-    if (longest <= (all_cus > read ? all_cus : read) + 20) return;
+    if (longest <= (all_cus > read ? all_cus : read) + 32) return;
   }
   p.prefill_wgs = wgs;
   p.ws_desc_bytes = roundup((int64_t)wgs * 32, 256);

@@ -86,6 +86,23 @@ def test_workspace_query_is_host_only():
     assert mts.mts_attn_workspace_bytes(_desc(dtype=B.MTS_F32), small) == 0
 
 
+@pytest.mark.parametrize("D,H,users,new,longest,prefix,cut", [
+    (128, 4, 1, 5189, 5189, 0, True),          # one first-time user: few blocks, the longest of them the whole launch
+    (64, 8, 1, 6000, 6000, 0, True),
+    (128, 4, 8, 9000, 5500, 48000, True),      # a few new tokens behind long histories, beside first-time users
+    (128, 4, 20, 10300, 800, 0, False),        # enough blocks of moderate length: cutting them costs more than it fills
+    (128, 4, 12, 12000, 1000, 0, False),
+    (64, 8, 12, 8600, 1200, 0, False),
+    (64, 4, 2, 2400, 1300, 0, False),
+    (128, 16, 16, 65536, 4096, 0, False),      # work for all CUs several times over
+])
+def test_long_segment_calls_ask_for_workspace_where_cutting_pays(D, H, users, new, longest, prefix, cut):
+    d = _desc(head_dim=D, num_heads=H, page_size=16)
+    m = _meta(batch=users, total_new=new, max_new=longest, max_total_len=max(longest, prefix // users * 2),
+              total_pages=(prefix + new) // 16 + users)
+    assert (mts.mts_attn_workspace_bytes(d, m) > 0) == cut
+
+
 def _code(fn, *a, **k):
     with pytest.raises(mts.MtsError) as e:
         fn(*a, **k)

@@ -65,7 +65,7 @@ def test_long_segments_run_without_the_buffer():
     import gpu_harness as G
     import paper_2604_22881_amd as mts
     from test_gpu_prefill_split import _same_but_for_fp32_order
-    w = W.custom_workload("noalloc_long", 34, "bf16", 1, 2, 128, 32, [0, 1700], [1500, 40], chunk_tokens=1024)
+    w = W.custom_workload("noalloc_long", 34, "bf16", 1, 2, 128, 32, [0, 2600], [1500, 40], chunk_tokens=1024)
     data = draw_step_data(w, layers=[0])
     step = G.GpuStep(w, fill_byte=0xFF)
     assert step.ws_bytes > 0                                       # cut where it gets the room
