@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "../../include/mtserve.h"
+#include "mts_attn_rules.hpp"
 #include "mts_internal.hpp"
 
 namespace {
@@ -207,7 +208,7 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
   p.ws_bytes = p.ws_desc_bytes + (int64_t)wgs * prefill_partial_bytes(g);
 }
 
-AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
+AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers) {
   AttnPlan p{};
   const int force = g_tune_kernel.load(std::memory_order_relaxed);
   p.use_mfma = (g.es == 2) && force != MTS_ATTN_KERNEL_PLAIN;
@@ -237,6 +238,8 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b) {
   const int64_t tiles_upper = items * ((b.max_total_len + 31) / 32 + 1 + p.pair_cost) * g.H;   // schedule units of the call
   if (items > 16384 || b.batch > 4096 || tiles_upper >= (1ll << 31)) { p.too_large = true; return p; }
   p.n_items = (int)items;
+  p.past_caches = p.q_tiles_max == 1 && kv_past_caches(g.D, (int64_t)b.total_pages * g.page_bytes, layers,
+                                                       (int64_t)b.total_pages * g.S / b.batch);
   // A wavefront's share is never shorter than this: below it, the start of a share costs more than
   // its tiles.  Swept 2..12 over calls of 1 to 64 users: flat within 5 % from 2 to 6 tiles (one user's
   // 6 K history of 4 heads of 128, 32 queries: 16.5 us at 3, 17.6 at 4, 19.9 at 8).  It decides where a
@@ -429,7 +432,7 @@ int64_t mts_attn_workspace_bytes(const mts_cache_desc* cache, const mts_batch_me
   int32_t st;
   if ((st = check_cache(cache, 0, false, &g)) != MTS_OK) return st;
   if ((st = check_meta(meta, true, false, &b)) != MTS_OK) return st;
-  const mts::AttnPlan plan = mts::plan_attention(g, b);
+  const mts::AttnPlan plan = mts::plan_attention(g, b, cache->num_layers);
   if (plan.too_large) return fail(MTS_ERR_UNSUPPORTED, "too many query tiles or kv tiles for one call");
   return plan.ws_bytes;
 }
@@ -465,7 +468,7 @@ int32_t attention_call(const char* name, const mts_cache_desc* cache, int32_t la
     if (!aligned(k_new, 16) || !aligned(v_new, 16))
       return fail(MTS_ERR_INVALID_ARG, "k_new / v_new is not 16-byte aligned");
   }
-  mts::AttnPlan plan = mts::plan_attention(g, b);
+  mts::AttnPlan plan = mts::plan_attention(g, b, cache->num_layers);
   if (plan.too_large)
     return fail(MTS_ERR_UNSUPPORTED, "batch %d exceeds 4096 users, batch x ceil(max_new %d / 64) exceeds 16384 "
                 "query tiles, or the call has 2^31 or more kv tiles", b.batch, b.max_new);
@@ -517,7 +520,7 @@ int32_t mts_attn_incremental_noalloc(const mts_cache_desc* cache, int32_t layer,
   int32_t st;
   if ((st = check_cache(cache, layer, true, &g)) != MTS_OK) return st;
   if ((st = check_meta(meta, true, true, &b)) != MTS_OK) return st;
-  const mts::AttnPlan plan = mts::plan_attention(g, b);
+  const mts::AttnPlan plan = mts::plan_attention(g, b, cache->num_layers);
   if (plan.too_large) return fail(MTS_ERR_UNSUPPORTED, "too many query tiles or kv tiles for one call");
   if (plan.ws_required > kScratchBytes)
     return fail(MTS_ERR_WORKSPACE, "this shape needs %lld bytes of scratch, the library-owned buffer of "
@@ -551,7 +554,7 @@ int32_t mts_attn_unappended_appends(const mts_cache_desc* cache, const mts_batch
   if ((st = check_cache(cache, 0, false, &g)) != MTS_OK) return st;
   if ((st = check_meta(meta, true, false, &b)) != MTS_OK) return st;
   if (b.batch == 0 || b.total_new == 0) return 0;
-  const mts::AttnPlan plan = mts::plan_attention(g, b);
+  const mts::AttnPlan plan = mts::plan_attention(g, b, cache->num_layers);
   return (plan.use_mfma && !plan.use_prefill && rows_fit_32bit(g, b)) ? 0 : 1;
 }
 

@@ -1,0 +1,23 @@
+// Where the streaming attention's forms change over: host-only rules on sizes.
+#pragma once
+#include <stdint.h>
+
+namespace mts {
+
+// Whether a call of one query tile per user loads its K/V tiles past the caches' retention.
+// It pays (8-11 % of the step at head_dim 64, 2-10 % at 128) where nothing of a tile is read again:
+// * The layers of a step together are larger than what the last-level cache (256 MB) hands to the next
+//   step.  Step time, past the caches / ordinary, of 290, 320, 350, 380 MB over 1 layer: 1.05 1.00 0.95 0.90 at
+//   head_dim 64, 1.15 1.11 1.00 0.98 at 128; over 2 layers 1.04 1.00 0.94 0.92 and 1.16 1.10 1.06 1.00.
+// * Users are long.  The ring of a segment loads its last tile again and again past the segment's end, which
+//   costs nothing while caches hold it: users of 40, 130, 200, 300, 450 tokens 1.12 1.05 0.99 0.96 0.94 at head_dim
+//   64 (8 layers of 150 MB; 1.02 at 200 and 1.00 at 260 in 2 layers of 1 GB), of 40, 200, 450, 700, 1000 tokens
+//   1.27 1.08 1.01 0.98 0.96 at 128 (4 layers of 260, 2 of 520 MB), whose ring and tiles are larger.
+// * The call is long enough for its bandwidth to matter: 4 layers of 135, 170, 210, 260, 400 MB 0.93 0.91 0.91
+//   0.91 0.90 at head_dim 64, 1.02 1.01 0.99 0.98 0.96 at 128.
+constexpr bool kv_past_caches(int head_dim, int64_t call_bytes, int64_t layers, int64_t tokens_per_user) {
+  return head_dim == 128 ? call_bytes >= (192ll << 20) && call_bytes >= (368ll << 20) / layers && tokens_per_user >= 768
+                         : call_bytes >= (128ll << 20) && call_bytes >= (320ll << 20) / layers && tokens_per_user >= 256;
+}
+
+}  // namespace mts

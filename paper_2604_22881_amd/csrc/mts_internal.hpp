@@ -58,13 +58,14 @@ struct AttnPlan {
   int64_t ws_desc_bytes; // per-wavefront merge descriptors at the start of the workspace
   int64_t ws_bytes;      // whole workspace
   int64_t ws_required;   // what the call cannot do without (the rest only lets it split further)
+  bool    past_caches;   // streaming kernel: K/V tiles are loaded past the caches' retention
   int32_t prefill_wgs;   // prefill kernel: workgroups of a split launch, 0 = one per query block
 };
 // Fits the plan to the workspace that the caller handed over (any pointer, any size).
 void fit_plan_to_workspace(AttnPlan& p, const PoolGeom& g, const void* workspace, int64_t workspace_bytes);
 constexpr int kPrefillMaxWgs = 512;          // 256 CUs x 2 resident workgroups
 constexpr int kPrefillSplitMaxBatch = 1024;  // users whose schedule a workgroup keeps in LDS
-AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b);
+AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers);   // layers of the cache
 constexpr int kAttnMaxWaves = 1024;   // 256 CUs x 4 SIMDs: one wavefront per SIMD
 
 

@@ -1,0 +1,29 @@
+// The rules by which the streaming attention chooses its forms, at sizes on both sides of each line;
+// compiling it is the check.
+#include "../../paper_2604_22881_amd/csrc/mts_attn_rules.hpp"
+
+using mts::kv_past_caches;
+constexpr int64_t MB = 1000000;
+
+// bound by reading K/V: past the caches
+static_assert(kv_past_caches(64, 219 * MB, 4, 1600), "64 users of about 1600 tokens");
+static_assert(kv_past_caches(64, 1400 * MB, 4, 2600), "");
+static_assert(kv_past_caches(128, 1300 * MB, 8, 10000), "");
+static_assert(kv_past_caches(128, 860 * MB, 8, 3300), "");
+static_assert(kv_past_caches(128, 400 * MB, 1, 3000), "");
+// the layers stay in the last-level cache from step to step
+static_assert(!kv_past_caches(128, 13 * MB, 8, 6400), "");
+static_assert(!kv_past_caches(128, 135 * MB, 1, 1000), "");
+static_assert(!kv_past_caches(128, 260 * MB, 1, 2000), "");
+static_assert(!kv_past_caches(64, 260 * MB, 1, 4000), "");
+static_assert(!kv_past_caches(64, 135 * MB, 2, 2000), "");
+// many short users: a segment's last tile is loaded several times
+static_assert(!kv_past_caches(128, 170 * MB, 4, 64), "1300 users of 40 tokens in 32-token pages");
+static_assert(!kv_past_caches(128, 445 * MB, 4, 64), "");
+static_assert(!kv_past_caches(64, 445 * MB, 4, 64), "");
+static_assert(!kv_past_caches(128, 520 * MB, 2, 450), "");
+static_assert(kv_past_caches(128, 520 * MB, 2, 1000), "");
+static_assert(!kv_past_caches(64, 520 * MB, 2, 200), "");
+static_assert(kv_past_caches(64, 520 * MB, 2, 300), "");
+// the largest values of the arguments do not overflow
+static_assert(kv_past_caches(64, 1ll << 62, INT32_MAX, 1ll << 37), "");

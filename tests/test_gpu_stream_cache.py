@@ -1,6 +1,6 @@
-"""Calls of 128 MB of K/V and more load their tiles past the caches: the same arithmetic on the same
-schedule, so the same bits as ordinary loads.  The form is chosen by the call's page count; here a
-small batch states a large one."""
+"""Large calls of long users load their K/V tiles past the caches: the same arithmetic on the same
+schedule, so the same bits as ordinary loads.  The form is chosen by the call's page count
+(kv_past_caches); here a small batch states a large one."""
 import numpy as np
 import pytest
 
@@ -30,6 +30,6 @@ def test_tiles_loaded_past_the_caches_give_the_same_bits(D, S, new, attn_tuning)
 
     plain = outputs()
     meta = step.batch.meta
-    meta.total_pages = (128 << 20) // step.cache.page_bytes + 1
+    meta.total_pages = (400 << 20) // step.cache.page_bytes + 1
     for a, b in zip(plain, outputs()):
         assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
