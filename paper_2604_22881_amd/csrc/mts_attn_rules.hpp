@@ -20,4 +20,16 @@ constexpr bool kv_past_caches(int head_dim, int64_t call_bytes, int64_t layers, 
                          : call_bytes >= (128ll << 20) && call_bytes >= (320ll << 20) / layers && tokens_per_user >= 256;
 }
 
+// Whether the pieces of a (query tile, head) that lie in one workgroup's shares are folded inside the
+// workgroup.  It saves partials and merge work, and costs a launch of few workgroups, which ends with its
+// longest chain, the barrier and the serial fold.  Step of 8 layers, us, folded / not:
+// * launches of 384 wavefronts and more: 16 users x 1000 keys + 16 new x 4 heads of 128 190 / 198, 32 x 600 + 24 x 4
+//   of 128 229 / 258, 16 x 300 + 64 x 8 of 64 172 / 176, 64 x 64 + 64 x 8 of 64 189 / 202; below, 1 x 300 + 64 x 4 of
+//   128 164 / 147, 16 x 300 + 64 x 4 of 128 223 / 206, 1 x 1500 + 50 x 8 of 64 138 / 132;
+// * pairs of so many pieces that the merge is the longer chain: 32 and more, 1 x 6400 + 32 x 4 of 128 191 / 197;
+//   8 and more where pieces are small, 4 x 1000 + 32 x 8 of 64 pointwise 116 / 125, 1 x 700 + 16 x 4 of 32 94 / 99.
+constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_tile, bool pointwise) {
+  return waves >= 384 || waves >= 32 * pairs || (waves >= 8 * pairs && q_tile <= 32 && (pointwise || head_dim == 32));
+}
+
 }  // namespace mts

@@ -2,6 +2,7 @@
 // compiling it is the check.
 #include "../../paper_2604_22881_amd/csrc/mts_attn_rules.hpp"
 
+using mts::joins_pieces;
 using mts::kv_past_caches;
 constexpr int64_t MB = 1000000;
 
@@ -27,3 +28,11 @@ static_assert(!kv_past_caches(64, 520 * MB, 2, 200), "");
 static_assert(kv_past_caches(64, 520 * MB, 2, 300), "");
 // the largest values of the arguments do not overflow
 static_assert(kv_past_caches(64, 1ll << 62, INT32_MAX, 1ll << 37), "");
+
+// launches that fill the chip fold pieces inside workgroups, a single user's do not ...
+static_assert(joins_pieces(400, 128, 64, 16, false) && joins_pieces(1024, 4, 128, 64, false), "");
+static_assert(!joins_pieces(20, 4, 128, 64, false) && !joins_pieces(112, 8, 64, 64, false), "");
+static_assert(!joins_pieces(336, 64, 128, 64, false) && !joins_pieces(152, 32, 64, 16, true), "");
+// ... unless the merge of their many pieces is the longer chain
+static_assert(joins_pieces(212, 4, 128, 32, false) && joins_pieces(336, 32, 64, 32, true) && joins_pieces(36, 4, 32, 16, false), "");
+static_assert(!joins_pieces(336, 32, 64, 32, false) && !joins_pieces(60, 4, 32, 64, false), "");

@@ -1,6 +1,7 @@
-"""Share boundaries that the streaming kernel closes inside a workgroup: pairs that end in the next
-wavefront's share, span several wavefronts, whole workgroups or several of them, pairs cut inside their
-schedule allowance; and the per-wavefront partials that a schedule of very many users falls back to."""
+"""Share boundaries that the streaming kernel closes inside a workgroup, where the launch is large enough or
+its pairs have many pieces (joins_pieces): pairs that end in the next wavefront's share, span several
+wavefronts, whole workgroups or several of them, pairs cut inside their schedule allowance; and the
+per-wavefront partials of the other launches and of schedules of very many users."""
 import numpy as np
 import pytest
 
@@ -52,12 +53,13 @@ def test_joined_pieces_match_oracle(D, top, attn_tuning):
             check()
 
 
-def test_joined_piece_with_a_far_larger_reference(attn_tuning):
+@pytest.mark.parametrize("heads", [2, 32])              # 32: enough wavefronts to fold inside workgroups
+def test_joined_piece_with_a_far_larger_reference(heads, attn_tuning):
     """One piece of a cut pair holds a key that outweighs everything in the others: the fold scales
     them down to nothing without overflow."""
     attn_tuning(kernel=KERNEL_STREAMING, min_tiles=2, pair_cost=1)
     G = _harness()
-    w = W.custom_workload("late_key", 13, "bf16", 1, 2, 64, 16, [900], [40])
+    w = W.custom_workload("late_key", 13, "bf16", 1, heads, 64, 16, [900], [40])
     data = draw_step_data(w)
     h = np.array(data["hist"][0][0])
     h[0] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(h[0]) * 0.01)
@@ -75,13 +77,14 @@ def test_joined_piece_with_a_far_larger_reference(attn_tuning):
 
 
 @pytest.mark.parametrize("min_tiles", [3, 5, 8])
+@pytest.mark.parametrize("heads", [2, 128])             # 128: enough wavefronts to fold inside workgroups
 @pytest.mark.parametrize("D", [64, 128])
-def test_pieces_after_a_first_tile_that_weighs_nothing(D, min_tiles, attn_tuning):
+def test_pieces_after_a_first_tile_that_weighs_nothing(D, heads, min_tiles, attn_tuning):
     """The first 48 tokens have logit -inf for every query (infinite keys): a piece whose first tile names
     no reference still counts when the pieces are joined or merged."""
     attn_tuning(kernel=KERNEL_STREAMING, min_tiles=min_tiles, pair_cost=1)
     G = _harness()
-    w = W.custom_workload("silent_start", 15, "bf16", 1, 2, D, 16, [900], [40])
+    w = W.custom_workload("silent_start", 15, "bf16", 1, heads, D, 16, [900], [40])
     data = draw_step_data(w)
     data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
     h = np.array(data["hist"][0][0])
