@@ -23,6 +23,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -92,6 +93,28 @@ def attention_flops_per_layer(w):
     """QK^T and PV multiply-adds over the visible (query, key) pairs only."""
     pairs = sum(int(n) * int(P) + int(n) * (int(n) + 1) // 2 for P, n in zip(w.prefix_lens, w.new_lens))
     return 4 * w.head_dim * w.heads * pairs
+
+
+def attention_sources_digest(csrc=os.path.join(ROOT, "paper_2604_22881_amd", "csrc")):
+    """Digest of the code, comments and spacing apart, that an attention call is made of."""
+    import hashlib
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(csrc)):
+        if name.startswith("mts_attn") or name in ("mts_api.hip", "mts_internal.hpp", "mts_layout.hpp"):
+            with open(os.path.join(csrc, name)) as f:
+                code = re.sub(r"//[^\n]*|/\*.*?\*/", "", f.read(), flags=re.S)
+            h.update(f"{name} {' '.join(code.split())}\n".encode())
+    return h.hexdigest()
+
+
+def measured_traffic(path):
+    """HBM bytes per attention launch that the file has from rocprofv3 --pmc runs; None without the file
+    or if it was measured on other attention code than the tree's."""
+    if not os.path.exists(path):
+        return None
+    with open(path) as f:
+        d = json.load(f)
+    return d.get("hbm_bytes_per_launch") if d.get("attention_sources") == attention_sources_digest() else None
 
 
 def spread(ms):
@@ -823,10 +846,8 @@ def bench_workload(args, name, steps, warmup, extras):
         res["roofline"].update({"bound": "mfma", "achieved": tf, "peak": MFMA_BF16_PEAK_TFLOPS,
                                 "unit": "TFLOP/s", "frac": tf / MFMA_BF16_PEAK_TFLOPS,
                                 "flops_per_launch": flops})
-    traffic_file = os.path.join(ROOT, "profiles", f"traffic_{w.name}.json")
-    if os.path.exists(traffic_file) and not pointwise:          # measured HBM bytes per launch, from rocprofv3 --pmc runs
-        with open(traffic_file) as f:
-            res["roofline"]["traffic"] = json.load(f).get("hbm_bytes_per_launch")
+    if not pointwise:
+        res["roofline"]["traffic"] = measured_traffic(os.path.join(ROOT, "profiles", f"traffic_{w.name}.json"))
     if name == "host_staging" and not args.no_pcie and not pointwise and len(w.miss_users):
         res["pcie"] = pcie_leg(w, cache, q, k_new, v_new, out, compute, side, max(10, K // 4), ms_per_step)
     if extras:
