@@ -23,6 +23,15 @@ struct MergeDesc {
   int pad[2];
 };
 
+// Above these, a softmax denominator or the absolute sum of a query's accumulators asks for a redo with the
+// exact max.  A piece's are lower by the number of pieces that a pair can be cut into, so that the sums
+// over pieces of one reference stay within fp32 too.
+struct RedoLimits { float den, mag; };
+constexpr RedoLimits redo_limits(bool cut) {
+  static_assert(kAttnMaxWaves <= 1024 && kPrefillMaxWgs <= 1024, "a share holds at most one piece of a pair");
+  return cut ? RedoLimits{1e37f / 1024, 3.0e38f / 1024} : RedoLimits{1e37f, 3.0e38f};
+}
+
 // A numerically safe weighted sum of a pair's pieces in a fixed order (deterministic).  Share
 // w_first holds its piece in slot `first_slot`; every later share holds its piece as the leading
 // one (slot 0).  A thread folds the 4 dims `d4` of one query, taking pieces four at a time with all

@@ -557,6 +557,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     // real query; then every wavefront of the block goes round again.
     // (the numerator overflows first when the values are large: the sum of a query's absolute
     // accumulator values is infinite or NaN as soon as one of them is)
+    const merge_detail::RedoLimits limit = merge_detail::redo_limits(SPLIT && (t_beg > 0 || t_end < tiles_blk));
     bool bad = false;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
@@ -566,7 +567,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int e = 0; e < 16; ++e) mag += fabsf(o[qb][db][e]);
-      bad |= (32 * qb + r < nq) && (!(l[qb] < 1e37f) || !(mag < 3.0e38f));
+      bad |= (32 * qb + r < nq) && (!(l[qb] < limit.den) || !(mag < limit.mag));
     }
     if (tid == 0) redo_flag = 0;
     __syncthreads();

@@ -7,7 +7,7 @@ import pytest
 
 import mts_workloads as W
 import oracle
-from conftest import KERNEL_STREAMING
+from conftest import KERNEL_PREFILL, KERNEL_STREAMING
 from helpers import as_values, draw_step_data
 from test_gpu_parity import FILL, _harness, _oracle_store, check_attention
 
@@ -135,3 +135,40 @@ def test_automatic_shares_are_cut_at_four_tiles(D, new, attn_tuning):
 
     assert (attention() == attention(min_tiles=4)).all()
     assert (attention() != attention(min_tiles=3)).any()
+
+
+@pytest.mark.parametrize("kernel,D,max_waves,heads", [(KERNEL_STREAMING, 64, 4, 1), (KERNEL_STREAMING, 128, 4, 1),
+                                                      (KERNEL_STREAMING, 32, 32, 1), (KERNEL_PREFILL, 64, 16, 1),
+                                                      (KERNEL_PREFILL, 128, 16, 1)])
+def test_sum_of_pieces_overflows_though_none_of_them_does(kernel, D, max_waves, heads, attn_tuning):
+    """Every piece of a cut pair holds one key of weight 2^120.7 to 2^121.7 against its reference, and values of
+    64 in one dim: 1.7e38 to 2.8e38 in a piece, beyond the fp32 range (3.4e38) in two.  32 wavefronts at
+    head_dim 32 fold inside workgroups (joins_pieces), the others leave their pieces to the merge."""
+    tiles, cost = 248, 8
+    attn_tuning(kernel=kernel, max_waves=max_waves, pair_cost=cost, min_tiles=4)
+    shares = max_waves // 4 if kernel == KERNEL_PREFILL else max_waves
+    G = _harness()
+    w = W.custom_workload("far_keys", 17, "bf16", 1, heads, D, 16, [tiles * 32 - 8], [8], chunk_tokens=1024)
+    data = draw_step_data(w)
+    k, v = np.zeros_like(W.bf16_bits_to_f32(np.array(data["hist"][0][0])))
+    x = np.float32(121.2 / (np.log2(np.e) * 16 / np.sqrt(D)))       # times a query of 16 / sqrt(D): 121.2 in base 2
+    far = [s * (tiles + cost) // shares - cost + (tiles + cost) // shares // 2 for s in range(shares)]
+    far = [t for t in far if t > 0]                                 # the allowance comes before the first tile
+    for t in far:
+        k[t * 32 + 5, :, 3] = x
+    v[:, :, 7] = 64.0
+    data["hist"][0][0] = W.f32_to_bf16_bits(np.stack([k, v]))
+    data["k_new"][0] = W.f32_to_bf16_bits(np.zeros_like(W.bf16_bits_to_f32(data["k_new"][0])))
+    data["v_new"][0] = data["k_new"][0].copy()
+    q = np.zeros_like(W.bf16_bits_to_f32(data["q"][0]))
+    q[..., 3] = 16.0
+    data["q"][0] = W.f32_to_bf16_bits(q)
+    log2_weight = float(W.bf16_bits_to_f32(W.f32_to_bf16_bits(np.array([x]))).item()) * 16 / np.sqrt(D) * np.log2(np.e)
+    assert 120.7 < log2_weight < 121.7 and 64 * 2 ** log2_weight < 3.0e38
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    store = _oracle_store(w, data)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    assert np.allclose(ref[:, 0, 7], 64.0)
+    check_attention(w, step.attention(data, 0), ref)
