@@ -20,8 +20,8 @@
 // while the matrix cores work on P.V.  One barrier per step, across which the newest fetch stays in
 // flight.
 //
-// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1135 to
-// 1165 us (942-970 TFLOP/s at about 1.93 GHz), 959 us on zeros; a library matrix product of 8192^3
+// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1113 to
+// 1165 us (942-986 TFLOP/s at 1.85 to 1.93 GHz), 959 us on zeros; a library matrix product of 8192^3
 // reaches 1250 TFLOP/s here.  With v_mfma_f32_16x16x32_bf16, tiles parked from registers and no
 // pipelining across tiles the same call took 1163 to 1200 us (1018 on zeros), 64-dim heads 697 (632
 // now), one user of 5189 tokens x 4 heads 55.5 (51).  Tried and slower: 256-query blocks of eight
@@ -30,8 +30,8 @@
 // The softmax reference is fixed, as in the streaming kernel (max of the block's first tile, no
 // rescaling; an overflowed denominator makes the whole workgroup redo its block, or its piece of a cut
 // one, with the exact max, found by a K-only pass); the denominator sums the rounded weights in fp32
-// (v_dot2_f32_bf16 against ones).  Workgroups of one (user, head) land on one XCD, longest block first, so that its K/V stays in that
-// XCD's L2 while the blocks re-read it.
+// (v_dot2_f32_bf16 against ones).  Workgroups of one (user, head) land on one XCD, longest block first,
+// so that its K/V stays in that XCD's L2 while the blocks re-read it.
 //
 // SPLIT is the form for calls that would leave the chip idle that way: a single first-time user
 // (fewer blocks than CUs, the longest of them the whole launch), or a batch in which some users
@@ -40,10 +40,10 @@
 // contiguous share of it, and a block that a share boundary cuts is written as unnormalised fp32
 // pieces that a merge kernel finishes.  Every workgroup derives the schedule by itself from the
 // device-resident lengths (a prefix sum over the users in LDS; positions inside a user are closed
-// forms).  Measured, attention of one layer, head_dim 128, unsplit -> split: 1 user x 5189 new tokens
-// x 4 heads 93 -> 51 us; 6 users with 4-12 K histories and 8-64 new tokens beside 2 first-time ones
-// 190 -> 75 us.  What is left there is a share's two or three block starts (about 4 us each) and the
-// fp32 pieces (64 KB each, about 45 MB written and read back).
+// forms).  Measured, attention and merge of one layer in a step, head_dim 128, unsplit -> split: 1 user x
+// 5189 new tokens x 4 heads 93 -> 53 us (merge 10); 6 users with 4-12 K histories and 8-64 new tokens
+// beside 2 first-time ones 190 -> 87 us.  What is left there is the block starts (1.2 and 1.5 segments a
+// share, about 4 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
 //
 // PW selects the pointwise aggregation out = inv_norm * sum_j silu(c * q.k_j) v_j: no reference
 // max, no denominator, no redo; hidden keys carry logit 0 (silu(0) = 0).
