@@ -212,7 +212,9 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers) {
   AttnPlan p{};
   const int force = g_tune_kernel.load(std::memory_order_relaxed);
   p.use_mfma = (g.es == 2) && force != MTS_ATTN_KERNEL_PLAIN;
-  p.use_f32 = (g.es == 4) && force != MTS_ATTN_KERNEL_PLAIN;
+  p.use_f32 = (g.es == 4) && force != MTS_ATTN_KERNEL_PLAIN &&
+              !(force == MTS_ATTN_KERNEL_AUTO && f32_takes_plain(g.D, g.H, b.batch, b.total_new, b.max_new, b.max_total_len,
+                                                                 (int64_t)b.total_pages * g.S));
   p.q_tile = 16; p.q_tiles_max = 1; p.n_items = 0; p.min_tiles = 4; p.max_waves = 4;
   if (!p.use_mfma || b.total_new <= 0 || b.batch <= 0) return p;
   const int max_new = b.max_new > 0 ? b.max_new : 1;

@@ -14,7 +14,7 @@
 // Bound: latency for the few-thousand-key calls this type is used for (page id -> K/V -> scores,
 // then the combination); the next sub-block's K and V travel while one is computed.  Measured, one
 // layer of 16 queries x 272 keys x 4 heads of 32: 73 us with one wavefront per (query, head) and
-// a scalar load per element, 6.2 us here.
+// a scalar load per element, 6.2 us here.  Many users of a few keys are the plain kernel's (f32_takes_plain).
 #include <math.h>
 
 #include <type_traits>

@@ -1,8 +1,9 @@
 // Plain incremental attention (Sec. 2, Eq. 6-7): one wavefront per (new token, head),
 // fp32 logits, running-max softmax and fp32 accumulation, no matrix cores.  PW selects the
 // pointwise aggregation instead (silu of the scaled logit, times a normaliser; no softmax).  It is
-// the slow, simple path: for bf16 calls that the matrix-core kernels do not take, and for either
-// type where MTS_ATTN_KERNEL_PLAIN asks for it, as a second implementation to check the others by.
+// the slow, simple path: for bf16 calls that the matrix-core kernels do not take, for fp32 calls of many
+// users of a few keys (f32_takes_plain), and for either type where MTS_ATTN_KERNEL_PLAIN asks for it, as a
+// second implementation to check the others by.
 #include <math.h>
 
 #include "mts_internal.hpp"

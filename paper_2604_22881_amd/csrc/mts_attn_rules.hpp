@@ -1,4 +1,4 @@
-// Where the streaming attention's forms change over: host-only rules on sizes.
+// Where the forms of the attention change over: host-only rules on sizes.
 #pragma once
 #include <stdint.h>
 
@@ -30,6 +30,25 @@ constexpr bool kv_past_caches(int head_dim, int64_t call_bytes, int64_t layers, 
 //   8 and more where pieces are small, 4 x 1000 + 32 x 8 of 64 pointwise 116 / 125, 1 x 700 + 16 x 4 of 32 94 / 99.
 constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_tile, bool pointwise) {
   return waves >= 384 || waves >= 32 * pairs || (waves >= 8 * pairs && q_tile <= 32 && (pointwise || head_dim == 32));
+}
+
+// Whether an fp32 call goes to the plain kernel.  A workgroup of the matrix-core kernel is eight wavefronts that
+// find their user, read at least one 16-token sub-block and combine: 7, 14, 22 ns of the whole chip at head_dim
+// 32, 64, 128 however short the user is.  The plain kernel pays per (query, key), as much for 64 of them (68 at head_dim
+// 128, and 18 where K/V come from beyond the caches) as for a workgroup, and for a query what 8 keys cost (16 at head_dim
+// 128).  us, matrix cores / plain, at 1000 users x 8 heads, 1 new token of 8 keys, 1 of 32, 2 of 32, 4 of 16:
+// head_dim 32 55 / 14, 56 / 36, 60 / 62, 62 / 65; 64 106 / 22, 104 / 70, 113 / 120, 112 / 101; 128 165 / 81, 177 / 304,
+// 194 / 579, 182 / 495.  A call that does not fill the chip waits for the plain kernel's longest chain of keys,
+// 0.3 us each: 16 users x 1000 keys 13 / 301 at head_dim 32.  `max_new` times all keys and `total_new` times the
+// longest user's both bound the (query, key) pairs of the call.
+constexpr bool f32_takes_plain(int head_dim, int64_t heads, int64_t users, int64_t total_new, int64_t max_new,
+                               int64_t max_len, int64_t page_tokens) {
+  const int64_t blocks = total_new / 16 + users;
+  if (300 * max_len + 3000 >= blocks * heads * (head_dim == 32 ? 7 : head_dim == 64 ? 14 : 22)) return false;
+  const bool far = head_dim == 128 && page_tokens * heads * 1024 > (96ll << 20);
+  const int64_t room = blocks * (head_dim <= 64 ? 64 : far ? 18 : 68) -
+                       total_new * (head_dim == 64 || far ? 0 : head_dim == 32 ? 8 : 16);
+  return total_new * max_len < room || (max_new <= room / (page_tokens > 0 ? page_tokens : 1) && max_new * page_tokens < room);
 }
 
 }  // namespace mts

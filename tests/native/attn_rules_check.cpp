@@ -1,7 +1,8 @@
-// The rules by which the streaming attention chooses its forms, at sizes on both sides of each line;
+// The rules by which the attention chooses its forms, at sizes on both sides of each line;
 // compiling it is the check.
 #include "../../paper_2604_22881_amd/csrc/mts_attn_rules.hpp"
 
+using mts::f32_takes_plain;
 using mts::joins_pieces;
 using mts::kv_past_caches;
 constexpr int64_t MB = 1000000;
@@ -36,3 +37,18 @@ static_assert(!joins_pieces(336, 64, 128, 64, false) && !joins_pieces(152, 32, 6
 // ... unless the merge of their many pieces is the longer chain
 static_assert(joins_pieces(212, 4, 128, 32, false) && joins_pieces(336, 32, 64, 32, true) && joins_pieces(36, 4, 32, 16, false), "");
 static_assert(!joins_pieces(336, 32, 64, 32, false) && !joins_pieces(60, 4, 32, 64, false), "");
+
+// fp32: many users of a few keys, in pages of 16 and 64 tokens ...
+static_assert(f32_takes_plain(32, 8, 1000, 1000, 1, 8, 16000) && f32_takes_plain(32, 8, 1000, 1000, 1, 32, 32000), "");
+static_assert(f32_takes_plain(64, 8, 1000, 1000, 1, 8, 16000) && f32_takes_plain(64, 8, 4000, 16000, 4, 16, 64000), "");
+static_assert(f32_takes_plain(128, 8, 256, 256, 1, 32, 8192) && f32_takes_plain(128, 8, 4000, 4000, 1, 4, 64000), "");
+static_assert(f32_takes_plain(64, 8, 1000, 1000, 1, 8, 64000), "");
+static_assert(f32_takes_plain(64, 8, 1000, 1000, 1, 100, 16000), "one longer user among them");
+// ... but no longer ones, no few, and none with many queries
+static_assert(!f32_takes_plain(32, 8, 1000, 1000, 1, 96, 96000) && !f32_takes_plain(64, 8, 1000, 4000, 4, 32, 32000), "");
+static_assert(!f32_takes_plain(128, 8, 1000, 1000, 1, 32, 32000) && !f32_takes_plain(128, 2, 1000, 4000, 4, 8, 16000), "");
+static_assert(!f32_takes_plain(32, 4, 1, 1, 1, 300, 304) && !f32_takes_plain(64, 8, 8, 8, 1, 8, 128), "");
+static_assert(!f32_takes_plain(64, 8, 1000, 1000, 1, 3000, 16000), "the launch would wait for the longest");
+static_assert(!f32_takes_plain(32, 8, 1000, 64000, 64, 64, 64000), "");
+// the largest values of the arguments do not overflow
+static_assert(!f32_takes_plain(128, 65535, INT32_MAX, INT32_MAX, INT32_MAX, 1 << 22, 1ll << 37), "");

@@ -1,4 +1,4 @@
-"""The size rules of the streaming attention, checked at compile time (they are host code)."""
+"""The size rules of the attention, checked at compile time (they are host code)."""
 import os
 import shutil
 import subprocess

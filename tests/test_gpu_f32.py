@@ -78,3 +78,30 @@ def test_f32_plain_kernel_can_be_forced(D, S, attn_tuning):
     for got, other, ref in zip(plain, automatic, (oracle.attn_incremental(*args), oracle.attn_pointwise(*args, inv))):
         check_attention(w, got, ref)
         assert (got != other).any()
+
+
+# users of a few keys, by the hundred: lengths of one page and of two, one with more new tokens; and as many that are too long
+MANY = {"short": ([0, 3, 6, 1, 9, 0, 4], [1, 1, 2, 1, 1, 2, 1], True), "too_long": ([90, 70, 110], [1, 2, 1], False)}
+
+
+@pytest.mark.parametrize("name", list(MANY))
+@pytest.mark.parametrize("D,S", [(32, 16), (64, 64), (128, 16)])
+def test_f32_many_short_users_take_the_plain_kernel(D, S, name, attn_tuning):
+    """A workgroup of the matrix-core kernel costs the same for 8 keys as for 128 (f32_takes_plain): calls of many
+    short users are the plain kernel's, with its bits, and match the oracle."""
+    G = _harness()
+    prefix, new, plain_taken = MANY[name]
+    w = W.custom_workload("f32_many", 90 + D, "f32", 1, 8, D, S, prefix * 60, new * 60, chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    args = (store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    inv = 1.0 / float(w.total_lens.max())
+    automatic = np.array(step.attention(data, 0)), np.array(step.attention_pointwise(data, 0, inv))
+    attn_tuning(kernel=KERNEL_PLAIN)
+    plain = np.array(step.attention(data, 0)), np.array(step.attention_pointwise(data, 0, inv))
+    for got, other, ref in zip(automatic, plain, (oracle.attn_incremental(*args), oracle.attn_pointwise(*args, inv))):
+        check_attention(w, got, ref)
+        assert (got == other).all() == plain_taken
