@@ -7,6 +7,7 @@
 // layout is [dim][token]); see kv_move_kernel for how the work is split.
 #include <type_traits>
 
+#include "mts_copy_rules.hpp"
 #include "mts_internal.hpp"
 
 namespace mts {
@@ -25,6 +26,11 @@ __device__ __forceinline__ I scalar_load(const I* p) {
 }
 
 // One granule past the caches' retention (KEEP = false: nothing reads it again soon) or the ordinary way.
+template <bool KEEP>
+__device__ __forceinline__ u32x4 load_granule(const void* p) {
+  if constexpr (KEEP) return *reinterpret_cast<const u32x4*>(p);
+  else return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+}
 template <bool KEEP>
 __device__ __forceinline__ void store_granule(void* p, u32x4 v) {
   if constexpr (KEEP) *reinterpret_cast<u32x4*>(p) = v;
@@ -45,7 +51,8 @@ constexpr int kBulkWaves = 4;      // wavefronts (= units) per bulk workgroup
 // the run are neither read nor written, K granules of other tokens are skipped and a V granule
 // that the run covers only in part is written element by element, so no slot outside the run
 // is ever written.
-template <typename T, int MODE, int DCH>
+// PAST: rows travel past the caches' retention (mts_copy_rules.hpp; short appends always do).
+template <typename T, int MODE, int DCH, bool PAST>
 __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, BatchDev b,
                                                       const T* __restrict__ src_a,
                                                       const T* __restrict__ src_b,
@@ -157,13 +164,12 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
   // masked_c: compile-time copy of `masked`, so that the whole-sub-block form carries no checks
   auto move_sub_block = [&](auto masked_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    // Rows are read once and, but for the whole sub-blocks of a long append, written for few or late
-    // readers: stored the plain way they fill an L2 that writes them back at the kernel's end and push
-    // out what the next kernel reads.  12 users' histories scattered and 12 gathered, 4 GB moved:
-    // 768 -> 712 us; a step's short appends too, 64 returning users 247 -> 230, 256 users 1109 -> 1064.
-    // A whole prefill's append keeps its rows, the attention that follows reads them all: 16 x 4096 rows
-    // x 16 heads of 128, a step of 8 layers, 10.45 ms kept, 10.6 not.
-    constexpr bool KEEP = MODE == MODE_APPEND && !MASKED;
+    // A short append's rows are written for late readers: stored the plain way they fill an L2 that writes
+    // them back at the kernel's end and push out what the next kernel reads; a step of 64 returning users 247 ->
+    // 230 us, 256 users 1109 -> 1064.  A whole prefill's append keeps its rows, the attention that follows
+    // reads them all: 16 x 4096 rows x 16 heads of 128, a step of 8 layers, 10.45 ms kept, 10.6 not.
+    constexpr bool KEEP = MODE == MODE_APPEND ? !MASKED : !PAST;
+    constexpr bool KEEP_READ = MODE != MODE_APPEND && !PAST;
     const int64_t row0 = sbase - ppos;                          // contiguous-side row of the sub-block's token 0
     T* lt = tile[wave];                                         // [16 tokens][PITCH]: K first, then V
     // LDS operations of one wavefront execute in order; the fence only pins the compiler's order
@@ -190,8 +196,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
         int t = gi / dch;
         if (MASKED) t = t < t_lo ? t_lo : (t < t_hi ? t : t_hi - 1);
         const int64_t off = (row0 + t) * H * D + (int64_t)h * D + c * G;
-        kg[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_plane + off));
-        vg[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_plane + off));
+        kg[j] = load_granule<KEEP_READ>(k_plane + off);
+        vg[j] = load_granule<KEEP_READ>(v_plane + off);
       }
 #pragma unroll
       for (int j = 0; j < NIT; ++j) {
@@ -281,8 +287,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
         const int gi = j * 64 + lane, t = gi / dch, c = gi % dch;
         if (in_run(t)) {
           const int64_t off = (row0 + t) * H * D + (int64_t)h * D + c * G;
-          store_granule<false>(k_out + off, kg[j]);
-          store_granule<false>(v_out + off, *reinterpret_cast<const u32x4*>(lt + t * PITCH + c * G));
+          store_granule<KEEP>(k_out + off, kg[j]);
+          store_granule<KEEP>(v_out + off, *reinterpret_cast<const u32x4*>(lt + t * PITCH + c * G));
         }
       }
     }
@@ -295,7 +301,13 @@ template <typename T, int MODE, int DCH>
 void launch_typed(const PoolGeom& g, const SegDev& segs, const BatchDev& b, dim3 grid, int bulk_blocks,
                   const void* a, const void* bsrc, void* dst, int64_t pool_layer_stride,
                   int64_t contig_layer_stride_bytes, hipStream_t stream) {
-  hipLaunchKernelGGL((kv_move_kernel<T, MODE, DCH>), grid, dim3(256, 1, 1), 0, stream, g, segs, b, (const T*)a,
+  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16)>;
+  if constexpr (MODE == MODE_UNPACK) {
+    if (!scatter_past_caches((int64_t)segs.num_segs * segs.max_seg_tokens, (int64_t)b.total_pages * g.S,
+                             2ll * g.H * g.D * g.es, grid.z))
+      kern = kv_move_kernel<T, MODE, DCH, false>;
+  }
+  hipLaunchKernelGGL(kern, grid, dim3(256, 1, 1), 0, stream, g, segs, b, (const T*)a,
                      (const T*)bsrc, (T*)dst, bulk_blocks, pool_layer_stride,
                      contig_layer_stride_bytes / (int64_t)sizeof(T));
 }

@@ -1,0 +1,22 @@
+// Which copies move their rows past the caches' retention: host-only rules on sizes.  Stored the plain way, many
+// rows fill an L2 that writes them back at the kernel's end; few find room in the last-level cache (256 MB).
+// Times are those past the caches over plain ones, of copies repeated on the same buffers.
+#pragma once
+#include <stdint.h>
+
+namespace mts {
+
+// Scatter, by the bytes of all layers of the launch: 100-120 MB 1.07, 140-270 MB 1.08 to 1.18, 300 MB 1.03, 360 MB and
+// more 0.91 to 0.98.  Below, plain loads and stores 0.92 to 0.95
+// of the time past the caches at 27-90 MB, and nothing differs under that.  `run_tokens` (runs times the longest) and `held_tokens` (the
+// batch's pages) both bound the tokens that are moved.
+constexpr bool scatter_past_caches(int64_t run_tokens, int64_t held_tokens, int64_t token_bytes, int64_t layers) {
+  return (held_tokens > 0 && held_tokens < run_tokens ? held_tokens : run_tokens) >= (336ll << 20) / token_bytes / layers;
+}
+
+// Gather, by the bytes of a token's row of one head: rows of 128 and more 0.99 to 1.00 up to 100 MB, 0.95 at 130,
+// 0.79 to 0.81 at 180-260, 0.94 to 0.98 beyond; rows of 64, half a cache line each, 1.10 to 1.21 at 35-115 MB,
+// 1.03 to 1.08 beyond 330.
+constexpr bool gather_past_caches(int row_bytes) { return row_bytes >= 128; }
+
+}  // namespace mts
