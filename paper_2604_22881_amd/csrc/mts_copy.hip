@@ -51,8 +51,8 @@ constexpr int kBulkWaves = 4;      // wavefronts (= units) per bulk workgroup
 // the run are neither read nor written, K granules of other tokens are skipped and a V granule
 // that the run covers only in part is written element by element, so no slot outside the run
 // is ever written.
-// PAST: rows travel past the caches' retention (mts_copy_rules.hpp; short appends always do).
-template <typename T, int MODE, int DCH, bool PAST>
+// PAST: which rows travel past the caches' retention (mts_copy_rules.hpp; an append's own rule is at KEEP).
+template <typename T, int MODE, int DCH, RowsPast PAST>
 __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, BatchDev b,
                                                       const T* __restrict__ src_a,
                                                       const T* __restrict__ src_b,
@@ -168,8 +168,8 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
     // them back at the kernel's end and push out what the next kernel reads; a step of 64 returning users 247 ->
     // 230 us, 256 users 1109 -> 1064.  A whole prefill's append keeps its rows, the attention that follows
     // reads them all: 16 x 4096 rows x 16 heads of 128, a step of 8 layers, 10.45 ms kept, 10.6 not.
-    constexpr bool KEEP = MODE == MODE_APPEND ? !MASKED : !PAST;
-    constexpr bool KEEP_READ = MODE != MODE_APPEND && !PAST;
+    constexpr bool KEEP = MODE == MODE_APPEND ? !MASKED : PAST != RowsPast::kReadAndWritten;
+    constexpr bool KEEP_READ = MODE != MODE_APPEND && PAST == RowsPast::kNone;
     const int64_t row0 = sbase - ppos;                          // contiguous-side row of the sub-block's token 0
     T* lt = tile[wave];                                         // [16 tokens][PITCH]: K first, then V
     // LDS operations of one wavefront execute in order; the fence only pins the compiler's order
@@ -301,11 +301,12 @@ template <typename T, int MODE, int DCH>
 void launch_typed(const PoolGeom& g, const SegDev& segs, const BatchDev& b, dim3 grid, int bulk_blocks,
                   const void* a, const void* bsrc, void* dst, int64_t pool_layer_stride,
                   int64_t contig_layer_stride_bytes, hipStream_t stream) {
-  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16)>;
+  constexpr RowsPast kBoth = RowsPast::kReadAndWritten, kRead = RowsPast::kRead, kNone = RowsPast::kNone;
+  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16) ? kBoth : kNone>;
   if constexpr (MODE == MODE_UNPACK) {
-    if (!scatter_past_caches((int64_t)segs.num_segs * segs.max_seg_tokens, (int64_t)b.total_pages * g.S,
-                             2ll * g.H * g.D * g.es, grid.z))
-      kern = kv_move_kernel<T, MODE, DCH, false>;
+    const RowsPast past = scatter_past_caches((int64_t)segs.num_segs * segs.max_seg_tokens, (int64_t)b.total_pages * g.S,
+                                              2ll * g.H * g.D * g.es, grid.z);
+    if (past != kBoth) kern = past == kRead ? kv_move_kernel<T, MODE, DCH, kRead> : kv_move_kernel<T, MODE, DCH, kNone>;
   }
   hipLaunchKernelGGL(kern, grid, dim3(256, 1, 1), 0, stream, g, segs, b, (const T*)a,
                      (const T*)bsrc, (T*)dst, bulk_blocks, pool_layer_stride,

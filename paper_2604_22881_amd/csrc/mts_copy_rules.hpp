@@ -6,12 +6,19 @@
 
 namespace mts {
 
-// Scatter, by the bytes of all layers of the launch: 100-120 MB 1.07, 140-270 MB 1.08 to 1.18, 300 MB 1.03, 360 MB and
-// more 0.91 to 0.98.  Below, plain loads and stores 0.92 to 0.95
-// of the time past the caches at 27-90 MB, and nothing differs under that.  `run_tokens` (runs times the longest) and `held_tokens` (the
-// batch's pages) both bound the tokens that are moved.
-constexpr bool scatter_past_caches(int64_t run_tokens, int64_t held_tokens, int64_t token_bytes, int64_t layers) {
-  return (held_tokens > 0 && held_tokens < run_tokens ? held_tokens : run_tokens) >= (336ll << 20) / token_bytes / layers;
+enum class RowsPast { kNone, kRead, kReadAndWritten };
+
+// Scatter, by the bytes of all layers of the launch.
+// * Stores: 100-120 MB 1.07, 140-270 MB 1.08 to 1.18, 300 MB 1.03, 360 MB and more 0.91 to 0.98; below, with plain
+//   loads beside them, 1.05 to 1.08 at 27-90 MB and nothing under that.
+// * Loads: where rows and pool pages together are more than the cache, plain loads push out what the stores put
+//   there; of both plain, 180-360 MB take 0.73 to 0.99 of the time with loads past the caches.
+// `run_tokens` (runs times the longest) and `held_tokens` (the batch's pages) both bound the tokens that are moved.
+constexpr RowsPast scatter_past_caches(int64_t run_tokens, int64_t held_tokens, int64_t token_bytes, int64_t layers) {
+  const int64_t tokens = held_tokens > 0 && held_tokens < run_tokens ? held_tokens : run_tokens;
+  return tokens >= (336ll << 20) / token_bytes / layers   ? RowsPast::kReadAndWritten
+         : tokens >= (160ll << 20) / token_bytes / layers ? RowsPast::kRead
+                                                          : RowsPast::kNone;
 }
 
 // Gather, by the bytes of a token's row of one head: rows of 128 and more 0.99 to 1.00 up to 100 MB, 0.95 at 130,

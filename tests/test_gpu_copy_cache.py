@@ -1,4 +1,4 @@
-"""A scatter above the last-level cache's size stores its rows past it; each of its layers alone does not."""
+"""A scatter of more than the last-level cache moves its rows past it; each of its layers alone, and two of them, less so."""
 import numpy as np
 import pytest
 
@@ -23,13 +23,10 @@ def test_layers_in_one_launch_and_one_by_one_agree(dtype, heads, head_dim):
     assert segs.total_tokens * row * layers >= 336 << 20 > segs.total_tokens * row
     staging = torch.randint(-2 ** 31, 2 ** 31 - 1, (layers, segs.total_tokens * row // 4), dtype=torch.int32, device=dev)
     pools = []
-    for whole in (True, False):
+    for at_once in (4, 2, 1):
         cache = PagedKVCache(layers, int(indptr[-1]), page, heads, head_dim, dtype, dev)
         cache.pool.zero_()
-        if whole:
-            mts.mts_kv_unpack_layers(cache.desc, 0, layers, staging, segs.total_tokens * row, *segs.args(), batch.meta)
-        else:
-            for l in range(layers):
-                mts.mts_kv_unpack(cache.desc, l, staging[l], *segs.args(), batch.meta)
+        for l in range(0, layers, at_once):
+            mts.mts_kv_unpack_layers(cache.desc, l, at_once, staging[l], segs.total_tokens * row, *segs.args(), batch.meta)
         pools.append(cache.pool)
-    assert bool((pools[0] != 0).any()) and torch.equal(pools[0], pools[1])
+    assert bool((pools[0] != 0).any()) and torch.equal(pools[0], pools[1]) and torch.equal(pools[0], pools[2])
