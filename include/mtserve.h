@@ -208,6 +208,7 @@ typedef struct mts_attn_tuning {
   int32_t pair_cost; /* schedule allowance per (query tile, head), in tiles */
   int32_t kernel;    /* MTS_ATTN_KERNEL_*: force the split-kv streaming kernel, the dense-prefill kernel
                         (where it applies) or the plain fp32-accumulate kernel */
+  /* with any field set, the streaming kernel takes even shares of wavefronts whatever the call's size */
 } mts_attn_tuning;
 int32_t mts_attn_set_tuning(const mts_attn_tuning* tuning);
 

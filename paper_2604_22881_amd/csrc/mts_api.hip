@@ -261,6 +261,30 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers) {
   p.ws_desc_bytes = roundup((int64_t)p.max_waves * 32, 256);
   p.ws_bytes = p.ws_desc_bytes + (int64_t)p.max_waves * 2 * p.q_tile * (g.D + 2) * (int64_t)sizeof(float);
   p.ws_required = p.ws_bytes;
+  const bool tuned = force != MTS_ATTN_KERNEL_AUTO || g_tune_min_tiles.load(std::memory_order_relaxed) > 0 ||
+                     g_tune_max_waves.load(std::memory_order_relaxed) > 0 || g_tune_pair_cost.load(std::memory_order_relaxed) > 0;
+  if (tuned || p.past_caches) return p;                          // even shares
+  const int64_t pairs = items * g.H, max_tiles = ((int64_t)b.max_total_len + 31) / 32;
+  switch (stream_form(g.D, p.q_tile, pairs, max_tiles, (int64_t)b.total_pages * g.page_bytes)) {
+    case StreamForm::kShares: break;
+    case StreamForm::kWholePairs:
+      p.piece_wgs = (int)pairs;
+      break;
+    case StreamForm::kPieces: {
+      // As many pieces as CUs, at most 32 of a pair (one user's 12 K keys of 4 heads of 128: 0.95 of even shares'
+      // time with 32, 1.04 with 64), of at least six tiles (one user's 6 K: 164 us a step, 175 with four).  Each pair rounds
+      // its number up, so `wgs` pieces hold what `wgs - pairs` of them would without rounding; a user's tiles
+      // are counted from its pages, and one more where prefix and new rows are tiled apart.
+      int64_t wgs = 32 * pairs < 256 ? 32 * pairs : 256;
+      if (wgs > p.max_waves) wgs = p.max_waves;                  // the partial buffers' capacity
+      if (items > 64 || wgs <= pairs) break;                     // a wavefront's lanes hold the schedule
+      const int64_t tiles = p.q_tiles_max * ((int64_t)b.total_pages * g.S / 32 + 2 * b.batch) * g.H;
+      const int64_t per_piece = (tiles + wgs - pairs - 1) / (wgs - pairs);
+      p.piece_tiles = (int)(per_piece > 6 ? per_piece : 6);
+      p.piece_wgs = (int)wgs;
+      break;
+    }
+  }
   return p;
 }
 

@@ -32,6 +32,32 @@ constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_ti
   return waves >= 384 || waves >= 32 * pairs || (waves >= 8 * pairs && q_tile <= 32 && (pointwise || head_dim == 32));
 }
 
+// How the streaming kernel divides a call's (query tile, head)s, `pairs` of at most `max_tiles` 32-token tiles: even
+// shares of wavefronts; a workgroup per pair; or a workgroup per equal piece of a pair, and a merge launch.
+// Step time over that of even shares, whole pairs / pieces, of 1000 random calls of up to 100 MB a layer (geometric
+// means; q: queries per tile):
+// * Up to 256 pairs a CU holds one, whose keys it alone reads: head_dim 128 16-32 tiles 0.77 / 0.89, 32-40 0.84 / 0.88,
+//   40-52 0.92 / 0.88, 64-80 1.16 / 0.90; 64, q <= 32 32-40 0.80 / 0.92, 40-52 0.84 / 0.94, 52-64 0.90 / 0.95, 80-110 1.04 / 0.94;
+//   32 0.73 / 0.93, 0.82 / 0.95, 64-80 0.89 / 0.94, 80-110 0.97 / 0.92; q > 32, both, 24-32 0.77 / 0.88, 32-40 0.88 / 0.92,
+//   64-80 1.1 / 0.95.
+// * Up to 512 pairs two share a CU where registers allow, and the longest ones are the launch's end: 8-32 tiles
+//   head_dim 128, q <= 16 0.88 to 0.92 of even shares, more queries 0.95 to 1.05; 64 0.71 to 0.85 (longer ones 0.91 to 1.2), 32
+//   0.67 to 0.75.  Beyond, a CU starts one after the other: head_dim 64, q <= 16 up to 16 tiles 0.82 to 0.9, more queries 0.97 to
+//   1.09; 32, q <= 32 up to 32 tiles 0.79 to 0.88, q > 32 0.92 to 1.03; 128 0.91 to 1.5.
+// * Pieces: 40 tiles and more, head_dim 128 up to 160 MB a layer 0.89 to 0.95, 200-300 MB 0.94 to 1.02; 64 up to 80 MB 0.93 to 0.95, 120
+//   MB 0.84 to 1.04, 160 MB 1.07 to 1.17.  Each pair rounds its pieces up, so of many pairs the longest ones wait: 97-128
+//   pairs 0.94 to 1.24, 129-255 0.98 to 1.26.
+enum class StreamForm { kShares, kWholePairs, kPieces };
+constexpr StreamForm stream_form(int head_dim, int q_tile, int64_t pairs, int64_t max_tiles, int64_t call_bytes) {
+  const int64_t whole = pairs <= 256   ? (head_dim == 128 ? 36 : q_tile > 32 ? 44 : head_dim == 64 ? 52 : 68)
+                        : pairs <= 512 ? (head_dim == 32 ? 32 : head_dim == 64 || q_tile <= 16 ? 24 : 0)
+                        : pairs > 2048 ? 0
+                        : head_dim == 32 ? (q_tile <= 32 ? 32 : 0)
+                                         : (head_dim == 64 && q_tile <= 16 ? 16 : 0);
+  if (max_tiles <= whole) return StreamForm::kWholePairs;
+  return pairs <= 96 && call_bytes <= (head_dim == 128 ? 160ll << 20 : 80ll << 20) ? StreamForm::kPieces : StreamForm::kShares;
+}
+
 // Whether an fp32 call goes to the plain kernel.  A workgroup of the matrix-core kernel is eight wavefronts that
 // find their user, read at least one 16-token sub-block and combine: 7, 14, 22 ns of the whole chip at head_dim
 // 32, 64, 128 however short the user is.  The plain kernel pays per (query, key), as much for 64 of them (68 at head_dim

@@ -59,6 +59,8 @@ struct AttnPlan {
   int64_t ws_bytes;      // whole workspace
   int64_t ws_required;   // what the call cannot do without (the rest only lets it split further)
   bool    past_caches;   // streaming kernel: K/V tiles are loaded past the caches' retention
+  int32_t piece_wgs;     // streaming kernel: workgroups of a launch of one piece each, 0 = even shares of wavefronts
+  int32_t piece_tiles;   // ... most kv tiles of such a piece, 0 = (query tile, head)s are not cut
   int32_t prefill_wgs;   // prefill kernel: workgroups of a split launch, 0 = one per query block
 };
 // Fits the plan to the workspace that the caller handed over (any pointer, any size).

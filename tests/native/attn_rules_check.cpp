@@ -5,6 +5,8 @@
 using mts::f32_takes_plain;
 using mts::joins_pieces;
 using mts::kv_past_caches;
+using mts::stream_form;
+using mts::StreamForm;
 constexpr int64_t MB = 1000000;
 
 // bound by reading K/V: past the caches
@@ -37,6 +39,20 @@ static_assert(!joins_pieces(336, 64, 128, 64, false) && !joins_pieces(152, 32, 6
 // ... unless the merge of their many pieces is the longer chain
 static_assert(joins_pieces(212, 4, 128, 32, false) && joins_pieces(336, 32, 64, 32, true) && joins_pieces(36, 4, 32, 16, false), "");
 static_assert(!joins_pieces(336, 32, 64, 32, false) && !joins_pieces(60, 4, 32, 64, false), "");
+
+// small calls: whole pairs up to the length that one CU reads in time ...
+static_assert(stream_form(128, 32, 4, 36, 1 * MB) == StreamForm::kWholePairs && stream_form(64, 32, 256, 52, 90 * MB) == StreamForm::kWholePairs, "");
+static_assert(stream_form(64, 64, 16, 44, 5 * MB) == StreamForm::kWholePairs && stream_form(32, 16, 16, 68, 5 * MB) == StreamForm::kWholePairs, "");
+static_assert(stream_form(128, 16, 512, 24, 90 * MB) == StreamForm::kWholePairs && stream_form(32, 32, 2048, 32, 90 * MB) == StreamForm::kWholePairs, "");
+// ... then pieces, of few pairs and while reading K/V is not yet the most of it
+static_assert(stream_form(128, 32, 4, 37, 1 * MB) == StreamForm::kPieces && stream_form(64, 64, 96, 45, 80 * MB) == StreamForm::kPieces, "");
+static_assert(stream_form(128, 32, 96, 300, 160 * MB) == StreamForm::kPieces && stream_form(64, 32, 96, 300, 84 * MB) == StreamForm::kShares, "");
+static_assert(stream_form(128, 32, 97, 37, 30 * MB) == StreamForm::kShares && stream_form(128, 32, 96, 400, 168 * MB) == StreamForm::kShares, "");
+// pairs that take their turns on a CU
+static_assert(stream_form(128, 32, 257, 1, 10 * MB) == StreamForm::kShares && stream_form(128, 16, 513, 1, 10 * MB) == StreamForm::kShares, "");
+static_assert(stream_form(64, 32, 513, 1, 10 * MB) == StreamForm::kShares && stream_form(64, 16, 513, 16, 90 * MB) == StreamForm::kWholePairs, "");
+static_assert(stream_form(32, 16, 2049, 1, 10 * MB) == StreamForm::kShares && stream_form(32, 48, 513, 1, 10 * MB) == StreamForm::kShares, "");
+static_assert(stream_form(64, 64, 1ll << 30, 1ll << 26, 1ll << 62) == StreamForm::kShares, "");
 
 // fp32: many users of a few keys, in pages of 16 and 64 tokens ...
 static_assert(f32_takes_plain(32, 8, 1000, 1000, 1, 8, 16000) && f32_takes_plain(32, 8, 1000, 1000, 1, 32, 32000), "");
