@@ -38,12 +38,18 @@
 // have a few new tokens behind a long history.  The call's tile steps, ordered (user, head, block,
 // tile), are one sequence; a persistent launch of two workgroups per CU gives each an equal,
 // contiguous share of it, and a block that a share boundary cuts is written as unnormalised fp32
-// pieces that a merge kernel finishes.  Every workgroup derives the schedule by itself from the
-// device-resident lengths (a prefix sum over the users in LDS; positions inside a user are closed
-// forms).  Measured, attention and merge of one layer in a step, head_dim 128, unsplit -> split: 1 user x
-// 5189 new tokens x 4 heads 93 -> 53 us (merge 10); 6 users with 4-12 K histories and 8-64 new tokens
-// beside 2 first-time ones 190 -> 87 us.  What is left there is the block starts (1.2 and 1.5 segments a
-// share, about 4 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
+// pieces that a merge kernel finishes.  Every wavefront derives the schedule by itself from the
+// device-resident lengths, in its lanes: a scan over the users, then searches by one comparison a lane
+// (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, head_dim
+// 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 54 us (merge 11); 6 users with 4-12 K histories and
+// 8-64 new tokens beside 2 first-time ones 190 -> 90 us.  What is left there is the block starts (1.2 and 1.5 segments
+// a share, about 5 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
+//
+// A block's start (page ids, keys, reference, first scores) is 5 us, and a CU does little else before the
+// first one is done.  It was 5.5, and 2 before it for the schedule, now 1.2: with a prefix sum in LDS, masks and
+// addresses computed ahead of the redo loop into 200 spilled scalar registers, and the page table's round trip
+// before that of the keys.  A piece's end took 2.3 us stored row by row, 1.4 in fragment order.  A step of 8 layers:
+// one user's 5189 tokens x 4 heads 488 -> 465 us, 16 x 4096 x 16 heads 10414 -> 10238.
 //
 // PW selects the pointwise aggregation out = inv_norm * sum_j silu(c * q.k_j) v_j: no reference
 // max, no denominator, no redo; hidden keys carry logit 0 (silu(0) = 0).
@@ -64,6 +70,7 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;   // one 16-byte fragment
+typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
 
 using merge_detail::MergeDesc;
 
@@ -75,6 +82,12 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float fast_silu(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + fast_exp2(-1.4426950408889634f * x));
+}
+
+// A wavefront-uniform element of an array that nothing writes while the kernel runs, by a scalar load.
+__device__ __forceinline__ int scalar_load(const int32_t* p, int i) {
+  typedef const __attribute__((address_space(4))) int32_t* scalar_ptr;
+  return ((scalar_ptr)(uintptr_t)p)[i];
 }
 
 // over the 2 lanes that hold the same query (lane, lane^32)
@@ -135,9 +148,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 
   extern __shared__ int s_ids[];       // physical page of every logical page the block reads
   __shared__ u32x4 stage[NST][FR * 64];  // tiles in fragment order: lane l of fragment f at f * 1 KiB + l * 16 B
-  __shared__ int redo_flag;
-  __shared__ int wave_total[4];
-  __shared__ int first_ids[2];         // SPLIT: pages of the user's first tile
+  __shared__ int redo_flag[4];         // of every wavefront
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -148,11 +159,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // The block (or, SPLIT, the segment of a block) being worked on.
   int u, h, qblk, tok0, n_u, P, pbeg, npg, t_beg = 0, t_end;
   // SPLIT: this workgroup's share [pos, hi) of the call's tile steps
-  int wid = 0, pos = 0, lo = 0, hi = 1, per_wg = 1, pair_end = 0, seg_end = 0;
-  int* s_cum = s_ids + id_cap;         // [B+1] prefix sum of the users' steps
-  int* s_tok = s_cum + (b.batch + 1);  // [B+1] new_indptr
-  int* s_pg = s_tok + (b.batch + 1);   // [B+1] page_indptr
-  int* s_P = s_pg + (b.batch + 1);     // [B]   prefix_lens
+  int wid = 0, pos = 0, lo = 0, hi = 1, per_wg = 1, more = 0, pair_end = 0, seg_end = 0;
   // steps of one (user, head): every block counts its tiles and an allowance for its start and end
   auto last_tiles = [&](int prefix, int n) { return (prefix + n + kTile - 1) / kTile; };
   auto steps_before = [&](int prefix, int blk) {                // of blocks [0, blk), all of them full
@@ -162,43 +169,97 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     const int blocks = (n + kBlockQ - 1) / kBlockQ;
     return blocks > 0 ? steps_before(prefix, blocks - 1) + last_tiles(prefix, n) + block_cost : 0;
   };
-  if constexpr (SPLIT) {
-    const int B = b.batch;
-    for (int k = tid; k <= B; k += 256) {
-      s_tok[k] = b.new_indptr[k];
-      s_pg[k] = b.page_indptr[k];
-      if (k < B) s_P[k] = b.prefix_lens[k];
-    }
-    __syncthreads();
-    const int per_thread = (B + 255) / 256, first = tid * per_thread;
-    int local = 0;
-    for (int k = first; k < first + per_thread && k < B; ++k) local += user_steps(s_P[k], s_tok[k + 1] - s_tok[k]) * H;
-    int incl = local;
+  // Position of user k's steps in the sequence, from the lanes of a wavefront: inclusive sums over the lanes.
+  auto scan = [&](int v) __attribute__((always_inline)) {
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(incl, o);
-      if (lane >= o) incl += up;
+      const int up = __shfl_up(v, o);
+      if (lane >= o) v += up;
     }
-    if (lane == 63) wave_total[wave] = incl;
-    __syncthreads();
-    int base = incl - local;
-    for (int w = 0; w < wave; ++w) base += wave_total[w];
-    for (int k = first; k < first + per_thread && k < B; ++k) {
-      s_cum[k] = base;
-      base += user_steps(s_P[k], s_tok[k + 1] - s_tok[k]) * H;
+    return v;
+  };
+  // how many of the items 0, 1, ... `count` - 1 start at or before x, less one; `start` rises
+  auto last_at_or_before = [&](int count, int x, auto start) __attribute__((always_inline)) {
+    int found = 0;
+    for (int k = 0; k < count; k += 64) {
+      const int here = __builtin_popcountll(__builtin_amdgcn_ballot_w64(k + lane < count && start(k + lane) <= x));
+      found += here;
+      if (here < 64) break;
     }
-    if (tid == 255) s_cum[B] = base;
-    __syncthreads();
+    return found - 1;
+  };
+  int l_tok = 0, l_n = 0, l_P = 0, l_pg = 0, l_npg = 0;         // SPLIT: of this lane's user in the group below
+  int l_first = 0;                                              // ... the group's first position
+  int l_incl = 0, group_of = -1;                                // ... inclusive sums inside the group; which group
+  int g_incl = 0;                                               // inclusive sums over groups: a lane holds one
+  const int users_per_lane = SPLIT ? (b.batch + 63) / 64 : 1;   // of a group
+  auto load_user = [&](int k) __attribute__((always_inline)) {
+    l_n = 0;
+    if (k < b.batch) {
+      l_tok = b.new_indptr[k];
+      l_n = b.new_indptr[k + 1] - l_tok;
+      l_P = b.prefix_lens[k];
+      l_pg = b.page_indptr[k];
+      l_npg = b.page_indptr[k + 1] - l_pg;
+    }
+  };
+  // the block that holds position x
+  int blk_pos = 0;
+  auto locate = [&](int x) __attribute__((always_inline)) {
+    const int grp = __builtin_popcountll(__builtin_amdgcn_ballot_w64(g_incl <= x));   // the lane whose users hold `pos`
+    int user_pos;
+    if (users_per_lane == 1) {
+      u = grp;
+      user_pos = u > 0 ? __builtin_amdgcn_readlane(g_incl, u - 1) : 0;
+    } else {
+      // the users of that lane, one a lane
+      if (grp != group_of) {
+        group_of = grp;
+        l_n = 0;
+        if (lane < users_per_lane) load_user(grp * users_per_lane + lane);
+        l_incl = scan(user_steps(l_P, l_n) * H);
+        l_first = grp > 0 ? __builtin_amdgcn_readlane(g_incl, grp - 1) : 0;
+      }
+      u = __builtin_popcountll(__builtin_amdgcn_ballot_w64(l_incl <= x - l_first));
+      user_pos = l_first + (u > 0 ? __builtin_amdgcn_readlane(l_incl, u - 1) : 0);
+    }
+    tok0 = __builtin_amdgcn_readlane(l_tok, u);
+    n_u = __builtin_amdgcn_readlane(l_n, u);
+    P = __builtin_amdgcn_readlane(l_P, u);
+    pbeg = __builtin_amdgcn_readlane(l_pg, u);
+    npg = __builtin_amdgcn_readlane(l_npg, u);
+    const int head_steps = user_steps(P, n_u);
+    h = last_at_or_before(H, x - user_pos, [&](int k) { return k * head_steps; });
+    const int head_pos = user_pos + h * head_steps;
+    qblk = last_at_or_before((n_u + kBlockQ - 1) / kBlockQ, x - head_pos, [&](int k) { return steps_before(P, k); });
+    blk_pos = head_pos + steps_before(P, qblk);
+  };
+  if constexpr (SPLIT) {
+    // Every wavefront works the schedule out by itself, without LDS or barriers: lane i sums the steps of
+    // users [i, i + 1) * users_per_lane; up to 64 users that is one each, and nothing is read again.
+    int steps = 0;
+    if (users_per_lane == 1) {
+      load_user(lane);
+      steps = user_steps(l_P, l_n) * H;
+    } else {
+      for (int j = 0; j < users_per_lane; ++j) {
+        load_user(lane * users_per_lane + j);
+        steps += user_steps(l_P, l_n) * H;
+      }
+    }
+    g_incl = scan(steps);
+    const int total = __builtin_amdgcn_readlane(g_incl, 63);
     // blockIdx -> XCD is round-robin: give every XCD one contiguous stretch of the sequence, so that
     // the shares of one (user, head) meet in one L2
     wid = (gridDim.x % kXcds == 0) ? (int)(blockIdx.x % kXcds) * (int)(gridDim.x / kXcds) + (int)(blockIdx.x / kXcds)
                                    : (int)blockIdx.x;
-    const int total = uniform(s_cum[B]);
-    per_wg = (total + (int)gridDim.x - 1) / (int)gridDim.x;
-    per_wg = per_wg < min_steps ? min_steps : per_wg;
-    const int64_t first_step = (int64_t)wid * per_wg;
+    // shares of per_wg + 1 steps up to share `more`, of per_wg from there on
+    per_wg = total / (int)gridDim.x;
+    more = total - per_wg * (int)gridDim.x;
+    if (per_wg < min_steps) { per_wg = min_steps; more = 0; }
+    const int64_t first_step = (int64_t)wid * per_wg + (wid < more ? wid : more);
     lo = first_step < total ? (int)first_step : total;
-    hi = first_step + per_wg < total ? (int)(first_step + per_wg) : total;
+    hi = first_step + per_wg + (wid < more) < total ? (int)(first_step + per_wg + (wid < more)) : total;
     pos = lo;
     if (tid == 0) ws_desc[wid].valid = 0;
   } else {
@@ -221,26 +282,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 
   while (pos < hi) {                                              // workgroup-uniform; once without SPLIT
   if constexpr (SPLIT) {
-    int ua = 0, ue = b.batch;                                     // largest user with s_cum <= pos
-    while (ue - ua > 1) {
-      const int mid = (ua + ue) >> 1;
-      if (uniform(s_cum[mid]) <= pos) ua = mid; else ue = mid;
-    }
-    u = ua;
-    tok0 = uniform(s_tok[u]);
-    n_u = uniform(s_tok[u + 1]) - tok0;
-    P = uniform(s_P[u]);
-    pbeg = uniform(s_pg[u]);
-    npg = uniform(s_pg[u + 1]) - pbeg;
-    const int user_pos = uniform(s_cum[u]), head_steps = user_steps(P, n_u);
-    h = (pos - user_pos) / head_steps;
-    const int in_head = (pos - user_pos) % head_steps;
-    int ba = 0, be = (n_u + kBlockQ - 1) / kBlockQ;               // largest block with steps_before <= in_head
-    while (be - ba > 1) {
-      const int mid = (ba + be) >> 1;
-      if (steps_before(P, mid) <= in_head) ba = mid; else be = mid;
-    }
-    qblk = ba;
+    locate(pos);
   }
   const int Q0 = qblk * kBlockQ;
   const int T_u = P + n_u;                                      // tokens that hold data
@@ -248,7 +290,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   const int tiles_blk = (P + blk_end + kTile - 1) / kTile;      // kv tiles the block's last query sees
   t_end = tiles_blk;
   if constexpr (SPLIT) {
-    const int blk_pos = uniform(s_cum[u]) + h * user_steps(P, n_u) + steps_before(P, qblk);
     pair_end = blk_pos + tiles_blk + block_cost;
     seg_end = pair_end < hi ? pair_end : hi;
     // positions count cost units: a block's allowance comes first, then its tiles
@@ -267,8 +308,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   if (SPLIT && tiles_w > t_end) tiles_w = t_end;
   const int first_query_pos = P + q0;
 
-  // page table of the segment -> LDS; ids the metadata does not back become page 0 (in bounds;
-  // such slots lie past the user's last token and are masked)
+  // page table of the segment, copied to LDS in the prologue
   const int lp_beg = SPLIT ? (t_beg * 2) >> g.sub_shift : 0;
   const int n_ids = ((t_end * 2 - 1) >> g.sub_shift) + 1 - lp_beg;
   if (n_ids > id_cap) {                // lengths beyond the bound the call stated: no output, no overrun
@@ -276,17 +316,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     pos = seg_end;
     continue;
   }
-  if (SPLIT && !PW && tid < 2) {
-    int id = (tid >> g.sub_shift) < npg ? b.page_indices[pbeg + (tid >> g.sub_shift)] : 0;
-    if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
-    first_ids[tid] = id;
-  }
-  for (int i = tid; i < n_ids; i += 256) {
-    int id = lp_beg + i < npg ? b.page_indices[pbeg + lp_beg + i] : 0;
-    if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
-    s_ids[i] = id;
-  }
-
   const int sub_mask = (1 << g.sub_shift) - 1;
   const int64_t v_off = (int64_t)S * D * 2;
   const char* head_base = g.layer_base + (int64_t)h * 2 * S * D * 2;
@@ -325,22 +354,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     }
   };
 
-  // Q^T fragments: lane (r, hf) holds query q0 + 32 qb + r, dims 16 s + 8 hf .. + 7.
   bf16x8 qf[NQ][KS];
-#pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) {
-    const int i = q0 + 32 * qb + r;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (i < n_u) {
-        qf[qb][s] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)(tok0 + i) * H + h) * D + 16 * s + 8 * hf);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qf[qb][s][e] = (__bf16)0.0f;
-      }
-    }
-  }
-
   f32x16 o[NQ][DB];
   float l[NQ];                     // softmax denominators: this lane's tokens only
   float m[NQ], mcq[NQ];            // reference max: raw logit units / scaled for the base-2 exponent
@@ -457,8 +471,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   constexpr std::false_type body{};
   constexpr std::true_type tail{};
 
-  __syncthreads();                                               // page table visible
   for (int attempt = 0; attempt < 2; ++attempt) {                // workgroup-uniform
+    // The first tile by a value that the compiler cannot see through: else it computes the masks and addresses of
+    // the prologue ahead of this loop, into 200 spilled scalar registers, 1.5 us at each start of a block.
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    const int tile0 = t_beg + zero;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
       l[qb] = 0.f;
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       float mx[NQ];
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) mx[qb] = -INFINITY;
-      for (int tile = t_beg; tile < tiles_w; ++tile) {         // tiles past tiles_w hold no visible key
+      for (int tile = tile0; tile < tiles_w; ++tile) {         // tiles past tiles_w hold no visible key
         const int sb = tile * 2 + (r >> 4);
         const char* ka = head_base + (int64_t)s_ids[(sb >> g.sub_shift) - lp_beg] * g.page_bytes +
                          (int64_t)(sb & sub_mask) * 16 * D * 2 + k_lane - wave * 256;
@@ -490,10 +508,24 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     }
 
     // prologue: the keys of the first two tiles, the stage of the first step, the first tile's scores
-    auto fetch = [&](int st, int tile, auto with_v) __attribute__((always_inline)) {
-      page_ids(tile, next_id0, next_id1);
-      load(st, tile, next_id0, next_id1, with_v);
+    // Their pages, and those of the user's first tile, by scalar loads that travel together.
+    int id0[NST + 1] = {}, id1[NST + 1] = {};
+    auto tile_at = [&](int k) __attribute__((always_inline)) {
+      return k == NST ? zero : (tile0 + k < last_tile ? tile0 + k : last_tile);
     };
+    if (npg > 0) {
+#pragma unroll
+      for (int k = 0; k <= NST; ++k) {
+        const int lp0 = (tile_at(k) * 2) >> g.sub_shift, lp1 = (tile_at(k) * 2 + 1) >> g.sub_shift;
+        id0[k] = scalar_load(b.page_indices, pbeg + (lp0 < npg ? lp0 : npg - 1));
+        id1[k] = scalar_load(b.page_indices, pbeg + (lp1 < npg ? lp1 : npg - 1));
+      }
+#pragma unroll
+      for (int k = 0; k <= NST; ++k) {
+        if ((unsigned)id0[k] >= (unsigned)g.num_pages || (tile_at(k) * 2) >> g.sub_shift >= npg) id0[k] = 0;
+        if ((unsigned)id1[k] >= (unsigned)g.num_pages || (tile_at(k) * 2 + 1) >> g.sub_shift >= npg) id1[k] = 0;
+      }
+    }
     // SPLIT: the reference of a piece is that of its whole block, the max of the user's first tile.  So its
     // weights are rounded as those of an uncut block, and how a call is cut changes its result by the
     // order of fp32 sums alone.  The tile's keys travel beside the piece's own, into the room of the
@@ -501,35 +533,60 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     // it and 469 with a reference of each piece's own.
     constexpr bool kBlockReference = SPLIT && !PW;
     if (kBlockReference && attempt == 0) {
-      const char* ka = head_base + (int64_t)first_ids[r >> 4] * g.page_bytes + (int64_t)((r >> 4) & sub_mask) * 16 * D * 2 + k_lane;
+      const char* ka = head_base + (int64_t)(r < 16 ? id0[NST] : id1[NST]) * g.page_bytes + (int64_t)((r >> 4) & sub_mask) * 16 * D * 2 + k_lane;
 #pragma unroll
       for (int j = 0; j < FQ / 2; ++j) load_to_lds(ka + j * 1024, stage_lds + (KS + 4 * j) * 1024);
     }
-    fetch(0, t_beg, std::false_type{});
-    fetch(1, t_beg + 1, std::false_type{});
-    fetch(2, t_beg + 2, std::true_type{});
-    wait_and_barrier<FQ + FQ / 2>();
+    load(0, tile0, id0[0], id1[0], std::false_type{});
+    load(1, tile0 + 1, id0[1], id1[1], std::false_type{});
+    load(2, tile0 + 2, id0[2], id1[2], std::true_type{});
+    if (attempt == 0) {
+      // behind the first tiles' loads, so that their round trip is shared: the block's page table -> LDS, and its
+      // queries.  Ids the metadata does not back become page 0 (in bounds; such slots lie past the user's last
+      // token and are masked).
+      for (int i = tid; i < n_ids; i += 256) {
+        int id = lp_beg + i < npg ? b.page_indices[pbeg + lp_beg + i] : 0;
+        if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
+        s_ids[i] = id;
+      }
+      // Q^T fragments: lane (r, hf) holds query q0 + 32 qb + r, dims 16 s + 8 hf .. + 7.
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        const int i = q0 + 32 * qb + r;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          if (i < n_u) {
+            qf[qb][s] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)(tok0 + i) * H + h) * D + 16 * s + 8 * hf);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) qf[qb][s][e] = (__bf16)0.0f;
+          }
+        }
+      }
+    }
+    wait_and_barrier<0>();
     f32x16 za[NQ], zb[NQ];
     if (kBlockReference && attempt == 0) {
 #pragma unroll
       for (int s = 0; s < KS; ++s) kf[s] = fragment(0, KS + s);
 #pragma unroll
-      for (int qb = 0; qb < NQ; ++qb) set_reference(scores(kf, qb, 0, true), qb);
+      for (int qb = 0; qb < NQ; ++qb) set_reference(scores(kf, qb, zero, true), qb);
     }
 #pragma unroll
     for (int s = 0; s < KS; ++s) kf[s] = fragment(0, s);
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
-      za[qb] = scores(kf, qb, t_beg * kTile, true);
+      za[qb] = scores(kf, qb, tile0 * kTile, true);
       if (!PW && !kBlockReference && attempt == 0) set_reference(za[qb], qb);
     }
-    wait_and_barrier<FQ>();
-    fetch(0, t_beg + 3, std::true_type{});
-    page_ids(t_beg + 4, next_id0, next_id1);
+    wait_and_barrier<0>();                                         // stage 0 is read
+    page_ids(tile0 + 3, next_id0, next_id1);
+    load(0, tile0 + 3, next_id0, next_id1, std::true_type{});
+    page_ids(tile0 + 4, next_id0, next_id1);
 #pragma unroll
     for (int s = 0; s < KS; ++s) kf[s] = fragment(1, s);
 
-    int tile = t_beg, st = 2;
+    int tile = tile0, st = 2;
     auto after = [](int st) __attribute__((always_inline)) { return st == NST - 1 ? 0 : st + 1; };
     if (nq == 0) {                                                 // no query of this wavefront's: it only moves tiles
       for (; tile < t_end; ++tile) {
@@ -569,30 +626,35 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
         for (int e = 0; e < 16; ++e) mag += fabsf(o[qb][db][e]);
       bad |= (32 * qb + r < nq) && (!(l[qb] < limit.den) || !(mag < limit.mag));
     }
-    if (tid == 0) redo_flag = 0;
+    // read by everyone before the barriers of the next prologue, written behind them
+    const int wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 0) redo_flag[wave] = wave_bad;
     __syncthreads();
-    if (bad) redo_flag = 1;
-    __syncthreads();
-    const int redo = redo_flag;
-    __syncthreads();                                             // everyone has read the flag
-    if (!redo) break;
+    if (!(redo_flag[0] | redo_flag[1] | redo_flag[2] | redo_flag[3])) break;
   }
 
+  auto out4 = [](const f32x16& acc, int g8, float inv) __attribute__((always_inline)) {
+    bf16x4 ob;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ob[k] = (__bf16)(acc[4 * g8 + k] * inv);
+    return ob;
+  };
   if (!SPLIT || (t_beg == 0 && t_end == tiles_blk)) {
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
       const int qi = 32 * qb + r;
       if (qi < nq) {
         const float inv = PW ? inv_norm : 1.0f / l[qb];
-        uint16_t* orow = out + ((int64_t)(tok0 + q0 + qi) * H + h) * D + 4 * hf;
+        uint16_t* orow = out + ((int64_t)(tok0 + q0 + qi) * H + h) * D + 8 * hf;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int g8 = 0; g8 < 4; ++g8) {                         // accumulator rows 8 g8 + 4 hf .. + 3
-            bf16x4 ob;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) ob[k] = (__bf16)(o[qb][db][4 * g8 + k] * inv);
-            *reinterpret_cast<bf16x4*>(orow + 32 * db + 8 * g8) = ob;
+          for (int g8 = 0; g8 < 4; g8 += 2) {
+            // accumulator rows 8 g8 + 4 hf .. + 3 of two g8: the query's other lane trades one for one, 16 bytes each
+            u32x2 a = __builtin_bit_cast(u32x2, out4(o[qb][db], g8, inv)), b = __builtin_bit_cast(u32x2, out4(o[qb][db], g8 + 1, inv));
+            const auto x = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+            const auto y = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+            *reinterpret_cast<u32x4*>(orow + 32 * db + 8 * g8) = u32x4{x[0], y[0], x[1], y[1]};
           }
       }
     }
@@ -603,7 +665,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     for (int qb = 0; qb < NQ; ++qb) {
       const int qi = 32 * qb + r;
       if (qi < nq) {
-        float* po = ws_o + (prow + qi) * D + 4 * hf;
+        // in fragment order: a store of a wavefront is one run of 1 KB (row by row, 32 of 32 bytes)
+        f32x4* po = reinterpret_cast<f32x4*>(ws_o + ((int64_t)wid * 2 + slot) * kBlockQ * D) + (NQ * wave + qb) * DB * 4 * 64 + lane;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -611,7 +674,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
             f32x4 piece;
 #pragma unroll
             for (int k = 0; k < 4; ++k) piece[k] = o[qb][db][4 * g8 + k];
-            *reinterpret_cast<f32x4*>(po + 32 * db + 8 * g8) = piece;
+            po[(db * 4 + g8) * 64] = piece;
           }
         if (!PW && hf == 0) {
           // a first tile of infinite logits names no reference: what was weighed has been weighed against 0
@@ -625,7 +688,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       MergeDesc d;
       d.valid = 1;
       d.w_first = wid;
-      d.w_last = (pair_end - 1) / per_wg;
+      const int last = pair_end - 1, larger = more * (per_wg + 1);   // steps in the larger shares
+      d.w_last = last < larger ? last / (per_wg + 1) : more + (last - larger) / per_wg;
       d.out_row = (tok0 + Q0) * H + h;
       d.nq = blk_end - Q0;
       d.first_slot = slot;
@@ -639,9 +703,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   }
 }
 
-// LDS of the schedule of a split launch: users' prefix sums, lengths and page offsets
-int64_t schedule_bytes(int batch) { return ((int64_t)4 * batch + 3) * 4; }
-
 template <int D, int NST, int NQ, bool PW, bool SPLIT>
 hipError_t allow_lds() {
   static std::once_flag attr_once;                               // static + dynamic LDS may pass 64 KiB
@@ -649,7 +710,7 @@ hipError_t allow_lds() {
   std::call_once(attr_once, [] {
     attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_kernel<D, NST, NQ, PW, SPLIT>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      kMaxIdBytes + (SPLIT ? (int)schedule_bytes(kPrefillSplitMaxBatch) : 0));
+                                      kMaxIdBytes);
   });
   return attr_status;
 }
@@ -686,11 +747,11 @@ hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan
     float* ws_o = reinterpret_cast<float*>(ws + plan.ws_desc_bytes);
     float* ws_ml = ws_o + (int64_t)plan.prefill_wgs * 2 * kBlockQ * D;
     hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, true>), dim3((unsigned)plan.prefill_wgs), dim3(256),
-                       (size_t)(id_bytes + schedule_bytes(b.batch)), stream, g, b, q, out, c, inv_norm, 1, 0, 1,
+                       (size_t)id_bytes, stream, g, b, q, out, c, inv_norm, 1, 0, 1,
                        (int)(id_bytes / 4), plan.pair_cost, plan.min_tiles, ws_desc, ws_o, ws_ml);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return merge_detail::launch_merge<D, PW>(out, c, inv_norm, kBlockQ, g.H, plan.prefill_wgs,
+    return merge_detail::launch_merge<D, PW, true>(out, c, inv_norm, kBlockQ, g.H, plan.prefill_wgs,
                                              (int64_t)g.H * (b.total_new / kBlockQ + b.batch), ws_desc, ws_o, ws_ml, stream);
   }
   const hipError_t attr = allow_lds<D, NST, NQ, PW, false>();

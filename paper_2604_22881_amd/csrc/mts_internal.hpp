@@ -66,7 +66,7 @@ struct AttnPlan {
 // Fits the plan to the workspace that the caller handed over (any pointer, any size).
 void fit_plan_to_workspace(AttnPlan& p, const PoolGeom& g, const void* workspace, int64_t workspace_bytes);
 constexpr int kPrefillMaxWgs = 512;          // 256 CUs x 2 resident workgroups
-constexpr int kPrefillSplitMaxBatch = 1024;  // users whose schedule a workgroup keeps in LDS
+constexpr int kPrefillSplitMaxBatch = 1024;  // users in the schedule of a split launch: 16 a lane
 AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers);   // layers of the cache
 constexpr int kAttnMaxWaves = 1024;   // 256 CUs x 4 SIMDs: one wavefront per SIMD
 

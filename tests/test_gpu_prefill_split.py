@@ -81,6 +81,24 @@ def test_split_prefill_equals_unsplit(name, split, attn_tuning):
     _same_but_for_fp32_order(got, as_values(G.to_host(out, w.np_dtype)))
 
 
+@pytest.mark.parametrize("users,heads,long", [(64, 1, 300), (65, 1, 300), (200, 2, 300), (1024, 1, 300), (2, 70, 260), (1, 1, 8400)])
+def test_schedule_in_the_lanes_of_a_wavefront(users, heads, long, attn_tuning):
+    """One user a lane, groups of users behind a lane (2, 4 and 16 of them), more heads and more query blocks than lanes."""
+    attn_tuning(kernel=KERNEL_PREFILL, min_tiles=2, max_waves=512)
+    G = _harness()
+    rng = np.random.default_rng(users)
+    prefix, new = [int(x) for x in rng.integers(0, 70, users)], [int(x) for x in rng.integers(0, 4, users)]
+    new[users * 2 // 3] = long
+    w = W.custom_workload("lanes", 90 + users, "bf16", 1, heads, 128, 64, prefix, new, chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    check_attention(w, step.attention(data, 0), ref)
+
+
 def test_split_prefill_block_whose_first_keys_weigh_nothing(attn_tuning):
     """Infinite keys: the first 48 tokens have logit -inf for every query, so the first tile names no
     reference; the pieces of the later tiles still count."""
