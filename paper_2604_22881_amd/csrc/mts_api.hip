@@ -240,6 +240,11 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers) {
   const int64_t tiles_upper = items * ((b.max_total_len + 31) / 32 + 1 + p.pair_cost) * g.H;   // schedule units of the call
   if (items > 16384 || b.batch > 4096 || tiles_upper >= (1ll << 31)) { p.too_large = true; return p; }
   p.n_items = (int)items;
+  // A tile in the onload buffer is 32 rows of one head out of many, half a cache line to two each, and a transpose.
+  // Steps of 4 layers with staged users, counted as 1, 2, 3, 4 tiles of the pool: 4 of 32 users x 3600 tokens x 8 heads of 64
+  // 308, 268, 265, 263 us; 16 of 32 384, 356, 379, 400; all of 24 380, 377, 383, 380; 2 of 24 x 1000-9000 x 4 of 128 285, 277,
+  // 283, 284; 7 of 100 x 4 of 32 204, 188, 190, 194.
+  p.staged_tile_cost = 2 * tiles_upper < (1ll << 31) ? 2 : 1;
   p.past_caches = p.q_tiles_max == 1 && kv_past_caches(g.D, (int64_t)b.total_pages * g.page_bytes, layers,
                                                        (int64_t)b.total_pages * g.S / b.batch);
   // A wavefront's share is never shorter than this: below it, the start of a share costs more than

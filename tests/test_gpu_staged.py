@@ -7,6 +7,7 @@ import pytest
 
 import mts_workloads as W
 import oracle
+from conftest import KERNEL_STREAMING
 from helpers import draw_step_data
 from test_gpu_parity import CASES, SCHEDULES, FILL, _case, _random_case, check_attention
 
@@ -126,6 +127,17 @@ def test_staged_prefix_lengths_around_run_and_tile_boundaries():
     w = W.custom_workload("staged_edges", 91, "bf16", 1, 2, 64, 16, prefix, [3, 17, 32, 33, 64, 1, 8, 40, 5, 2])
     _run(w, list(range(w.batch)), 64)
     _run(w, [0, 3, 4, 9], 32)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("plan", [dict(min_tiles=1, pair_cost=1), dict(min_tiles=3, pair_cost=2), dict(min_tiles=7, pair_cost=1),
+                                  dict(max_waves=4, pair_cost=3), dict(max_waves=28, pair_cost=1)])
+def test_staged_shares_that_begin_and_end_inside_a_tile(plan, D, attn_tuning):
+    """A staged tile counts more than one unit of the schedule: shares of the least and of odd lengths cut its units,
+    and pairs whose last units lie alone in a share."""
+    attn_tuning(kernel=KERNEL_STREAMING, **plan)
+    w = W.custom_workload("staged_units", 93 + D, "bf16", 1, 3, D, 16, [1201, 700, 33, 0, 5, 320], [20, 1, 40, 9, 2, 33])
+    _run(w, [0, 2, 4, 5], 96)
 
 
 def test_staged_nobody_staged_equals_the_unappended_call():
