@@ -81,6 +81,21 @@ def test_split_prefill_equals_unsplit(name, split, attn_tuning):
     _same_but_for_fp32_order(got, as_values(G.to_host(out, w.np_dtype)))
 
 
+@pytest.mark.parametrize("heads", [5, 8, 30])                   # shares of 2 and 1 steps, of 3 and 1 or 4 and 2, of 10 to 13 and 5 to 7
+@pytest.mark.parametrize("D", [64, 128])
+def test_unequal_shares_of_a_full_launch(D, heads, attn_tuning):
+    """A launch that fills the chip gives a CU two neighbouring shares, the first of them larger."""
+    attn_tuning(kernel=KERNEL_PREFILL, min_tiles=1, max_waves=2048, pair_cost=1)
+    w = W.custom_workload("unequal", 310 + D + heads, "bf16", 1, heads, D, 16, [1500, 0, 700, 0], [8, 600, 200, 0], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = _harness().GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    check_attention(w, step.attention(data, 0), ref)
+
+
 @pytest.mark.parametrize("users,heads,long", [(64, 1, 300), (65, 1, 300), (200, 2, 300), (1024, 1, 300), (2, 70, 260), (1, 1, 8400)])
 def test_schedule_in_the_lanes_of_a_wavefront(users, heads, long, attn_tuning):
     """One user a lane, groups of users behind a lane (2, 4 and 16 of them), more heads and more query blocks than lanes."""
