@@ -90,6 +90,9 @@ def test_workspace_query_is_host_only():
     (128, 4, 1, 5189, 5189, 0, True),          # one first-time user: few blocks, the longest of them the whole launch
     (64, 8, 1, 6000, 6000, 0, True),
     (128, 4, 8, 9000, 5500, 48000, True),      # a few new tokens behind long histories, beside first-time users
+    (128, 8, 23, 25605, 3517, 117083, True),   # ... where the mean lengths promise work for all CUs: the long users are not the new ones
+    (128, 4, 17, 7444, 2638, 46860, True),
+    (128, 8, 8, 4800, 1600, 1200, False),      # ... and where the histories are short
     (128, 4, 20, 10300, 800, 0, False),        # enough blocks of moderate length: cutting them costs more than it fills
     (128, 4, 12, 12000, 1000, 0, False),
     (64, 8, 12, 8600, 1200, 0, False),
