@@ -53,6 +53,26 @@ def test_joined_pieces_match_oracle(D, top, attn_tuning):
             check()
 
 
+@pytest.mark.parametrize("users,top", [(64, 3), (65, 3), (32, 90), (33, 90), (1, 1)])
+@pytest.mark.parametrize("plan", [PLANS[0], PLANS[3], PLANS[4]])
+def test_schedule_up_to_the_lanes_of_a_wavefront(plan, users, top, attn_tuning):
+    """64 (user, query tile)s are scheduled in the lanes, more through LDS; users without new tokens and query tiles
+    without queries among them, in the first and the last lanes too."""
+    rng = np.random.default_rng(users + top)
+    prefix = [int(x) for x in rng.integers(0, 200, users)]
+    new = [int(x) for x in rng.integers(0, 4, users)]
+    new[0], new[-1] = 0, 0
+    new[users // 2] = top
+    attn_tuning(kernel=KERNEL_STREAMING, **plan)
+    w = W.custom_workload("lanes", 90 + users, "bf16", 1, 2, 64, 16, prefix, new, chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = _harness().GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    for check in _check_all_forms(w, step, data):
+        check()
+
+
 @pytest.mark.parametrize("heads", [2, 32])              # 32: enough wavefronts to fold inside workgroups
 def test_joined_piece_with_a_far_larger_reference(heads, attn_tuning):
     """One piece of a cut pair holds a key that outweighs everything in the others: the fold scales
