@@ -147,6 +147,12 @@ def _check(code):
 
 def _ptr(x):
     """Address of a torch tensor / numpy array / int / None."""
+    if type(x) is int:
+        return x
+    try:
+        return x.data_ptr()             # tensors before the rest: the smallest calls take as long as the host needs
+    except AttributeError:
+        pass
     if x is None:
         return None
     if isinstance(x, int):
@@ -197,50 +203,51 @@ def mts_attn_set_tuning(min_tiles=0, max_waves=0, pair_cost=0, kernel=0):
 
 
 # ---- device entry points ----------------------------------------------------------------
+# A structure goes to a POINTER parameter as it is: ctypes passes its address, without an object for it.
 
 def mts_kv_unpack(desc, layer, staging, num_segs, seg_user, seg_pos, seg_tok_indptr, max_seg_tokens,
                   meta, stream=None):
-    return _check(lib().mts_kv_unpack(C.byref(desc), layer, _ptr(staging), num_segs, _ptr(seg_user),
+    return _check(lib().mts_kv_unpack(desc, layer, _ptr(staging), num_segs, _ptr(seg_user),
                                       _ptr(seg_pos), _ptr(seg_tok_indptr), max_seg_tokens,
-                                      C.byref(meta), _stream(stream)))
+                                      meta, _stream(stream)))
 
 
 def mts_kv_pack(desc, layer, staging_out, num_segs, seg_user, seg_pos, seg_tok_indptr, max_seg_tokens,
                 meta, stream=None):
-    return _check(lib().mts_kv_pack(C.byref(desc), layer, _ptr(staging_out), num_segs, _ptr(seg_user),
+    return _check(lib().mts_kv_pack(desc, layer, _ptr(staging_out), num_segs, _ptr(seg_user),
                                     _ptr(seg_pos), _ptr(seg_tok_indptr), max_seg_tokens,
-                                    C.byref(meta), _stream(stream)))
+                                    meta, _stream(stream)))
 
 
 def mts_kv_unpack_layers(desc, layer_begin, layer_count, staging, staging_layer_stride_bytes, num_segs,
                          seg_user, seg_pos, seg_tok_indptr, max_seg_tokens, meta, stream=None):
-    return _check(lib().mts_kv_unpack_layers(C.byref(desc), layer_begin, layer_count, _ptr(staging),
+    return _check(lib().mts_kv_unpack_layers(desc, layer_begin, layer_count, _ptr(staging),
                                              staging_layer_stride_bytes, num_segs, _ptr(seg_user),
                                              _ptr(seg_pos), _ptr(seg_tok_indptr), max_seg_tokens,
-                                             C.byref(meta), _stream(stream)))
+                                             meta, _stream(stream)))
 
 
 def mts_kv_pack_layers(desc, layer_begin, layer_count, staging_out, staging_layer_stride_bytes, num_segs,
                        seg_user, seg_pos, seg_tok_indptr, max_seg_tokens, meta, stream=None):
-    return _check(lib().mts_kv_pack_layers(C.byref(desc), layer_begin, layer_count, _ptr(staging_out),
+    return _check(lib().mts_kv_pack_layers(desc, layer_begin, layer_count, _ptr(staging_out),
                                            staging_layer_stride_bytes, num_segs, _ptr(seg_user),
                                            _ptr(seg_pos), _ptr(seg_tok_indptr), max_seg_tokens,
-                                           C.byref(meta), _stream(stream)))
+                                           meta, _stream(stream)))
 
 
 def mts_kv_append(desc, layer, k_new, v_new, meta, stream=None):
-    return _check(lib().mts_kv_append(C.byref(desc), layer, _ptr(k_new), _ptr(v_new), C.byref(meta),
+    return _check(lib().mts_kv_append(desc, layer, _ptr(k_new), _ptr(v_new), meta,
                                       _stream(stream)))
 
 
 def mts_kv_append_layers(desc, layer_begin, layer_count, k_new, v_new, rows_layer_stride_bytes, meta, stream=None):
-    return _check(lib().mts_kv_append_layers(C.byref(desc), layer_begin, layer_count, _ptr(k_new), _ptr(v_new),
-                                             int(rows_layer_stride_bytes), C.byref(meta), _stream(stream)))
+    return _check(lib().mts_kv_append_layers(desc, layer_begin, layer_count, _ptr(k_new), _ptr(v_new),
+                                             int(rows_layer_stride_bytes), meta, _stream(stream)))
 
 
 def mts_attn_incremental(desc, layer, q, out, meta, sm_scale=0.0, workspace=None, workspace_bytes=0,
                          stream=None):
-    return _check(lib().mts_attn_incremental(C.byref(desc), layer, _ptr(q), _ptr(out), C.byref(meta),
+    return _check(lib().mts_attn_incremental(desc, layer, _ptr(q), _ptr(out), meta,
                                              float(sm_scale), _ptr(workspace), int(workspace_bytes),
                                              _stream(stream)))
 
@@ -249,40 +256,40 @@ MTS_NOALLOC_SCRATCH_BYTES = 40 << 20
 
 
 def mts_attn_incremental_noalloc(desc, layer, q, out, meta, sm_scale=0.0, stream=None):
-    return _check(lib().mts_attn_incremental_noalloc(C.byref(desc), layer, _ptr(q), _ptr(out), C.byref(meta),
+    return _check(lib().mts_attn_incremental_noalloc(desc, layer, _ptr(q), _ptr(out), meta,
                                                      float(sm_scale), _stream(stream)))
 
 
 def mts_attn_pointwise(desc, layer, q, out, meta, inv_norm, sm_scale=0.0, workspace=None, workspace_bytes=0,
                        stream=None):
-    return _check(lib().mts_attn_pointwise(C.byref(desc), layer, _ptr(q), _ptr(out), C.byref(meta),
+    return _check(lib().mts_attn_pointwise(desc, layer, _ptr(q), _ptr(out), meta,
                                            float(sm_scale), float(inv_norm), _ptr(workspace),
                                            int(workspace_bytes), _stream(stream)))
 
 
 def mts_attn_unappended_appends(desc: CacheDesc, meta: BatchMeta):
-    return bool(_check(lib().mts_attn_unappended_appends(C.byref(desc), C.byref(meta))))
+    return bool(_check(lib().mts_attn_unappended_appends(desc, meta)))
 
 
 def mts_attn_incremental_unappended(desc, layer, q, k_new, v_new, out, meta, sm_scale=0.0, workspace=None,
                                     workspace_bytes=0, stream=None):
-    return _check(lib().mts_attn_incremental_unappended(C.byref(desc), layer, _ptr(q), _ptr(k_new), _ptr(v_new),
-                                                        _ptr(out), C.byref(meta), float(sm_scale), _ptr(workspace),
+    return _check(lib().mts_attn_incremental_unappended(desc, layer, _ptr(q), _ptr(k_new), _ptr(v_new),
+                                                        _ptr(out), meta, float(sm_scale), _ptr(workspace),
                                                         int(workspace_bytes), _stream(stream)))
 
 
 def mts_attn_pointwise_unappended(desc, layer, q, k_new, v_new, out, meta, inv_norm, sm_scale=0.0, workspace=None,
                                   workspace_bytes=0, stream=None):
-    return _check(lib().mts_attn_pointwise_unappended(C.byref(desc), layer, _ptr(q), _ptr(k_new), _ptr(v_new),
-                                                      _ptr(out), C.byref(meta), float(sm_scale), float(inv_norm),
+    return _check(lib().mts_attn_pointwise_unappended(desc, layer, _ptr(q), _ptr(k_new), _ptr(v_new),
+                                                      _ptr(out), meta, float(sm_scale), float(inv_norm),
                                                       _ptr(workspace), int(workspace_bytes), _stream(stream)))
 
 
 def mts_attn_incremental_staged(desc, layer, q, k_new, v_new, staged_rows, staged_first_run, staged_run_tok,
                                 chunk_tokens, out, meta, sm_scale=0.0, workspace=None, workspace_bytes=0, stream=None):
-    return _check(lib().mts_attn_incremental_staged(C.byref(desc), layer, _ptr(q), _ptr(k_new), _ptr(v_new),
+    return _check(lib().mts_attn_incremental_staged(desc, layer, _ptr(q), _ptr(k_new), _ptr(v_new),
                                                     _ptr(staged_rows), _ptr(staged_first_run), _ptr(staged_run_tok),
-                                                    int(chunk_tokens), _ptr(out), C.byref(meta), float(sm_scale),
+                                                    int(chunk_tokens), _ptr(out), meta, float(sm_scale),
                                                     _ptr(workspace), int(workspace_bytes), _stream(stream)))
 
 
