@@ -37,7 +37,7 @@
 // (fewer blocks than CUs, the longest of them the whole launch), or a batch in which some users
 // have a few new tokens behind a long history.  The call's tile steps, ordered (user, head, block,
 // tile), are one sequence; a persistent launch of two workgroups per CU gives each a contiguous
-// share of it (the first on a CU a larger one, see kFirstShare's use), and a block that a share boundary cuts is written as unnormalised fp32
+// share of it (the first on a CU a larger one, see kFirstShare), and a block that a share boundary cuts is written as unnormalised fp32
 // pieces that a merge kernel finishes.  Every wavefront derives the schedule by itself from the
 // device-resident lengths, in its lanes: a scan over the users, then searches by one comparison a lane
 // (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, head_dim
@@ -59,6 +59,7 @@
 #include <type_traits>
 
 #include "mts_attn_merge.hpp"
+#include "mts_attn_rules.hpp"
 #include "mts_internal.hpp"
 
 namespace mts {
@@ -77,7 +78,6 @@ using merge_detail::MergeDesc;
 constexpr int kTile = 32;        // kv tokens per step
 constexpr int kXcds = 8;
 constexpr int kMaxIdBytes = 64 * 1024;   // LDS page table of one block
-constexpr int kFirstShare = 60;           // per cent of a CU's two shares, for the workgroup that comes first
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -160,7 +160,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // The block (or, SPLIT, the segment of a block) being worked on.
   int u, h, qblk, tok0, n_u, P, pbeg, npg, t_beg = 0, t_end;
   // SPLIT: this workgroup's share [pos, hi) of the call's tile steps
-  int wid = 0, pos = 0, lo = 0, hi = 1, per_two = 2, per_first = 1, pair_end = 0, seg_end = 0;   // shares 2 k and 2 k + 1, the first of them
+  int wid = 0, pos = 0, lo = 0, hi = 1, pair_end = 0, seg_end = 0;
+  PrefillShares shares{2, 1, false};
   // steps of one (user, head): every block counts its tiles and an allowance for its start and end
   auto last_tiles = [&](int prefix, int n) { return (prefix + n + kTile - 1) / kTile; };
   auto steps_before = [&](int prefix, int blk) {                // of blocks [0, blk), all of them full
@@ -252,25 +253,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     const int total = __builtin_amdgcn_readlane(g_incl, 63);
     // blockIdx -> XCD is round-robin, and inside an XCD the first half of a full launch's workgroups come first to
     // their CUs, the second half to the same ones.  Every XCD gets one contiguous stretch of the sequence, so
-    // that the shares of one (user, head) meet in one L2, and a CU two neighbouring shares, the first of
-    // them larger: the workgroup that came first is served first (of equal shares the first ended after 59 us of a launch
-    // and the second after 72).  A step by the first one's part, 50 / 58 / 62 / 66 / 70 per cent: one user's 5189 tokens x 4
-    // heads of 128 445, 441, 439, 446, 461 us; beside two of 4-6 K six users behind 5-11 K 764, 742, 749, 757, 771; 12000 x 4 of
-    // 64 846, 811, 796, 830, 822; 2 of 4-6 K and 25 behind 600 x 8 of 64 920, 891, 899, 921, 953.
+    // that the shares of one (user, head) meet in one L2, and a CU two neighbouring shares.
     const int slots = (int)gridDim.x / kXcds, xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-    const bool full = (int)gridDim.x == kPrefillMaxWgs && total / (int)gridDim.x >= min_steps;
-    if (full) {
+    shares = prefill_shares(total, (int)gridDim.x, min_steps, (int)gridDim.x == kPrefillMaxWgs);
+    if (shares.paired) {
       wid = 2 * (xcd * (slots / 2) + slot % (slots / 2)) + slot / (slots / 2);
-      per_two = (total - 1) / (kPrefillMaxWgs / 2) + 1;
-      per_first = per_two * kFirstShare / 100 + 1 < per_two ? per_two * kFirstShare / 100 + 1 : per_two - 1;
     } else {
-      per_first = (total - 1) / (int)gridDim.x + 1;
-      if (per_first < min_steps) per_first = min_steps;
-      per_two = 2 * per_first;
       wid = gridDim.x % kXcds == 0 ? xcd * slots + slot : (int)blockIdx.x;
     }
-    const int64_t first_step = (int64_t)(wid >> 1) * per_two + (wid & 1) * per_first;
-    const int64_t last_step = first_step + ((wid & 1) ? per_two - per_first : per_first);
+    const int64_t first_step = shares.begin(wid), last_step = shares.end(wid);
     lo = first_step < total ? (int)first_step : total;
     hi = last_step < total ? (int)last_step : total;
     pos = lo;
@@ -701,8 +692,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       MergeDesc d;
       d.valid = 1;
       d.w_first = wid;
-      const int last = pair_end - 1, two = last / per_two;
-      d.w_last = 2 * two + (last - two * per_two >= per_first);
+      d.w_last = shares.of(pair_end - 1);
       d.out_row = (tok0 + Q0) * H + h;
       d.nq = blk_end - Q0;
       d.first_slot = slot;

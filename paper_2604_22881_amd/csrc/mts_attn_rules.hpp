@@ -1,4 +1,4 @@
-// Where the forms of the attention change over: host-only rules on sizes.
+// Where the forms of the attention change over, and how a split prefill launch is shared out: rules on sizes.
 #pragma once
 #include <stdint.h>
 
@@ -56,6 +56,34 @@ constexpr StreamForm stream_form(int head_dim, int q_tile, int64_t pairs, int64_
                                          : (head_dim == 64 && q_tile <= 16 ? 16 : 0);
   if (max_tiles <= whole) return StreamForm::kWholePairs;
   return pairs <= 96 && call_bytes <= (head_dim == 128 ? 160ll << 20 : 80ll << 20) ? StreamForm::kPieces : StreamForm::kShares;
+}
+
+// Shares of a split prefill launch: workgroup `wid` of it takes the tile steps [begin(wid), end(wid)) of the call's
+// sequence of `total`.  Shares 2 k and 2 k + 1 are a CU's two in a launch that fills the chip, and there the first is
+// the larger one, kFirstShare per cent of both: the workgroup that came first is served first (of equal shares the first
+// ended after 59 us of a launch and the second after 72).  A step by the first one's part, 50 / 58 / 62 / 66 / 70 per cent: one
+// user's 5189 tokens x 4 heads of 128 445, 441, 439, 446, 461 us; beside two of 4-6 K six users behind 5-11 K 764, 742, 749,
+// 757, 771; 12000 x 4 of 64 846, 811, 796, 830, 822; 2 of 4-6 K and 25 behind 600 x 8 of 64 920, 891, 899, 921, 953.
+constexpr int kFirstShare = 60;
+struct PrefillShares {
+  int per_two, per_first;      // steps of shares 2 k and 2 k + 1 together, of the first of them
+  bool paired;                 // the two are a CU's, and unequal
+  constexpr int64_t begin(int wid) const { return (int64_t)(wid >> 1) * per_two + (wid & 1) * per_first; }
+  constexpr int64_t end(int wid) const { return begin(wid) + ((wid & 1) ? per_two - per_first : per_first); }
+  constexpr int of(int pos) const {                             // the share that holds step `pos`
+    const int two = pos / per_two;
+    return 2 * two + (pos - two * per_two >= per_first);
+  }
+};
+// `min_steps`, the least share, may be any positive number: where twice it does not fit, share 1 ends past every step.
+constexpr PrefillShares prefill_shares(int total, int wgs, int min_steps, bool fills_chip) {
+  if (fills_chip && total / wgs >= min_steps) {
+    const int two = (total - 1) / (wgs / 2) + 1, first = two * kFirstShare / 100 + 1;
+    return {two, first < two ? first : two - 1, true};
+  }
+  int first = (total - 1) / wgs + 1;
+  if (first < min_steps) first = min_steps;
+  return {first < (1 << 30) ? 2 * first : INT32_MAX, first, false};
 }
 
 // Whether an fp32 call goes to the plain kernel.  A workgroup of the matrix-core kernel is eight wavefronts that

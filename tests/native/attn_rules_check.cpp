@@ -5,6 +5,8 @@
 using mts::f32_takes_plain;
 using mts::joins_pieces;
 using mts::kv_past_caches;
+using mts::prefill_shares;
+using mts::PrefillShares;
 using mts::stream_form;
 using mts::StreamForm;
 constexpr int64_t MB = 1000000;
@@ -53,6 +55,28 @@ static_assert(stream_form(128, 32, 257, 1, 10 * MB) == StreamForm::kShares && st
 static_assert(stream_form(64, 32, 513, 1, 10 * MB) == StreamForm::kShares && stream_form(64, 16, 513, 16, 90 * MB) == StreamForm::kWholePairs, "");
 static_assert(stream_form(32, 16, 2049, 1, 10 * MB) == StreamForm::kShares && stream_form(32, 48, 513, 1, 10 * MB) == StreamForm::kShares, "");
 static_assert(stream_form(64, 64, 1ll << 30, 1ll << 26, 1ll << 62) == StreamForm::kShares, "");
+
+// split prefill: the shares are the sequence, one after the other, and every step finds its own
+constexpr bool shares_cover(int total, int wgs, int min_steps, bool fills_chip) {
+  const PrefillShares s = prefill_shares(total, wgs, min_steps, fills_chip);
+  if (s.begin(0) != 0 || s.end(wgs - 1) < total) return false;
+  for (int w = 0; w < wgs; ++w) {
+    const int64_t lo = s.begin(w), hi = s.end(w);
+    if (lo < 0 || hi < lo || (w + 1 < wgs && s.begin(w + 1) != hi)) return false;
+    if (!fills_chip && hi < total && hi - lo < min_steps) return false;
+    if (lo < total && (hi == lo || s.of((int)lo) != w || s.of((int)((hi < total ? hi : total) - 1)) != w)) return false;
+  }
+  return true;
+}
+static_assert(shares_cover(1, 512, 12, true) && shares_cover(511, 512, 1, true) && shares_cover(512, 512, 1, true), "");
+static_assert(shares_cover(513, 512, 1, true) && shares_cover(1537, 512, 3, true) && shares_cover(26624, 512, 12, true), "");
+static_assert(shares_cover(26624, 510, 12, false) && shares_cover(100, 7, 3, false) && shares_cover(100, 1, 1, false), "");
+static_assert(shares_cover(INT32_MAX, 512, 12, true) && shares_cover(INT32_MAX, 128, 1, false), "");
+// the least share may be any number that the tuning takes: everything in the first share, or in two
+static_assert(shares_cover(26624, 512, 1 << 29, true) && shares_cover(26624, 512, (1 << 30) - 1, true), "");
+static_assert(shares_cover(26624, 512, 1 << 30, true) && shares_cover(26624, 512, INT32_MAX, true), "");
+static_assert(shares_cover(26624, 7, 1 << 30, false) && shares_cover(1, 1, INT32_MAX, false), "");
+static_assert(shares_cover(INT32_MAX, 512, 1 << 30, true) && shares_cover(INT32_MAX, 8, INT32_MAX, false), "");
 
 // fp32: many users of a few keys, in pages of 16 and 64 tokens ...
 static_assert(f32_takes_plain(32, 8, 1000, 1000, 1, 8, 16000) && f32_takes_plain(32, 8, 1000, 1000, 1, 32, 32000), "");

@@ -24,6 +24,7 @@ SPLITS = {
     "one_workgroup": dict(max_waves=4),
     "odd_shares": dict(min_tiles=3, max_waves=28, pair_cost=7),
     "xcd_shares": dict(min_tiles=2, max_waves=32),
+    "least_share_past_every_step": dict(min_tiles=1 << 30, max_waves=64),
 }
 
 
