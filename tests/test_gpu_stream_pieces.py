@@ -37,9 +37,10 @@ def test_small_launches_match_oracle(form, D, top):
         check()
 
 
-@pytest.mark.parametrize("users,heads,long", [(64, 1, 3000), (65, 1, 3000), (1, 1, 9000), (1, 96, 2500), (1, 97, 2500)])
+@pytest.mark.parametrize("users,heads,long", [(64, 1, 3000), (65, 1, 3000), (1, 1, 8861), (1, 96, 2500), (1, 97, 2500)])
 def test_pieces_up_to_the_lanes_and_the_pairs_of_a_schedule(users, heads, long):
-    """64 users fill the lanes that hold the schedule, 65 take even shares; one pair in 32 pieces; 96 pairs and 97."""
+    """64 users fill the lanes that hold the schedule, 65 take even shares; one pair in 31 pieces, the most there are of one; 96
+    pairs and 97."""
     prefix = [long] + [int(x) for x in np.random.default_rng(7).integers(0, 90, users - 1)]
     w = W.custom_workload("lanes", 70 + users, "bf16", 1, heads, 64, 32, prefix, [3] * users, chunk_tokens=1024)
     data = draw_step_data(w)
@@ -47,15 +48,20 @@ def test_pieces_up_to_the_lanes_and_the_pairs_of_a_schedule(users, heads, long):
         check()
 
 
-def test_more_pieces_than_the_stated_bounds_allow():
-    """Fewer pages stated than the users hold: their tiles would make more pieces than workgroups, so pairs stay whole."""
-    w = W.custom_workload("understated", 81, "bf16", 1, 2, 64, 16, [3000, 2800, 2600], [8, 20, 5], chunk_tokens=1024)
+# 95 + 89 + 82 tiles x 2 heads in pieces of 6 are 90 for up to 156 workgroups; 376 x 2 are 126 for 64
+@pytest.mark.parametrize("prefix,new,whole", [([3000, 2800, 2600], [8, 20, 5], False), ([12000], [8], True)])
+def test_more_pieces_than_the_stated_bounds_allow(prefix, new, whole):
+    """Fewer pages stated than the users hold: their tiles make more pieces than they would, as long as there are as many
+    workgroups; beyond, pairs stay whole.  A whole pair leaves nothing in the workspace but descriptors."""
+    w = W.custom_workload("understated", 81, "bf16", 1, 2, 64, 16, prefix, new, chunk_tokens=1024)
     data = draw_step_data(w)
     step = _step(w, data)
     store = _oracle_store(w, data)
     ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
     step.batch.meta.total_pages = 4
     check_attention(w, step.attention(data, 0), ref)
+    descriptors = 32 * 256                                          # bytes, of as many workgroups as such a launch has at most
+    assert (int((step.ws != 0xA5).sum()) <= descriptors) == whole
 
 
 @pytest.mark.parametrize("history", [900, 4000])                # a whole pair, and one in pieces
