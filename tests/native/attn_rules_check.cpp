@@ -50,6 +50,9 @@ static_assert(stream_form(128, 16, 512, 24, 90 * MB) == StreamForm::kWholePairs 
 static_assert(stream_form(128, 32, 4, 37, 1 * MB) == StreamForm::kPieces && stream_form(64, 64, 96, 45, 80 * MB) == StreamForm::kPieces, "");
 static_assert(stream_form(128, 32, 96, 300, 160 * MB) == StreamForm::kPieces && stream_form(64, 32, 96, 300, 84 * MB) == StreamForm::kShares, "");
 static_assert(stream_form(128, 32, 97, 37, 30 * MB) == StreamForm::kShares && stream_form(128, 32, 96, 400, 168 * MB) == StreamForm::kShares, "");
+// (the pairs of the piece tests, on the pool's rows and on staged ones)
+static_assert(stream_form(32, 16, 15, 96, 1 * MB) == StreamForm::kPieces && stream_form(64, 64, 30, 98, 2 * MB) == StreamForm::kPieces, "");
+static_assert(stream_form(128, 64, 42, 98, 4 * MB) == StreamForm::kPieces && stream_form(64, 16, 2, 376, 3 * MB) == StreamForm::kPieces, "");
 // pairs that take their turns on a CU
 static_assert(stream_form(128, 32, 257, 1, 10 * MB) == StreamForm::kShares && stream_form(128, 16, 513, 1, 10 * MB) == StreamForm::kShares, "");
 static_assert(stream_form(64, 32, 513, 1, 10 * MB) == StreamForm::kShares && stream_form(64, 16, 513, 16, 90 * MB) == StreamForm::kWholePairs, "");

@@ -140,6 +140,17 @@ def test_staged_shares_that_begin_and_end_inside_a_tile(plan, D, attn_tuning):
     _run(w, [0, 2, 4, 5], 96)
 
 
+@pytest.mark.parametrize("chunk", [32, 96, 1024])
+@pytest.mark.parametrize("top", [16, 48, 64, 100])
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_staged_pairs_in_pieces(D, top, chunk):
+    """Few pairs of up to 95 tiles: a workgroup per piece of a (query tile, head), whose parts start and end inside runs,
+    hold tiles of a staged prefix and of new rows both, and leave their sums to the merge; one long user staged, one not."""
+    w = W.custom_workload("staged_pieces", 94 + D + top, "bf16", 1, 3, D, 16, [3030, 5, 2901, 0, 333],
+                          [top, 1, min(33, top), 16, top - 7], chunk_tokens=1024)
+    _run(w, [0, 1, 4], chunk)
+
+
 def test_staged_nobody_staged_equals_the_unappended_call():
     _run(_case("bf16_ragged"), [], 64)
 
@@ -156,6 +167,19 @@ def test_staged_dominant_key_in_the_onload_buffer():
         data["hist"][0][u] = h
     data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
     _run(w, [0, 2], 128, data=data)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_staged_dominant_key_in_a_late_piece(D):
+    """As above in a pair that is cut into pieces: the part that holds the key is redone, the others weigh nothing."""
+    w = W.custom_workload("staged_late_piece", 80, "bf16", 1, 2, D, 16, [3030, 90], [20, 3], chunk_tokens=1024)
+    data = draw_step_data(w)
+    h = np.array(data["hist"][0][0])
+    h[0] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(h[0]) * 0.01)
+    h[0, 2777] = W.f32_to_bf16_bits(np.full((w.heads, w.head_dim), 60.0, np.float32))
+    data["hist"][0][0] = h
+    data["q"][0] = W.f32_to_bf16_bits(np.abs(W.bf16_bits_to_f32(data["q"][0])) + 0.5)
+    _run(w, [0], 96, data=data)
 
 
 def test_staged_is_refused_for_other_kernels():
