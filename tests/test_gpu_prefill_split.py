@@ -97,6 +97,33 @@ def test_unequal_shares_of_a_full_launch(D, heads, attn_tuning):
     check_attention(w, step.attention(data, 0), ref)
 
 
+@pytest.mark.parametrize("heads", [5, 8, 30])
+@pytest.mark.parametrize("D", [64, 128])
+def test_unequal_shares_equal_unsplit(D, heads, attn_tuning):
+    """... whose results, softmax and pointwise, are those of uncut blocks but for the order of sums."""
+    import torch
+    import paper_2604_22881_amd as mts
+    attn_tuning(kernel=KERNEL_PREFILL, min_tiles=1, max_waves=2048, pair_cost=1)
+    G = _harness()
+    w = W.custom_workload("unequal", 310 + D + heads, "bf16", 1, heads, D, 16, [1500, 0, 700, 0], [8, 600, 200, 0], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    q = G.to_dev(data["q"][0])
+    inv = 1.0 / float(w.total_lens.max())
+    ref = oracle.attn_pointwise(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr, inv)
+    softmax, pointwise = step.attention(data, 0), step.attention_pointwise(data, 0, inv)
+    check_attention(w, pointwise, ref)
+    whole = [torch.full((w.total_new, w.heads, w.head_dim), -1, dtype=q.dtype, device=G.DEV) for _ in range(2)]
+    mts.mts_attn_incremental(step.cache.desc, 0, q, whole[0], step.batch.meta, 0.0, None, 0)
+    mts.mts_attn_pointwise(step.cache.desc, 0, q, whole[1], step.batch.meta, inv, 0.0, None, 0)
+    torch.cuda.synchronize()
+    for got, want in zip((softmax, pointwise), whole):
+        _same_but_for_fp32_order(as_values(got), as_values(G.to_host(want, w.np_dtype)))
+
+
 @pytest.mark.parametrize("users,heads,long", [(64, 1, 300), (65, 1, 300), (200, 2, 300), (1024, 1, 300), (2, 70, 260), (1, 1, 8400)])
 def test_schedule_in_the_lanes_of_a_wavefront(users, heads, long, attn_tuning):
     """One user a lane, groups of users behind a lane (2, 4 and 16 of them), more heads and more query blocks than lanes."""
