@@ -145,19 +145,25 @@ def _check(code):
     return code
 
 
+_ndarray = np.ndarray
+
+
 def _ptr(x):
     """Address of a torch tensor / numpy array / int / None."""
-    if type(x) is int:
-        return x
-    try:
-        return x.data_ptr()             # tensors before the rest: the smallest calls take as long as the host needs
-    except AttributeError:
-        pass
     if x is None:
         return None
+    kind = type(x)
+    if kind is int:
+        return x
+    if kind is _ndarray:
+        return x.ctypes.data
+    try:
+        return x.data_ptr()             # a tensor, without the isinstance calls: the smallest calls take as long as the host needs
+    except AttributeError:
+        pass
     if isinstance(x, int):
         return x
-    if isinstance(x, np.ndarray):
+    if isinstance(x, _ndarray):
         return x.ctypes.data
     return x.data_ptr()
 
