@@ -145,25 +145,24 @@ def _check(code):
     return code
 
 
-_ndarray = np.ndarray
-
-
 def _ptr(x):
+    """Address of a torch tensor / int, or what _any_ptr takes: tensors without isinstance calls, since the smallest calls
+    take as long as the host needs."""
+    if type(x) is int:
+        return x
+    try:
+        return x.data_ptr()
+    except AttributeError:
+        return _any_ptr(x)
+
+
+def _any_ptr(x):
     """Address of a torch tensor / numpy array / int / None."""
     if x is None:
         return None
-    kind = type(x)
-    if kind is int:
-        return x
-    if kind is _ndarray:
-        return x.ctypes.data
-    try:
-        return x.data_ptr()             # a tensor, without the isinstance calls: the smallest calls take as long as the host needs
-    except AttributeError:
-        pass
     if isinstance(x, int):
         return x
-    if isinstance(x, _ndarray):
+    if isinstance(x, np.ndarray):
         return x.ctypes.data
     return x.data_ptr()
 
@@ -254,8 +253,8 @@ def mts_kv_append_layers(desc, layer_begin, layer_count, k_new, v_new, rows_laye
 def mts_attn_incremental(desc, layer, q, out, meta, sm_scale=0.0, workspace=None, workspace_bytes=0,
                          stream=None):
     return _check(lib().mts_attn_incremental(desc, layer, _ptr(q), _ptr(out), meta,
-                                             float(sm_scale), _ptr(workspace), int(workspace_bytes),
-                                             _stream(stream)))
+                                             float(sm_scale), None if workspace is None else _ptr(workspace),
+                                             int(workspace_bytes), _stream(stream)))
 
 
 MTS_NOALLOC_SCRATCH_BYTES = 40 << 20
@@ -269,8 +268,9 @@ def mts_attn_incremental_noalloc(desc, layer, q, out, meta, sm_scale=0.0, stream
 def mts_attn_pointwise(desc, layer, q, out, meta, inv_norm, sm_scale=0.0, workspace=None, workspace_bytes=0,
                        stream=None):
     return _check(lib().mts_attn_pointwise(desc, layer, _ptr(q), _ptr(out), meta,
-                                           float(sm_scale), float(inv_norm), _ptr(workspace),
-                                           int(workspace_bytes), _stream(stream)))
+                                           float(sm_scale), float(inv_norm),
+                                           None if workspace is None else _ptr(workspace), int(workspace_bytes),
+                                           _stream(stream)))
 
 
 def mts_attn_unappended_appends(desc: CacheDesc, meta: BatchMeta):
@@ -280,7 +280,8 @@ def mts_attn_unappended_appends(desc: CacheDesc, meta: BatchMeta):
 def mts_attn_incremental_unappended(desc, layer, q, k_new, v_new, out, meta, sm_scale=0.0, workspace=None,
                                     workspace_bytes=0, stream=None):
     return _check(lib().mts_attn_incremental_unappended(desc, layer, _ptr(q), _ptr(k_new), _ptr(v_new),
-                                                        _ptr(out), meta, float(sm_scale), _ptr(workspace),
+                                                        _ptr(out), meta, float(sm_scale),
+                                                        None if workspace is None else _ptr(workspace),
                                                         int(workspace_bytes), _stream(stream)))
 
 
@@ -288,7 +289,8 @@ def mts_attn_pointwise_unappended(desc, layer, q, k_new, v_new, out, meta, inv_n
                                   workspace_bytes=0, stream=None):
     return _check(lib().mts_attn_pointwise_unappended(desc, layer, _ptr(q), _ptr(k_new), _ptr(v_new),
                                                       _ptr(out), meta, float(sm_scale), float(inv_norm),
-                                                      _ptr(workspace), int(workspace_bytes), _stream(stream)))
+                                                      None if workspace is None else _ptr(workspace),
+                                                      int(workspace_bytes), _stream(stream)))
 
 
 def mts_attn_incremental_staged(desc, layer, q, k_new, v_new, staged_rows, staged_first_run, staged_run_tok,
@@ -296,7 +298,8 @@ def mts_attn_incremental_staged(desc, layer, q, k_new, v_new, staged_rows, stage
     return _check(lib().mts_attn_incremental_staged(desc, layer, _ptr(q), _ptr(k_new), _ptr(v_new),
                                                     _ptr(staged_rows), _ptr(staged_first_run), _ptr(staged_run_tok),
                                                     int(chunk_tokens), _ptr(out), meta, float(sm_scale),
-                                                    _ptr(workspace), int(workspace_bytes), _stream(stream)))
+                                                    None if workspace is None else _ptr(workspace),
+                                                    int(workspace_bytes), _stream(stream)))
 
 
 # ---- transfer pipeline --------------------------------------------------------------------
@@ -402,11 +405,11 @@ class CacheManager:
 
 
 def mts_stage_h2d_async(device_dst, host_src, nbytes, stream=None):
-    return _check(lib().mts_stage_h2d_async(_ptr(device_dst), _ptr(host_src), int(nbytes), _stream(stream)))
+    return _check(lib().mts_stage_h2d_async(_ptr(device_dst), _any_ptr(host_src), int(nbytes), _stream(stream)))
 
 
 def mts_stage_d2h_async(host_dst, device_src, nbytes, stream=None):
-    return _check(lib().mts_stage_d2h_async(_ptr(host_dst), _ptr(device_src), int(nbytes), _stream(stream)))
+    return _check(lib().mts_stage_d2h_async(_any_ptr(host_dst), _ptr(device_src), int(nbytes), _stream(stream)))
 
 
 def mts_diag_stream_read(src, nbytes, sink, stream=None):
