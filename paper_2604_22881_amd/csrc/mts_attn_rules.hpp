@@ -58,6 +58,13 @@ constexpr StreamForm stream_form(int head_dim, int q_tile, int64_t pairs, int64_
   return pairs <= 96 && call_bytes <= (head_dim == 128 ? 160ll << 20 : 80ll << 20) ? StreamForm::kPieces : StreamForm::kShares;
 }
 
+// Least share of a wavefront of the streaming kernel, in units of the schedule: a whole tile of the onload buffer, so that
+// every share between a pair's first and last has a piece of it.  mts_attn_tuning takes any number; four of them, a
+// workgroup's, are held in 32 bits.
+constexpr int least_share(int min_tiles, int tile_cost) {
+  return min_tiles < tile_cost ? tile_cost : min_tiles < INT32_MAX / 4 ? min_tiles : INT32_MAX / 4;
+}
+
 // Shares of a split prefill launch: workgroup `wid` of it takes the tile steps [begin(wid), end(wid)) of the call's
 // sequence of `total`.  Shares 2 k and 2 k + 1 are a CU's two in a launch that fills the chip, and there the first is
 // the larger one, kFirstShare per cent of both: the workgroup that came first is served first (of equal shares the first

@@ -5,6 +5,7 @@
 using mts::f32_takes_plain;
 using mts::joins_pieces;
 using mts::kv_past_caches;
+using mts::least_share;
 using mts::prefill_shares;
 using mts::PrefillShares;
 using mts::stream_form;
@@ -58,6 +59,10 @@ static_assert(stream_form(128, 32, 257, 1, 10 * MB) == StreamForm::kShares && st
 static_assert(stream_form(64, 32, 513, 1, 10 * MB) == StreamForm::kShares && stream_form(64, 16, 513, 16, 90 * MB) == StreamForm::kWholePairs, "");
 static_assert(stream_form(32, 16, 2049, 1, 10 * MB) == StreamForm::kShares && stream_form(32, 48, 513, 1, 10 * MB) == StreamForm::kShares, "");
 static_assert(stream_form(64, 64, 1ll << 30, 1ll << 26, 1ll << 62) == StreamForm::kShares, "");
+
+// a wavefront's least share is a whole tile, and a workgroup's four fit 32 bits
+static_assert(least_share(1, 1) == 1 && least_share(1, 2) == 2 && least_share(4, 2) == 4 && least_share(1 << 28, 1) == 1 << 28, "");
+static_assert(4ll * least_share(1 << 29, 1) <= INT32_MAX && 4ll * least_share(INT32_MAX, 2) <= INT32_MAX, "");
 
 // split prefill: the shares are the sequence, one after the other, and every step finds its own
 constexpr bool shares_cover(int total, int wgs, int min_steps, bool fills_chip) {

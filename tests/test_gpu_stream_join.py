@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 # shares of one to a few tiles over 95-tile, 22-tile and single-tile pairs; launches of one workgroup,
 # of few, and of as many as the shares fill; allowances that shares begin and end in
 PLANS = [dict(min_tiles=1, pair_cost=1), dict(min_tiles=2, pair_cost=3), dict(min_tiles=5, pair_cost=9),
-         dict(max_waves=4, pair_cost=1), dict(max_waves=28, pair_cost=4), {}]
+         dict(max_waves=4, pair_cost=1), dict(max_waves=28, pair_cost=4), dict(min_tiles=2 ** 31 - 1), {}]
 
 
 def _check_all_forms(w, step, data):
