@@ -214,7 +214,7 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
   p.ws_bytes = p.ws_desc_bytes + (int64_t)wgs * prefill_partial_bytes(g);
 }
 
-AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers) {
+AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers, StreamCall call) {
   AttnPlan p{};
   const int force = g_tune_kernel.load(std::memory_order_relaxed);
   p.use_mfma = (g.es == 2) && force != MTS_ATTN_KERNEL_PLAIN;
@@ -276,7 +276,7 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers) {
                      g_tune_max_waves.load(std::memory_order_relaxed) > 0 || g_tune_pair_cost.load(std::memory_order_relaxed) > 0;
   if (tuned || p.past_caches) return p;                          // even shares
   const int64_t pairs = items * g.H, max_tiles = ((int64_t)b.max_total_len + 31) / 32;
-  switch (stream_form(g.D, p.q_tile, pairs, max_tiles, (int64_t)b.total_pages * g.page_bytes)) {
+  switch (stream_form(g.D, p.q_tile, pairs, max_tiles, (int64_t)b.total_pages * g.page_bytes, p.q_tiles_max, call)) {
     case StreamForm::kShares: break;
     case StreamForm::kWholePairs:
       p.piece_wgs = (int)pairs;
@@ -505,7 +505,9 @@ int32_t attention_call(const char* name, const mts_cache_desc* cache, int32_t la
     if (!aligned(k_new, 16) || !aligned(v_new, 16))
       return fail(MTS_ERR_INVALID_ARG, "k_new / v_new is not 16-byte aligned");
   }
-  mts::AttnPlan plan = mts::plan_attention(g, b, cache->num_layers);
+  const mts::StreamCall call = hist ? mts::StreamCall::kStaged : inv_norm > 0.f ? mts::StreamCall::kPointwise
+                                                                                : mts::StreamCall::kSoftmax;
+  mts::AttnPlan plan = mts::plan_attention(g, b, cache->num_layers, call);
   if (plan.too_large)
     return fail(MTS_ERR_UNSUPPORTED, "batch %d exceeds 4096 users, batch x ceil(max_new %d / 64) exceeds 16384 "
                 "query tiles, or the call has 2^31 or more kv tiles", b.batch, b.max_new);

@@ -47,15 +47,29 @@ constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_ti
 // * Pieces: 40 tiles and more, head_dim 128 up to 160 MB a layer 0.89 to 0.95, 200-300 MB 0.94 to 1.02; 64 up to 80 MB 0.93 to 0.95, 120
 //   MB 0.84 to 1.04, 160 MB 1.07 to 1.17.  Each pair rounds its pieces up, so of many pairs the longest ones wait: 97-128
 //   pairs 0.94 to 1.24, 129-255 0.98 to 1.26.
+// * head_dim 32: K/V are little to read, and a launch of many tiles ends with the CUs that the rounding of the pieces
+//   left more of them, each wavefront of more than 32 queries with one tile in flight.  By tiles of the call, thousands, more than
+//   32 queries: softmax up to 6 0.85 to 1.02, 6-8 0.93 to 1.02, 8-10 0.92 to 1.07, 10-14 0.99 to 1.24, 14-31 0.98 to
+//   1.32; pointwise up to 6 0.88 to 0.95, 6-8 0.96 to 1.13, 11-19 1.05 to 1.38.  Staged, 16 queries: up to 8 0.88 to 1.07,
+//   8-18 0.97 to 1.18; more: up to 16 0.85 to 1.00, 17-38 0.97 to 1.13.  Else up to the 20 of 80 MB 0.92 to 1.08.
 enum class StreamForm { kShares, kWholePairs, kPieces };
-constexpr StreamForm stream_form(int head_dim, int q_tile, int64_t pairs, int64_t max_tiles, int64_t call_bytes) {
+enum class StreamCall { kSoftmax, kPointwise, kStaged };
+// `q_tiles`: query tiles of a user, each of which reads the call's bytes
+constexpr StreamForm stream_form(int head_dim, int q_tile, int64_t pairs, int64_t max_tiles, int64_t call_bytes, int64_t q_tiles = 1,
+                                 StreamCall call = StreamCall::kSoftmax) {
   const int64_t whole = pairs <= 256   ? (head_dim == 128 ? 36 : q_tile > 32 ? 44 : head_dim == 64 ? 52 : 68)
                         : pairs <= 512 ? (head_dim == 32 ? 32 : head_dim == 64 || q_tile <= 16 ? 24 : 0)
                         : pairs > 2048 ? 0
                         : head_dim == 32 ? (q_tile <= 32 ? 32 : 0)
                                          : (head_dim == 64 && q_tile <= 16 ? 16 : 0);
   if (max_tiles <= whole) return StreamForm::kWholePairs;
-  return pairs <= 96 && call_bytes <= (head_dim == 128 ? 160ll << 20 : 80ll << 20) ? StreamForm::kPieces : StreamForm::kShares;
+  if (pairs > 96 || call_bytes > (head_dim == 128 ? 160ll << 20 : 80ll << 20)) return StreamForm::kShares;
+  if (head_dim != 32) return StreamForm::kPieces;
+  const int64_t tiles = call_bytes / (128 * head_dim) * q_tiles;          // a tile of K/V of a head is 128 * head_dim bytes
+  const int64_t most = call == StreamCall::kStaged ? (q_tile > 16 ? 16384 : 8192)
+                       : q_tile <= 32              ? INT64_MAX
+                                                   : (call == StreamCall::kPointwise ? 6144 : 8192);
+  return tiles <= most ? StreamForm::kPieces : StreamForm::kShares;
 }
 
 // Least share of a wavefront of the streaming kernel, in units of the schedule: a whole tile of the onload buffer, so that

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mts_attn_rules.hpp"
 #include "mts_layout.hpp"
 
 namespace mts {
@@ -68,7 +69,8 @@ struct AttnPlan {
 void fit_plan_to_workspace(AttnPlan& p, const PoolGeom& g, const void* workspace, int64_t workspace_bytes);
 constexpr int kPrefillMaxWgs = 512;          // 256 CUs x 2 resident workgroups
 constexpr int kPrefillSplitMaxBatch = 1024;  // users in the schedule of a split launch: 16 a lane
-AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers);   // layers of the cache
+// `layers` of the cache; the call's kind chooses between forms of the same workspace
+AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers, StreamCall call = StreamCall::kSoftmax);
 constexpr int kAttnMaxWaves = 1024;   // 256 CUs x 4 SIMDs: one wavefront per SIMD
 
 

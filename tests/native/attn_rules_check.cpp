@@ -9,6 +9,7 @@ using mts::least_share;
 using mts::prefill_shares;
 using mts::PrefillShares;
 using mts::stream_form;
+using mts::StreamCall;
 using mts::StreamForm;
 constexpr int64_t MB = 1000000;
 
@@ -54,6 +55,16 @@ static_assert(stream_form(128, 32, 97, 37, 30 * MB) == StreamForm::kShares && st
 // (the pairs of the piece tests, on the pool's rows and on staged ones)
 static_assert(stream_form(32, 16, 15, 96, 1 * MB) == StreamForm::kPieces && stream_form(64, 64, 30, 98, 2 * MB) == StreamForm::kPieces, "");
 static_assert(stream_form(128, 64, 42, 98, 4 * MB) == StreamForm::kPieces && stream_form(64, 16, 2, 376, 3 * MB) == StreamForm::kPieces, "");
+// ... and, of head_dim 32, while they are few tiles, each query tile's own counted
+static_assert(stream_form(32, 64, 96, 300, 32 << 20) == StreamForm::kPieces && stream_form(32, 64, 96, 300, 33 << 20) == StreamForm::kShares, "");
+static_assert(stream_form(32, 48, 8, 800, 16 << 20, 2) == StreamForm::kPieces && stream_form(32, 48, 8, 800, 17 << 20, 2) == StreamForm::kShares, "");
+static_assert(stream_form(32, 64, 8, 800, 24 << 20, 1, StreamCall::kPointwise) == StreamForm::kPieces, "");
+static_assert(stream_form(32, 64, 8, 800, 25 << 20, 1, StreamCall::kPointwise) == StreamForm::kShares, "");
+static_assert(stream_form(32, 64, 8, 800, 64 << 20, 1, StreamCall::kStaged) == StreamForm::kPieces, "");
+static_assert(stream_form(32, 32, 8, 800, 65 << 20, 1, StreamCall::kStaged) == StreamForm::kShares, "");
+static_assert(stream_form(32, 16, 8, 800, 32 << 20, 1, StreamCall::kStaged) == StreamForm::kPieces, "");
+static_assert(stream_form(32, 16, 8, 800, 33 << 20, 1, StreamCall::kStaged) == StreamForm::kShares, "");
+static_assert(stream_form(32, 32, 96, 300, 80 << 20) == StreamForm::kPieces && stream_form(64, 64, 96, 300, 80 << 20, 2) == StreamForm::kPieces, "");
 // pairs that take their turns on a CU
 static_assert(stream_form(128, 32, 257, 1, 10 * MB) == StreamForm::kShares && stream_form(128, 16, 513, 1, 10 * MB) == StreamForm::kShares, "");
 static_assert(stream_form(64, 32, 513, 1, 10 * MB) == StreamForm::kShares && stream_form(64, 16, 513, 16, 90 * MB) == StreamForm::kWholePairs, "");
