@@ -47,6 +47,9 @@ constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_ti
 // * Pieces: 40 tiles and more, head_dim 128 up to 160 MB a layer 0.89 to 0.95, 200-300 MB 0.94 to 1.02; 64 up to 80 MB 0.93 to 0.95, 120
 //   MB 0.84 to 1.04, 160 MB 1.07 to 1.17.  Each pair rounds its pieces up, so of many pairs the longest ones wait: 97-128
 //   pairs 0.94 to 1.24, 129-255 0.98 to 1.26.
+// * Staged users' tiles take longer, and of few pairs theirs are the longest: from three quarters of these lengths, all head sizes,
+//   1-2 users whole pairs 0.88 to 1.21 / pieces 0.83 to 0.89 of the time before either (up to 32 pairs), 3-8 users 0.79 to 1.13 / 0.85 to 0.96;
+//   more pairs 0.74 to 1.05 / 0.83 to 0.91.
 // * head_dim 32: K/V are little to read, and a launch of many tiles ends with the CUs that the rounding of the pieces
 //   left more of them, each wavefront of more than 32 queries with one tile in flight.  By tiles of the call, thousands, more than
 //   32 queries: softmax up to 6 0.85 to 1.02, 6-8 0.93 to 1.02, 8-10 0.92 to 1.07, 10-14 0.99 to 1.24, 14-31 0.98 to
@@ -62,7 +65,7 @@ constexpr StreamForm stream_form(int head_dim, int q_tile, int64_t pairs, int64_
                         : pairs > 2048 ? 0
                         : head_dim == 32 ? (q_tile <= 32 ? 32 : 0)
                                          : (head_dim == 64 && q_tile <= 16 ? 16 : 0);
-  if (max_tiles <= whole) return StreamForm::kWholePairs;
+  if (max_tiles <= (call == StreamCall::kStaged && pairs <= 32 ? whole * 3 / 4 : whole)) return StreamForm::kWholePairs;
   if (pairs > 96 || call_bytes > (head_dim == 128 ? 160ll << 20 : 80ll << 20)) return StreamForm::kShares;
   if (head_dim != 32) return StreamForm::kPieces;
   const int64_t tiles = call_bytes / (128 * head_dim) * q_tiles;          // a tile of K/V of a head is 128 * head_dim bytes

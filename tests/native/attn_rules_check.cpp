@@ -65,6 +65,11 @@ static_assert(stream_form(32, 32, 8, 800, 65 << 20, 1, StreamCall::kStaged) == S
 static_assert(stream_form(32, 16, 8, 800, 32 << 20, 1, StreamCall::kStaged) == StreamForm::kPieces, "");
 static_assert(stream_form(32, 16, 8, 800, 33 << 20, 1, StreamCall::kStaged) == StreamForm::kShares, "");
 static_assert(stream_form(32, 32, 96, 300, 80 << 20) == StreamForm::kPieces && stream_form(64, 64, 96, 300, 80 << 20, 2) == StreamForm::kPieces, "");
+// staged histories: few whole pairs are shorter ones
+static_assert(stream_form(64, 32, 32, 39, 5 * MB, 1, StreamCall::kStaged) == StreamForm::kWholePairs, "");
+static_assert(stream_form(64, 32, 32, 40, 5 * MB, 1, StreamCall::kStaged) == StreamForm::kPieces, "");
+static_assert(stream_form(64, 32, 33, 52, 5 * MB, 1, StreamCall::kStaged) == StreamForm::kWholePairs, "");
+static_assert(stream_form(64, 32, 32, 52, 5 * MB) == StreamForm::kWholePairs, "");
 // pairs that take their turns on a CU
 static_assert(stream_form(128, 32, 257, 1, 10 * MB) == StreamForm::kShares && stream_form(128, 16, 513, 1, 10 * MB) == StreamForm::kShares, "");
 static_assert(stream_form(64, 32, 513, 1, 10 * MB) == StreamForm::kShares && stream_form(64, 16, 513, 16, 90 * MB) == StreamForm::kWholePairs, "");
