@@ -191,9 +191,12 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
     // on its CU, 0.75 where the blocks fill the CUs twice) or as its work takes on all CUs (0.45 us per
     // step and CU, counted from the mean length, which overstates it); split, only the latter, plus 32 us
     // for block starts, partial blocks, their merge and the second launch; neither is shorter than
-    // reading K and V once.  Fitted to 437 calls of 1 to 100 users, head_dim 64 and 128: 1.1 % above the
-    // faster form on average (with 20 us, 0.55, 1.1 and 0.56 per step: 2.7 %, up to 58 %).  Measured, us
-    // unsplit / split (steps of the longest block, steps per CU, blocks): 98 / 40 (194, 39, 176),
+    // reading K and V once.  Fitted to 437 calls of 1 to 100 users, head_dim 64 and 128, when a split call's block
+    // starts, shares and pieces took longer than they do now: of 1089 calls timed in both forms since, this rule alone
+    // is 2.2 % above the faster one on average, 88 calls by more than 10 %, one by 1.70 times; with the one below it is 1.5 %, 62
+    // and 1.54 (18 users, 4 heads of 64, 6807 new tokens, the longest 2371: 60 us unsplit, 39 split; the other way one
+    // user's 1923 x 4 of 128, 47 split, 35 unsplit).  Measured for the fit, us unsplit / split (steps of the
+    // longest block, steps per CU, blocks): 98 / 40 (194, 39, 176),
     // 102 / 79 (162, 79, 252), 60 / 55 (93, 34, 224), 214 / 103 (382, 336, 408), 157 / 174 (165, 249, 884), 40 / 54
     // (52, 43, 432), 58 / 74 (80, 59, 612), 29 / 45 (46, 4, 60), 24 / 38 (28, 13, 380).
     const double mean_total = (double)b.total_pages * g.S / b.batch, mean_new = (double)b.total_new / b.batch;
@@ -203,7 +206,7 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
     const double read = (double)b.total_pages * (double)g.page_bytes / 5e6;
     // Where few users bring most of the new tokens, the mean lengths overstate the work (long histories belong to
     // the others) or understate it, and unsplit a call takes about both, its work and 0.4 us per step of the longest block.  Of
-    // 1089 more calls, half of them such batches, this sends 29 to the split form, 0.59 to 0.93 of the unsplit time.
+    // those 1089 calls, half of them such batches, this sends 29 to the split form, 0.59 to 0.95 of the unsplit time.
     const double prefix = mean_total - mean_new;
     const double long_prefix = (double)b.total_new >= 0.7 * b.batch * b.max_new ? prefix : 0.0;
     const double work = 0.45 / 256 * g.H * ((double)b.total_new / QB * (long_prefix + 0.5 * b.max_new) + 0.5 * b.batch * prefix) / 32;
@@ -249,7 +252,8 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers, Stream
   // A tile in the onload buffer is 32 rows of one head out of many, half a cache line to two each, and a transpose.
   // Steps of 4 layers with staged users, counted as 1, 2, 3, 4 tiles of the pool: 4 of 32 users x 3600 tokens x 8 heads of 64
   // 308, 268, 265, 263 us; 16 of 32 384, 356, 379, 400; all of 24 380, 377, 383, 380; 2 of 24 x 1000-9000 x 4 of 128 285, 277,
-  // 283, 284; 7 of 100 x 4 of 32 204, 188, 190, 194.
+  // 283, 284; 7 of 100 x 4 of 32 204, 188, 190, 194.  That is of rows that lie in memory; a first pass on rows just written, which
+  // the caches still hold in part, gains 2 % where repeated ones gain 17.
   p.staged_tile_cost = 2 * tiles_upper < (1ll << 31) ? 2 : 1;
   p.past_caches = p.q_tiles_max == 1 && kv_past_caches(g.D, (int64_t)b.total_pages * g.page_bytes, layers,
                                                        (int64_t)b.total_pages * g.S / b.batch);
@@ -282,8 +286,8 @@ AttnPlan plan_attention(const PoolGeom& g, const BatchDev& b, int layers, Stream
       p.piece_wgs = (int)pairs;
       break;
     case StreamForm::kPieces: {
-      // As many pieces as CUs, at most 32 of a pair (one user's 12 K keys of 4 heads of 128: 0.95 of even shares'
-      // time with 32, 1.04 with 64), of at least six tiles (one user's 6 K: 164 us a step, 175 with four).  Each pair rounds
+      // As many pieces as CUs, at most 32 of a pair (one user's 12 K keys of 4 heads of 128, 8 layers: 164 us with 32, 180
+      // with 64), of at least six tiles (4500 keys: 135 us, 140.5 with four; 3000: 126, 129.5).  Each pair rounds
       // its number up, so `wgs` pieces hold what `wgs - pairs` of them would without rounding; a user's tiles
       // are counted from its pages, and one more where prefix and new rows are tiled apart.
       int64_t wgs = 32 * pairs < 256 ? 32 * pairs : 256;

@@ -40,16 +40,17 @@
 // share of it (the first on a CU a larger one, see kFirstShare), and a block that a share boundary cuts is written as unnormalised fp32
 // pieces that a merge kernel finishes.  Every wavefront derives the schedule by itself from the
 // device-resident lengths, in its lanes: a scan over the users, then searches by one comparison a lane
-// (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, head_dim
-// 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 49 us (merge 10); 6 users with 4-12 K histories and
-// 8-64 new tokens beside 2 first-time ones 190 -> 81 us.  What is left there is the block starts (1.2 and 1.5 segments
+// (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, means, head_dim
+// 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 53 us (merge 10.5); 6 users with 4-12 K histories and
+// 8-64 new tokens beside 2 first-time ones 190 -> 94 us (merge 10.3).  What is left there is the block starts (1.2 and 1.5 segments
 // a share, about 5 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
 //
 // A block's start (page ids, keys, reference, first scores) is 5 us, and a CU does little else before the
 // first one is done.  It was 5.5, and 2 before it for the schedule, now 1.2: with a prefix sum in LDS, masks and
 // addresses computed ahead of the redo loop into 200 spilled scalar registers, and the page table's round trip
-// before that of the keys.  A piece's end took 2.3 us stored row by row, 1.4 in fragment order.  A step of 8 layers:
-// one user's 5189 tokens x 4 heads 488 -> 465 us, 16 x 4096 x 16 heads 10414 -> 10238.
+// before that of the keys.  A piece's end took 2.3 us stored row by row, 1.4 in fragment order.  A step of 8 layers, by all of
+// it: one user's 5189 tokens x 4 heads 488 -> 465 us (446 since a CU's two shares are unequal), 16 x 4096 x 16 heads 10414 ->
+// 10238.
 //
 // PW selects the pointwise aggregation out = inv_norm * sum_j silu(c * q.k_j) v_j: no reference
 // max, no denominator, no redo; hidden keys carry logit 0 (silu(0) = 0).
@@ -533,8 +534,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     // SPLIT: the reference of a piece is that of its whole block, the max of the user's first tile.  So its
     // weights are rounded as those of an uncut block, and how a call is cut changes its result by the
     // order of fp32 sums alone.  The tile's keys travel beside the piece's own, into the room of the
-    // values that stage 0 does not hold yet; 8 layers of one user's 5189 tokens x 4 heads take 478 us with
-    // it and 469 with a reference of each piece's own.
+    // values that stage 0 does not hold yet; 8 layers of one user's 5189 tokens x 4 heads take 446 us with
+    // it and 441 with a reference of each piece's own, six returning users beside two first-time ones 750 and 741.
     constexpr bool kBlockReference = SPLIT && !PW;
     if (kBlockReference && attempt == 0) {
       const char* ka = head_base + (int64_t)(r < 16 ? id0[NST] : id1[NST]) * g.page_bytes + (int64_t)((r >> 4) & sub_mask) * 16 * D * 2 + k_lane;
