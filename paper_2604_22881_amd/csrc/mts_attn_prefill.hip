@@ -40,9 +40,9 @@
 // share of it (the first on a CU a larger one, see kFirstShare), and a block that a share boundary cuts is written as unnormalised fp32
 // pieces that a merge kernel finishes.  Every wavefront derives the schedule by itself from the
 // device-resident lengths, in its lanes: a scan over the users, then searches by one comparison a lane
-// (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, means, head_dim
-// 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 53 us (merge 10.5); 6 users with 4-12 K histories and
-// 8-64 new tokens beside 2 first-time ones 190 -> 94 us (merge 10.3).  What is left there is the block starts (1.2 and 1.5 segments
+// (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, means of runs on
+// several cards, head_dim 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 53 to 55 us (merge 10.7); 6 users with
+// 4-12 K histories and 8-64 new tokens beside 2 first-time ones 190 -> 94 to 99 us (merge 10.5).  What is left there is the block starts (1.2 and 1.5 segments
 // a share, about 5 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
 //
 // A block's start (page ids, keys, reference, first scores) is 5 us, and a CU does little else before the
