@@ -10,19 +10,28 @@ import mts_workloads as W
 pytestmark = pytest.mark.gpu
 
 
+# pairs cut into pieces and merged; whole pairs; first-time users whose blocks are cut into shares and merged
+SHAPES = {"pieces": ([700, 90, 300, 0, 1500, 15, 260], [20, 3, 40, 64, 33, 17, 8]),
+          "whole": ([700, 90, 300, 0, 500, 15, 260], [20, 3, 40, 64, 33, 17, 8]),
+          "split_prefill": ([700, 90, 300, 0, 2500], [40, 2600, 300, 24, 33])}
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
 @pytest.mark.parametrize("deferred", [False, True])
-def test_captured_step_replays_equal_the_eager_step(deferred):
+def test_captured_step_replays_equal_the_eager_step(deferred, shape):
     import torch
     import paper_2604_22881_amd as mts
     from paper_2604_22881_amd.runtime import DeviceBatch, PagedKVCache, SegmentList
     dev = "cuda:0"
-    w = W.custom_workload("graph", 21, "bf16", 3, 4, 64, 16, [700, 90, 300, 0, 1500, 15, 260], [20, 3, 40, 64, 33, 17, 8],
-                          miss_users=np.array([1, 4], np.int32), evict_users=np.array([2, 6], np.int32), chunk_tokens=256)
+    prefix, new = SHAPES[shape]
+    w = W.custom_workload("graph", 21, "bf16", 3, 4, 64, 16, prefix, new, miss_users=np.array([1, 4], np.int32),
+                          evict_users=np.array([2, 3 if len(new) == 5 else 6], np.int32), chunk_tokens=256)
     L, H, D, N = w.layers, w.heads, w.head_dim, w.total_new
     torch.manual_seed(3)
     cache = PagedKVCache(L, w.num_pages, w.page_size, H, D, w.dtype, dev)
     batch = DeviceBatch.from_workload(w, dev)
     ws_bytes = mts.mts_attn_workspace_bytes(cache.desc, batch.meta)
+    assert ws_bytes > 0                                      # of a prefill call: it is split
     ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=dev)
     miss = [int(u) for u in w.miss_users]
     msegs = SegmentList.for_histories(miss, [w.prefix_lens[u] for u in miss], w.chunk_tokens, dev)
