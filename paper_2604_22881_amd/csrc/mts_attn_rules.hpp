@@ -35,7 +35,7 @@ constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_ti
 // How the streaming kernel divides a call's (query tile, head)s, `pairs` of at most `max_tiles` 32-token tiles: even
 // shares of wavefronts; a workgroup per pair; or a workgroup per equal piece of a pair, and a merge launch.
 // Step time over that of even shares, whole pairs / pieces, of 1000 random calls of up to 100 MB a layer (geometric
-// means; q: queries per tile):
+// means; q: queries per tile; the kernels of pairs and pieces take 0.95 to 1.00 of the time they took then):
 // * Up to 256 pairs a CU holds one, whose keys it alone reads: head_dim 128 16-32 tiles 0.77 / 0.89, 32-40 0.84 / 0.88,
 //   40-52 0.92 / 0.88, 64-80 1.16 / 0.90; 64, q <= 32 32-40 0.80 / 0.92, 40-52 0.84 / 0.94, 52-64 0.90 / 0.95, 80-110 1.04 / 0.94;
 //   32 0.73 / 0.93, 0.82 / 0.95, 64-80 0.89 / 0.94, 80-110 0.97 / 0.92; q > 32, both, 24-32 0.77 / 0.88, 32-40 0.88 / 0.92,
@@ -48,8 +48,8 @@ constexpr bool joins_pieces(int64_t waves, int64_t pairs, int head_dim, int q_ti
 //   MB 0.84 to 1.04, 160 MB 1.07 to 1.17.  Each pair rounds its pieces up, so of many pairs the longest ones wait: 97-128
 //   pairs 0.94 to 1.24, 129-255 0.98 to 1.26.
 // * Staged users' tiles take longer, and of few pairs theirs are the longest: from three quarters of these lengths, all head sizes,
-//   1-2 users whole pairs 0.88 to 1.21 / pieces 0.83 to 0.89 of the time before either (up to 32 pairs), 3-8 users 0.79 to 1.13 / 0.85 to 0.96;
-//   more pairs 0.74 to 1.05 / 0.83 to 0.91.
+//   1-2 users whole pairs 0.88 to 1.21 / pieces 0.83 to 0.89 of the time before either (up to 32 pairs), 3-8 users 0.79 to
+//   1.13 / 0.85 to 0.96; more pairs 0.74 to 1.05 / 0.83 to 0.91.
 // * head_dim 32: K/V are little to read, and a launch of many tiles ends with the CUs that the rounding of the pieces
 //   left more of them, each wavefront of more than 32 queries with one tile in flight.  By tiles of the call, thousands, more than
 //   32 queries: softmax up to 6 0.85 to 1.02, 6-8 0.93 to 1.02, 8-10 0.92 to 1.07, 10-14 0.99 to 1.24, 14-31 0.98 to
