@@ -18,6 +18,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     "-Wno-unknown-warning-option",
+    # the leading scalar arguments of a kernel arrive in registers (mts_internal.hpp, TableWords)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     # packed fp32 arithmetic is kept off for all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]

@@ -42,9 +42,22 @@ __device__ __forceinline__ float quad_row_sum(float v) {
   return v + __shfl_xor(v, 32);
 }
 
+struct F32Args {                 // one argument, see TableWords
+  PoolGeom g;
+  const float* q;
+  float* out;
+  float scale, inv_norm;
+};
+
 template <int D, bool PW>
-__global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(PoolGeom g, BatchDev b, const float* __restrict__ q,
-                                                               float* __restrict__ out, float scale, float inv_norm) {
+__global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, TableWords pages, CallWords2 call, F32Args args) {
+  const int32_t *new_indptr = table(runs[0]), *prefix_lens = table(runs[1]), *page_indptr = table(pages[0]),
+                *page_indices = table(pages[1]);
+  const int batch = call[0], total_new = call[1];
+  const PoolGeom& g = args.g;
+  const float* __restrict__ q = args.q;
+  float* __restrict__ out = args.out;
+  const float scale = args.scale, inv_norm = args.inv_norm;
   constexpr int NF = D / 16;       // 16-byte fragments per lane of a sub-block's K, V, of Q and of the output
   __shared__ f32x4 s_o[kWaves / 2][NF][64];
   __shared__ float s_m[kWaves / 2][kQ], s_l[kWaves / 2][kQ];
@@ -56,19 +69,19 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(PoolGeom g, Batch
   // Blocks of user u start at new_indptr[u] / 16 + u: at least ceil(n_u / 16) of them before the next
   // user's, so no prefix sum over the users is needed and the grid stays below total_new / 16 + batch.
   const int blk = blockIdx.x;
-  int lo = 0, hi = b.batch;
+  int lo = 0, hi = batch;
   while (hi - lo > 1) {                                 // largest u that starts at or before blk
     const int mid = (lo + hi) >> 1;
-    if (b.new_indptr[mid] / kQ + mid <= blk) lo = mid; else hi = mid;
+    if (new_indptr[mid] / kQ + mid <= blk) lo = mid; else hi = mid;
   }
-  const int u = lo, tok0 = b.new_indptr[u];
-  const int n_u = b.new_indptr[u + 1] - tok0;
+  const int u = lo, tok0 = new_indptr[u];
+  const int n_u = new_indptr[u + 1] - tok0;
   const int q0 = (blk - (tok0 / kQ + u)) * kQ;
-  if (q0 < 0 || q0 >= n_u || tok0 + q0 >= b.total_new) return;    // workgroup-uniform
-  const int P = b.prefix_lens[u];
-  const int pbeg = b.page_indptr[u], npg = b.page_indptr[u + 1] - pbeg;
+  if (q0 < 0 || q0 >= n_u || tok0 + q0 >= total_new) return;    // workgroup-uniform
+  const int P = prefix_lens[u];
+  const int pbeg = page_indptr[u], npg = page_indptr[u + 1] - pbeg;
   int nq = n_u - q0 < kQ ? n_u - q0 : kQ;
-  nq = nq < b.total_new - tok0 - q0 ? nq : b.total_new - tok0 - q0;
+  nq = nq < total_new - tok0 - q0 ? nq : total_new - tok0 - q0;
   const int kv_len = P + q0 + nq;                       // keys the last query sees
   const int n_sb = (kv_len + kSub - 1) / kSub;
   const int sub_mask = (1 << g.sub_shift) - 1;
@@ -88,7 +101,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(PoolGeom g, Batch
   auto load = [&](auto slot_c, int sb) __attribute__((always_inline)) {
     constexpr int p = decltype(slot_c)::value;
     const int lp = sb >> g.sub_shift;
-    int page = sb < n_sb && lp < npg ? b.page_indices[pbeg + lp] : -1;
+    int page = sb < n_sb && lp < npg ? page_indices[pbeg + lp] : -1;
     held[p] = (unsigned)page < (unsigned)g.num_pages;
     if (!held[p]) return;                               // wavefront-uniform
     const char* kb = head_base + (int64_t)page * g.page_bytes + (int64_t)(sb & sub_mask) * kSub * D * 4;
@@ -231,7 +244,8 @@ template <int D>
 void launch_d(dim3 grid, const PoolGeom& g, const BatchDev& b, const float* q, float* out, float scale, float inv_norm,
               hipStream_t stream) {
   auto kern = inv_norm > 0.f ? attn_f32_kernel<D, true> : attn_f32_kernel<D, false>;
-  hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), 0, stream, g, b, q, out, scale, inv_norm);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), 0, stream, run_tables(b), page_tables(b), CallWords2{b.batch, b.total_new},
+                     F32Args{g, q, out, scale, inv_norm});
 }
 
 }  // namespace

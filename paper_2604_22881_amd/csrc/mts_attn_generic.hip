@@ -34,25 +34,27 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 template <typename T, bool PW>
-__global__ __launch_bounds__(64) void attn_generic_kernel(PoolGeom g, BatchDev b,
+__global__ __launch_bounds__(64) void attn_generic_kernel(TableWords runs, TableWords pages, int batch, PoolGeom g,
                                                           const T* __restrict__ q,
                                                           T* __restrict__ out, float scale, float inv_norm) {
+  const int32_t *new_indptr = table(runs[0]), *prefix_lens = table(runs[1]), *page_indptr = table(pages[0]),
+                *page_indices = table(pages[1]);
   constexpr int G = 16 / sizeof(T);
   const int tok = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
   const int H = g.H, D = g.D, S = g.S;
 
   // user of this token: the largest u with new_indptr[u] <= tok
-  int lo = 0, hi = b.batch;
+  int lo = 0, hi = batch;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (b.new_indptr[mid] <= tok) lo = mid; else hi = mid;
+    if (new_indptr[mid] <= tok) lo = mid; else hi = mid;
   }
   const int u = lo;
-  const int i = tok - b.new_indptr[u];
-  const int P = b.prefix_lens[u];
+  const int i = tok - new_indptr[u];
+  const int P = prefix_lens[u];
   const int kv_len = P + i + 1;                       // keys 0 .. P+i are visible
-  const int pbeg = b.page_indptr[u];
-  const int npg = b.page_indptr[u + 1] - pbeg;
+  const int pbeg = page_indptr[u];
+  const int npg = page_indptr[u + 1] - pbeg;
 
   __shared__ float qs[128];
   __shared__ float ps[64];
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(PoolGeom g, BatchDev b
     const int j = base + lane;
     float z = -INFINITY;
     if (j < kv_len && j / S < npg) {
-      const int page = b.page_indices[pbeg + j / S];
+      const int page = page_indices[pbeg + j / S];
       if ((unsigned)page < (unsigned)g.num_pages) {
         const int slot = j % S;
         const T* kblk = reinterpret_cast<const T*>(g.layer_base + (int64_t)page * g.page_bytes +
@@ -93,7 +95,7 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(PoolGeom g, BatchDev b
     for (int jj = 0; jj < cnt; ++jj) {
       const int t = base + jj;
       if (t / S >= npg) break;
-      const int page = b.page_indices[pbeg + t / S];
+      const int page = page_indices[pbeg + t / S];
       if ((unsigned)page >= (unsigned)g.num_pages) continue;
       const int slot = t % S;
       const T* vblk = reinterpret_cast<const T*>(g.layer_base + (int64_t)page * g.page_bytes +
@@ -119,10 +121,10 @@ hipError_t launch_attn_generic(const PoolGeom& g, const void* q, void* out, cons
   const bool pw = inv_norm > 0.f;
   if (g.es == 2) {
     auto kern = pw ? attn_generic_kernel<uint16_t, true> : attn_generic_kernel<uint16_t, false>;
-    hipLaunchKernelGGL(kern, grid, block, 0, stream, g, b, (const uint16_t*)q, (uint16_t*)out, sm_scale, inv_norm);
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, run_tables(b), page_tables(b), b.batch, g, (const uint16_t*)q, (uint16_t*)out, sm_scale, inv_norm);
   } else {
     auto kern = pw ? attn_generic_kernel<uint32_t, true> : attn_generic_kernel<uint32_t, false>;
-    hipLaunchKernelGGL(kern, grid, block, 0, stream, g, b, (const uint32_t*)q, (uint32_t*)out, sm_scale, inv_norm);
+    hipLaunchKernelGGL(kern, grid, block, 0, stream, run_tables(b), page_tables(b), b.batch, g, (const uint32_t*)q, (uint32_t*)out, sm_scale, inv_norm);
   }
   return hipGetLastError();
 }

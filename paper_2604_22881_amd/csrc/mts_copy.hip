@@ -41,6 +41,15 @@ enum { MODE_UNPACK = 0, MODE_APPEND = 1, MODE_PACK = 2 };
 
 constexpr int kBulkWaves = 4;      // wavefronts (= units) per bulk workgroup
 
+// The two sides of a move, strides from one layer to the next.
+template <typename T>
+struct MoveSides {
+  PoolGeom g;
+  const T *src_a, *src_b;
+  T* dst_contig;
+  int64_t pool_layer_stride, contig_layer_stride;     // bytes, elements
+};
+
 // One wavefront moves one (16-token sub-block, head): the contiguous side moves in whole rows
 // (D*es bytes per token and head), the pool side in whole 16-byte granules in pool order, so that
 // BOTH sides of every copy are 16-byte-per-lane accesses over full cache lines; the reordering
@@ -51,25 +60,28 @@ constexpr int kBulkWaves = 4;      // wavefronts (= units) per bulk workgroup
 // the run are neither read nor written, K granules of other tokens are skipped and a V granule
 // that the run covers only in part is written element by element, so no slot outside the run
 // is ever written.
+// `runs`: seg_user and seg_pos of a segment list (`run_tok`: seg_tok_indptr) or an append's new_indptr and prefix_lens;
+// `pages`: page_indptr and page_indices.
 // PAST: which rows travel past the caches' retention (mts_copy_rules.hpp; an append's own rule is at KEEP).
 template <typename T, int MODE, int DCH, RowsPast PAST>
-__global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, BatchDev b,
-                                                      const T* __restrict__ src_a,
-                                                      const T* __restrict__ src_b,
-                                                      T* __restrict__ dst_contig, int bulk_blocks,
-                                                      int64_t pool_layer_stride, int64_t contig_layer_stride) {
+__global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWords pages, CallWords call, const int64_t* run_tok,
+                                                      MoveSides<T> sides) {
+  const int32_t *run_user = table(runs[0]), *run_pos = table(runs[1]), *page_indptr = table(pages[0]),
+                *page_indices = table(pages[1]);
+  const int batch = call[0], H = call[1], bulk_blocks = call[2];
   constexpr int G = 16 / sizeof(T);
   constexpr int D = DCH * G;
   constexpr int PITCH = D + G;       // LDS row pitch in elements (one granule of padding)
   constexpr int NIT = 16 * DCH / 64; // 64-granule rounds per 16-token sub-block
-  const int H = g.H, S = g.S;
   constexpr int dch = DCH;
   const int s = blockIdx.y;
   // several layers in one launch: blockIdx.z picks the layer on both sides
-  g.layer_base += (int64_t)blockIdx.z * pool_layer_stride;
-  src_a += (int64_t)blockIdx.z * contig_layer_stride;
-  if (MODE == MODE_APPEND) src_b += (int64_t)blockIdx.z * contig_layer_stride;
-  if (MODE == MODE_PACK) dst_contig += (int64_t)blockIdx.z * contig_layer_stride;
+  PoolGeom& g = sides.g;
+  const int S = g.S;
+  g.layer_base += (int64_t)blockIdx.z * sides.pool_layer_stride;
+  const T* src_a = sides.src_a + (int64_t)blockIdx.z * sides.contig_layer_stride;
+  const T* src_b = MODE == MODE_APPEND ? sides.src_b + (int64_t)blockIdx.z * sides.contig_layer_stride : nullptr;
+  T* dst_contig = MODE == MODE_PACK ? sides.dst_contig + (int64_t)blockIdx.z * sides.contig_layer_stride : nullptr;
 
   // Resolve the run: user, first pool token, length, and the contiguous K / V planes.  A step's append
   // moves little and costs its chain of memory round trips, so whatever can travel together does: the
@@ -82,24 +94,24 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
   bool user_ok = true;                                          // an append's grid has one row per user
   if (MODE == MODE_APPEND) {
     u = s;
-    int r0 = scalar_load(b.new_indptr + u), r1 = scalar_load(b.new_indptr + u + 1);
-    pos = scalar_load(b.prefix_lens + u);
-    pbeg = scalar_load(b.page_indptr + u);
-    pend = scalar_load(b.page_indptr + u + 1);
+    int r0 = scalar_load(run_user + u), r1 = scalar_load(run_user + u + 1);
+    pos = scalar_load(run_pos + u);
+    pbeg = scalar_load(page_indptr + u);
+    pend = scalar_load(page_indptr + u + 1);
     asm volatile("" : "+s"(r0), "+s"(r1), "+s"(pos), "+s"(pbeg), "+s"(pend));   // one wait for all of them
     t0 = r0;
     n = (int64_t)r1 - t0;
   } else {
-    u = scalar_load(segs.seg_user + s);
-    pos = scalar_load(segs.seg_pos + s);
-    t0 = scalar_load(segs.seg_tok_indptr + s);
-    int64_t t1 = scalar_load(segs.seg_tok_indptr + s + 1);
+    u = scalar_load(run_user + s);
+    pos = scalar_load(run_pos + s);
+    t0 = scalar_load(run_tok + s);
+    int64_t t1 = scalar_load(run_tok + s + 1);
     asm volatile("" : "+s"(u), "+s"(pos), "+s"(t0), "+s"(t1));
     n = t1 - t0;
-    user_ok = u >= 0 && u < b.batch;
+    user_ok = u >= 0 && u < batch;
     const int uc = user_ok ? u : 0;
-    pbeg = scalar_load(b.page_indptr + uc);
-    pend = scalar_load(b.page_indptr + uc + 1);
+    pbeg = scalar_load(page_indptr + uc);
+    pend = scalar_load(page_indptr + uc + 1);
   }
   const int npg = pend - pbeg;
 
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(PoolGeom g, SegDev segs, B
     u32x4 kg[NIT], vg[NIT];
     const int64_t lp = sb >> g.sub_shift;
     if (lp >= npg) return;
-    const int page = scalar_load(b.page_indices + pbeg + lp);
+    const int page = scalar_load(page_indices + pbeg + lp);
     const bool page_ok = (unsigned)page < (unsigned)g.num_pages;
     const int sub = (int)(sb & ((S >> 4) - 1));
     char* head = g.layer_base + (int64_t)page * g.page_bytes;
@@ -308,9 +320,12 @@ void launch_typed(const PoolGeom& g, const SegDev& segs, const BatchDev& b, dim3
                                               2ll * g.H * g.D * g.es, grid.z);
     if (past != kBoth) kern = past == kRead ? kv_move_kernel<T, MODE, DCH, kRead> : kv_move_kernel<T, MODE, DCH, kNone>;
   }
-  hipLaunchKernelGGL(kern, grid, dim3(256, 1, 1), 0, stream, g, segs, b, (const T*)a,
-                     (const T*)bsrc, (T*)dst, bulk_blocks, pool_layer_stride,
-                     contig_layer_stride_bytes / (int64_t)sizeof(T));
+  constexpr bool kAppend = MODE == MODE_APPEND;
+  hipLaunchKernelGGL(kern, grid, dim3(256, 1, 1), 0, stream,
+                     kAppend ? run_tables(b) : table_words(segs.seg_user, segs.seg_pos), page_tables(b),
+                     CallWords{b.batch, g.H, bulk_blocks, 0}, segs.seg_tok_indptr,
+                     MoveSides<T>{g, (const T*)a, (const T*)bsrc, (T*)dst, pool_layer_stride,
+                                  contig_layer_stride_bytes / (int64_t)sizeof(T)});
 }
 
 template <int MODE>

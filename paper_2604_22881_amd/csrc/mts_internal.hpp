@@ -24,6 +24,25 @@ struct BatchDev {            // device metadata arrays, as in mts_batch_meta
   int32_t        total_pages;
 };
 
+// What a kernel's first loads need comes first among its arguments: the compiler is told to have up to 14 words of such
+// arguments in scalar registers when a wavefront starts (vectors and scalars, not structures), so that the tables'
+// loads do not wait until the arguments have come from memory; those behind them travel beside the tables.  A kernel
+// that is a chain of round trips gets 0.3 us shorter: 8 layers of one user's 32 new tokens behind 6375 x 4 heads of 128,
+// 24 launches, 152.1 -> 143.9 us; 64 users x 8 heads of 64, 4 layers, 230.2 -> 228.9.  (Not the prefill kernel's: its registers
+// are full, 442 -> 444 us for one user's 5189 tokens, where without it 439.)  As vectors and few structures, because every argument
+// costs the host at a launch: with each table an argument, 2 layers of 16 queries x 272 keys x 4 heads of 32 in fp32, four
+// launches that the host is the limit of, 21.4 -> 22.2 us; as it is, 21.3.
+typedef uint64_t TableWords __attribute__((ext_vector_type(2)));   // addresses of two tables
+typedef int32_t CallWords __attribute__((ext_vector_type(4)));
+typedef int32_t CallWords2 __attribute__((ext_vector_type(2)));
+inline TableWords table_words(const void* a, const void* b) { return TableWords{(uint64_t)(uintptr_t)a, (uint64_t)(uintptr_t)b}; }
+inline TableWords run_tables(const BatchDev& b) { return table_words(b.new_indptr, b.prefix_lens); }
+inline TableWords page_tables(const BatchDev& b) { return table_words(b.page_indptr, b.page_indices); }
+// (by way of the global address space, so that loads through it are global ones)
+__device__ __forceinline__ const int32_t* table(uint64_t address) {
+  return (const int32_t*)(const __attribute__((address_space(1))) int32_t*)address;
+}
+
 struct SegDev {              // segment lists of unpack / pack
   int32_t        num_segs;
   const int32_t* seg_user;
