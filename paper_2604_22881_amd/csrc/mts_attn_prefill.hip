@@ -6,9 +6,13 @@
 // A workgroup (4 wavefronts) owns one (user, head, block of 128*NQ new tokens): wavefront w takes
 // queries 32*NQ*w .. 32*NQ*(w+1)-1 of the block.  All four walk the same kv tiles, so each 32-token
 // K/V tile is fetched from global memory ONCE per workgroup: every wavefront moves a quarter of it
-// straight into LDS (16 bytes per lane, no registers), in fragment order (lane l of fragment f at
-// f*1 KiB + l*16 B), so that all reads back are whole, conflict-free operands.  The block's page ids
-// are copied to LDS once, so that no load in the loop depends on another load.
+// straight into LDS (16 bytes per lane, no registers), in an order from which all reads back are whole, conflict-free
+// operands.  A wavefront's quarter comes from one of the tile's two 16-token sub-blocks, at an address that is one for all
+// lanes, and lies as far apart in LDS as in the page: one page id, one multiplication and two m0 a step, and four loads with
+// nothing between them.  (Quarters that took both sub-blocks, with 64-bit addresses a lane: 80 instructions more in two
+// steps, which at the power limit cost time whatever they overlap with: 1168 -> 1095 us for the call below, one user of 5189
+// tokens x 4 heads 49.6 -> 47.6, split and merged.)
+// The block's page ids are copied to LDS once, so that no load in the loop depends on another load.
 //
 // Operand flow: S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16; queries are the columns,
 // so a lane's 16 scores belong to ONE query, and the order in which a tile's tokens are the rows of
@@ -20,12 +24,13 @@
 // while the matrix cores work on P.V.  One barrier per step, across which the newest fetch stays in
 // flight.
 //
-// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1113 to
-// 1165 us (942-986 TFLOP/s at 1.85 to 1.93 GHz), 959 us on zeros; a library matrix product of 8192^3
+// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1050 to
+// 1095 us (1004-1047 TFLOP/s), 780 us on zeros; a library matrix product of 8192^3
 // reaches 1250 TFLOP/s here.  With v_mfma_f32_16x16x32_bf16, tiles parked from registers and no
-// pipelining across tiles the same call took 1163 to 1200 us (1018 on zeros), 64-dim heads 697 (632
-// now), one user of 5189 tokens x 4 heads 55.5 (51).  Tried and slower: 256-query blocks of eight
-// wavefronts (1192 against 1162), raised wavefront priority around the matrix work (1-3 %).
+// pipelining across tiles the same call took 1163 to 1200 us (1018 on zeros), 64-dim heads 697 (628
+// now).  Tried and slower: 256-query blocks of eight wavefronts (1192 against 1162), raised wavefront priority around the
+// matrix work (1-3 %); 64 queries of 128 dims a wavefront, one wavefront a SIMD, matrix and vector instructions dealt out
+// one by one (957 on zeros, 1072 to 1127 on random data where this one took 1095; split calls 1.25 times as long).
 //
 // The softmax reference is fixed, as in the streaming kernel (max of the block's first tile, no
 // rescaling; an overflowed denominator makes the whole workgroup redo its block, or its piece of a cut
@@ -104,15 +109,22 @@ __device__ __forceinline__ float pair_sum(float v) {
   return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
-// 16 bytes per lane from global memory to LDS byte address `to` (wavefront-uniform) + 16 * lane, without
-// passing through registers.  As an instruction of its own because the compiler, given the builtin,
-// waits for all such loads before any LDS read; here the waits are wait_and_barrier's.  m0 is declared
-// as overwritten, so that no value of the compiler's own is taken to outlive the statement in it; the
-// warning says that the statement does not restore it.
+// `N` times 16 bytes per lane from global memory, `from` + `lane_at` + k * STRIDE, to LDS byte address `to` (both
+// wavefront-uniform) + k * STRIDE + 16 * lane, without passing through registers.  As instructions of its own because the
+// compiler, given the builtin, waits for all such loads before any LDS read; here the waits are wait_and_barrier's.
+// m0 is declared as overwritten, so that no value of the compiler's own is taken to outlive the statement in it; the
+// warning says that the statement does not restore it.  (`from` is a product and sums, all scalar instructions: a register that a
+// vector instruction has just written would need five wait states before the load.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void load_to_lds(const char* from, uint32_t to) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(from), "s"(to) : "m0", "memory");
+template <int N, int STRIDE>
+__device__ __forceinline__ void load_to_lds(const char* from, uint32_t lane_at, uint32_t to) {
+  static_assert(N == 1 || N == 2, "one m0 for both");
+  if constexpr (N == 1)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_at), "s"(from), "s"(to) : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+                 : : "v"(lane_at), "s"(from), "s"(to), "n"(STRIDE) : "m0", "memory");
 }
 #pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
@@ -149,7 +161,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   static_assert(FQ % 2 == 0 && FQ >= 2 && NST == 3, "fragment split");
 
   extern __shared__ int s_ids[];       // physical page of every logical page the block reads
-  __shared__ u32x4 stage[NST][FR * 64];  // tiles in fragment order: lane l of fragment f at f * 1 KiB + l * 16 B
+  __shared__ u32x4 stage[NST][FR * 64];  // K in KS KiB, then V (k_lane, v_lane and the reads below have the order)
   __shared__ int redo_flag[4];         // of every wavefront
 
   const int tid = threadIdx.x;
@@ -326,37 +338,34 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   const char* head_base = g.layer_base + (int64_t)h * 2 * S * D * 2;
 
   const int last_tile = t_end - 1;
+  // A wavefront moves what comes from one of a tile's two sub-blocks, number wave & 1: one page id a tile, one address
+  // that is the same for all lanes.
   // K fragment s: lane (r, hf) holds dims 16 s + 8 hf .. + 7 of tile row r.  The row order makes the 16
-  // accumulator values of a lane its tokens 8 hf .. + 7 of sub-block 0, then of sub-block 1.
-  const int k_lane = ((((r >> 3) & 1) * (D / 8) + 2 * wave + hf) * 8 + (r & 7)) * 16;
-  // V^T fragment (db, sb): dim 32 db + r, tokens 8 hf .. + 7 of sub-block sb
-  const int64_t v_lane = v_off + (r * 2 + hf) * 16 + (wave >> 1) * 1024;
-  const uint32_t stage_lds = lds_address(&stage[0][0]) + wave * 1024;
-  // page ids of a tile (past the end: of the last one, whose data is then fetched again, never used)
-  auto page_ids = [&](int tile, int& id0, int& id1) __attribute__((always_inline)) {
-    const int sb0 = (tile < last_tile ? tile : last_tile) * 2;
-    id0 = s_ids[(sb0 >> g.sub_shift) - lp_beg];
-    id1 = s_ids[((sb0 + 1) >> g.sub_shift) - lp_beg];
-  };
+  // accumulator values of a lane its tokens 8 hf .. + 7 of sub-block 0, then of sub-block 1.  In LDS, 1 KiB holds the rows
+  // of one sub-block of fragments 2 x and 2 x + 1; x = wave / 2 and wave / 2 + 2 are the wavefront's, as far apart there as
+  // in the page.
+  const uint32_t k_lane = ((((lane >> 3) & 1) * (D / 8) + 4 * (wave >> 1) + (lane >> 4)) * 8 + (lane & 7)) * 16;
+  const int k_read = (r >> 4) * (KS / 2 * 64) + hf * 16 + (r & 15);
+  // V^T fragment (db, sb): dim 32 db + r, tokens 8 hf .. + 7 of sub-block sb; db = wave / 2 and wave / 2 + 2 are the wavefront's
+  const uint32_t v_lane = (uint32_t)v_off + (r * 2 + hf) * 16 + (wave >> 1) * 1024;
+  const uint32_t k_lds = lds_address(&stage[0][0]) + ((wave & 1) * (KS / 2) + (wave >> 1) * (KS / 4)) * 1024;
+  const uint32_t v_lds = lds_address(&stage[0][0]) + (KS + (wave & 1) + (wave >> 1) * DB) * 1024;
+  // a tile's sub-block (past the end: of the last one, whose data is then fetched again, never used), its page
+  auto sub_block = [&](int tile) __attribute__((always_inline)) { return (tile < last_tile ? tile : last_tile) * 2 + (wave & 1); };
+  auto page_id = [&](int tile) __attribute__((always_inline)) { return s_ids[(sub_block(tile) >> g.sub_shift) - lp_beg]; };
   // A stage holds the keys of tile `tile` and the values of the tile two before it.  Fetches this
-  // wavefront's quarter of it (fragments 4 j + wave) straight into LDS; the first two stages of a
-  // segment are keys only.
-  const char *v_1 = nullptr, *v_2 = nullptr;                     // the values of tiles tile - 1 and tile - 2
-  auto load = [&](int st, int tile, int id0, int id1, auto with_v) __attribute__((always_inline)) {
-    const int sb0 = (tile < last_tile ? tile : last_tile) * 2;
+  // wavefront's quarter of it straight into LDS; the first two stages of a segment are keys only.
+  const char *v_1 = head_base, *v_2 = head_base;                 // of tiles tile - 1 and tile - 2
+  auto sub_block_at = [&](int tile, int id) __attribute__((always_inline)) {
     const uint32_t page = (uint32_t)g.page_bytes;                // at most 2 GiB: 65535 heads of 64 x 128 bf16
-    const char* kb0 = head_base + (uint64_t)(uint32_t)uniform(id0) * page + (uint32_t)((sb0 & sub_mask) * 16 * D * 2);
-    const char* kb1 = head_base + (uint64_t)(uint32_t)uniform(id1) * page + (uint32_t)(((sb0 + 1) & sub_mask) * 16 * D * 2);
-    const char* ka = (r < 16 ? kb0 : kb1) + k_lane;
-    const char* va = v_2 + v_lane;
+    return head_base + (uint64_t)(uint32_t)uniform(id) * page + (uint32_t)((sub_block(tile) & sub_mask) * 16 * D * 2);
+  };
+  auto load = [&](int st, int tile, int id, auto with_v) __attribute__((always_inline)) {
+    const char* at = sub_block_at(tile, id);
+    load_to_lds<FQ / 2, 1024>(at, k_lane, k_lds + st * (FR * 1024));
+    if constexpr (decltype(with_v)::value) load_to_lds<FQ / 2, 2048>(v_2, v_lane, v_lds + st * (FR * 1024));
     v_2 = v_1;
-    v_1 = (wave & 1) ? kb1 : kb0;
-    const uint32_t to = stage_lds + st * (FR * 1024);
-#pragma unroll
-    for (int j = 0; j < FQ / 2; ++j) {
-      load_to_lds(ka + j * 1024, to + 4 * j * 1024);
-      if constexpr (decltype(with_v)::value) load_to_lds(va + j * 2048, to + (KS + 4 * j) * 1024);
-    }
+    v_1 = at;
   };
 
   bf16x8 qf[NQ][KS];
@@ -366,8 +375,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) { m[qb] = -INFINITY; mcq[qb] = 0.f; }
 
-  auto fragment = [&](int st, int f) __attribute__((always_inline)) {
-    return __builtin_bit_cast(bf16x8, stage[st][f * 64 + lane]);
+  auto key_fragment = [&](int st, int s, int room = 0) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, stage[st][(room + (s >> 2) + KS / 4 * (s >> 1 & 1)) * 64 + (s & 1) * 32 + k_read]);
+  };
+  auto value_fragment = [&](int st, int f) __attribute__((always_inline)) {        // f = 2 db + sb
+    return __builtin_bit_cast(bf16x8, stage[st][(KS + (f >> 2) * 2 + (f & 1) + DB * (f >> 1 & 1)) * 64 + lane]);
   };
   // S^T of query block qb; with `masked`, keys the query must not see (causal order among the new
   // tokens) are set to -inf.
@@ -422,35 +434,43 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // which travel to registers while the matrix cores work on P.V.
   // The barrier publishes the stage and retires every read of the one before it, which the fetch
   // for step t+2 overwrites; the fetch for step t+1 stays in flight across it.
-  int next_id0 = 0, next_id1 = 0;      // page ids of the tile that the next step fetches
+  int next_id = 0;                     // page of the tile that the next step fetches
   bf16x8 kf[KS];
   auto move = [&](int t, int st) __attribute__((always_inline)) {
     wait_and_barrier<FQ>();
-    load(st == 0 ? NST - 1 : st - 1, t + 4, next_id0, next_id1, std::true_type{});
-    page_ids(t + 5, next_id0, next_id1);
+    load(st == 0 ? NST - 1 : st - 1, t + 4, next_id, std::true_type{});
+    next_id = page_id(t + 5);
   };
-  auto step = [&](auto masked_c, int t, int st, f32x16 (&z)[NQ], f32x16 (&z_next)[NQ]) __attribute__((always_inline)) {
+  auto read_values = [&](int st, bf16x8 (&vf)[2 * DB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < 2 * DB; ++f) vf[f] = value_fragment(st, f);
+  };
+  auto read_keys = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = key_fragment(st, s);
+  };
+  auto add_values = [&](int qb, const bf16x8 (&vf)[2 * DB], const bf16x8 (&pf)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * db + sb], pf[sb], o[qb][db], 0, 0, 0);
+  };
+  // Tiles past the wavefront's own last query hold no key it may see (the later wavefronts of the block still need
+  // them): it only helps to move them.
+  // NQ = 1
+  auto step = [&](auto masked_c, int t, int st, f32x16& z, f32x16& z_next) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
     move(t, st);
-    // tiles past the wavefront's own last query hold no key it may see (the later wavefronts of
-    // the block still need them): it only helps to move them
     const bool here = !MASKED || t < tiles_w, next = !MASKED || t + 1 < tiles_w;
     bf16x8 vf[2 * DB];
+    if (here) read_values(st, vf);
+    if (next) z_next = scores(kf, 0, (t + 1) * kTile, MASKED);
     if (here) {
-#pragma unroll
-      for (int f = 0; f < 2 * DB; ++f) vf[f] = fragment(st, KS + f);
-    }
-    if (next) {
-#pragma unroll
-      for (int qb = 0; qb < NQ; ++qb) z_next[qb] = scores(kf, qb, (t + 1) * kTile, MASKED);
-    }
-    if (here) {
-      bf16x8 pf[NQ][2];
-#pragma unroll
-      for (int qb = 0; qb < NQ; ++qb) weights(z[qb], qb, pf[qb]);
+      bf16x8 pf[2];
+      weights(z, 0, pf);
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) kf[s] = fragment(st, s);
+      read_keys(st);
       const int tb = t * kTile;
       if constexpr (MASKED) {                                      // slots past the user's last token may hold anything
         if (tb + kTile > T_u) {
@@ -461,14 +481,40 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
               if (tb + 16 * (f & 1) + 8 * hf + e >= T_u) vf[f][e] = (__bf16)0.0f;
         }
       }
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int qb = 0; qb < NQ; ++qb)
-            o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * db + sb], pf[qb][sb], o[qb][db], 0, 0, 0);
+      add_values(0, vf, pf);
     }
+  };
+  // NQ = 2: the query blocks are half a step apart, so that all of the matrix work has weights to be taken beside it.  On
+  // entry p0 are the weights of block 0 and z1 the scores of block 1; z0 holds nothing between steps (both blocks in step keep two
+  // sets of scores each, spilled 22 registers in the split form, and took 1-2 % longer: heads of 64, one user's 6000 tokens x 8
+  // 62.6 -> 61.5 us a layer, 8 users x 1150 x 8 37.2 -> 36.4).
+  auto step_apart = [&](auto masked_c, int t, int st, f32x16& z0, f32x16& z1, bf16x8 (&p0)[2]) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    move(t, st);
+    const bool here = !MASKED || t < tiles_w, next = !MASKED || t + 1 < tiles_w;
+    bf16x8 vf[2 * DB], p1[2];
+    if (here) read_values(st, vf);
+    if (next) z0 = scores(kf, 0, (t + 1) * kTile, MASKED);
+    if (here) {
+      weights(z1, NQ - 1, p1);
+      const int tb = t * kTile;
+      if constexpr (MASKED) {                                      // slots past the user's last token may hold anything
+        if (tb + kTile > T_u) {
+#pragma unroll
+          for (int f = 0; f < 2 * DB; ++f)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (tb + 16 * (f & 1) + 8 * hf + e >= T_u) vf[f][e] = (__bf16)0.0f;
+        }
+      }
+      add_values(0, vf, p0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (next) z1 = scores(kf, NQ - 1, (t + 1) * kTile, MASKED);
+    if (here) read_keys(st);
+    if (next) weights(z0, 0, p0);
+    if (here) add_values(NQ - 1, vf, p1);
+    __builtin_amdgcn_sched_barrier(0);
   };
   // tiles below hide no key from any query of the block (its first wavefront sees the least)
   int fast_all = (P + Q0 + 1) / kTile;
@@ -498,7 +544,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       for (int tile = tile0; tile < tiles_w; ++tile) {         // tiles past tiles_w hold no visible key
         const int sb = tile * 2 + (r >> 4);
         const char* ka = head_base + (int64_t)s_ids[(sb >> g.sub_shift) - lp_beg] * g.page_bytes +
-                         (int64_t)(sb & sub_mask) * 16 * D * 2 + k_lane - wave * 256;
+                         (int64_t)(sb & sub_mask) * 16 * D * 2 + (((r >> 3 & 1) * (D / 8) + hf) * 8 + (r & 7)) * 16;
         bf16x8 kf[KS];
 #pragma unroll
         for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(ka + s * 256);
@@ -514,22 +560,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 
     // prologue: the keys of the first two tiles, the stage of the first step, the first tile's scores
     // Their pages, and those of the user's first tile, by scalar loads that travel together.
-    int id0[NST + 1] = {}, id1[NST + 1] = {};
-    auto tile_at = [&](int k) __attribute__((always_inline)) {
-      return k == NST ? zero : (tile0 + k < last_tile ? tile0 + k : last_tile);
-    };
+    int id[NST + 1] = {};
+    auto tile_at = [&](int k) __attribute__((always_inline)) { return k == NST ? zero : tile0 + k; };
     if (npg > 0) {
 #pragma unroll
       for (int k = 0; k <= NST; ++k) {
-        const int lp0 = (tile_at(k) * 2) >> g.sub_shift, lp1 = (tile_at(k) * 2 + 1) >> g.sub_shift;
-        id0[k] = scalar_load(b.page_indices, pbeg + (lp0 < npg ? lp0 : npg - 1));
-        id1[k] = scalar_load(b.page_indices, pbeg + (lp1 < npg ? lp1 : npg - 1));
+        const int lp = sub_block(tile_at(k)) >> g.sub_shift;
+        id[k] = scalar_load(b.page_indices, pbeg + (lp < npg ? lp : npg - 1));
       }
 #pragma unroll
-      for (int k = 0; k <= NST; ++k) {
-        if ((unsigned)id0[k] >= (unsigned)g.num_pages || (tile_at(k) * 2) >> g.sub_shift >= npg) id0[k] = 0;
-        if ((unsigned)id1[k] >= (unsigned)g.num_pages || (tile_at(k) * 2 + 1) >> g.sub_shift >= npg) id1[k] = 0;
-      }
+      for (int k = 0; k <= NST; ++k)
+        if ((unsigned)id[k] >= (unsigned)g.num_pages || sub_block(tile_at(k)) >> g.sub_shift >= npg) id[k] = 0;
     }
     // SPLIT: the reference of a piece is that of its whole block, the max of the user's first tile.  So its
     // weights are rounded as those of an uncut block, and how a call is cut changes its result by the
@@ -538,13 +579,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     // it and 441 with a reference of each piece's own, six returning users beside two first-time ones 750 and 741.
     constexpr bool kBlockReference = SPLIT && !PW;
     if (kBlockReference && attempt == 0) {
-      const char* ka = head_base + (int64_t)(r < 16 ? id0[NST] : id1[NST]) * g.page_bytes + (int64_t)((r >> 4) & sub_mask) * 16 * D * 2 + k_lane;
-#pragma unroll
-      for (int j = 0; j < FQ / 2; ++j) load_to_lds(ka + j * 1024, stage_lds + (KS + 4 * j) * 1024);
+      load_to_lds<FQ / 2, 1024>(sub_block_at(zero, id[NST]), k_lane, k_lds + KS * 1024);
     }
-    load(0, tile0, id0[0], id1[0], std::false_type{});
-    load(1, tile0 + 1, id0[1], id1[1], std::false_type{});
-    load(2, tile0 + 2, id0[2], id1[2], std::true_type{});
+    load(0, tile0, id[0], std::false_type{});
+    load(1, tile0 + 1, id[1], std::false_type{});
+    load(2, tile0 + 2, id[2], std::true_type{});
     if (attempt == 0) {
       // behind the first tiles' loads, so that their round trip is shared: the block's page table -> LDS, and its
       // queries.  Ids the metadata does not back become page 0 (in bounds; such slots lie past the user's last
@@ -570,26 +609,26 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       }
     }
     wait_and_barrier<0>();
-    f32x16 za[NQ], zb[NQ];
+    f32x16 za[NQ], zb;
     if (kBlockReference && attempt == 0) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) kf[s] = fragment(0, KS + s);
+      for (int s = 0; s < KS; ++s) kf[s] = key_fragment(0, s, KS);
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) set_reference(scores(kf, qb, zero, true), qb);
     }
 #pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = fragment(0, s);
+    for (int s = 0; s < KS; ++s) kf[s] = key_fragment(0, s);
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
       za[qb] = scores(kf, qb, tile0 * kTile, true);
       if (!PW && !kBlockReference && attempt == 0) set_reference(za[qb], qb);
     }
     wait_and_barrier<0>();                                         // stage 0 is read
-    page_ids(tile0 + 3, next_id0, next_id1);
-    load(0, tile0 + 3, next_id0, next_id1, std::true_type{});
-    page_ids(tile0 + 4, next_id0, next_id1);
+    next_id = page_id(tile0 + 3);
+    load(0, tile0 + 3, next_id, std::true_type{});
+    next_id = page_id(tile0 + 4);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) kf[s] = fragment(1, s);
+    for (int s = 0; s < KS; ++s) kf[s] = key_fragment(1, s);
 
     int tile = tile0, st = 2;
     auto after = [](int st) __attribute__((always_inline)) { return st == NST - 1 ? 0 : st + 1; };
@@ -599,18 +638,31 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
         st = after(st);
       }
     }
-    while (tile + 2 < fast_all) {                                  // steady state: fully visible tiles
-      step(body, tile, st, za, zb);
-      st = after(st);
-      step(body, tile + 1, st, zb, za);
-      st = after(st);
-      tile += 2;
-    }
-    for (; tile < t_end; tile += 2) {                              // causal tail, and what is left over
-      step(tail, tile, st, za, zb);
-      st = after(st);
-      if (tile + 1 < t_end) step(tail, tile + 1, st, zb, za);
-      st = after(st);
+    // steady state: fully visible tiles; then the causal tail, and what is left over
+    if constexpr (NQ == 1) {
+      for (; tile + 2 < fast_all; tile += 2) {
+        step(body, tile, st, za[0], zb);
+        st = after(st);
+        step(body, tile + 1, st, zb, za[0]);
+        st = after(st);
+      }
+      for (; tile < t_end; tile += 2) {
+        step(tail, tile, st, za[0], zb);
+        st = after(st);
+        if (tile + 1 < t_end) step(tail, tile + 1, st, zb, za[0]);
+        st = after(st);
+      }
+    } else {
+      bf16x8 p0[2];
+      weights(za[0], 0, p0);
+      for (; tile + 1 < fast_all; ++tile) {
+        step_apart(body, tile, st, za[0], za[NQ - 1], p0);
+        st = after(st);
+      }
+      for (; tile < t_end; ++tile) {
+        step_apart(tail, tile, st, za[0], za[NQ - 1], p0);
+        st = after(st);
+      }
     }
     wait_and_barrier<0>();                                         // no load is in flight, no stage is read
 
