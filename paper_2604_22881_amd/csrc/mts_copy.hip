@@ -58,12 +58,13 @@ struct MoveSides {
 // bank).  Workgroups [0, bulk_blocks) take the sub-blocks that a run covers completely; those
 // behind them take partly covered sub-blocks with the same code under a token mask: rows outside
 // the run are neither read nor written, K granules of other tokens are skipped and a V granule
-// that the run covers only in part is written element by element, so no slot outside the run
+// that the run covers only in part is written piece by piece, so no slot outside the run
 // is ever written.
 // `runs`: seg_user and seg_pos of a segment list (`run_tok`: seg_tok_indptr) or an append's new_indptr and prefix_lens;
 // `pages`: page_indptr and page_indices.
+// PLANES: a launch of masked units, K and V of each by a wavefront of its own (append_by_planes).
 // PAST: which rows travel past the caches' retention (mts_copy_rules.hpp; an append's own rule is at KEEP).
-template <typename T, int MODE, int DCH, RowsPast PAST>
+template <typename T, int MODE, int DCH, RowsPast PAST, bool PLANES>
 __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWords pages, CallWords call, const int64_t* run_tok,
                                                       MoveSides<T> sides) {
   const int32_t *run_user = table(runs[0]), *run_pos = table(runs[1]), *page_indptr = table(pages[0]),
@@ -144,10 +145,20 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
   // unit = 4 * block + wave of a part, as (sub-block, head) = (unit / H, unit % H) in 32 bits
   const bool in_bulk = (int)blockIdx.x < bulk_blocks;
   const unsigned blk = in_bulk ? blockIdx.x : blockIdx.x - (unsigned)bulk_blocks;
-  const unsigned blk_q = blk / (unsigned)H, rest = (blk - blk_q * (unsigned)H) * kBulkWaves + (unsigned)wave;
-  const unsigned rest_q = rest / (unsigned)H;
-  const int64_t k = (int64_t)blk_q * kBulkWaves + rest_q;
-  const int h = (int)(rest - rest_q * (unsigned)H);
+  int64_t k;
+  int h, plane = 0;
+  if (const unsigned inverse = (unsigned)call[3]) {              // two divisions were 0.1 to 0.3 us of a short launch
+    unsigned unit = blk * kBulkWaves + (unsigned)wave;
+    if (PLANES) { plane = unit & 1; unit >>= 1; }
+    const unsigned quotient = __umulhi(2 * unit, inverse);
+    k = quotient;
+    h = (int)(unit - quotient * (unsigned)H);
+  } else {
+    const unsigned blk_q = blk / (unsigned)H, rest = (blk - blk_q * (unsigned)H) * kBulkWaves + (unsigned)wave;
+    const unsigned rest_q = rest / (unsigned)H;
+    k = (int64_t)blk_q * kBulkWaves + rest_q;
+    h = (int)(rest - rest_q * (unsigned)H);
+  }
   int64_t sb;
   const bool masked = !in_bulk;
   if (in_bulk) {
@@ -173,9 +184,10 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
     t_hi = (int)(ppos + npos < sbase + 16 ? ppos + npos - sbase : 16);
   }
   __shared__ __attribute__((aligned(16))) T tile[kBulkWaves][16 * PITCH];
-  // masked_c: compile-time copy of `masked`, so that the whole-sub-block form carries no checks
-  auto move_sub_block = [&](auto masked_c) __attribute__((always_inline)) {
+  // masked_c: compile-time copy of `masked`, so that the whole-sub-block form carries no checks; planes_c: K, V or both
+  auto move_sub_block = [&](auto masked_c, auto planes_c) __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
+    constexpr bool KP = decltype(planes_c)::value & 1, VP = decltype(planes_c)::value & 2;
     // A short append's rows are written for late readers: stored the plain way they fill an L2 that writes
     // them back at the kernel's end and push out what the next kernel reads; a step of 64 returning users 247 ->
     // 230 us, 256 users 1109 -> 1064.  A whole prefill's append keeps its rows, the attention that follows
@@ -208,58 +220,105 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
         int t = gi / dch;
         if (MASKED) t = t < t_lo ? t_lo : (t < t_hi ? t : t_hi - 1);
         const int64_t off = (row0 + t) * H * D + (int64_t)h * D + c * G;
-        kg[j] = load_granule<KEEP_READ>(k_plane + off);
-        vg[j] = load_granule<KEEP_READ>(v_plane + off);
+        if constexpr (KP) kg[j] = load_granule<KEEP_READ>(k_plane + off);
+        if constexpr (VP) vg[j] = load_granule<KEEP_READ>(v_plane + off);
       }
+      if constexpr (KP) {
 #pragma unroll
-      for (int j = 0; j < NIT; ++j) {
-        const int gi = j * 64 + lane, t = gi / dch, c = gi % dch;
-        *reinterpret_cast<u32x4*>(lt + t * PITCH + c * G) = kg[j];
+        for (int j = 0; j < NIT; ++j) {
+          const int gi = j * 64 + lane, t = gi / dch, c = gi % dch;
+          *reinterpret_cast<u32x4*>(lt + t * PITCH + c * G) = kg[j];
+        }
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < NIT; ++j) {
+          const int p = j * 64 + lane;                          // K granule in pool order
+          const int half = p / (dch * 8), c = (p / 8) % dch, slot = p % 8;
+          const int t = ((slot >> 2) << 3) + half * 4 + (slot & 3);
+          kg[j] = *reinterpret_cast<const u32x4*>(lt + t * PITCH + c * G);
+        }
       }
-      wave_sync();
+      if constexpr (KP && VP) wave_sync();
+      if constexpr (VP) {
 #pragma unroll
-      for (int j = 0; j < NIT; ++j) {
-        const int p = j * 64 + lane;                            // K granule in pool order
-        const int half = p / (dch * 8), c = (p / 8) % dch, slot = p % 8;
-        const int t = ((slot >> 2) << 3) + half * 4 + (slot & 3);
-        kg[j] = *reinterpret_cast<const u32x4*>(lt + t * PITCH + c * G);
-      }
-      wave_sync();
+        for (int j = 0; j < NIT; ++j) {
+          const int gi = j * 64 + lane, t = gi / dch, c = gi % dch;
+          *reinterpret_cast<u32x4*>(lt + t * PITCH + c * G) = vg[j];
+        }
+        wave_sync();
 #pragma unroll
-      for (int j = 0; j < NIT; ++j) {
-        const int gi = j * 64 + lane, t = gi / dch, c = gi % dch;
-        *reinterpret_cast<u32x4*>(lt + t * PITCH + c * G) = vg[j];
-      }
-      wave_sync();
+        for (int j = 0; j < NIT; ++j) {
+          const int p = j * 64 + lane;                          // V granule: G tokens of one dim
+          const int d = p / (16 / G), part = p % (16 / G);
+          EV o;
 #pragma unroll
-      for (int j = 0; j < NIT; ++j) {
-        const int p = j * 64 + lane;                            // V granule: G tokens of one dim
-        const int d = p / (16 / G), part = p % (16 / G);
-        EV o;
-#pragma unroll
-        for (int e = 0; e < G; ++e) o[e] = lt[(part * G + e) * PITCH + d];
-        vg[j] = __builtin_bit_cast(u32x4, o);
+          for (int e = 0; e < G; ++e) o[e] = lt[(part * G + e) * PITCH + d];
+          vg[j] = __builtin_bit_cast(u32x4, o);
+        }
       }
       if (!page_ok) return;                                     // here, so that the rows do not wait for the page id
 #pragma unroll
       for (int j = 0; j < NIT; ++j) {
         const int p = j * 64 + lane;
-        const int slot = p % 8, half = p / (dch * 8);
-        const int t = ((slot >> 2) << 3) + half * 4 + (slot & 3);         // token of K granule p
-        if (in_run(t)) store_granule<KEEP>(kblk + (int64_t)p * G, kg[j]);
-        // V granule p holds tokens part*G .. part*G+G-1 of one dim: whole if the run covers all
-        // of them, else element by element - no slot outside the run is written
-        const int part = p % (16 / G);
-        int e_lo = t_lo - part * G, e_hi = t_hi - part * G;
-        e_lo = e_lo < 0 ? 0 : e_lo;
-        e_hi = e_hi > G ? G : e_hi;
-        if (!MASKED || (e_lo == 0 && e_hi == G)) {
-          store_granule<KEEP>(vblk + (int64_t)p * G, vg[j]);
-        } else if (e_lo < e_hi) {
-          const EV o = __builtin_bit_cast(EV, vg[j]);
+        if constexpr (KP) {
+          const int slot = p % 8, half = p / (dch * 8);
+          const int t = ((slot >> 2) << 3) + half * 4 + (slot & 3);       // token of K granule p
+          if (in_run(t)) store_granule<KEEP>(kblk + (int64_t)p * G, kg[j]);
+        }
+        if constexpr (VP) if (!MASKED || (t_lo == 0 && t_hi == 16)) store_granule<KEEP>(vblk + (int64_t)p * G, vg[j]);
+      }
+      if constexpr (VP && MASKED) {
+        // V granule p holds tokens part*G .. part*G+G-1 of one dim: of a sub-block that the run covers in part it is whole
+        // if the run covers all of them, else it goes in the widest aligned pieces that the run covers - no slot outside the
+        // run is written.  Which pieces those are is the same for all lanes of a part.  (Element by element, eight stores of
+        // 2 bytes a lane: an append of one user's 32 rows of 4 heads of 128 4.05 -> 3.65 us, of 128 users' 1 row 5.1 -> 4.7.)
+        if (t_lo == 0 && t_hi == 16) return;
+        const int own = lane % (16 / G);                        // the part of this lane's granules, whatever j
 #pragma unroll
-          for (int e = 0; e < G; ++e)
-            if (e >= e_lo && e < e_hi) vblk[(int64_t)p * G + e] = o[e];
+        for (int part = 0; part < 16 / G; ++part) {
+          const int lo = t_lo - part * G, hi = t_hi - part * G;
+          auto covers = [&](int first, int count) { return lo <= first && first + count <= hi; };
+          auto misses = [&](int first, int count) { return hi <= first || first + count <= lo; };
+          auto store_piece = [&](int first, auto piece) {       // elements `first` .. of the granules, as wide as `piece`
+            typedef decltype(piece) Piece;
+            constexpr int kCount = sizeof(Piece) / sizeof(T);
+            if (own != part) return;
+#pragma unroll
+            for (int j = 0; j < NIT; ++j) {
+              const EV o = __builtin_bit_cast(EV, vg[j]);
+              T e[kCount];
+#pragma unroll
+              for (int k = 0; k < kCount; ++k) e[k] = o[first + k];
+              *reinterpret_cast<Piece*>(vblk + (int64_t)(j * 64 + lane) * G + first) = __builtin_bit_cast(Piece, e);
+            }
+          };
+          constexpr int kHalf = G / 2, kQuarter = 4 / sizeof(T);           // elements of 8 and of 4 bytes
+          if (misses(0, G)) continue;
+          if (covers(0, G)) {
+            if (own == part) {
+#pragma unroll
+              for (int j = 0; j < NIT; ++j) store_granule<KEEP>(vblk + (int64_t)(j * 64 + lane) * G, vg[j]);
+            }
+            continue;
+          }
+#pragma unroll
+          for (int half = 0; half < G; half += kHalf) {
+            if (misses(half, kHalf)) continue;
+            if (covers(half, kHalf)) {
+              store_piece(half, uint64_t{});
+              continue;
+            }
+#pragma unroll
+            for (int quarter = half; quarter < half + kHalf; quarter += kQuarter) {
+              if (covers(quarter, kQuarter)) {
+                store_piece(quarter, uint32_t{});
+              } else if constexpr (kQuarter > 1) {
+#pragma unroll
+                for (int e = quarter; e < quarter + kQuarter; ++e)
+                  if (covers(e, 1)) store_piece(e, T{});
+              }
+            }
+          }
         }
       }
     } else {
@@ -305,25 +364,32 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
       }
     }
   };
-  if (masked) move_sub_block(std::true_type{});
-  else move_sub_block(std::false_type{});
+  if constexpr (PLANES) {
+    if (plane == 0) move_sub_block(std::true_type{}, std::integral_constant<int, 1>{});
+    else move_sub_block(std::true_type{}, std::integral_constant<int, 2>{});
+  } else {
+    constexpr std::integral_constant<int, 3> both{};
+    if (masked) move_sub_block(std::true_type{}, both);
+    else move_sub_block(std::false_type{}, both);
+  }
 }
 
 template <typename T, int MODE, int DCH>
 void launch_typed(const PoolGeom& g, const SegDev& segs, const BatchDev& b, dim3 grid, int bulk_blocks,
                   const void* a, const void* bsrc, void* dst, int64_t pool_layer_stride,
-                  int64_t contig_layer_stride_bytes, hipStream_t stream) {
+                  int64_t contig_layer_stride_bytes, unsigned inverse, bool planes, hipStream_t stream) {
   constexpr RowsPast kBoth = RowsPast::kReadAndWritten, kRead = RowsPast::kRead, kNone = RowsPast::kNone;
-  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16) ? kBoth : kNone>;
+  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16) ? kBoth : kNone, false>;
   if constexpr (MODE == MODE_UNPACK) {
     const RowsPast past = scatter_past_caches((int64_t)segs.num_segs * segs.max_seg_tokens, (int64_t)b.total_pages * g.S,
                                               2ll * g.H * g.D * g.es, grid.z);
-    if (past != kBoth) kern = past == kRead ? kv_move_kernel<T, MODE, DCH, kRead> : kv_move_kernel<T, MODE, DCH, kNone>;
+    if (past != kBoth) kern = past == kRead ? kv_move_kernel<T, MODE, DCH, kRead, false> : kv_move_kernel<T, MODE, DCH, kNone, false>;
   }
   constexpr bool kAppend = MODE == MODE_APPEND;
+  if constexpr (kAppend) if (planes) kern = kv_move_kernel<T, MODE, DCH, kBoth, true>;
   hipLaunchKernelGGL(kern, grid, dim3(256, 1, 1), 0, stream,
                      kAppend ? run_tables(b) : table_words(segs.seg_user, segs.seg_pos), page_tables(b),
-                     CallWords{b.batch, g.H, bulk_blocks, 0}, segs.seg_tok_indptr,
+                     CallWords{b.batch, g.H, bulk_blocks, (int)inverse}, segs.seg_tok_indptr,
                      MoveSides<T>{g, (const T*)a, (const T*)bsrc, (T*)dst, pool_layer_stride,
                                   contig_layer_stride_bytes / (int64_t)sizeof(T)});
 }
@@ -344,13 +410,17 @@ hipError_t launch_move(const PoolGeom& g, const SegDev& segs, const BatchDev& b,
   const int64_t bulk_units = bulk ? (max_run_tokens / 16) * (int64_t)g.H : 0;
   const int64_t bulk_blocks = (bulk_units + kBulkWaves - 1) / kBulkWaves;
   const int64_t end_units = (bulk ? 2 : (max_run_tokens + 15) / 16 + 1) * (int64_t)g.H;
-  const int64_t blocks = bulk_blocks + (end_units + kBulkWaves - 1) / kBulkWaves;
+  // unit / H = the upper word of 2 * unit * inverse while unit * H < 2^31
+  const int64_t most_units = (bulk_units > end_units ? bulk_units : end_units) + kBulkWaves;
+  const unsigned inverse = 2 * most_units * g.H < (1ll << 31) ? (unsigned)(((1ull << 31) + g.H - 1) / g.H) : 0;
+  const bool planes = MODE == MODE_APPEND && !bulk && inverse != 0 && append_by_planes(g.D * g.es, end_units * runs * layers);
+  const int64_t blocks = bulk_blocks + (end_units * (planes ? 2 : 1) + kBulkWaves - 1) / kBulkWaves;
   if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks, (unsigned)runs, (unsigned)layers);
   const int dch = g.D / G;
 #define MTS_MOVE_CASE(T, DCH_) \
   case DCH_: launch_typed<T, MODE, DCH_>(g, segs, b, grid, (int)bulk_blocks, a, bsrc, dst, pool_layer_stride, \
-                                         contig_layer_stride_bytes, stream); break;
+                                         contig_layer_stride_bytes, inverse, planes, stream); break;
   if (g.es == 2) {
     switch (dch) {
       MTS_MOVE_CASE(uint16_t, 4) MTS_MOVE_CASE(uint16_t, 8) MTS_MOVE_CASE(uint16_t, 16)

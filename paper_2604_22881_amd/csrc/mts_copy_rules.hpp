@@ -26,4 +26,12 @@ constexpr RowsPast scatter_past_caches(int64_t run_tokens, int64_t held_tokens, 
 // 1.03 to 1.08 beyond 330.
 constexpr bool gather_past_caches(int row_bytes) { return row_bytes >= 128; }
 
+// Whether K and V of a short append's sub-block are moved by a wavefront each, `units` of them (sub-block, head, user,
+// layer) in the launch.  A launch of few is its longest chain, half as long then: rows of 256 bytes and more 0.74 to 0.97
+// of the time up to 9 000 units, 1.00 to 1.05 at 19 000 and more; of 128 bytes 0.93 to 0.97 up to 500, 1.02 to 1.12
+// at 1 100 to 6 000 (more wavefronts, each with little to do); of 64 bytes 1.00 to 1.06.
+constexpr bool append_by_planes(int row_bytes, int64_t units) {
+  return row_bytes >= 256 ? units <= 16384 : row_bytes == 128 && units <= 1024;
+}
+
 }  // namespace mts

@@ -1,6 +1,7 @@
 // Compiles if the copies' size rules lie where they were measured.
 #include "../../paper_2604_22881_amd/csrc/mts_copy_rules.hpp"
 
+using mts::append_by_planes;
 using mts::gather_past_caches;
 using mts::scatter_past_caches;
 
@@ -14,3 +15,5 @@ static_assert(scatter_past_caches(1024 * 1024, 16384, 2048, 4) == none && scatte
 static_assert(scatter_past_caches(43007, 1 << 30, 2048, 4) == read && scatter_past_caches(43008, 1 << 30, 2048, 4) == both, "");
 static_assert(scatter_past_caches(20479, 1 << 30, 2048, 4) == none && scatter_past_caches(20480, 1 << 30, 2048, 4) == read, "");
 static_assert(!gather_past_caches(64) && gather_past_caches(128) && gather_past_caches(512), "");
+static_assert(append_by_planes(256, 16384) && !append_by_planes(512, 16385), "");
+static_assert(append_by_planes(128, 1024) && !append_by_planes(128, 1025) && !append_by_planes(64, 1), "");

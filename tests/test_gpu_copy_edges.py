@@ -34,6 +34,31 @@ def test_append_at_sub_block_edges(dtype, H, D, S, new):
         assert g.tobytes() == oracle.pack(store, 0, w.user_pages(u), p, n).tobytes(), f"user {u}"
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_every_range_inside_a_sub_block_is_stored(dtype, D):
+    """A partly covered sub-block's values go in the widest aligned pieces: every first and last token, in a
+    launch whose K and V wavefronts are apart if the rows are wide enough."""
+    G = _harness()
+    ranges = [(lo, hi) for lo in range(16) for hi in range(lo + 1, 17)]
+    w = W.custom_workload("ranges", 77 + D, dtype, 1, 3, D, 16, [lo for lo, _ in ranges], [hi - lo for lo, hi in ranges], chunk_tokens=16)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    assert np.array_equal(step.pool_image(0), G.expected_pool_image(w, _oracle_store(w, data), 0, FILL))
+
+
+def test_more_heads_than_a_multiplication_divides_by():
+    G = _harness()
+    w = W.custom_workload("heads", 78, "bf16", 1, 24000, 32, 16, [3], [2], chunk_tokens=16)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    assert np.array_equal(step.pool_image(0), G.expected_pool_image(w, _oracle_store(w, data), 0, FILL))
+
+
 @pytest.mark.parametrize("new", [40, 200])
 @pytest.mark.parametrize("page", [-1, 1 << 20])
 def test_rows_of_a_page_outside_the_pool_go_nowhere(page, new):
