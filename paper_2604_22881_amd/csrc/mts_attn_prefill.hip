@@ -50,10 +50,10 @@
 // 4-12 K histories and 8-64 new tokens beside 2 first-time ones 190 -> 94 to 99 us (merge 10.5).  What is left there is the block starts (1.2 and 1.5 segments
 // a share, about 5 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
 //
-// A block's start (page ids, keys, reference, first scores) is 5 us, and a CU does little else before the
+// A block's start (page ids, keys, queries, reference, first scores) is 3.4 to 4 us, and a CU does little else before the
 // first one is done.  It was 5.5, and 2 before it for the schedule, now 1.2: with a prefix sum in LDS, masks and
-// addresses computed ahead of the redo loop into 200 spilled scalar registers, and the page table's round trip
-// before that of the keys.  A piece's end took 2.3 us stored row by row, 1.4 in fragment order.  A step of 8 layers, by all of
+// addresses computed ahead of the redo loop into 200 spilled scalar registers, the page table's round trip
+// before that of the keys, and queries loaded as fragments.  A piece's end took 2.3 us stored row by row, 1.4 in fragment order.  A step of 8 layers, by all of
 // it: one user's 5189 tokens x 4 heads 488 -> 465 us (446 since a CU's two shares are unequal), 16 x 4096 x 16 heads 10414 ->
 // 10238.
 //
@@ -141,6 +141,22 @@ __device__ __forceinline__ void wait_and_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// The wavefront's LDS reads are done before what follows.
+__device__ __forceinline__ void wait_for_lds() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));           // lgkmcnt(0)
+  asm volatile("" ::: "memory");
+}
+
+// f(0), f(1), ... f(N - 1), each with its argument as a constant
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  if constexpr (N > 0) {
+    unrolled<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
 // SPLIT: a persistent launch over one sequence of tile steps (see the head of the file) instead of
 // one workgroup per (user, head, query block).
 template <int D, int NST, int NQ, bool PW, bool SPLIT>
@@ -162,6 +178,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 
   extern __shared__ int s_ids[];       // physical page of every logical page the block reads
   __shared__ u32x4 stage[NST][FR * 64];  // K in KS KiB, then V (k_lane, v_lane and the reads below have the order)
+  // A wavefront's queries come by way of LDS, 1 KiB of rows a load: into the wavefront's own room of the stages that are not
+  // filled yet, and what does not fit there into q_room.
+  constexpr bool kBlockReference = SPLIT && !PW;
+  constexpr int kRooms = (kBlockReference ? 3 : 4) * (FQ / 2), kOwnRooms = kRooms < 8 ? 8 - kRooms : 0;
+  __shared__ u32x4 q_room[kOwnRooms > 0 ? 4 * kOwnRooms * 64 : 1];
   __shared__ int redo_flag[4];         // of every wavefront
 
   const int tid = threadIdx.x;
@@ -367,6 +388,35 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     v_2 = v_1;
     v_1 = at;
   };
+
+  // Row `row` of the wavefront's 32 NQ queries lies in room row / kRoomRows, its 16-byte pieces turned by the row, so that the
+  // 32 rows of a fragment are read without conflicts.
+  constexpr int kPieces = D / 8, kRoomRows = 64 / kPieces;
+  auto turn = [](int row) __attribute__((always_inline)) { return D == 128 ? row & 15 : (row >> 1) & 7; };
+  auto room = [&](int j) __attribute__((always_inline)) -> uint32_t {
+    constexpr int N = FQ / 2;
+    const int own = (int)lds_address(q_room) + (wave * kOwnRooms - kRooms) * 1024;
+    return j < N       ? k_lds + 2 * FR * 1024 + j * 1024
+           : j < 2 * N ? v_lds + 2 * FR * 1024 + (j - N) * 2048
+           : j < 3 * N ? v_lds + FR * 1024 + (j - 2 * N) * 2048
+           : j < kRooms ? v_lds + (j - 3 * N) * 2048
+                        : (uint32_t)(own + j * 1024);
+  };
+  {
+    // The queries, whose addresses need no page id, in whole rows; those past the user's last repeat it and go nowhere.
+    // Loaded as fragments, 32 bytes of 32 rows an instruction, they held up the tiles they came behind: the first block's
+    // scores began 5.3 us after the schedule, now 4.0 (6.8 and 5.0 with eight users), later blocks' after 3.4 instead of 4.4.
+    // And only what the first scores need is asked for before them: the third stage waits in the queries' room.
+    const char* from = reinterpret_cast<const char*>(q + ((int64_t)(tok0 + Q0) * H + h) * D);
+    int ln = lane;                                                 // hidden, or eight offsets a lane are kept, spilled, for the next segment
+    asm volatile("" : "+v"(ln));
+    unrolled<8>([&](auto j_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(j_c)::value;
+      const int row = j * kRoomRows + ln / kPieces, at = kWaveQ * wave + row;
+      const int there = at < n_u - Q0 ? at : n_u - Q0 - 1;
+      load_to_lds<1, 0>(from, (uint32_t)there * (uint32_t)(H * D * 2) + (uint32_t)((ln % kPieces) ^ turn(row)) * 16, room(j));
+    });
+  }
 
   bf16x8 qf[NQ][KS];
   f32x16 o[NQ][DB];
@@ -577,38 +627,37 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     // order of fp32 sums alone.  The tile's keys travel beside the piece's own, into the room of the
     // values that stage 0 does not hold yet; 8 layers of one user's 5189 tokens x 4 heads take 446 us with
     // it and 441 with a reference of each piece's own, six returning users beside two first-time ones 750 and 741.
-    constexpr bool kBlockReference = SPLIT && !PW;
     if (kBlockReference && attempt == 0) {
       load_to_lds<FQ / 2, 1024>(sub_block_at(zero, id[NST]), k_lane, k_lds + KS * 1024);
     }
     load(0, tile0, id[0], std::false_type{});
     load(1, tile0 + 1, id[1], std::false_type{});
-    load(2, tile0 + 2, id[2], std::true_type{});
     if (attempt == 0) {
-      // behind the first tiles' loads, so that their round trip is shared: the block's page table -> LDS, and its
-      // queries.  Ids the metadata does not back become page 0 (in bounds; such slots lie past the user's last
+      // behind the first tiles' loads, so that their round trip is shared: the block's page table -> LDS.  Ids the metadata does not back become page 0 (in bounds; such slots lie past the user's last
       // token and are masked).
       for (int i = tid; i < n_ids; i += 256) {
         int id = lp_beg + i < npg ? b.page_indices[pbeg + lp_beg + i] : 0;
         if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
         s_ids[i] = id;
       }
+    }
+    wait_and_barrier<0>();
+    if (attempt == 0) {
       // Q^T fragments: lane (r, hf) holds query q0 + 32 qb + r, dims 16 s + 8 hf .. + 7.
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) {
-        const int i = q0 + 32 * qb + r;
+        int row = 32 * qb + r;
+        asm volatile("" : "+v"(row));
+        const uint32_t at = room(row / kRoomRows) + (row % kRoomRows) * (D * 2);
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-          if (i < n_u) {
-            qf[qb][s] = *reinterpret_cast<const bf16x8*>(q + ((int64_t)(tok0 + i) * H + h) * D + 16 * s + 8 * hf);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qf[qb][s][e] = (__bf16)0.0f;
-          }
+          typedef const __attribute__((address_space(3))) bf16x8* lds_fragment;
+          qf[qb][s] = *(lds_fragment)(uintptr_t)(at + (uint32_t)(((2 * s + hf) ^ turn(row)) * 16));
         }
       }
+      wait_for_lds();
     }
-    wait_and_barrier<0>();
+    load(2, tile0 + 2, id[2], std::true_type{});                   // into the room that the queries have left
     f32x16 za[NQ], zb;
     if (kBlockReference && attempt == 0) {
 #pragma unroll
@@ -623,7 +672,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       za[qb] = scores(kf, qb, tile0 * kTile, true);
       if (!PW && !kBlockReference && attempt == 0) set_reference(za[qb], qb);
     }
-    wait_and_barrier<0>();                                         // stage 0 is read
+    wait_and_barrier<FQ>();                                        // stage 0 is read
     next_id = page_id(tile0 + 3);
     load(0, tile0 + 3, next_id, std::true_type{});
     next_id = page_id(tile0 + 4);
