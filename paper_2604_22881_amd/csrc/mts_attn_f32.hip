@@ -12,9 +12,13 @@
 // the pool's [dim][16 tokens] order of V makes the other operand one 16-byte load as well.
 //
 // Bound: latency for the few-thousand-key calls this type is used for (page id -> K/V -> scores,
-// then the combination); the next sub-block's K and V travel while one is computed.  Measured, one
-// layer of 16 queries x 272 keys x 4 heads of 32: 73 us with one wavefront per (query, head) and
-// a scalar load per element, 6.2 us here.  Many users of a few keys are the plain kernel's (f32_takes_plain).
+// then the combination), and then the two wavefronts of a SIMD, whose products and weights take 0.85 us a sub-block at
+// head_dim 32.  The next sub-block's K and V travel while one is computed, requested without a branch (behind a load that
+// may not have been made the compiler waits for all of them), and the page ids of 64 sub-blocks came with one load; head_dim
+// 64 is held to 128 registers, two workgroups a CU.  us a layer, with a branch, a page id a sub-block and the library's exponential /
+// now: 16 queries x 272 keys x 4 heads of 32 5.75 / 4.80 (73 with one wavefront per (query, head) and a scalar load per
+// element), of 64 8.1 / 6.9, of 128 13.0 / 11.2; 30 x 3030 x 8 of 64 42.5 / 37.1; 40 x 1440 x 8 of 128 43.8 / 37.1; 100 users' 10 x
+// 110 x 8 of 64 19.6 / 14.9.  Many users of a few keys are the plain kernel's (f32_takes_plain).
 #include <math.h>
 
 #include <type_traits>
@@ -33,14 +37,22 @@ constexpr int kSub = 16;         // tokens per step of a wavefront
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // max over the 4 lanes that hold the same query (lane, lane^16, lane^32, lane^48)
+template <typename F>
+__device__ __forceinline__ float over_quad_rows(float v, F f) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 __device__ __forceinline__ float quad_row_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16));
-  return fmaxf(v, __shfl_xor(v, 32));
+  return over_quad_rows(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ float quad_row_sum(float v) {
-  v += __shfl_xor(v, 16);
-  return v + __shfl_xor(v, 32);
+  return over_quad_rows(v, [](float a, float b) { return a + b; });
 }
+
+// Weights are at most 1: what is below the smallest normal number counts as 0.
+__device__ __forceinline__ float exp2_of(float x) { return __builtin_amdgcn_exp2f(x); }
 
 struct F32Args {                 // one argument, see TableWords
   PoolGeom g;
@@ -50,7 +62,7 @@ struct F32Args {                 // one argument, see TableWords
 };
 
 template <int D, bool PW>
-__global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, TableWords pages, CallWords2 call, F32Args args) {
+__global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 4) void attn_f32_kernel(TableWords runs, TableWords pages, CallWords2 call, F32Args args) {
   const int32_t *new_indptr = table(runs[0]), *prefix_lens = table(runs[1]), *page_indptr = table(pages[0]),
                 *page_indices = table(pages[1]);
   const int batch = call[0], total_new = call[1];
@@ -58,6 +70,10 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
   const float* __restrict__ q = args.q;
   float* __restrict__ out = args.out;
   const float scale = args.scale, inv_norm = args.inv_norm;
+  // Softmax: references are in units of the base-2 exponent, c = scale log2(e), and a weight is 2^(c z - m), with one
+  // rounding ahead of the exponential.  Against 64 bits, 24 random calls of 32 to 1900 keys: 4.47e-7 (geometric mean), with
+  // the scaled logit, its difference and the library's exponential 4.48e-7.
+  const float c = scale * 1.4426950408889634f;
   constexpr int NF = D / 16;       // 16-byte fragments per lane of a sub-block's K, V, of Q and of the output
   __shared__ f32x4 s_o[kWaves / 2][NF][64];
   __shared__ float s_m[kWaves / 2][kQ], s_l[kWaves / 2][kQ];
@@ -96,14 +112,21 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
     if (r < nq) qf[s] = *reinterpret_cast<const f32x4*>(q + ((int64_t)(tok0 + q0 + r) * H + h) * D + 16 * s + 4 * gq);
   }
 
+  // The wavefront's i-th sub-block is number wave + 8 i; a lane holds the page of one, 64 of them at a time.
+  const int n_mine = n_sb > wave ? (n_sb - wave - 1) / kWaves + 1 : 0;
+  int ids = -1;
+  auto load_ids = [&](int first) __attribute__((always_inline)) {
+    const int sb = wave + kWaves * (first + lane), lp = sb >> g.sub_shift;
+    ids = sb < n_sb && lp < npg ? page_indices[pbeg + lp] : -1;
+  };
   f32x4 kf[2][NF], vf[2][NF];
   bool held[2];                                         // the sub-block's page exists
-  auto load = [&](auto slot_c, int sb) __attribute__((always_inline)) {
+  auto load = [&](auto slot_c, int i) __attribute__((always_inline)) {
     constexpr int p = decltype(slot_c)::value;
-    const int lp = sb >> g.sub_shift;
-    int page = sb < n_sb && lp < npg ? page_indices[pbeg + lp] : -1;
+    const int sb = wave + kWaves * i;
+    int page = __builtin_amdgcn_readlane(ids, i & 63);
     held[p] = (unsigned)page < (unsigned)g.num_pages;
-    if (!held[p]) return;                               // wavefront-uniform
+    page = held[p] ? page : 0;                          // no branch: behind a load that may not have been made all are waited for
     const char* kb = head_base + (int64_t)page * g.page_bytes + (int64_t)(sb & sub_mask) * kSub * D * 4;
     // K rows are the tokens in order: token r lies at half (r / 4) % 2, slot (r / 8) * 4 + r % 4
     const char* kl = kb + ((((r >> 2) & 1) * (D / 4) + gq) * 8 + ((r >> 3) << 2) + (r & 3)) * 16;
@@ -118,9 +141,10 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
 #pragma unroll
   for (int s = 0; s < NF; ++s) o[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;                         // l: this lane's tokens only
-  auto compute = [&](auto slot_c, int sb) __attribute__((always_inline)) {
+  auto compute = [&](auto slot_c, int i) __attribute__((always_inline)) {
     constexpr int p = decltype(slot_c)::value;
-    if (sb >= n_sb || !held[p]) return;
+    const int sb = wave + kWaves * i;
+    if (!held[p]) return;
     f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < NF; ++s)
@@ -137,12 +161,12 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) z[e] = e < visible ? z[e] * scale : -INFINITY;
-      const float m_new = fmaxf(m, quad_row_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]))));
+      for (int e = 0; e < 4; ++e) z[e] = e < visible ? z[e] : -INFINITY;
+      const float m_new = fmaxf(m, quad_row_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]))) * c);
       const float m_ref = m_new == -INFINITY ? 0.f : m_new;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = expf(z[e] - m_ref);
-      const float alpha = expf(m - m_ref);
+      for (int e = 0; e < 4; ++e) w[e] = exp2_of(fmaf(z[e], c, -m_ref));
+      const float alpha = exp2_of(m - m_ref);
       l = l * alpha + ((w[0] + w[1]) + (w[2] + w[3]));
       m = m_new;
 #pragma unroll
@@ -186,12 +210,19 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
 
   constexpr std::integral_constant<int, 0> slot0{};
   constexpr std::integral_constant<int, 1> slot1{};
-  load(slot0, wave);
-  for (int sb = wave; sb < n_sb; sb += 2 * kWaves) {
-    load(slot1, sb + kWaves);
-    compute(slot0, sb);
-    load(slot0, sb + 2 * kWaves);
-    compute(slot1, sb + kWaves);
+  if (n_mine > 0) {
+    load_ids(0);
+    load(slot0, 0);
+    int i = 0;
+    for (; i + 1 < n_mine; ++i) {
+      if (((i + 1) & 63) == 0) load_ids(i + 1);
+      load(slot1, i + 1);
+      compute(slot0, i);
+#pragma unroll
+      for (int s = 0; s < NF; ++s) { kf[0][s] = kf[1][s]; vf[0][s] = vf[1][s]; }
+      held[0] = held[1];
+    }
+    compute(slot0, i);
   }
 
   // Combination, in wavefront order: wavefronts 4-7 hand theirs to 0-3, whose sums every thread then
@@ -208,8 +239,8 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
     float wa = 1.f, wb = 1.f;
     if (!PW) {
       const float mb = s_m[wave][r], mn = fmaxf(m, mb), m_ref = mn == -INFINITY ? 0.f : mn;
-      wa = expf(m - m_ref);
-      wb = expf(mb - m_ref);
+      wa = exp2_of(m - m_ref);
+      wb = exp2_of(mb - m_ref);
       l = l * wa + s_l[wave][r] * wb;
       m = mn;
     }
@@ -229,7 +260,7 @@ __global__ __launch_bounds__(64 * kWaves) void attn_f32_kernel(TableWords runs, 
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < kWaves / 2; ++w) {
-      wgt[w] = PW ? 1.f : expf(s_m[w][qi] - mx);
+      wgt[w] = PW ? 1.f : exp2_of(s_m[w][qi] - mx);
       if (!PW) den = fmaf(wgt[w], s_l[w][qi], den);
       sum += s_o[w][s][ln] * wgt[w];
     }

@@ -33,6 +33,21 @@ def test_f32_matches_oracle(D, S, shape):
     check_attention(w, step.attention_pointwise(data, 0, inv), oracle.attn_pointwise(*args, inv))
 
 
+@pytest.mark.parametrize("D,S", [(32, 16), (64, 64), (128, 32)])
+def test_f32_histories_of_more_pages_than_lanes(D, S):
+    """A wavefront's lanes hold the pages of its next 64 sub-blocks: histories that end around 8 x 64 of them and
+    past twice as many."""
+    G = _harness()
+    w = W.custom_workload("f32_long", 70 + D, "f32", 1, 1, D, S, [8175, 8192, 8300, 16500], [16, 1, 20, 2], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    args = (store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr)
+    check_attention(w, step.attention(data, 0), oracle.attn_incremental(*args))
+
+
 @pytest.mark.parametrize("pointwise", [False, True])
 def test_f32_hidden_infinity_stays_hidden(pointwise):
     """An infinite or NaN value row of a new token reaches its own query and later ones only: the
