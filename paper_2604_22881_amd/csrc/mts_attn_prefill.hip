@@ -205,15 +205,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     const int blocks = (n + kBlockQ - 1) / kBlockQ;
     return blocks > 0 ? steps_before(prefix, blocks - 1) + last_tiles(prefix, n) + block_cost : 0;
   };
-  // Position of user k's steps in the sequence, from the lanes of a wavefront: inclusive sums over the lanes.
-  auto scan = [&](int v) __attribute__((always_inline)) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(v, o);
-      if (lane >= o) v += up;
-    }
-    return v;
-  };
+  // Position of user k's steps in the sequence, from the lanes of a wavefront: inclusive sums over the lanes (scan_lanes).
   // how many of the items 0, 1, ... `count` - 1 start at or before x, less one; `start` rises
   auto last_at_or_before = [&](int count, int x, auto start) __attribute__((always_inline)) {
     int found = 0;
@@ -253,7 +245,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
         group_of = grp;
         l_n = 0;
         if (lane < users_per_lane) load_user(grp * users_per_lane + lane);
-        l_incl = scan(user_steps(l_P, l_n) * H);
+        l_incl = scan_lanes(user_steps(l_P, l_n) * H);
         l_first = grp > 0 ? __builtin_amdgcn_readlane(g_incl, grp - 1) : 0;
       }
       u = __builtin_popcountll(__builtin_amdgcn_ballot_w64(l_incl <= x - l_first));
@@ -283,7 +275,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
         steps += user_steps(l_P, l_n) * H;
       }
     }
-    g_incl = scan(steps);
+    g_incl = scan_lanes(steps);
     const int total = __builtin_amdgcn_readlane(g_incl, 63);
     // blockIdx -> XCD is round-robin, and inside an XCD the first half of a full launch's workgroups come first to
     // their CUs, the second half to the same ones.  Every XCD gets one contiguous stretch of the sequence, so

@@ -43,6 +43,19 @@ __device__ __forceinline__ const int32_t* table(uint64_t address) {
   return (const int32_t*)(const __attribute__((address_space(1))) int32_t*)address;
 }
 
+// Inclusive sums over the 64 lanes of a wavefront, all of them active: six additions that read other lanes on the way (six
+// shuffles through LDS took 0.25 us more of every launch that schedules itself: 8 layers of one user's 32 new tokens behind
+// 6375 x 4 heads of 128 133.6 -> 131.7 us).
+__device__ __forceinline__ int scan_lanes(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: inside 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
 struct SegDev {              // segment lists of unpack / pack
   int32_t        num_segs;
   const int32_t* seg_user;
