@@ -40,16 +40,17 @@ constexpr RedoLimits redo_limits(bool cut) {
 // PG = 1: one descriptor per blockIdx.x, all its pieces folded by one thread per 4 dims.
 // PG > 1, for calls of a few long pairs cut into many pieces (one user's 6 K history, 4 pairs of 50
 // pieces: 12.6 us folded serially, the whole call 27 us; 18.5 us with 8 groups): the pieces are dealt to PG groups of
-// threads in contiguous runs and the groups' sums folded through LDS in group order; a block looks
-// at kDescs neighbouring descriptors, of which such a call fills few.
+// threads in contiguous runs and the groups' sums folded through LDS in group order.
+// A block looks at DESCS neighbouring descriptors: one where there is a descriptor per pair (launches of pieces) or
+// most of them are filled, else four, of which a call of few long pairs fills few.
 // FRAGS: a piece lies in the fragment order of the prefill kernel's accumulators (32 queries x 32 dims: 4 x 64 lanes of 4
 // dims), else row by row.
-template <int D, bool PW, int PG, bool FRAGS>
+template <int D, bool PW, int PG, bool FRAGS, int DESCS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(uint16_t* __restrict__ out, float c, float inv_norm, int q_tile,
                                                          int H, int n_desc, const MergeDesc* __restrict__ ws_desc,
                                                          const float* __restrict__ ws_o,
                                                          const float* __restrict__ ws_ml) {
-  constexpr int D4 = D / 4, kCols = 256 / PG, kDescs = PG > 1 ? 4 : 1;
+  constexpr int D4 = D / 4, kCols = 256 / PG, kDescs = DESCS;
   __shared__ merge_f32x4 s_num[PG > 1 ? 256 : 1];
   __shared__ float s_m[PG > 1 ? 256 : 1], s_den[PG > 1 ? 256 : 1];
   const int grp = threadIdx.x / kCols, e = blockIdx.y * kCols + threadIdx.x % kCols;
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(uint16_t* __restrict__ 
   const int d4 = FRAGS ? (e >> 8) % (D / 32) * 8 + (e >> 6 & 3) * 2 + (e >> 5 & 1) : e % D4;
   for (int k = 0; k < kDescs; ++k) {
     const int wd = blockIdx.x * kDescs + k;
-    if (PG > 1 && wd >= n_desc) return;
+    if (DESCS > 1 && wd >= n_desc) return;
     const MergeDesc d = ws_desc[wd];
     if (!d.valid || (int)blockIdx.y * kCols >= (FRAGS ? (d.nq + 31) / 32 * 32 : d.nq) * D4) continue;      // workgroup-uniform
     const bool mine = qi < d.nq;
@@ -208,21 +209,29 @@ __global__ __launch_bounds__(256) void attn_merge_frags_kernel(uint16_t* __restr
   }
 }
 
-// `shares` descriptors of at most `pairs` cut pairs.  Eight or more shares per pair: the pieces of a
+// `shares` descriptors of at most `pairs` cut pairs, or (`per_pair`) one of each.  Eight or more shares per pair: the pieces of a
 // pair are many and its pairs few, so they are folded by groups.
 template <int D, bool PW, bool FRAGS = false>
 hipError_t launch_merge(uint16_t* out, float c, float inv_norm, int q_tile, int H, int shares, int64_t pairs,
-                        const MergeDesc* ws_desc, const float* ws_o, const float* ws_ml, hipStream_t stream) {
+                        const MergeDesc* ws_desc, const float* ws_o, const float* ws_ml, hipStream_t stream,
+                        bool per_pair = false) {
   constexpr int kGroups = 8;
   const int cols = q_tile * (D / 4);
-  if (shares >= 8 * pairs) {
-    hipLaunchKernelGGL((attn_merge_kernel<D, PW, kGroups, FRAGS>), dim3((shares + 3) / 4, (cols + 256 / kGroups - 1) / (256 / kGroups)),
+  if (per_pair && !FRAGS) {
+    if (shares >= 8 * pairs)
+      hipLaunchKernelGGL((attn_merge_kernel<D, PW, kGroups, false, 1>), dim3((unsigned)pairs, (cols + 256 / kGroups - 1) / (256 / kGroups)),
+                         dim3(256), 0, stream, out, c, inv_norm, q_tile, H, (int)pairs, ws_desc, ws_o, ws_ml);
+    else
+      hipLaunchKernelGGL((attn_merge_kernel<D, PW, 1, false, 1>), dim3((unsigned)pairs, (cols + 255) / 256), dim3(256), 0, stream, out, c,
+                         inv_norm, q_tile, H, (int)pairs, ws_desc, ws_o, ws_ml);
+  } else if (shares >= 8 * pairs) {
+    hipLaunchKernelGGL((attn_merge_kernel<D, PW, kGroups, FRAGS, 4>), dim3((shares + 3) / 4, (cols + 256 / kGroups - 1) / (256 / kGroups)),
                        dim3(256), 0, stream, out, c, inv_norm, q_tile, H, shares, ws_desc, ws_o, ws_ml);
   } else if constexpr (FRAGS) {
     hipLaunchKernelGGL((attn_merge_frags_kernel<D, PW>), dim3(shares, q_tile / 32 * (D / kFragDims)), dim3(256), 0, stream, out, c, inv_norm,
                        q_tile, H, ws_desc, ws_o, ws_ml);
   } else {
-    hipLaunchKernelGGL((attn_merge_kernel<D, PW, 1, FRAGS>), dim3(shares, (cols + 255) / 256), dim3(256), 0, stream, out, c,
+    hipLaunchKernelGGL((attn_merge_kernel<D, PW, 1, FRAGS, 1>), dim3(shares, (cols + 255) / 256), dim3(256), 0, stream, out, c,
                        inv_norm, q_tile, H, shares, ws_desc, ws_o, ws_ml);
   }
   return hipGetLastError();
