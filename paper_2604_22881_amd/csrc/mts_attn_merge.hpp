@@ -217,22 +217,18 @@ hipError_t launch_merge(uint16_t* out, float c, float inv_norm, int q_tile, int 
                         bool per_pair = false) {
   constexpr int kGroups = 8;
   const int cols = q_tile * (D / 4);
-  if (per_pair && !FRAGS) {
-    if (shares >= 8 * pairs)
-      hipLaunchKernelGGL((attn_merge_kernel<D, PW, kGroups, false, 1>), dim3((unsigned)pairs, (cols + 256 / kGroups - 1) / (256 / kGroups)),
-                         dim3(256), 0, stream, out, c, inv_norm, q_tile, H, (int)pairs, ws_desc, ws_o, ws_ml);
-    else
-      hipLaunchKernelGGL((attn_merge_kernel<D, PW, 1, false, 1>), dim3((unsigned)pairs, (cols + 255) / 256), dim3(256), 0, stream, out, c,
-                         inv_norm, q_tile, H, (int)pairs, ws_desc, ws_o, ws_ml);
-  } else if (shares >= 8 * pairs) {
-    hipLaunchKernelGGL((attn_merge_kernel<D, PW, kGroups, FRAGS, 4>), dim3((shares + 3) / 4, (cols + 256 / kGroups - 1) / (256 / kGroups)),
-                       dim3(256), 0, stream, out, c, inv_norm, q_tile, H, shares, ws_desc, ws_o, ws_ml);
+  const int descs = per_pair ? (int)pairs : shares;
+  if (shares >= 8 * pairs) {
+    constexpr int kGroupCols = 256 / kGroups;
+    auto kern = per_pair ? attn_merge_kernel<D, PW, kGroups, FRAGS, 1> : attn_merge_kernel<D, PW, kGroups, FRAGS, 4>;
+    hipLaunchKernelGGL(kern, dim3(per_pair ? descs : (descs + 3) / 4, (cols + kGroupCols - 1) / kGroupCols), dim3(256), 0, stream, out, c,
+                       inv_norm, q_tile, H, descs, ws_desc, ws_o, ws_ml);
   } else if constexpr (FRAGS) {
-    hipLaunchKernelGGL((attn_merge_frags_kernel<D, PW>), dim3(shares, q_tile / 32 * (D / kFragDims)), dim3(256), 0, stream, out, c, inv_norm,
+    hipLaunchKernelGGL((attn_merge_frags_kernel<D, PW>), dim3(descs, q_tile / 32 * (D / kFragDims)), dim3(256), 0, stream, out, c, inv_norm,
                        q_tile, H, ws_desc, ws_o, ws_ml);
   } else {
-    hipLaunchKernelGGL((attn_merge_kernel<D, PW, 1, FRAGS, 1>), dim3(shares, (cols + 255) / 256), dim3(256), 0, stream, out, c,
-                       inv_norm, q_tile, H, shares, ws_desc, ws_o, ws_ml);
+    hipLaunchKernelGGL((attn_merge_kernel<D, PW, 1, FRAGS, 1>), dim3(descs, (cols + 255) / 256), dim3(256), 0, stream, out, c,
+                       inv_norm, q_tile, H, descs, ws_desc, ws_o, ws_ml);
   }
   return hipGetLastError();
 }

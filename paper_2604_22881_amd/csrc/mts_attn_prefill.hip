@@ -220,6 +220,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   int l_first = 0;                                              // ... the group's first position
   int l_incl = 0, group_of = -1;                                // ... inclusive sums inside the group; which group
   int g_incl = 0;                                               // inclusive sums over groups: a lane holds one
+  // Descriptors per block (n_pairs > 0 of them, as many as the call's bounds allow): sums of the users' blocks as above, and
+  // the number of the user's first one
+  const bool per_block = SPLIT && n_pairs > 0;
+  int gb_incl = 0, lb_incl = 0, first_block = 0;
+  auto user_blocks = [&](int n) { return n > 0 ? (n + kBlockQ - 1) / kBlockQ * H : 0; };
   const int users_per_lane = SPLIT ? (b.batch + 63) / 64 : 1;   // of a group
   auto load_user = [&](int k) __attribute__((always_inline)) {
     l_n = 0;
@@ -239,6 +244,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     if (users_per_lane == 1) {
       u = grp;
       user_pos = u > 0 ? __builtin_amdgcn_readlane(g_incl, u - 1) : 0;
+      if (per_block) first_block = u > 0 ? __builtin_amdgcn_readlane(gb_incl, u - 1) : 0;
     } else {
       // the users of that lane, one a lane
       if (grp != group_of) {
@@ -246,10 +252,14 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
         l_n = 0;
         if (lane < users_per_lane) load_user(grp * users_per_lane + lane);
         l_incl = scan_lanes(user_steps(l_P, l_n) * H);
+        if (per_block) lb_incl = scan_lanes(user_blocks(l_n));
         l_first = grp > 0 ? __builtin_amdgcn_readlane(g_incl, grp - 1) : 0;
       }
       u = __builtin_popcountll(__builtin_amdgcn_ballot_w64(l_incl <= x - l_first));
       user_pos = l_first + (u > 0 ? __builtin_amdgcn_readlane(l_incl, u - 1) : 0);
+      if (per_block)
+        first_block = (grp > 0 ? __builtin_amdgcn_readlane(gb_incl, grp - 1) : 0) +
+                      (u > 0 ? __builtin_amdgcn_readlane(lb_incl, u - 1) : 0);
     }
     tok0 = __builtin_amdgcn_readlane(l_tok, u);
     n_u = __builtin_amdgcn_readlane(l_n, u);
@@ -265,17 +275,20 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   if constexpr (SPLIT) {
     // Every wavefront works the schedule out by itself, without LDS or barriers: lane i sums the steps of
     // users [i, i + 1) * users_per_lane; up to 64 users that is one each, and nothing is read again.
-    int steps = 0;
+    int steps = 0, blocks = 0;
     if (users_per_lane == 1) {
       load_user(lane);
       steps = user_steps(l_P, l_n) * H;
+      blocks = user_blocks(l_n);
     } else {
       for (int j = 0; j < users_per_lane; ++j) {
         load_user(lane * users_per_lane + j);
         steps += user_steps(l_P, l_n) * H;
+        blocks += user_blocks(l_n);
       }
     }
     g_incl = scan_lanes(steps);
+    if (per_block) gb_incl = scan_lanes(blocks);
     const int total = __builtin_amdgcn_readlane(g_incl, 63);
     // blockIdx -> XCD is round-robin, and inside an XCD the first half of a full launch's workgroups come first to
     // their CUs, the second half to the same ones.  Every XCD gets one contiguous stretch of the sequence, so
@@ -291,7 +304,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     lo = first_step < total ? (int)first_step : total;
     hi = last_step < total ? (int)last_step : total;
     pos = lo;
-    if (tid == 0) ws_desc[wid].valid = 0;
+    if (!per_block) {
+      if (tid == 0) ws_desc[wid].valid = 0;
+    } else {
+      const int k = __builtin_amdgcn_readlane(gb_incl, 63) + (int)blockIdx.x;     // numbers that no block has
+      if ((unsigned)k < (unsigned)n_pairs && tid == 0) ws_desc[k].valid = 0;
+    }
   } else {
     // blockIdx -> XCD is round-robin: all blocks of one (user, head) share blockIdx % 8.  An XCD
     // takes `pair_group` pairs at a time, the longest causal rows of all of them first.
@@ -341,8 +359,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // page table of the segment, copied to LDS in the prologue
   const int lp_beg = SPLIT ? (t_beg * 2) >> g.sub_shift : 0;
   const int n_ids = ((t_end * 2 - 1) >> g.sub_shift) + 1 - lp_beg;
+  const int block = SPLIT ? first_block + h * ((n_u + kBlockQ - 1) / kBlockQ) + qblk : 0;
   if (n_ids > id_cap) {                // lengths beyond the bound the call stated: no output, no overrun
     if (!SPLIT) return;
+    if (per_block && t_beg == 0 && (unsigned)block < (unsigned)n_pairs && tid == 0) ws_desc[block].valid = 0;
     pos = seg_end;
     continue;
   }
@@ -738,6 +758,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     return ob;
   };
   if (!SPLIT || (t_beg == 0 && t_end == tiles_blk)) {
+    if (per_block && (unsigned)block < (unsigned)n_pairs && tid == 0) ws_desc[block].valid = 0;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
       const int qi = 32 * qb + r;
@@ -791,7 +812,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       d.nq = blk_end - Q0;
       d.first_slot = slot;
       d.pad[0] = d.pad[1] = 0;
-      ws_desc[wid] = d;
+      if (!per_block) ws_desc[wid] = d;
+      else if ((unsigned)block < (unsigned)n_pairs) ws_desc[block] = d;
     }
   }
   if constexpr (!SPLIT) break;
@@ -843,13 +865,17 @@ hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan
     MergeDesc* ws_desc = reinterpret_cast<MergeDesc*>(ws);
     float* ws_o = reinterpret_cast<float*>(ws + plan.ws_desc_bytes);
     float* ws_ml = ws_o + (int64_t)plan.prefill_wgs * 2 * kBlockQ * D;
+    // A descriptor per block where that is not more than one per share: the merge then launches no workgroups that find none.
+    const int64_t blocks = (int64_t)g.H * (b.total_new / kBlockQ + b.batch);   // at most
+    // (in eights, an XCD's in a row: the merge reads pieces on the XCD that wrote most of them)
+    const int descs = blocks <= plan.prefill_wgs / 8 * 8 ? (int)((blocks + 7) / 8 * 8) : 0;
     hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, true>), dim3((unsigned)plan.prefill_wgs), dim3(256),
-                       (size_t)id_bytes, stream, g, b, q, out, c, inv_norm, 1, 0, 1,
+                       (size_t)id_bytes, stream, g, b, q, out, c, inv_norm, 1, descs, 1,
                        (int)(id_bytes / 4), plan.pair_cost, plan.min_tiles, ws_desc, ws_o, ws_ml);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return merge_detail::launch_merge<D, PW, true>(out, c, inv_norm, kBlockQ, g.H, plan.prefill_wgs,
-                                             (int64_t)g.H * (b.total_new / kBlockQ + b.batch), ws_desc, ws_o, ws_ml, stream);
+                                                   descs > 0 ? descs : blocks, ws_desc, ws_o, ws_ml, stream, descs > 0);
   }
   const hipError_t attr = allow_lds<D, NST, NQ, PW, false>();
   if (attr != hipSuccess) return attr;
