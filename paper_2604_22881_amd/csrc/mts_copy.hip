@@ -39,6 +39,11 @@ __device__ __forceinline__ void store_granule(void* p, u32x4 v) {
 
 enum { MODE_UNPACK = 0, MODE_APPEND = 1, MODE_PACK = 2 };
 
+// How a launch's units, (sub-block of a run, head) and layer, are numbered.  kRuns: blockIdx.y is the run.  kPlanes: the same,
+// K and V of a masked unit by a wavefront of its own (append_by_planes).  kFlat: an append's units follow one another and each
+// wavefront finds its user (append_flat).
+enum class Units { kRuns, kPlanes, kFlat };
+
 constexpr int kBulkWaves = 4;      // wavefronts (= units) per bulk workgroup
 
 // The two sides of a move, strides from one layer to the next.
@@ -62,9 +67,8 @@ struct MoveSides {
 // is ever written.
 // `runs`: seg_user and seg_pos of a segment list (`run_tok`: seg_tok_indptr) or an append's new_indptr and prefix_lens;
 // `pages`: page_indptr and page_indices.
-// PLANES: a launch of masked units, K and V of each by a wavefront of its own (append_by_planes).
 // PAST: which rows travel past the caches' retention (mts_copy_rules.hpp; an append's own rule is at KEEP).
-template <typename T, int MODE, int DCH, RowsPast PAST, bool PLANES>
+template <typename T, int MODE, int DCH, RowsPast PAST, Units UNITS>
 __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWords pages, CallWords call, const int64_t* run_tok,
                                                       MoveSides<T> sides) {
   const int32_t *run_user = table(runs[0]), *run_pos = table(runs[1]), *page_indptr = table(pages[0]),
@@ -75,6 +79,7 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
   constexpr int PITCH = D + G;       // LDS row pitch in elements (one granule of padding)
   constexpr int NIT = 16 * DCH / 64; // 64-granule rounds per 16-token sub-block
   constexpr int dch = DCH;
+  constexpr bool PLANES = UNITS == Units::kPlanes, FLAT = UNITS == Units::kFlat;
   const int s = blockIdx.y;
   // several layers in one launch: blockIdx.z picks the layer on both sides
   PoolGeom& g = sides.g;
@@ -83,6 +88,26 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
   const T* src_a = sides.src_a + (int64_t)blockIdx.z * sides.contig_layer_stride;
   const T* src_b = MODE == MODE_APPEND ? sides.src_b + (int64_t)blockIdx.z * sides.contig_layer_stride : nullptr;
   T* dst_contig = MODE == MODE_PACK ? sides.dst_contig + (int64_t)blockIdx.z * sides.contig_layer_stride : nullptr;
+
+  // Which sub-block this wavefront moves
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  // unit = 4 * block + wave of a part, as (sub-block, head) = (unit / H, unit % H) in 32 bits
+  const bool in_bulk = (int)blockIdx.x < bulk_blocks;
+  const unsigned blk = in_bulk ? blockIdx.x : blockIdx.x - (unsigned)bulk_blocks;
+  int64_t k;
+  int h, plane = 0;
+  if (const unsigned inverse = (unsigned)call[3]) {              // two divisions were 0.1 to 0.3 us of a short launch
+    unsigned unit = blk * kBulkWaves + (unsigned)wave;
+    if (PLANES) { plane = unit & 1; unit >>= 1; }
+    const unsigned quotient = __umulhi(2 * unit, inverse);
+    k = quotient;
+    h = (int)(unit - quotient * (unsigned)H);
+  } else {
+    const unsigned blk_q = blk / (unsigned)H, rest = (blk - blk_q * (unsigned)H) * kBulkWaves + (unsigned)wave;
+    const unsigned rest_q = rest / (unsigned)H;
+    k = (int64_t)blk_q * kBulkWaves + rest_q;
+    h = (int)(rest - rest_q * (unsigned)H);
+  }
 
   // Resolve the run: user, first pool token, length, and the contiguous K / V planes.  A step's append
   // moves little and costs its chain of memory round trips, so whatever can travel together does: the
@@ -93,7 +118,38 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
   int u, pos, pbeg, pend;
   int64_t n, t0;
   bool user_ok = true;                                          // an append's grid has one row per user
-  if (MODE == MODE_APPEND) {
+  if constexpr (FLAT) {
+    // User u's sub-blocks start at (its first row) / 16 + 2 u: its rows touch at most as many as there are before the next
+    // user's, so no sum over the users is needed.  The lanes look at 64 users at a time, or at every so many of them.
+    int first = 0, count = batch;
+    const int rows0 = scalar_load(run_user);
+    while (count > 64) {
+      const int every = (count + 63) / 64, k64 = first + lane * every;
+      const bool at_or_before = lane * every < count && (run_user[k64] - rows0) / 16 + 2 * k64 <= k;
+      const uint64_t some = __builtin_amdgcn_ballot_w64(at_or_before);
+      const int step = (some ? 63 - __builtin_clzll(some) : 0) * every;
+      first += step;
+      count = count - step < every ? count - step : every;
+    }
+    int l_r0 = 0, l_r1 = 0, l_pos = 0, l_pbeg = 0, l_pend = 0;
+    if (lane < count) {
+      l_r0 = run_user[first + lane];
+      l_r1 = run_user[first + lane + 1];
+      l_pos = run_pos[first + lane];
+      l_pbeg = page_indptr[first + lane];
+      l_pend = page_indptr[first + lane + 1];
+    }
+    const uint64_t some = __builtin_amdgcn_ballot_w64(lane < count && (l_r0 - rows0) / 16 + 2 * (first + lane) <= k);
+    const int at = some ? 63 - __builtin_clzll(some) : 0;
+    u = first + at;
+    const int r0 = __builtin_amdgcn_readlane(l_r0, at);
+    t0 = r0;
+    n = (int64_t)__builtin_amdgcn_readlane(l_r1, at) - t0;
+    pos = __builtin_amdgcn_readlane(l_pos, at);
+    pbeg = __builtin_amdgcn_readlane(l_pbeg, at);
+    pend = __builtin_amdgcn_readlane(l_pend, at);
+    k -= (r0 - rows0) / 16 + 2 * u;                             // of this user's
+  } else if (MODE == MODE_APPEND) {
     u = s;
     int r0 = scalar_load(run_user + u), r1 = scalar_load(run_user + u + 1);
     pos = scalar_load(run_pos + u);
@@ -134,34 +190,20 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
   }
   const bool run_ok = user_ok && n > 0 && pos >= 0;
   const int64_t npos = run_ok ? n : 1, ppos = run_ok ? pos : 0;
+  const int64_t first_sb = ppos >> 4, last_sb = (ppos + npos - 1) >> 4;
   // 16-token sub-blocks the run covers completely: [full_lo, full_hi) in units of sub-blocks
   const int64_t full_lo = (ppos + 15) >> 4;
   int64_t full_hi = (ppos + npos) >> 4;
-  if (full_hi < full_lo || bulk_blocks == 0) full_hi = full_lo;   // a launch of short runs: every sub-block takes the masked form
+  if (full_hi < full_lo || (!FLAT && bulk_blocks == 0)) full_hi = full_lo;   // a launch of short runs: every sub-block takes the masked form
 
-  // Which sub-block this wavefront moves, and which of its 16 tokens belong to the run.
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int64_t first_sb = ppos >> 4, last_sb = (ppos + npos - 1) >> 4;
-  // unit = 4 * block + wave of a part, as (sub-block, head) = (unit / H, unit % H) in 32 bits
-  const bool in_bulk = (int)blockIdx.x < bulk_blocks;
-  const unsigned blk = in_bulk ? blockIdx.x : blockIdx.x - (unsigned)bulk_blocks;
-  int64_t k;
-  int h, plane = 0;
-  if (const unsigned inverse = (unsigned)call[3]) {              // two divisions were 0.1 to 0.3 us of a short launch
-    unsigned unit = blk * kBulkWaves + (unsigned)wave;
-    if (PLANES) { plane = unit & 1; unit >>= 1; }
-    const unsigned quotient = __umulhi(2 * unit, inverse);
-    k = quotient;
-    h = (int)(unit - quotient * (unsigned)H);
-  } else {
-    const unsigned blk_q = blk / (unsigned)H, rest = (blk - blk_q * (unsigned)H) * kBulkWaves + (unsigned)wave;
-    const unsigned rest_q = rest / (unsigned)H;
-    k = (int64_t)blk_q * kBulkWaves + rest_q;
-    h = (int)(rest - rest_q * (unsigned)H);
-  }
+  // ... and which of its 16 tokens belong to the run
   int64_t sb;
-  const bool masked = !in_bulk;
-  if (in_bulk) {
+  bool masked = !in_bulk;
+  if constexpr (FLAT) {
+    sb = first_sb + k;
+    if (!run_ok || k < 0 || sb > last_sb) return;
+    masked = sb < full_lo || sb >= full_hi;
+  } else if (in_bulk) {
     // whole sub-blocks: one wavefront per (sub-block, head)
     sb = full_lo + k;
     if (!run_ok || sb >= full_hi) return;                       // wavefront-uniform; no block barrier below
@@ -377,16 +419,19 @@ __global__ __launch_bounds__(256) void kv_move_kernel(TableWords runs, TableWord
 template <typename T, int MODE, int DCH>
 void launch_typed(const PoolGeom& g, const SegDev& segs, const BatchDev& b, dim3 grid, int bulk_blocks,
                   const void* a, const void* bsrc, void* dst, int64_t pool_layer_stride,
-                  int64_t contig_layer_stride_bytes, unsigned inverse, bool planes, hipStream_t stream) {
+                  int64_t contig_layer_stride_bytes, unsigned inverse, Units units, hipStream_t stream) {
   constexpr RowsPast kBoth = RowsPast::kReadAndWritten, kRead = RowsPast::kRead, kNone = RowsPast::kNone;
-  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16) ? kBoth : kNone, false>;
+  auto kern = kv_move_kernel<T, MODE, DCH, MODE != MODE_PACK || gather_past_caches(DCH * 16) ? kBoth : kNone, Units::kRuns>;
   if constexpr (MODE == MODE_UNPACK) {
     const RowsPast past = scatter_past_caches((int64_t)segs.num_segs * segs.max_seg_tokens, (int64_t)b.total_pages * g.S,
                                               2ll * g.H * g.D * g.es, grid.z);
-    if (past != kBoth) kern = past == kRead ? kv_move_kernel<T, MODE, DCH, kRead, false> : kv_move_kernel<T, MODE, DCH, kNone, false>;
+    if (past != kBoth) kern = past == kRead ? kv_move_kernel<T, MODE, DCH, kRead, Units::kRuns> : kv_move_kernel<T, MODE, DCH, kNone, Units::kRuns>;
   }
   constexpr bool kAppend = MODE == MODE_APPEND;
-  if constexpr (kAppend) if (planes) kern = kv_move_kernel<T, MODE, DCH, kBoth, true>;
+  if constexpr (kAppend) {
+    if (units == Units::kPlanes) kern = kv_move_kernel<T, MODE, DCH, kBoth, Units::kPlanes>;
+    if (units == Units::kFlat) kern = kv_move_kernel<T, MODE, DCH, kBoth, Units::kFlat>;
+  }
   hipLaunchKernelGGL(kern, grid, dim3(256, 1, 1), 0, stream,
                      kAppend ? run_tables(b) : table_words(segs.seg_user, segs.seg_pos), page_tables(b),
                      CallWords{b.batch, g.H, bulk_blocks, (int)inverse}, segs.seg_tok_indptr,
@@ -410,17 +455,27 @@ hipError_t launch_move(const PoolGeom& g, const SegDev& segs, const BatchDev& b,
   const int64_t bulk_units = bulk ? (max_run_tokens / 16) * (int64_t)g.H : 0;
   const int64_t bulk_blocks = (bulk_units + kBulkWaves - 1) / kBulkWaves;
   const int64_t end_units = (bulk ? 2 : (max_run_tokens + 15) / 16 + 1) * (int64_t)g.H;
+  int64_t blocks = bulk_blocks + (end_units + kBulkWaves - 1) / kBulkWaves;
+  const int64_t flat_units = MODE == MODE_APPEND ? ((int64_t)b.total_new / 16 + 2ll * b.batch) * g.H : 0;
+  const int64_t flat_blocks = (flat_units + kBulkWaves - 1) / kBulkWaves;
+  const bool flat = MODE == MODE_APPEND && append_flat(blocks * runs * layers, flat_blocks * layers);
   // unit / H = the upper word of 2 * unit * inverse while unit * H < 2^31
-  const int64_t most_units = (bulk_units > end_units ? bulk_units : end_units) + kBulkWaves;
+  const int64_t most_units = (flat ? flat_units : bulk_units > end_units ? bulk_units : end_units) + kBulkWaves;
   const unsigned inverse = 2 * most_units * g.H < (1ll << 31) ? (unsigned)(((1ull << 31) + g.H - 1) / g.H) : 0;
-  const bool planes = MODE == MODE_APPEND && !bulk && inverse != 0 && append_by_planes(g.D * g.es, end_units * runs * layers);
-  const int64_t blocks = bulk_blocks + (end_units * (planes ? 2 : 1) + kBulkWaves - 1) / kBulkWaves;
+  const bool planes = MODE == MODE_APPEND && !flat && !bulk && inverse != 0 && append_by_planes(g.D * g.es, end_units * runs * layers);
+  const Units units = flat ? Units::kFlat : planes ? Units::kPlanes : Units::kRuns;
+  if (flat) {
+    blocks = flat_blocks;
+    runs = 1;
+  } else if (planes) {
+    blocks = (end_units * 2 + kBulkWaves - 1) / kBulkWaves;
+  }
   if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks, (unsigned)runs, (unsigned)layers);
   const int dch = g.D / G;
 #define MTS_MOVE_CASE(T, DCH_) \
-  case DCH_: launch_typed<T, MODE, DCH_>(g, segs, b, grid, (int)bulk_blocks, a, bsrc, dst, pool_layer_stride, \
-                                         contig_layer_stride_bytes, inverse, planes, stream); break;
+  case DCH_: launch_typed<T, MODE, DCH_>(g, segs, b, grid, flat ? 0 : (int)bulk_blocks, a, bsrc, dst, pool_layer_stride, \
+                                         contig_layer_stride_bytes, inverse, units, stream); break;
   if (g.es == 2) {
     switch (dch) {
       MTS_MOVE_CASE(uint16_t, 4) MTS_MOVE_CASE(uint16_t, 8) MTS_MOVE_CASE(uint16_t, 16)

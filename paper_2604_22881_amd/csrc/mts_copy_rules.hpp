@@ -34,4 +34,11 @@ constexpr bool append_by_planes(int row_bytes, int64_t units) {
   return row_bytes >= 256 ? units <= 16384 : row_bytes == 128 && units <= 1024;
 }
 
+// Whether an append's workgroups are numbered through the users' rows, `flat` of them at most, and not by the longest user's for
+// each user, `rectangle` of them: a workgroup that finds nothing to move costs the launch up to a nanosecond, finding one's user
+// half a microsecond.  Of 70 random calls of 2 to 180 users, one to four of them with 100 to 4000 rows, times flat over
+// rectangle, by how many workgroups fewer: under 128 1.02 to 1.17, 128 to 511 0.82 to 1.06, 512 and more 0.48 to 0.99 (60 users of 40
+// rows beside one of 200, 8 heads of 128: 1.06).
+constexpr bool append_flat(int64_t rectangle, int64_t flat) { return rectangle - flat >= 512; }
+
 }  // namespace mts

@@ -2,6 +2,7 @@
 #include "../../paper_2604_22881_amd/csrc/mts_copy_rules.hpp"
 
 using mts::append_by_planes;
+using mts::append_flat;
 using mts::gather_past_caches;
 using mts::scatter_past_caches;
 
@@ -17,3 +18,4 @@ static_assert(scatter_past_caches(20479, 1 << 30, 2048, 4) == none && scatter_pa
 static_assert(!gather_past_caches(64) && gather_past_caches(128) && gather_past_caches(512), "");
 static_assert(append_by_planes(256, 16384) && !append_by_planes(512, 16385), "");
 static_assert(append_by_planes(128, 1024) && !append_by_planes(128, 1025) && !append_by_planes(64, 1), "");
+static_assert(append_flat(1024, 512) && !append_flat(1024, 513) && !append_flat(100, 200), "");

@@ -49,6 +49,24 @@ def test_every_range_inside_a_sub_block_is_stored(dtype, D):
     assert np.array_equal(step.pool_image(0), G.expected_pool_image(w, _oracle_store(w, data), 0, FILL))
 
 
+@pytest.mark.parametrize("users", [3, 64, 65, 300])
+@pytest.mark.parametrize("dtype,H,D", [("bf16", 3, 128), ("f32", 5, 32)])
+def test_append_of_one_long_user_among_short_ones(users, dtype, H, D):
+    """Workgroups numbered through the users' rows: users without rows, with rows that end inside and at
+    sub-blocks, one long one in the middle, more of them than lanes, and as many as two rounds of lanes."""
+    G = _harness()
+    rng = np.random.default_rng(users)
+    new = [int(x) for x in rng.integers(0, 40, users)]
+    new[users // 2] = 12000 if users < 64 else 2500
+    prefix = [int(x) for x in rng.integers(0, 40, users)]
+    w = W.custom_workload("flat", 79 + users, dtype, 1, H, D, 16, prefix, new, chunk_tokens=64)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    assert np.array_equal(step.pool_image(0), G.expected_pool_image(w, _oracle_store(w, data), 0, FILL))
+
+
 def test_more_heads_than_a_multiplication_divides_by():
     G = _harness()
     w = W.custom_workload("heads", 78, "bf16", 1, 24000, 32, 16, [3], [2], chunk_tokens=16)
