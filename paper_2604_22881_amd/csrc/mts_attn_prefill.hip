@@ -24,8 +24,8 @@
 // while the matrix cores work on P.V.  One barrier per step, across which the newest fetch stays in
 // flight.
 //
-// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1050 to
-// 1095 us (1004-1047 TFLOP/s), 780 us on zeros; a library matrix product of 8192^3
+// Bound: on random data the chip's power.  16 users x 4096 tokens x 16 heads of 128, one layer: 1014 to
+// 1095 us on several cards (1004-1085 TFLOP/s), 780 us on zeros; a library matrix product of 8192^3
 // reaches 1250 TFLOP/s here.  With v_mfma_f32_16x16x32_bf16, tiles parked from registers and no
 // pipelining across tiles the same call took 1163 to 1200 us (1018 on zeros), 64-dim heads 697 (628
 // now).  Tried and slower: 256-query blocks of eight wavefronts (1192 against 1162), raised wavefront priority around the
@@ -46,16 +46,16 @@
 // pieces that a merge kernel finishes.  Every wavefront derives the schedule by itself from the
 // device-resident lengths, in its lanes: a scan over the users, then searches by one comparison a lane
 // (positions inside a user are closed forms).  Measured, attention and merge of one layer in a step, means of runs on
-// several cards, head_dim 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 53 to 55 us (merge 10.7); 6 users with
-// 4-12 K histories and 8-64 new tokens beside 2 first-time ones 190 -> 94 to 99 us (merge 10.5).  What is left there is the block starts (1.2 and 1.5 segments
-// a share, about 5 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
+// several cards, head_dim 128, unsplit -> split: 1 user x 5189 new tokens x 4 heads 93 -> 45 to 50 us (merge 9.5); 6 users with
+// 4-12 K histories and 8-64 new tokens beside 2 first-time ones 190 -> 82 to 92 us (merge 9.8).  What is left there is the block starts (1.2 and 1.5 segments
+// a share, about 4 us each) and the fp32 pieces (64 KB each, about 40 and 47 MB written and read back).
 //
 // A block's start (page ids, keys, queries, reference, first scores) is 3.4 to 4 us, and a CU does little else before the
-// first one is done.  It was 5.5, and 2 before it for the schedule, now 1.2: with a prefix sum in LDS, masks and
+// first one is done.  It was 5.5, and 2 before it for the schedule, now 0.9: with a prefix sum in LDS, masks and
 // addresses computed ahead of the redo loop into 200 spilled scalar registers, the page table's round trip
 // before that of the keys, and queries loaded as fragments.  A piece's end took 2.3 us stored row by row, 1.4 in fragment order.  A step of 8 layers, by all of
-// it: one user's 5189 tokens x 4 heads 488 -> 465 us (446 since a CU's two shares are unequal), 16 x 4096 x 16 heads 10414 ->
-// 10238.
+// it: one user's 5189 tokens x 4 heads 488 -> 465 us (446 since a CU's two shares are unequal, 413 with all of the above), 16 x 4096 x 16 heads
+// 10414 -> 10238 (9627).
 //
 // PW selects the pointwise aggregation out = inv_norm * sum_j silu(c * q.k_j) v_j: no reference
 // max, no denominator, no redo; hidden keys carry logit 0 (silu(0) = 0).

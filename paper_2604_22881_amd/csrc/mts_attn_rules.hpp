@@ -116,7 +116,7 @@ constexpr PrefillShares prefill_shares(int total, int wgs, int min_steps, bool f
 // 128, and 18 where K/V come from beyond the caches) as for a workgroup, and for a query what 8 keys cost (16 at head_dim
 // 128).  us, matrix cores / plain, at 1000 users x 8 heads, 1 new token of 8 keys, 1 of 32, 2 of 32, 4 of 16:
 // head_dim 32 55 / 14, 56 / 36, 60 / 62, 62 / 65; 64 106 / 22, 104 / 70, 113 / 120, 112 / 101; 128 165 / 81, 177 / 304,
-// 194 / 579, 182 / 495.  A call that does not fill the chip waits for the plain kernel's longest chain of keys,
+// 194 / 579, 182 / 495 (measured before the matrix-core kernel took 8 to 24 % less).  A call that does not fill the chip waits for the plain kernel's longest chain of keys,
 // 0.3 us each: 16 users x 1000 keys 13 / 301 at head_dim 32.  `max_new` times all keys and `total_new` times the
 // longest user's both bound the (query, key) pairs of the call.
 constexpr bool f32_takes_plain(int head_dim, int64_t heads, int64_t users, int64_t total_new, int64_t max_new,
