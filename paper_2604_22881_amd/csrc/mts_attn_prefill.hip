@@ -84,6 +84,21 @@ using merge_detail::MergeDesc;
 constexpr int kTile = 32;        // kv tokens per step
 constexpr int kXcds = 8;
 constexpr int kMaxIdBytes = 64 * 1024;   // LDS page table of one block
+// The queries' own rooms (see the kernel) lie in the LDS of the page table from word `at` on: behind the table, but inside it
+// where two workgroups have room on a CU only so, as with 98 to 131 K tokens at 16 a page in a split launch of head_dim 128.  The
+// ids that lie there are then filled in when the queries have been read.  Behind any table, two users of 105 and 112 K tokens
+// with 900 and 600 new x 8 heads took 941 us, one workgroup on a CU; so 830, and 861 before the queries came by way of LDS.
+template <int D, bool BLOCK_REFERENCE>
+struct QueryRooms {
+  static constexpr int kFree = (BLOCK_REFERENCE ? 3 : 4) * (D / 64);  // rooms of a wavefront in the stages, of its eight
+  static constexpr int kOwn = kFree < 8 ? 8 - kFree : 0, kWords = 4 * kOwn * 256;
+  static constexpr int kTwo = (80 * 1024 - 3 * 32 * D * 4 - 64) / 4;  // words of a workgroup of two, with three stages and the flags
+  static constexpr int at(int id_cap) {
+    return id_cap > kTwo - kWords && id_cap <= kTwo ? kTwo - kWords : (id_cap + 3) & ~3;
+  }
+  static constexpr int64_t bytes(int id_cap) { return kOwn > 0 ? ((int64_t)at(id_cap) + kWords) * 4 : (int64_t)id_cap * 4; }
+  static_assert(kTwo % 4 == 0 && kWords < kTwo, "16-byte rooms");
+};
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -179,10 +194,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   extern __shared__ int s_ids[];       // physical page of every logical page the block reads
   __shared__ u32x4 stage[NST][FR * 64];  // K in KS KiB, then V (k_lane, v_lane and the reads below have the order)
   // A wavefront's queries come by way of LDS, 1 KiB of rows a load: into the wavefront's own room of the stages that are not
-  // filled yet, and what does not fit there into q_room.
+  // filled yet, and what does not fit there into rooms beside the page table (QueryRooms).
   constexpr bool kBlockReference = SPLIT && !PW;
-  constexpr int kRooms = (kBlockReference ? 3 : 4) * (FQ / 2), kOwnRooms = kRooms < 8 ? 8 - kRooms : 0;
-  __shared__ u32x4 q_room[kOwnRooms > 0 ? 4 * kOwnRooms * 64 : 1];
+  using Rooms = QueryRooms<D, kBlockReference>;
+  constexpr int kRooms = Rooms::kFree, kOwnRooms = Rooms::kOwn, kOwnWords = kOwnRooms * 256;
+  static_assert(kRooms == (kBlockReference ? 3 : 4) * (FQ / 2) && sizeof(stage) == 3 * 32 * D * 4, "as the launch allows for");
   __shared__ int redo_flag[4];         // of every wavefront
 
   const int tid = threadIdx.x;
@@ -386,6 +402,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // a tile's sub-block (past the end: of the last one, whose data is then fetched again, never used), its page
   auto sub_block = [&](int tile) __attribute__((always_inline)) { return (tile < last_tile ? tile : last_tile) * 2 + (wave & 1); };
   auto page_id = [&](int tile) __attribute__((always_inline)) { return s_ids[(sub_block(tile) >> g.sub_shift) - lp_beg]; };
+  auto put_id = [&](int i) __attribute__((always_inline)) {
+    int id = lp_beg + i < npg ? b.page_indices[pbeg + lp_beg + i] : 0;
+    if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
+    s_ids[i] = id;
+  };
   // A stage holds the keys of tile `tile` and the values of the tile two before it.  Fetches this
   // wavefront's quarter of it straight into LDS; the first two stages of a segment are keys only.
   const char *v_1 = head_base, *v_2 = head_base;                 // of tiles tile - 1 and tile - 2
@@ -407,7 +428,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   auto turn = [](int row) __attribute__((always_inline)) { return D == 128 ? row & 15 : (row >> 1) & 7; };
   auto room = [&](int j) __attribute__((always_inline)) -> uint32_t {
     constexpr int N = FQ / 2;
-    const int own = (int)lds_address(q_room) + (wave * kOwnRooms - kRooms) * 1024;
+    const int own = (int)lds_address(s_ids + Rooms::at(id_cap)) + (wave * kOwnRooms - kRooms) * 1024;
     return j < N       ? k_lds + 2 * FR * 1024 + j * 1024
            : j < 2 * N ? v_lds + 2 * FR * 1024 + (j - N) * 2048
            : j < 3 * N ? v_lds + FR * 1024 + (j - 2 * N) * 2048
@@ -647,11 +668,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
     if (attempt == 0) {
       // behind the first tiles' loads, so that their round trip is shared: the block's page table -> LDS.  Ids the metadata does not back become page 0 (in bounds; such slots lie past the user's last
       // token and are masked).
-      for (int i = tid; i < n_ids; i += 256) {
-        int id = lp_beg + i < npg ? b.page_indices[pbeg + lp_beg + i] : 0;
-        if ((unsigned)id >= (unsigned)g.num_pages) id = 0;
-        s_ids[i] = id;
-      }
+      const int n_first = kOwnRooms > 0 && n_ids > Rooms::at(id_cap) ? Rooms::at(id_cap) : n_ids;
+      for (int i = tid; i < n_first; i += 256) put_id(i);
     }
     wait_and_barrier<0>();
     if (attempt == 0) {
@@ -668,6 +686,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
         }
       }
       wait_for_lds();
+      if constexpr (kOwnRooms > 0) {                               // ids of the wavefront's own room, free now; the next barrier shows them
+        const int mine = Rooms::at(id_cap) + wave * kOwnWords, end = n_ids < mine + kOwnWords ? n_ids : mine + kOwnWords;
+        for (int i = mine + lane; i < end; i += 64) put_id(i);
+      }
     }
     load(2, tile0 + 2, id[2], std::true_type{});                   // into the room that the queries have left
     f32x16 za[NQ], zb;
@@ -829,7 +851,7 @@ hipError_t allow_lds() {
   std::call_once(attr_once, [] {
     attr_status = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_kernel<D, NST, NQ, PW, SPLIT>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      kMaxIdBytes);
+                                      kMaxIdBytes + 16 + QueryRooms<D, SPLIT && !PW>::kWords * 4);
   });
   return attr_status;
 }
@@ -869,8 +891,9 @@ hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan
     const int64_t blocks = (int64_t)g.H * (b.total_new / kBlockQ + b.batch);   // at most
     // (in eights, an XCD's in a row: the merge reads pieces on the XCD that wrote most of them)
     const int descs = blocks <= plan.prefill_wgs / 8 * 8 ? (int)((blocks + 7) / 8 * 8) : 0;
+    const int64_t lds_bytes = QueryRooms<D, !PW>::bytes((int)(id_bytes / 4));
     hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, true>), dim3((unsigned)plan.prefill_wgs), dim3(256),
-                       (size_t)id_bytes, stream, g, b, q, out, c, inv_norm, 1, descs, 1,
+                       (size_t)lds_bytes, stream, g, b, q, out, c, inv_norm, 1, descs, 1,
                        (int)(id_bytes / 4), plan.pair_cost, plan.min_tiles, ws_desc, ws_o, ws_ml);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -886,7 +909,9 @@ hipError_t launch_one(const PoolGeom& g, const BatchDev& b, const AttnPlan& plan
   const int pair_group = prefill_pair_group(g, b, xcd_pairs, q_blocks_max);
   const int64_t grid = (int64_t)((xcd_pairs + pair_group - 1) / pair_group * pair_group) * kXcds * q_blocks_max;
   if (grid <= 0 || grid > 0x7fffffffll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, false>), dim3((unsigned)grid), dim3(256), (size_t)id_bytes,
+  const int64_t lds_bytes = QueryRooms<D, false>::bytes((int)(id_bytes / 4));
+  hipLaunchKernelGGL((attn_prefill_kernel<D, NST, NQ, PW, false>), dim3((unsigned)grid), dim3(256),
+                     (size_t)lds_bytes,
                      stream, g, b, q, out, c, inv_norm, q_blocks_max, n_pairs, pair_group, (int)(id_bytes / 4), 0, 0, nullptr, nullptr,
                      nullptr);
   return hipGetLastError();

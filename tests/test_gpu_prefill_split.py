@@ -203,3 +203,30 @@ def test_split_prefill_redoes_a_piece_whose_reference_overflows(attn_tuning):
     got = step.attention(data, 0)
     assert np.isfinite(as_values(got)).all()
     check_attention(w, got, ref)
+
+
+# The queries' rooms lie behind the page table, or inside its end where two workgroups fit a CU only so: the last length in front
+# of that range, its first, one within, its last, the first past it (head_dim 64: its first).
+@pytest.mark.parametrize("D,tokens", [(128, 97984), (128, 97985), (128, 114000), (128, 130752), (128, 130753), (64, 147137)])
+def test_split_prefill_of_a_page_table_around_the_queries_rooms(D, tokens, attn_tuning):
+    import torch
+    import paper_2604_22881_amd as mts
+    attn_tuning(kernel=KERNEL_PREFILL, max_waves=12)
+    G = _harness()
+    w = W.custom_workload("long_table", 17, "bf16", 1, 1, D, 16, [tokens - 300], [300], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    assert step.ws_bytes > 0
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    got = as_values(step.attention(data, 0))
+    q = G.to_dev(data["q"][0])
+    out = torch.full((w.total_new, w.heads, w.head_dim), -1, dtype=q.dtype, device=G.DEV)
+    mts.mts_attn_incremental(step.cache.desc, 0, q, out, step.batch.meta, 0.0, None, 0)     # no overlap at these lengths
+    torch.cuda.synchronize()
+    want = as_values(G.to_host(out, w.np_dtype))
+    # Sums of 1e5 terms in fp32 move by up to sqrt(1e5) 2^-24 = 2e-5 of sum |w v|, which is sqrt(1e5) 0.8 = 250 times an
+    # average of independent values: 5e-3 of the result's root mean square, and a unit of bf16.  Ids of other pages in a
+    # wavefront's room (512 of up to 8176) would change the average by sqrt(2 / 16) = 0.35 of it.
+    rms = np.sqrt((want * want).mean())
+    assert (np.abs(got - want) <= 2.0 ** -7 * np.maximum(np.abs(got), np.abs(want)) + 5e-3 * rms).all()
