@@ -16,9 +16,9 @@
 // head_dim 32.  The next sub-block's K and V travel while one is computed, requested without a branch (behind a load that
 // may not have been made the compiler waits for all of them), and the page ids of 64 sub-blocks came with one load; head_dim
 // 64 is held to 128 registers, two workgroups a CU.  us a layer, with a branch, a page id a sub-block and the library's exponential /
-// now: 16 queries x 272 keys x 4 heads of 32 5.75 / 4.80 (73 with one wavefront per (query, head) and a scalar load per
-// element), of 64 8.1 / 6.9, of 128 13.0 / 11.2; 30 x 3030 x 8 of 64 42.5 / 37.1; 40 x 1440 x 8 of 128 43.8 / 37.1; 100 users' 10 x
-// 110 x 8 of 64 19.6 / 14.9.  Many users of a few keys are the plain kernel's (f32_takes_plain).
+// now: 16 queries x 272 keys x 4 heads of 32 5.75 / 4.87 (73 with one wavefront per (query, head) and a scalar load per
+// element), of 64 8.1 / 6.8, of 128 13.0 / 11.8; 30 x 3030 x 8 of 64 42.5 / 36.9; 40 x 1440 x 8 of 128 43.8 / 37.3; 100 users' 10 x
+// 110 x 8 of 64 19.6 / 15.0.  Many users of a few keys are the plain kernel's (f32_takes_plain).
 #include <math.h>
 
 #include <type_traits>
@@ -51,7 +51,7 @@ __device__ __forceinline__ float quad_row_sum(float v) {
   return over_quad_rows(v, [](float a, float b) { return a + b; });
 }
 
-// Weights are at most 1: what is below the smallest normal number counts as 0.
+// Weights are at most 1, the largest logit's is 1: what is below the smallest normal number counts as 0.
 __device__ __forceinline__ float exp2_of(float x) { return __builtin_amdgcn_exp2f(x); }
 
 struct F32Args {                 // one argument, see TableWords
@@ -70,9 +70,11 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 4) void attn_f32_kernel
   const float* __restrict__ q = args.q;
   float* __restrict__ out = args.out;
   const float scale = args.scale, inv_norm = args.inv_norm;
-  // Softmax: references are in units of the base-2 exponent, c = scale log2(e), and a weight is 2^(c z - m), with one
-  // rounding ahead of the exponential.  Against 64 bits, 24 random calls of 32 to 1900 keys: 4.47e-7 (geometric mean), with
-  // the scaled logit, its difference and the library's exponential 4.48e-7.
+  // Softmax: references are raw logits, and a weight is 2^(c (z - m)), c = scale log2(e): exactly 1 at the reference, however
+  // large the logits are.  (As 2^(c z - m) by one fma, m the rounded c z of the largest, that one's exponent is off by up to half a
+  // unit in the last place of c z, and from 2^31 on its weight infinite or 0.  us a layer so / now: 16 queries x 272 keys x 4 heads
+  // of 32 4.82 / 4.87, of 64 6.85 / 6.82, of 128 11.2 / 11.8; eleven other calls within 0.7 %.)  Against 64 bits, 24 random
+  // calls of 32 to 1900 keys: 4.47e-7 (geometric mean), with the scaled logit, its difference and the library's exponential 4.48e-7.
   const float c = scale * 1.4426950408889634f;
   constexpr int NF = D / 16;       // 16-byte fragments per lane of a sub-block's K, V, of Q and of the output
   __shared__ f32x4 s_o[kWaves / 2][NF][64];
@@ -162,11 +164,11 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 4) void attn_f32_kernel
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) z[e] = e < visible ? z[e] : -INFINITY;
-      const float m_new = fmaxf(m, quad_row_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]))) * c);
+      const float m_new = fmaxf(m, quad_row_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]))));
       const float m_ref = m_new == -INFINITY ? 0.f : m_new;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = exp2_of(fmaf(z[e], c, -m_ref));
-      const float alpha = exp2_of(m - m_ref);
+      for (int e = 0; e < 4; ++e) w[e] = exp2_of((z[e] - m_ref) * c);
+      const float alpha = exp2_of((m - m_ref) * c);
       l = l * alpha + ((w[0] + w[1]) + (w[2] + w[3]));
       m = m_new;
 #pragma unroll
@@ -239,8 +241,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 4) void attn_f32_kernel
     float wa = 1.f, wb = 1.f;
     if (!PW) {
       const float mb = s_m[wave][r], mn = fmaxf(m, mb), m_ref = mn == -INFINITY ? 0.f : mn;
-      wa = exp2_of(m - m_ref);
-      wb = exp2_of(mb - m_ref);
+      wa = exp2_of((m - m_ref) * c);
+      wb = exp2_of((mb - m_ref) * c);
       l = l * wa + s_l[wave][r] * wb;
       m = mn;
     }
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 4) void attn_f32_kernel
     f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < kWaves / 2; ++w) {
-      wgt[w] = PW ? 1.f : exp2_of(s_m[w][qi] - mx);
+      wgt[w] = PW ? 1.f : exp2_of((s_m[w][qi] - mx) * c);
       if (!PW) den = fmaf(wgt[w], s_l[w][qi], den);
       sum += s_o[w][s][ln] * wgt[w];
     }

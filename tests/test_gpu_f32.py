@@ -120,3 +120,21 @@ def test_f32_many_short_users_take_the_plain_kernel(D, S, name, attn_tuning):
     for got, other, ref in zip(automatic, plain, (oracle.attn_incremental(*args), oracle.attn_pointwise(*args, inv))):
         check_attention(w, got, ref)
         assert (got == other).all() == plain_taken
+
+
+@pytest.mark.parametrize("scale", [1e10, 1e30])
+@pytest.mark.parametrize("D,S", [(32, 16), (64, 64), (128, 32)])
+def test_f32_logits_beyond_the_exponents_whole_numbers(D, S, scale):
+    """Logits whose unit in the last place is many times the exponential's range: a row is its largest key's value, from
+    one wavefront's keys and from several's."""
+    G = _harness()
+    w = W.custom_workload("f32_large", 95 + D, "f32", 1, 3, D, S, *SHAPES[0], chunk_tokens=1024)
+    data = draw_step_data(w)
+    step = G.GpuStep(w, fill_byte=FILL)
+    store = _oracle_store(w, data)
+    step.unpack_histories(data, 0)
+    step.append(data, 0)
+    ref = oracle.attn_incremental(store, 0, data["q"][0], w.page_indptr, w.page_indices, w.prefix_lens, w.new_indptr, sm_scale=scale)
+    got = step.attention(data, 0, sm_scale=scale)
+    assert np.isfinite(got).all()
+    check_attention(w, got, ref)
