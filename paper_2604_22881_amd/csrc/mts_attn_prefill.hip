@@ -128,18 +128,21 @@ __device__ __forceinline__ float pair_sum(float v) {
 // wavefront-uniform) + k * STRIDE + 16 * lane, without passing through registers.  As instructions of its own because the
 // compiler, given the builtin, waits for all such loads before any LDS read; here the waits are wait_and_barrier's.
 // m0 is declared as overwritten, so that no value of the compiler's own is taken to outlive the statement in it; the
-// warning says that the statement does not restore it.  (`from` is a product and sums, all scalar instructions: a register that a
-// vector instruction has just written would need five wait states before the load.)
+// warning says that the statement does not restore it.  A load must not read a scalar register that a vector instruction wrote
+// within the last five wait states, a lane read that brings back a spilled `from` among them, and the compiler does not look into
+// the statement: so the load reads a copy that a scalar instruction has made, in the place of the wait state that m0 needs.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <int N, int STRIDE>
 __device__ __forceinline__ void load_to_lds(const char* from, uint32_t lane_at, uint32_t to) {
   static_assert(N == 1 || N == 2, "one m0 for both");
+  uint64_t base;
   if constexpr (N == 1)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_at), "s"(from), "s"(to) : "m0", "memory");
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(base) : "v"(lane_at), "s"(from), "s"(to) : "m0", "memory");
   else
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
-                 : : "v"(lane_at), "s"(from), "s"(to), "n"(STRIDE) : "m0", "memory");
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0\n\tglobal_load_lds_dwordx4 %1, %0 offset:%4"
+                 : "=&s"(base) : "v"(lane_at), "s"(from), "s"(to), "n"(STRIDE) : "m0", "memory");
 }
 #pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_address(const void* p) {

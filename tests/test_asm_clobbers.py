@@ -1,5 +1,7 @@
 """Inline assembly states what it writes: a register that an asm statement sets by name, without being
-one of its outputs, is in its clobber list, or the compiler may keep a value of its own there."""
+one of its outputs, is in its clobber list, or the compiler may keep a value of its own there.  And it keeps the waits
+that the compiler does not see inside it: a vector-memory instruction must not read a scalar register within five wait
+states of a vector instruction's write to it, which may stand right before the statement."""
 import os
 import re
 
@@ -24,12 +26,30 @@ def _statements(text):
         yield text[m.end():i - 1]
 
 
-def _undeclared(statement):
+def _parts(statement):
+    """Its instructions, the constraints of its operands in order, its clobbers."""
     strings = re.findall(r'"((?:[^"\\]|\\.)*)"', statement)
-    colons = re.sub(r'"(?:[^"\\]|\\.)*"', '""', statement).split(":")
-    code = " ".join(strings[:colons[0].count('""')]).replace("\\n", " \n ").replace("\\t", " ")
-    clobbers = strings[len(strings) - colons[3].count('""'):] if len(colons) > 3 else []
+    counts = [p.count('""') for p in re.sub(r'"(?:[^"\\]|\\.)*"', '""', statement).split(":")] + [0, 0, 0]
+    code = " ".join(strings[:counts[0]]).replace("\\n", " \n ").replace("\\t", " ")
+    clobbers = counts[0] + counts[1] + counts[2]
+    return code, strings[counts[0]:clobbers], strings[clobbers:clobbers + counts[3]]
+
+
+def _undeclared(statement):
+    code, _, clobbers = _parts(statement)
     return sorted({r for r in WRITES.findall(code)} - set(clobbers))
+
+
+def _unawaited(statement):
+    """Operands that a vector-memory instruction takes from scalar registers which no scalar instruction of the statement
+    has written before it."""
+    code, constraints, _ = _parts(statement)
+    written, found = set(), set()
+    for line in code.split("\n"):
+        if re.search(r"\b(global|buffer|flat|scratch)_", line):
+            found |= {k for k in map(int, re.findall(r"%(\d+)", line)) if "s" in constraints[k]} - written
+        written |= {int(k) for k in re.findall(r"\bs_[a-z0-9_]+\s+%(\d+)", line)}
+    return sorted(found)
 
 
 def test_the_scan_sees_an_undeclared_register():
@@ -37,7 +57,24 @@ def test_the_scan_sees_an_undeclared_register():
     assert _undeclared(r'"s_mov_b32 m0, %1\n\tglobal_load %0" : : "v"(a), "s"(b) : "m0", "memory"') == []
 
 
-@pytest.mark.parametrize("name", sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".inc", ".hpp"))))
+def test_the_scan_sees_an_unawaited_register():
+    assert _unawaited(r'"s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load %0, %1" : : "v"(a), "s"(b), "s"(c) : "m0", "memory"') == [1]
+    assert _unawaited(r'"s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load %1, %0" : "=&s"(t) : "v"(a), "s"(b), "s"(c) : "m0"') == []
+    assert _unawaited(r'"s_mov_b32 m0, %1\n\tglobal_load %0, %1" : : "v"(a), "s"(b) : "m0", "memory"') == [1]
+    assert _unawaited(r'"global_load %1, %0\n\ts_mov_b64 %0, %2" : "=&s"(t) : "v"(a), "s"(b)') == [0]
+
+
+SOURCES = sorted(f for f in os.listdir(CSRC) if f.endswith((".hip", ".inc", ".hpp")))
+
+
+@pytest.mark.parametrize("name", SOURCES)
+def test_loads_read_scalar_registers_that_scalar_instructions_wrote(name):
+    with open(os.path.join(CSRC, name)) as f:
+        for statement in _statements(f.read()):
+            assert not _unawaited(statement), statement
+
+
+@pytest.mark.parametrize("name", SOURCES)
 def test_registers_written_by_name_are_clobbers(name):
     with open(os.path.join(CSRC, name)) as f:
         for statement in _statements(f.read()):
