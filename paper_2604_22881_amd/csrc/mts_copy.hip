@@ -447,18 +447,18 @@ hipError_t launch_move(const PoolGeom& g, const SegDev& segs, const BatchDev& b,
   if (runs <= 0 || max_run_tokens <= 0 || layers <= 0) return hipSuccess;
   if (layers > 65535) return hipErrorInvalidValue;
   const int G = 16 / g.es;
-  // One wavefront per (16-token sub-block, head).  Runs of at least 128 tokens: the sub-blocks a
+  // One wavefront per (16-token sub-block, head).  Runs of at least kBulkRun tokens: the sub-blocks a
   // run covers completely (of the longest run) take the unmasked form, the at most two partly
   // covered ones at its ends the masked form.  Shorter runs (a step's few new tokens): every
   // sub-block a run touches, at most ceil(max / 16) + 1, takes the masked form.
-  const bool bulk = max_run_tokens >= 128;
+  const bool bulk = max_run_tokens >= kBulkRun;
   const int64_t bulk_units = bulk ? (max_run_tokens / 16) * (int64_t)g.H : 0;
   const int64_t bulk_blocks = (bulk_units + kBulkWaves - 1) / kBulkWaves;
   const int64_t end_units = (bulk ? 2 : (max_run_tokens + 15) / 16 + 1) * (int64_t)g.H;
   int64_t blocks = bulk_blocks + (end_units + kBulkWaves - 1) / kBulkWaves;
   const int64_t flat_units = MODE == MODE_APPEND ? ((int64_t)b.total_new / 16 + 2ll * b.batch) * g.H : 0;
   const int64_t flat_blocks = (flat_units + kBulkWaves - 1) / kBulkWaves;
-  const bool flat = MODE == MODE_APPEND && append_flat(blocks * runs * layers, flat_blocks * layers);
+  const bool flat = MODE == MODE_APPEND && append_flat(max_run_tokens, blocks * runs * layers, flat_blocks * layers);
   // unit / H = the upper word of 2 * unit * inverse while unit * H < 2^31
   const int64_t most_units = (flat ? flat_units : bulk_units > end_units ? bulk_units : end_units) + kBulkWaves;
   const unsigned inverse = 2 * most_units * g.H < (1ll << 31) ? (unsigned)(((1ull << 31) + g.H - 1) / g.H) : 0;

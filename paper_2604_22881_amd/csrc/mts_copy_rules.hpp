@@ -34,11 +34,18 @@ constexpr bool append_by_planes(int row_bytes, int64_t units) {
   return row_bytes >= 256 ? units <= 16384 : row_bytes == 128 && units <= 1024;
 }
 
+// The shortest longest run of a launch whose whole sub-blocks take a form of their own, without a token mask.
+constexpr int64_t kBulkRun = 128;
+
 // Whether an append's workgroups are numbered through the users' rows, `flat` of them at most, and not by the longest user's for
 // each user, `rectangle` of them: a workgroup that finds nothing to move costs the launch up to a nanosecond, finding one's user
 // half a microsecond.  Of 70 random calls of 2 to 180 users, one to four of them with 100 to 4000 rows, times flat over
-// rectangle, by how many workgroups fewer: under 128 1.02 to 1.17, 128 to 511 0.82 to 1.06, 512 and more 0.48 to 0.99 (60 users of 40
-// rows beside one of 200, 8 heads of 128: 1.06).
-constexpr bool append_flat(int64_t rectangle, int64_t flat) { return rectangle - flat >= 512; }
+// rectangle, by how many workgroups fewer: under 128 1.02 to 1.17, 128 to 511 0.82 to 1.06, 512 and more 0.48 to 1.01 and
+// one of 1.07 (60 users of 40 rows beside one of 200, 8 heads of 128; 1.006 with the attention behind it, where the others are 0.92 to 1.00).
+// A launch of short runs leaves few out, and its whole sub-blocks would be kept in the L2 that the next kernel needs: eight calls of
+// 64 to 512 users of 1 to 127 rows, with their attention, 1.00 to 1.04; stored past it, 0.99 to 1.00.
+constexpr bool append_flat(int64_t longest_run, int64_t rectangle, int64_t flat) {
+  return longest_run >= kBulkRun && rectangle - flat >= 512;
+}
 
 }  // namespace mts

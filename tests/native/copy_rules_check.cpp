@@ -18,4 +18,5 @@ static_assert(scatter_past_caches(20479, 1 << 30, 2048, 4) == none && scatter_pa
 static_assert(!gather_past_caches(64) && gather_past_caches(128) && gather_past_caches(512), "");
 static_assert(append_by_planes(256, 16384) && !append_by_planes(512, 16385), "");
 static_assert(append_by_planes(128, 1024) && !append_by_planes(128, 1025) && !append_by_planes(64, 1), "");
-static_assert(append_flat(1024, 512) && !append_flat(1024, 513) && !append_flat(100, 200), "");
+static_assert(append_flat(128, 1024, 512) && !append_flat(128, 1024, 513) && !append_flat(4000, 100, 200), "");
+static_assert(!append_flat(127, 1 << 20, 512), "short runs: their whole sub-blocks would be kept in the L2");

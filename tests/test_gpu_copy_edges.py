@@ -96,3 +96,34 @@ def test_rows_of_a_page_outside_the_pool_go_nowhere(page, new):
     torch.cuda.synchronize()
     again.append(data, 0)
     assert np.array_equal(again.pool_image(0).reshape(w.num_pages, -1), want)
+
+
+@pytest.mark.parametrize("dtype,H,D", [("bf16", 3, 64), ("f32", 5, 32)])
+def test_append_of_one_long_user_over_several_layers(dtype, H, D):
+    """Workgroups numbered through the users' rows, over layers of a larger cache whose row buffers lie a padded stride
+    apart: those layers hold the oracle's rows, the others are untouched."""
+    import torch
+    import paper_2604_22881_amd as mts
+    G = _harness()
+    L, lo, count = 5, 1, 3
+    rng = np.random.default_rng(81)
+    new = [int(x) for x in rng.integers(0, 40, 70)]
+    new[33] = 700
+    prefix = [int(x) for x in rng.integers(0, 40, 70)]
+    w = W.custom_workload("flat_layers", 81, dtype, L, H, D, 32, prefix, new, chunk_tokens=64)
+    data = draw_step_data(w, layers=range(lo, lo + count))
+    step = G.GpuStep(w, fill_byte=FILL)
+    for l in range(lo, lo + count):
+        step.unpack_histories(data, l)
+    n = w.total_new * H * D
+    stride = n + 40                                           # elements; 80 or 160 bytes of padding
+    rows = {kv: np.zeros(count * stride, dtype=w.np_dtype) for kv in ("k_new", "v_new")}
+    for kv, to in rows.items():
+        for i in range(count):
+            to[i * stride:i * stride + n] = np.ascontiguousarray(data[kv][lo + i]).reshape(-1)
+    mts.mts_kv_append_layers(step.cache.desc, lo, count, G.to_dev(rows["k_new"]), G.to_dev(rows["v_new"]),
+                             stride * w.elem_bytes, step.batch.meta)
+    torch.cuda.synchronize()
+    store = _oracle_store(w, data, do_append=True)
+    for l in range(L):
+        assert np.array_equal(step.pool_image(l), G.expected_pool_image(w, store, l, FILL)), f"layer {l}"
