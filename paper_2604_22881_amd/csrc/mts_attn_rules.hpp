@@ -111,21 +111,24 @@ constexpr PrefillShares prefill_shares(int total, int wgs, int min_steps, bool f
 }
 
 // Whether an fp32 call goes to the plain kernel.  A workgroup of the matrix-core kernel is eight wavefronts that
-// find their user, read at least one 16-token sub-block and combine: 7, 14, 22 ns of the whole chip at head_dim
-// 32, 64, 128 however short the user is.  The plain kernel pays per (query, key), as much for 64 of them (68 at head_dim
-// 128, and 18 where K/V come from beyond the caches) as for a workgroup, and for a query what 8 keys cost (16 at head_dim
-// 128).  us, matrix cores / plain, at 1000 users x 8 heads, 1 new token of 8 keys, 1 of 32, 2 of 32, 4 of 16:
-// head_dim 32 55 / 14, 56 / 36, 60 / 62, 62 / 65; 64 106 / 22, 104 / 70, 113 / 120, 112 / 101; 128 165 / 81, 177 / 304,
-// 194 / 579, 182 / 495 (measured before the matrix-core kernel took 8 to 24 % less).  A call that does not fill the chip waits for the plain kernel's longest chain of keys,
-// 0.3 us each: 16 users x 1000 keys 13 / 301 at head_dim 32.  `max_new` times all keys and `total_new` times the
-// longest user's both bound the (query, key) pairs of the call.
+// find their user, read at least one 16-token sub-block and combine: 6.3, 8, 19.5 ns of the whole chip at head_dim
+// 32, 64, 128 however short the user is.  The plain kernel pays per (query, key).  us, matrix cores / plain, at 1000 users x 8
+// heads, 1 new token of 8 keys, 1 of 32, 1 of 48, 2 of 32, 4 of 16: head_dim 32 51 / 14, 50 / 35, 52 / 51, 53 / 61, 56 / 64; 64
+// 63 / 22, 68 / 68, 78 / 108, 74 / 123, 69 / 104; 128 166 / 90, 175 / 338, 191 / 510, 191 / 590, 191 / 494; at 256 users of 32
+// keys 14 / 15, 19 / 18, 42 / 29.  `max_new` times all keys and `total_new` times the longest user's both bound the (query, key)
+// pairs of the call, by half as much again where lengths differ, twice where new tokens do too; the limits are for
+// such calls: 64 a workgroup less 8 a query at head_dim 32; 38 and 7 more a query, 64 at most, at 64 (58 random calls between this and
+// the 64 of the time when a workgroup took 14 ns, matrix cores over plain: 0.56 to 1.05 and one of 1.10; 1.00 to 1.35 just below it); 68 less 16
+// at 128, and 18 where K/V come from beyond the caches (1.65 to 1.95 just below).  A call that does not fill the chip waits for the plain kernel's longest chain of keys, 0.3 us each: 16 users x
+// 1000 keys 13 / 301 at head_dim 32.
 constexpr bool f32_takes_plain(int head_dim, int64_t heads, int64_t users, int64_t total_new, int64_t max_new,
                                int64_t max_len, int64_t page_tokens) {
   const int64_t blocks = total_new / 16 + users;
-  if (300 * max_len + 3000 >= blocks * heads * (head_dim == 32 ? 7 : head_dim == 64 ? 14 : 22)) return false;
+  if (300 * max_len + 3000 >= blocks * heads * (head_dim == 32 ? 7 : head_dim == 64 ? 11 : 22)) return false;
   const bool far = head_dim == 128 && page_tokens * heads * 1024 > (96ll << 20);
-  const int64_t room = blocks * (head_dim <= 64 ? 64 : far ? 18 : 68) -
-                       total_new * (head_dim == 64 || far ? 0 : head_dim == 32 ? 8 : 16);
+  const int64_t more = 7 * total_new < 26 * blocks ? 7 * total_new : 26 * blocks;      // head_dim 64's, up to 64 a workgroup in all
+  const int64_t room = head_dim == 64 ? blocks * 38 + more
+                                      : blocks * (head_dim == 32 ? 64 : far ? 18 : 68) - total_new * (head_dim == 32 ? 8 : far ? 0 : 16);
   return total_new * max_len < room || (max_new <= room / (page_tokens > 0 ? page_tokens : 1) && max_new * page_tokens < room);
 }
 

@@ -110,6 +110,8 @@ static_assert(f32_takes_plain(64, 8, 1000, 1000, 1, 8, 64000), "");
 static_assert(f32_takes_plain(64, 8, 1000, 1000, 1, 100, 16000), "one longer user among them");
 // ... but no longer ones, no few, and none with many queries
 static_assert(!f32_takes_plain(32, 8, 1000, 1000, 1, 96, 96000) && !f32_takes_plain(64, 8, 1000, 4000, 4, 32, 32000), "");
+static_assert(!f32_takes_plain(64, 8, 1000, 1000, 1, 48, 48000) && !f32_takes_plain(64, 8, 1000, 2000, 2, 32, 32000), "");
+static_assert(!f32_takes_plain(64, 8, 1000, 8000, 8, 13, 16000), "never beyond 64 a workgroup");
 static_assert(!f32_takes_plain(128, 8, 1000, 1000, 1, 32, 32000) && !f32_takes_plain(128, 2, 1000, 4000, 4, 8, 16000), "");
 static_assert(!f32_takes_plain(32, 4, 1, 1, 1, 300, 304) && !f32_takes_plain(64, 8, 8, 8, 1, 8, 128), "");
 static_assert(!f32_takes_plain(64, 8, 1000, 1000, 1, 3000, 16000), "the launch would wait for the longest");
