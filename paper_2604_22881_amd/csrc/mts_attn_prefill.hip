@@ -458,8 +458,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   f32x16 o[NQ][DB];
   float l[NQ];                     // softmax denominators: this lane's tokens only
   float m[NQ], mcq[NQ];            // reference max: raw logit units / scaled for the base-2 exponent
+  float cq[NQ];                    // what scales the logits: c, but for huge ones (row_scale)
 #pragma unroll
-  for (int qb = 0; qb < NQ; ++qb) { m[qb] = -INFINITY; mcq[qb] = 0.f; }
+  for (int qb = 0; qb < NQ; ++qb) { m[qb] = -INFINITY; mcq[qb] = 0.f; cq[qb] = c; }
 
   auto key_fragment = [&](int st, int s, int room = 0) __attribute__((always_inline)) {
     return __builtin_bit_cast(bf16x8, stage[st][(room + (s >> 2) + KS / 4 * (s >> 1 & 1)) * 64 + (s & 1) * 32 + k_read]);
@@ -493,7 +494,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
   // reference max from the scores of a tile; with nothing visible or all of them -inf, any will do
   auto set_reference = [&](const f32x16& z, int qb) __attribute__((always_inline)) {
     m[qb] = pair_max(max16(z));
-    mcq[qb] = (m[qb] == -INFINITY ? 0.f : m[qb]) * c;
+    const float ref = m[qb] == -INFINITY ? 0.f : m[qb];
+    cq[qb] = merge_detail::row_scale(ref, c);
+    mcq[qb] = ref * cq[qb];
   };
   // Weights of a tile from its scores, and their sum.
   auto weights = [&](const f32x16& z, int qb, bf16x8 (&pf)[2]) __attribute__((always_inline)) {
@@ -503,7 +506,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
       for (int e = 0; e < 8; ++e) {
         const float x = z[8 * sb + e];
         if constexpr (PW) pf[sb][e] = (__bf16)fast_silu(x * c);
-        else pf[sb][e] = (__bf16)fast_exp2(fmaf(x, c, -mcq[qb]));
+        else pf[sb][e] = (__bf16)fast_exp2(fmaf(x, cq[qb], -mcq[qb]));
       }
       if constexpr (!PW) {
         // the rounded weights are summed, as P.V does
@@ -640,7 +643,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PoolGeom g, BatchD
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) {
         m[qb] = pair_max(mx[qb]);
-        mcq[qb] = (m[qb] == -INFINITY ? 0.f : m[qb]) * c;
+        const float ref = m[qb] == -INFINITY ? 0.f : m[qb];
+        cq[qb] = merge_detail::row_scale(ref, c);
+        mcq[qb] = ref * cq[qb];
       }
     }
 
