@@ -230,3 +230,36 @@ def test_split_prefill_of_a_page_table_around_the_queries_rooms(D, tokens, attn_
     # wavefront's room (512 of up to 8176) would change the average by sqrt(2 / 16) = 0.35 of it.
     rms = np.sqrt((want * want).mean())
     assert (np.abs(got - want) <= 2.0 ** -7 * np.maximum(np.abs(got), np.abs(want)) + 5e-3 * rms).all()
+
+
+# Blocks whose own ids reach into the queries' rooms, one workgroup taking them whole: the last id in the room of each
+# wavefront, of 512 words from id 6128 on at head_dim 128 (the split softmax form's alone), of 1280 from 9200 (split softmax) and of 1024
+# from 10224 (pointwise and unsplit) at 64, up to the last table that overlaps.
+@pytest.mark.parametrize("D,ids", [(64, 10300), (64, 11300), (64, 12300), (64, 14316), (128, 6300), (128, 6800), (128, 7400), (128, 8172)])
+def test_page_ids_in_every_wavefronts_room(D, ids, attn_tuning):
+    """The same keys in pages of 64 tokens, whose table is a quarter as long and lies beside the rooms: the same bits."""
+    import torch
+    import paper_2604_22881_amd as mts
+    attn_tuning(kernel=KERNEL_PREFILL, max_waves=4)
+    G = _harness()
+    outs, data = [], None
+    for S in (16, 64):
+        w = W.custom_workload("long_table", 19, "bf16", 1, 1, D, S, [16 * ids - 305], [300], chunk_tokens=1 << 20)
+        data = draw_step_data(w) if data is None else data
+        step = G.GpuStep(w, fill_byte=FILL)
+        assert step.ws_bytes > 0
+        step.unpack_histories(data, 0)
+        step.append(data, 0)
+        q, got = G.to_dev(data["q"][0]), []
+        for pointwise in (False, True):
+            for ws, nbytes in ((step.ws, step.ws_bytes), (None, 0)):                        # split, unsplit
+                out = torch.full((w.total_new, w.heads, w.head_dim), -1, dtype=q.dtype, device=G.DEV)
+                if pointwise:
+                    mts.mts_attn_pointwise(step.cache.desc, 0, q, out, step.batch.meta, 1.0 / 300, 0.0, ws, nbytes)
+                else:
+                    mts.mts_attn_incremental(step.cache.desc, 0, q, out, step.batch.meta, 0.0, ws, nbytes)
+                torch.cuda.synchronize()
+                got.append(G.to_host(out, w.np_dtype))
+        outs.append(got)
+    for form, a, b in zip(("split", "unsplit", "pointwise split", "pointwise unsplit"), *outs):
+        assert np.isfinite(as_values(b)).all() and np.array_equal(a, b), form
