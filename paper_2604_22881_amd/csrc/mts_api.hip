@@ -177,9 +177,10 @@ static void plan_prefill_split(AttnPlan& p, const PoolGeom& g, const BatchDev& b
   const int64_t max_tiles = ((int64_t)b.max_total_len + 31) / 32 + 1;
   const int QB = attn_prefill_block(g);
   const int64_t blocks = (int64_t)g.H * (b.total_new / QB + b.batch);        // at most
-  // allowance of a block and least share, in tile steps: swept 4..13 and 8..24, flat within 5 % (head_dim 64, 8 over 10: one
-  // user's 6000 tokens x 8 heads 57.9 / 59.1 us, 2 of 5000 beside 25 of 600 x 8 86.4 / 87.4, three others even; 128: 1
-  // user's 5189 x 4 44.3 / 44.7, 4 of 2300 x 8 70.9 / 67.6)
+  // allowance of a block and least share, in tile steps: swept 4..13 and 8..24, flat within 5 %.  head_dim 64, 8 / 10, us a
+  // step of 4 layers: 2 users of 5000 tokens beside 25 of 600 x 8 heads 467 / 475, 20 returning ones beside 2 of 2000 to 4000 x 8 252 / 256, 8
+  // beside 1 of 5000 x 4 197 / 200, 40 beside 4 of 800 to 1200 x 8 182 / 184, 4 of 2300 x 8 222 / 223, 1 of 6000 x 8 255.7 / 256.2, four others
+  // even.  128, a layer: 1 user's 5189 x 4 44.3 / 44.7, 4 of 2300 x 8 70.9 / 67.6.
   p.pair_cost = g.D == 64 ? 8 : 10;
   if (const int v = g_tune_pair_cost.load(std::memory_order_relaxed); v > 0) p.pair_cost = v < 64 ? v : 64;
   p.min_tiles = 12;
